@@ -263,7 +263,7 @@ struct pft_ctx {
     DevTables tabs{};
     KsConsts kc{};
     TwPair* rescale_qinv = nullptr;  // [2][L][L]: row l-1 holds q_{l-1}^-1 mod q_k (Shoup pairs, then fp64 pairs)
-    TwPair* gadget = nullptr;        // [L]: (P mod q_i) as Shoup pairs
+    TwPair* gadget = nullptr;        // [2L]: (P mod q_i) as Shoup pairs, then fp64 pairs
     TwPair* to_mont = nullptr;       // [L+K]: 2^64 mod m as Shoup pairs
     std::vector<void*> allocs;
     uint64_t device_bytes = 0;
@@ -517,7 +517,7 @@ static int build_tables(pft_ctx* c) {
             }
         }
     }
-    std::vector<TwPair> phatinv(K), pinv(2 * L), gadget(L), tomont(L + K);
+    std::vector<TwPair> phatinv(K), pinv(2 * L), gadget(2 * L), tomont(L + K);
     std::vector<uint64_t> downc((size_t)K * L);
     for (uint32_t k = 0; k < K; ++k) {
         uint64_t h = 1;
@@ -537,6 +537,7 @@ static int build_tables(pft_ctx* c) {
         pinv[i] = pair(invmod(pm, P->q[i]), P->q[i]);
         pinv[L + i] = twiddle(invmod(pm, P->q[i]), P->q[i]);  // fp64 form for q < 2^50
         gadget[i] = pair(pm, P->q[i]);
+        gadget[L + i] = twiddle(pm, P->q[i]);
     }
     for (uint32_t m = 0; m < L + K; ++m) tomont[m] = pair(to_mont(1, P->mods[m]), P->mods[m]);
     std::vector<TwPair> rq(2 * (size_t)L * L, TwPair{0, 0});
@@ -924,9 +925,10 @@ static void ntt_jobs(pft_ctx* c, const std::vector<NttJob>& jobs, uint32_t n_lim
             for (uint32_t i = 0; i < PFT_MAX_POLYS / 2; ++i) {
                 e.out[i] = s / 2 + i < PFT_MAX_POLYS / 2 ? epi->out[s / 2 + i] : nullptr;
                 e.acc_item[i] = s / 2 + i < PFT_MAX_POLYS / 2 ? epi->acc_item[s / 2 + i] : nullptr;
-                // perm_src is per item for a forward epilogue, per polynomial for an inverse transform
+                // src is per item for a forward epilogue, per polynomial for an inverse transform
                 const size_t pi = inverse ? s + i : s / 2 + i;
-                e.perm_src[i] = pi < PFT_MAX_POLYS / 2 ? epi->perm_src[pi] : nullptr;
+                e.src[i] = pi < PFT_MAX_POLYS / 2 ? epi->src[pi] : nullptr;
+                e.src2[i] = pi < PFT_MAX_POLYS / 2 ? epi->src2[pi] : nullptr;
             }
             launch_ntt(b, c->tabs, P->log_n, inverse, sched, c->stream, hook(c), &e, first);
         } else {
@@ -1671,28 +1673,43 @@ static bool last_pass_col16(pft_ctx* c, uint64_t limbs) {
     return s.n_passes >= 2 && s.radix[0] == 4;
 }
 
-// The input of a rotation's key switch: item z's ciphertext src[z]
-// ([2][level][N], NTT domain) under X -> X^kappa.  Its c1 image is d and
-// its c0 image is the addend of the first output polynomial.
-struct KsRot {
+// What a key switch takes: the polynomial d (NTT domain) and what is added
+// to its result, per item z (the modes of launch_ks_rows).
+//   KS_WS       d = [level][N] at ws_z + off_d
+//   KS_PRODUCT  the tensor of ciphertexts src, src2: d = d2, (d0, d1) added
+//   KS_ROTATE   src ([2][level][N]) under X -> X^kappa: d = c1's image, c0's added
+// has_add: the ciphertext src2 is added too (KS_WS, KS_ROTATE).  off_pre: a
+// workspace region ([3][level][N] for KS_PRODUCT, [2][level][N] for
+// KS_ROTATE) for the tensor or the images where the kernels that read their
+// operands directly do not run.  out may be a has_add ciphertext of its own
+// item (each element is read before it is written); overlap: an output
+// overlaps another operand.
+struct KsInput {
+    uint32_t mode;
+    uint64_t off_d, off_pre;
+    ItemPtrs src, src2;
+    bool has_add, overlap;
     uint64_t kappa, kappa_inv;
-    ItemPtrs src;
 };
 
-// Key switching of d (NTT domain, [level][N] at ws_z + off_d) for n items:
-// out_z = ModDown(sum_j ModUp_j(d) key_j) + (ws rows at off_add0/off_add1),
-// plus, for the first polynomial, the rows at off_add0b (out may be those
-// rows: each element is read before it is written).
-// rot: d and the first addend are the X^kappa images of rot->src (out must
-// not overlap rot->src).  Where the inner product is fused with the row pass
-// of ModUp's rows, the permutation is folded into the loads of the kernels
-// that read them (the first pass of d's inverse transform, the own rows of
-// the inner product, the ModDown epilogue); otherwise both images are first
-// written to the workspace at off_add0 (c0) and off_d = off_add0 + level N
-// (c1).
-static void key_switch_b(pft_ctx* c, uint32_t n, WsRef ws, const KsLayout& K, uint64_t off_d,
-                         const SwitchKeyDev& key, uint64_t off_add0, uint64_t off_add1, const ItemPtrs& out,
-                         uint64_t off_add0b = PFT_NO_OFFSET, const KsRot* rot = nullptr) {
+// Whether any of the n outputs ([2][level][N]) overlaps any operand.
+static bool ks_overlap(uint32_t n, const ItemPtrs& out, const ItemPtrs& x, uint64_t words) {
+    for (uint32_t z = 0; z < n; ++z)
+        for (uint32_t u = 0; u < n; ++u)
+            if (out.p[z] < x.p[u] + words && x.p[u] < out.p[z] + words) return true;
+    return false;
+}
+
+// Key switching for n items: out_z = ModDown(sum_j ModUp_j(d) key_j) + addends.
+//
+// Fused path: where the forward transforms of ModUp's and ModDown's rows start
+// with a radix-16 column pass, the conversion kernels apply that pass, and
+// launch_ks_rows does the rest of ModUp's rows, the key products and the rest
+// of ModDown in two launches, reading the operands of d and of the addends
+// directly.  Otherwise one launch per step, from the tensor or the images in
+// the workspace.
+static void key_switch_b(pft_ctx* c, uint32_t n, WsRef ws, const KsLayout& K, const SwitchKeyDev& key,
+                         const KsInput& in, const ItemPtrs& out) {
     const pft_params* P = c->P;
     const uint32_t lg = P->log_n, A = P->alpha, level = K.level, rows = K.rows, beta = K.beta;
     const double N = (double)P->n;
@@ -1715,43 +1732,58 @@ static void key_switch_b(pft_ctx* c, uint32_t n, WsRef ws, const KsLayout& K, ui
     // applies that pass itself; then d's inverse transform also stops before
     // its final radix-16 column pass (a schedule chosen among those ending
     // with one) and ModUp applies that pass to its inputs.
-    const uint32_t nkb = (std::min(P->alpha, level) + 1) / 2;
+    const uint32_t nkb = (std::min(P->alpha, level) + 1) / 2, down_kb = (P->K + 1) / 2;
     const bool fuse = c->bconv_mfma && c->bconv_fuse && lg >= 8 && nkb <= 6 && col16(full, rows - A) &&
                       col16(last, rows - na_last);
+    const bool fuse_down = c->bconv_mfma && c->bconv_fuse && lg >= 8 && down_kb <= 6 &&
+                           first_pass_col16(c, 2ull * n * level);
     const bool ifuse_up = fuse && last_pass_col16(c, (uint64_t)n * level);
-    // the remaining (row) pass of the rows' forward transform, and the key
-    // inner product: fused in one kernel where that pass is the row pass of
-    // a (4, log_n - 4) schedule, else a transform launch per digit group and
-    // the inner-product kernel
-    const uint64_t rs_limbs =
-        full.empty() ? (uint64_t)last.size() * (rows - na_last) : (uint64_t)full.size() * (rows - A);
-    const NttSchedule rs = ntt_schedule(c, false, rs_limbs, fuse && fwd_col16_restricted(c, rs_limbs));
-    const bool fuse_inner =
-        fuse && c->inner_fuse && beta <= 8 && row_inner_supported(lg) && rs.n_passes == 2 && rs.radix[0] == 4;
-    const bool fold = rot && fuse_inner;
-    if (rot && !fold) {
-        // both X^kappa images into the workspace
+    const bool merged = fuse && fuse_down && c->inner_fuse && beta <= 8 && ks_rows_supported(lg);
+    // the operands of d and of the addends, read directly on the fused path
+    // unless an output overlaps them
+    uint32_t mode = in.mode;
+    uint64_t off_d = in.off_d, off_add0 = PFT_NO_OFFSET;
+    ItemPtrs src = in.src, src2 = in.src2;
+    bool has_add = in.has_add;
+    if (mode == KS_PRODUCT && (!merged || in.overlap)) {
+        timed(c, PK_TENSOR, 8.0 * nl * 7 * n, 4.0 * nl * n,
+              [&] { launch_tensor_b(n, src, src2, ws, in.off_pre, level, c->tabs, lg, c->stream); });
+        mode = KS_WS;
+        off_d = in.off_pre + 2 * nl;
+        src2 = ws_items(ws, n, in.off_pre);
+        has_add = true;
+    } else if (mode == KS_ROTATE && !merged) {
+        // both X^kappa images
         timed(c, PK_AUTOMORPHISM, 8.0 * 4 * nl * n, 0,
-              [&] { launch_automorphism_b(n, rot->src, 2 * level, ws, off_add0, rot->kappa, lg, c->stream); });
+              [&] { launch_automorphism_b(n, src, 2 * level, ws, in.off_pre, in.kappa, lg, c->stream); });
+        mode = KS_WS;
+        off_d = in.off_pre + nl;
+        off_add0 = in.off_pre;
+    } else if (mode == KS_ROTATE && in.overlap) {
+        launch_copy_rows_b(n, src, 0, ws_items(ws, n, in.off_pre), 0, 2 * level, lg, c->stream);
+        src = ws_items(ws, n, in.off_pre);
     }
-    // d -> coefficient form at off_dcoef (the first pass reads d in place, or
-    // through the permutation from rot->src; d stays in the NTT domain for
-    // the inner product)
+    // d -> coefficient form at off_dcoef (d itself stays in the NTT domain for
+    // the products with the key)
     {
         std::vector<NttJob> jobs;
         for (uint32_t z = 0; z < n; ++z) jobs.push_back(NttJob{ws.base + z * ws.stride + K.off_dcoef, 255u, 0u});
-        if (fold) {
+        if (mode != KS_WS) {
             NttEpilogue pe{};
-            for (uint32_t z = 0; z < n; ++z) pe.perm_src[z] = rot->src.p[z] + nl;
-            pe.kappa = rot->kappa;
-            pe.kappa_inv = rot->kappa_inv;
+            for (uint32_t z = 0; z < n; ++z) {
+                pe.src[z] = src.p[z] + nl;
+                if (mode == KS_PRODUCT) pe.src2[z] = src2.p[z] + nl;
+            }
+            pe.source = mode == KS_PRODUCT ? NTT_SRC_PROD : NTT_SRC_PERM;
+            pe.kappa = in.kappa;
+            pe.kappa_inv = in.kappa_inv;
             ntt_jobs(c, jobs, level, ~0u, true, 0, &pe, 0, ifuse_up ? 1u : 0u, ifuse_up);
         } else {
             ntt_jobs(c, jobs, level, ~0u, true, 0, nullptr, (int64_t)off_d - (int64_t)K.off_dcoef, ifuse_up ? 1u : 0u,
                      ifuse_up);
         }
     }
-    // ModUp base conversion and the forward transforms of its rows
+    // ModUp base conversion
     {
         double rd = 0, wr = 0, macs = 0;
         for (uint32_t j = 0; j < beta; ++j) {
@@ -1775,65 +1807,58 @@ static void key_switch_b(pft_ctx* c, uint32_t n, WsRef ws, const KsLayout& K, ui
                 launch_modup_b(n, ws, K.off_dcoef, K.off_ext, level, c->kc, c->tabs, lg, c->bconv_mfma, c->stream);
             }, c->bconv_mfma ? nkb : 0);
         }
-        if (fuse_inner) {
-            // each launch (one per arithmetic kind of row) is timed on its own
-            const uint64_t* c1[PFT_MAX_ITEMS] = {};
-            if (fold)
-                for (uint32_t z = 0; z < n; ++z) c1[z] = rot->src.p[z] + nl;
-            auto inner = [&](hipStream_t st, uint32_t rows_sel) {
-                launch_row_inner(n, ws, off_d, K.off_ext, K.off_acc, key.data, level, c->kc, c->tabs,
-                                 c->fp_rows.data(), lg, c1, fold ? rot->kappa : 0, fold ? rot->kappa_inv : 0,
-                                 c->inner_pairs, st, hook(c), rows_sel);
-            };
-            // on the context's own stream the 60-bit rows run on the helper
-            // stream beside the fp64 rows, so that each launch fills the
-            // other's tail; the helper's work is joined back before ModDown
-            // (and before anything later reads the accumulators or the key).
-            // While this family is being timed per launch the two run one
-            // after the other, so that each launch's time is its own.
-            const bool split = c->inner_st && c->stream == c->home && !c->prof.on(PK_KEY_INNER) &&
-                               hipEventRecord(c->inner_fork, c->stream) == hipSuccess &&
-                               hipStreamWaitEvent(c->inner_st, c->inner_fork, 0) == hipSuccess;
-            if (split) {
-                inner(c->inner_st, ROW_INNER_INT);
-                inner(c->stream, ROW_INNER_FP);
-                if (hipEventRecord(c->inner_join, c->inner_st) != hipSuccess ||
-                    hipStreamWaitEvent(c->stream, c->inner_join, 0) != hipSuccess)
-                    (void)hipStreamSynchronize(c->inner_st);  // last resort: never read unfinished rows
-            } else {
-                inner(c->stream, ROW_INNER_ALL);
-            }
-        } else {
-            const uint32_t first = fuse ? 1u : 0u;
-            if (!full.empty())
-                ntt_jobs(c, full, rows - A, level, false, 0, nullptr, 0, first,
-                         fuse && fwd_col16_restricted(c, (uint64_t)full.size() * (rows - A)));
-            if (!last.empty())
-                ntt_jobs(c, last, rows - na_last, level, false, 0, nullptr, 0, first,
-                         fuse && fwd_col16_restricted(c, (uint64_t)last.size() * (rows - na_last)));
-            // key inner product over level + K rows: the key is read once per
-            // launch (shared by the batch); each item reads beta inputs and
-            // writes two outputs per row
-            const double key_once = beta <= 8 ? 1.0 : (double)n;
-            timed(c, PK_KEY_INNER,
-                  8.0 * N * ((double)beta * rows * n + 2.0 * beta * rows * key_once + 2.0 * rows * n),
-                  2.0 * N * beta * rows * n, [&] {
-                launch_key_inner_b(n, ws, off_d, K.off_ext, K.off_acc, key.data, level, c->kc, c->tabs, lg,
-                                   c->stream);
-            }, beta <= 8 ? beta : 0);
+    }
+    KsRows kr{};
+    if (merged) {
+        kr.base = ws.base;
+        kr.stride = ws.stride;
+        kr.off_d = off_d;
+        kr.off_ext = K.off_ext;
+        kr.off_acc = K.off_acc;
+        kr.off_conv = K.off_conv;
+        kr.key = key.data;
+        kr.gadget = c->gadget;
+        kr.gadget_fp = c->gadget + P->L;
+        kr.pinv = c->kc.down_pinv;
+        kr.pinv_fp = c->kc.down_pinv + P->L;
+        kr.level = level;
+        kr.mode = mode;
+        kr.has_add = has_add ? 1u : 0u;
+        kr.kappa = in.kappa;
+        kr.kappa_inv = in.kappa_inv;
+        for (uint32_t z = 0; z < n; ++z) {
+            kr.src[z] = src.p[z];
+            kr.src2[z] = src2.p[z];
+            kr.out[z] = out.p[z];
         }
+        // the special rows of both accumulators, ready for ModDown's conversion
+        launch_ks_rows(n, kr, true, c->kc, c->tabs, c->fp_rows.data(), lg, c->inner_pairs, c->stream, hook(c));
+    } else {
+        const uint32_t first = fuse ? 1u : 0u;
+        if (!full.empty())
+            ntt_jobs(c, full, rows - A, level, false, 0, nullptr, 0, first,
+                     fuse && fwd_col16_restricted(c, (uint64_t)full.size() * (rows - A)));
+        if (!last.empty())
+            ntt_jobs(c, last, rows - na_last, level, false, 0, nullptr, 0, first,
+                     fuse && fwd_col16_restricted(c, (uint64_t)last.size() * (rows - na_last)));
+        // key inner product over level + K rows: the key is read once per
+        // launch (shared by the batch); each item reads beta inputs and
+        // writes two outputs per row
+        const double key_once = beta <= 8 ? 1.0 : (double)n;
+        timed(c, PK_KEY_INNER,
+              8.0 * N * ((double)beta * rows * n + 2.0 * beta * rows * key_once + 2.0 * rows * n),
+              2.0 * N * beta * rows * n, [&] {
+            launch_key_inner_b(n, ws, off_d, K.off_ext, K.off_acc, key.data, level, c->kc, c->tabs, lg,
+                               c->stream);
+        }, beta <= 8 ? beta : 0);
     }
     // ModDown: the conversion of the special rows to the q-limbs is fused
     // with the first pass of conv's forward transform where its schedule
     // allows, and then also with the final pass of the special rows' inverse
-    // transform (as for ModUp); the forward transform of conv finishes
-    // ModDown in its final pass: out_b[i] = (acc_b[i] - conv_b[i]) P^-1 (+ add_b)
-    const uint32_t down_kb = (P->K + 1) / 2;
-    const bool fuse_down = c->bconv_mfma && c->bconv_fuse && lg >= 8 && down_kb <= 6 &&
-                           first_pass_col16(c, 2ull * n * level);
-    const bool ifuse_down = fuse_down && last_pass_col16(c, 2ull * n * P->K);
-    // special rows of both accumulators to coefficient form
-    {
+    // transform (as for ModUp)
+    const bool ifuse_down = merged || (fuse_down && last_pass_col16(c, 2ull * n * P->K));
+    if (!merged) {
+        // special rows of both accumulators to coefficient form
         std::vector<NttJob> jobs;
         for (uint32_t z = 0; z < n; ++z)
             for (uint32_t b = 0; b < 2; ++b)
@@ -1852,34 +1877,53 @@ static void key_switch_b(pft_ctx* c, uint32_t n, WsRef ws, const KsLayout& K, ui
             launch_moddown_conv_b(n, ws, K.off_acc, K.off_conv, level, c->kc, c->tabs, lg, c->bconv_mfma, c->stream);
         }, c->bconv_mfma ? down_kb : 0);
     }
-    {
-        std::vector<NttJob> jobs;
-        for (uint32_t z = 0; z < n; ++z)
-            for (uint32_t b = 0; b < 2; ++b)
-                jobs.push_back(NttJob{ws.base + z * ws.stride + K.off_conv + ((uint64_t)b * level << lg), 255u, 0u});
-        NttEpilogue epi{};
-        const uint64_t off_add[2] = {off_add0, off_add1};
-        const uint64_t off_add2[2] = {off_add0b, PFT_NO_OFFSET};
-        for (uint32_t b = 0; b < 2; ++b) {
-            const int64_t conv0 = (int64_t)(K.off_conv + ((uint64_t)b * level << lg));
-            epi.d_acc[b] = (int64_t)(K.off_acc + ((uint64_t)b * K.rows << lg)) - conv0;
-            epi.d_add[b] = off_add[b] == PFT_NO_OFFSET ? PFT_EPI_NO_ADD : (int64_t)off_add[b] - conv0;
-            epi.d_add2[b] = off_add2[b] == PFT_NO_OFFSET ? PFT_EPI_NO_ADD : (int64_t)off_add2[b] - conv0;
+    if (merged) {
+        auto finish = [&](hipStream_t st, uint32_t kinds) {
+            launch_ks_rows(n, kr, false, c->kc, c->tabs, c->fp_rows.data(), lg, c->inner_pairs, st, hook(c), kinds);
+        };
+        // on the context's own stream the 60-bit rows run on the helper
+        // stream beside the fp64 rows, so that each launch fills the
+        // other's tail; the helper's work is joined back before anything
+        // later reads the output or the key.  While this family is being
+        // timed per launch the two run one after the other, so that each
+        // launch's time is its own.
+        const bool split = c->inner_st && c->stream == c->home && !c->prof.on(PK_KEY_INNER) &&
+                           hipEventRecord(c->inner_fork, c->stream) == hipSuccess &&
+                           hipStreamWaitEvent(c->inner_st, c->inner_fork, 0) == hipSuccess;
+        if (split) {
+            finish(c->inner_st, KS_ROWS_INT);
+            finish(c->stream, KS_ROWS_FP);
+            if (hipEventRecord(c->inner_join, c->inner_st) != hipSuccess ||
+                hipStreamWaitEvent(c->stream, c->inner_join, 0) != hipSuccess)
+                (void)hipStreamSynchronize(c->inner_st);  // last resort: never read unfinished rows
+        } else {
+            finish(c->stream, KS_ROWS_ALL);
         }
-        for (uint32_t z = 0; z < n; ++z) epi.out[z] = out.p[z];
-        epi.pinv = c->kc.down_pinv;
-        epi.pinv_fp = c->kc.down_pinv + P->L;
-        epi.level = level;
-        if (fold) {
-            // the c0 image comes through the permutation in place of off_add0
-            epi.d_add[0] = PFT_EPI_NO_ADD;
-            for (uint32_t z = 0; z < n; ++z) epi.perm_src[z] = rot->src.p[z];
-            epi.kappa = rot->kappa;
-            epi.kappa_inv = rot->kappa_inv;
-        }
-        ntt_jobs(c, jobs, level, ~0u, false, 0, &epi, 0, fuse_down ? 1u : 0u,
-                 fuse_down && fwd_col16_restricted(c, 2ull * n * level));
+        return;
     }
+    // the forward transform of conv finishes ModDown in its final pass:
+    // out_b[i] = (acc_b[i] - conv_b[i]) P^-1 (+ addends)
+    std::vector<NttJob> jobs;
+    for (uint32_t z = 0; z < n; ++z)
+        for (uint32_t b = 0; b < 2; ++b)
+            jobs.push_back(NttJob{ws.base + z * ws.stride + K.off_conv + ((uint64_t)b * level << lg), 255u, 0u});
+    NttEpilogue epi{};
+    const uint64_t off_add[2] = {off_add0, PFT_NO_OFFSET};
+    for (uint32_t b = 0; b < 2; ++b) {
+        const int64_t conv0 = (int64_t)(K.off_conv + ((uint64_t)b * level << lg));
+        epi.d_acc[b] = (int64_t)(K.off_acc + ((uint64_t)b * K.rows << lg)) - conv0;
+        epi.d_add[b] = off_add[b] == PFT_NO_OFFSET ? PFT_EPI_NO_ADD : (int64_t)off_add[b] - conv0;
+    }
+    epi.has_add = has_add ? 1u : 0u;
+    for (uint32_t z = 0; z < n; ++z) {
+        epi.out[z] = out.p[z];
+        epi.src[z] = src2.p[z];
+    }
+    epi.pinv = c->kc.down_pinv;
+    epi.pinv_fp = c->kc.down_pinv + P->L;
+    epi.level = level;
+    ntt_jobs(c, jobs, level, ~0u, false, 0, &epi, 0, fuse_down ? 1u : 0u,
+             fuse_down && fwd_col16_restricted(c, 2ull * n * level));
 }
 
 // Items of one batched call grouped into launches of at most PFT_MAX_ITEMS
@@ -1968,9 +2012,12 @@ static int mul_relin_core(pft_ctx* c, uint32_t n, const pft_ct* a, const pft_ct*
             B.p[z] = b[g[z]].data;
             O.p[z] = out[g[z]].data;
         }
-        timed(c, PK_TENSOR, 8.0 * nl * 7 * cnt, 4.0 * nl * cnt,
-              [&] { launch_tensor_b(cnt, A, B, ws, 0, l, c->tabs, P->log_n, c->stream); });
-        key_switch_b(c, cnt, ws, K, 2 * nl, c->rlk, 0, nl, O);
+        KsInput ki{};
+        ki.mode = KS_PRODUCT;
+        ki.src = A;
+        ki.src2 = B;
+        ki.overlap = ks_overlap(cnt, O, A, 2 * nl) || ks_overlap(cnt, O, B, 2 * nl);
+        key_switch_b(c, cnt, ws, K, c->rlk, ki, O);
         for (uint32_t z = 0; z < cnt; ++z) {
             out[g[z]].level = l;
             out[g[z]].scale = a[g[z]].scale * b[g[z]].scale;
@@ -2033,7 +2080,7 @@ extern "C" int pft_rescale_batch(pft_ctx* c, uint32_t n, const pft_ct* in, uint3
         NttEpilogue epi{};
         for (uint32_t b = 0; b < 2; ++b) {
             epi.d_acc[b] = PFT_EPI_ITEM_ACC;
-            epi.d_add[b] = epi.d_add2[b] = PFT_EPI_NO_ADD;
+            epi.d_add[b] = PFT_EPI_NO_ADD;
         }
         for (uint32_t z = 0; z < cnt; ++z) {
             epi.out[z] = O.p[z];
@@ -2160,8 +2207,13 @@ extern "C" int pft_rotate_batch(pft_ctx* c, uint32_t n, const pft_ct* in, int32_
             I.p[z] = in[g[z]].data;
             O.p[z] = out[g[z]].data;
         }
-        KsRot kr{kappa, kappa_inv, I};
-        key_switch_b(c, cnt, ws, K, nl, *key, 0, PFT_NO_OFFSET, O, PFT_NO_OFFSET, &kr);
+        KsInput ki{};
+        ki.mode = KS_ROTATE;
+        ki.src = I;
+        ki.overlap = ks_overlap(cnt, O, I, 2 * nl);
+        ki.kappa = kappa;
+        ki.kappa_inv = kappa_inv;
+        key_switch_b(c, cnt, ws, K, *key, ki, O);
         for (uint32_t z = 0; z < cnt; ++z) {
             out[g[z]].level = l;
             out[g[z]].scale = in[g[z]].scale;
@@ -2215,8 +2267,13 @@ extern "C" int pft_rotate_pow2_batch(pft_ctx* c, uint32_t n, const pft_ct* in, i
             int ke;
             const SwitchKeyDev* rk = use_rot(c, (int32_t)(1u << k), &ke);
             if (!rk) return ke;
-            KsRot kr{kappa, galois_inverse(kappa, P->n), ws_items(ws, cnt, src)};
-            key_switch_b(c, cnt, ws, K, dst + nl, *rk, dst, PFT_NO_OFFSET, ws_items(ws, cnt, dst), PFT_NO_OFFSET, &kr);
+            KsInput ki{};
+            ki.mode = KS_ROTATE;
+            ki.off_pre = dst;
+            ki.src = ws_items(ws, cnt, src);
+            ki.kappa = kappa;
+            ki.kappa_inv = galois_inverse(kappa, P->n);
+            key_switch_b(c, cnt, ws, K, *rk, ki, ws_items(ws, cnt, dst));
             cur = 1 - cur;
         }
         launch_copy_rows_b(cnt, ws_items(ws, cnt, offs[cur]), 0, O, 0, 2 * l, lg, c->stream);
@@ -2269,8 +2326,14 @@ extern "C" int pft_total_sum_batch(pft_ctx* c, uint32_t n, const pft_ct* in, uin
             int ke;
             const SwitchKeyDev* rk = use_rot(c, (int32_t)s, &ke);
             if (!rk) return ke;
-            KsRot kr{kappa, galois_inverse(kappa, P->n), ws_items(ws, cnt, a)};
-            key_switch_b(c, cnt, ws, K, b + nl, *rk, b, a + nl, ws_items(ws, cnt, b), a, &kr);
+            KsInput ki{};
+            ki.mode = KS_ROTATE;
+            ki.off_pre = b;
+            ki.src = ki.src2 = ws_items(ws, cnt, a);
+            ki.has_add = true;
+            ki.kappa = kappa;
+            ki.kappa_inv = galois_inverse(kappa, P->n);
+            key_switch_b(c, cnt, ws, K, *rk, ki, ws_items(ws, cnt, b));
             std::swap(a, b);
         }
         launch_copy_rows_b(cnt, ws_items(ws, cnt, a), 0, O, 0, 2 * l, lg, c->stream);
@@ -2800,7 +2863,13 @@ extern "C" int pft_ctmatvec(pft_ctx* c, uint32_t n_o, uint32_t n_i, uint32_t n_i
             for (uint32_t g = 0; g < n_g; ++g) {
                 ItemPtrs O{};
                 for (uint32_t u = 0; u < cnt; ++u) O.p[u] = A + (z0 + u) * stride + off_acc + (g0 + g) * ct_words;
-                key_switch_b(c, cnt, WsRef{c->ws + (size_t)g * cnt * K.end, K.end}, K, 2 * nl, c->rlk, 0, nl, O);
+                const WsRef wg{c->ws + (size_t)g * cnt * K.end, K.end};
+                KsInput ki{};
+                ki.mode = KS_WS;
+                ki.off_d = 2 * nl;
+                ki.src2 = ws_items(wg, cnt);
+                ki.has_add = true;
+                key_switch_b(c, cnt, wg, K, c->rlk, ki, O);
             }
         }
     }

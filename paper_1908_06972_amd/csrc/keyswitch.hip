@@ -1,0 +1,465 @@
+// keyswitch.hip -- the fused kernels of hybrid key switching around the base
+// conversions: everything between ModUp's rows and the finished ciphertext
+// in two launches.
+//
+// The conversion kernels (ntt.hip) leave every extended row after the first
+// (radix-16 column) pass of its forward transform, so each still needs one
+// row pass of LOG_M = log_n - 4 stages, over tiles that no other tile
+// touches.  All that follows is tile-local as well: the products with the
+// key, ModDown's subtraction, the addends.  So a workgroup takes one tile of
+// one row of one item through the whole of it, in registers:
+//   * k_ks_rows<.., SPECIAL true>, the K special rows: every digit through
+//     the row pass, products with the key summed into two accumulators, and
+//     the accumulators through the row pass of the inverse transform that
+//     ModDown's conversion needs (it applies the last pass itself);
+//   * k_ks_rows<.., SPECIAL false>, the ciphertext rows, once the conversion
+//     of the special rows is there: the digits and their products as above,
+//     the two converted rows through their row pass, and the output
+//     out_b = (acc_b - conv_b) P^-1.  An addend enters the accumulators as P
+//     times itself, so the output is (acc_b - conv_b) P^-1 + add_b.
+// No accumulator of a ciphertext row, no transformed row and no tensor of a
+// product (d0, d1, d2 below) goes to memory.
+#include "ntt_device.h"
+#include "pft_device.h"
+#include "pft_kernels.h"
+
+#include <algorithm>
+#include <cstdio>
+#include <cstdlib>
+#include <type_traits>
+#include <vector>
+
+namespace {
+
+// Twiddles of the next register phase loaded ahead of an exchange (PhaseTw):
+// more spill at four waves per SIMD.
+constexpr int TW_PRE_FP2 = 3;
+constexpr int TW_PRE_FP1 = 1;
+constexpr int TW_PRE_INT = 1;
+
+// One tile's work (see the head of this file).  FP (rows with q < 2^50, the
+// key holding integer-valued doubles): every product is an fmulmod against
+// the quotient w (1/q); a term lies within 0.9q, an addend's P product
+// within q, and the accumulators are reduced to within q/2 after the own
+// digit and the addends, so with at most 7 further terms they stay below
+// 6.8q < 2^53.  Otherwise the Montgomery products with the key (stored times
+// 2^64) are summed without REDC's final subtraction (terms below 2q) onto
+// accumulators brought below 2q after the own digit and the addends: with at
+// most 7 further terms below 16q < 2^64, reduced once at the end.
+//
+// G digits go through the row pass together (G = 2: each twiddle load and
+// each LDS barrier serves two tiles, and their butterflies are independent
+// instruction streams); the two converted rows of the output are such a pair
+// too.
+template <int LOG_M, int EB, int TB, bool FP, int G, bool SPECIAL>
+__device__ __forceinline__ void ks_row(const KsRows& a, uint64_t* lds, uint32_t z, uint32_t tile, uint32_t t,
+                                       uint32_t mi, const DevMod& md, const TwPair* __restrict__ tw,
+                                       const TwPair* __restrict__ tw_inv, uint32_t log_n) {
+    constexpr int M = 1 << LOG_M;
+    constexpr int E = 1 << EB;
+    constexpr uint32_t NT = (1u << TB) >> EB;
+    constexpr int T = M / E;
+    constexpr int C = NT / T;
+    constexpr int NPH = (LOG_M + EB - 1) / EB;
+    using PIN = Phase<LOG_M, 0, EB>;
+    using POUT = Phase<LOG_M, NPH - 1, EB>;
+    static_assert(PIN::WLO >= 4, "the row pass reads its input directly");
+    static_assert(POUT::WLO == 0, "each thread ends with E consecutive words");
+    static_assert(G == 1 || G == 2, "one or two tiles per row pass");
+    constexpr int PRE = FP ? (G == 2 ? TW_PRE_FP2 : TW_PRE_FP1) : TW_PRE_INT;
+
+    const uint32_t tid = threadIdx.x;
+    const uint64_t q = md.q, two_q = md.two_q;
+    const double qd = md.qd, qinv = md.qinv;
+    const TwPair* __restrict__ twt = tw + ((size_t)mi << log_n);
+    const uint32_t s0 = log_n - LOG_M;
+    const uint32_t sp0 = tile * (uint32_t)C;
+    const uint32_t c = C == 1 ? 0u : tid / T;
+    const uint32_t l = C == 1 ? tid : tid % T;
+    uint64_t* __restrict__ item = a.base + (size_t)z * a.stride;
+    // this thread's E consecutive words of the row: [w0, w0 + E)
+    const size_t w0 = ((size_t)(sp0 + c) << LOG_M) + (size_t)l * E;
+
+    auto load_vec = [&](const uint64_t* __restrict__ p, uint64_t (&v)[E]) {
+        const ulonglong2* __restrict__ pv = reinterpret_cast<const ulonglong2*>(p + w0);
+#pragma unroll
+        for (int e = 0; e < E / 2; ++e) {
+            const ulonglong2 u = pv[e];
+            v[2 * e] = u.x;
+            v[2 * e + 1] = u.y;
+        }
+    };
+    uint64_t acc0[E], acc1[E];  // FP: doubles; otherwise residues
+#pragma unroll
+    for (int e = 0; e < E; ++e) acc0[e] = acc1[e] = 0;  // also the bits of +0.0
+    // acc += x k, one residue
+    auto mac1 = [&](uint64_t x, uint64_t k, uint64_t& acc) {
+        if constexpr (FP) {
+#pragma clang fp contract(off)
+            const double w = as_f(k);
+            acc = as_u(as_f(acc) + fmulmod(as_f(x), w, w * qinv, qd));
+        } else {
+            // REDC without its final subtraction: each term lies in [0, 2q)
+            const uint64_t lo = x * k, m = lo * md.mont_neg_qinv;
+            acc += mulhi64(x, k) + mulhi64(m, q) + (lo != 0 ? 1u : 0u);
+        }
+    };
+    // acc_b += x k, k the key tile key_{j,b}[t] of this thread's words
+    auto mac = [&](const uint64_t (&x)[E], uint32_t j, int b, uint64_t (&acc)[E]) {
+        uint64_t k[E];
+        load_vec(a.key + ((size_t)((2 * j + b) * a.krows + mi) << log_n), k);
+#pragma unroll
+        for (int e = 0; e < E; ++e) mac1(x[e], k[e], acc[e]);
+    };
+    auto accumulate = [&](const uint64_t (&x)[E], uint32_t j) {
+        mac(x, j, 0, acc0);
+        mac(x, j, 1, acc1);
+    };
+    // a row after the conversion kernel's column pass into x
+    auto load_row = [&](const uint64_t* __restrict__ src, uint64_t (&x)[E]) {
+#pragma unroll
+        for (int e = 0; e < E; ++e) x[e] = src[((size_t)(sp0 + c) << LOG_M) | PIN::r_of(l, e)];
+    };
+    auto ext = [&](uint32_t j) { return item + a.off_ext + ((size_t)(j * a.rows + t) << log_n); };
+    // an integer accumulator below 16q brought below q
+    [[maybe_unused]] auto settle_acc = [&](uint64_t v) -> uint64_t {
+#pragma unroll
+        for (int sh = 3; sh >= 0; --sh) {
+            const uint64_t m = q << sh;
+            v = v >= m ? v - m : v;
+        }
+        return v;
+    };
+    // the row pass's output brought within q/2 (FP) or below q
+    auto settle = [&](uint64_t (&x)[E]) {
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            if constexpr (FP) {
+                x[e] = as_u(freduce(as_f(x[e]), qd, qinv));
+            } else {
+                const uint64_t v = x[e] >= two_q ? x[e] - two_q : x[e];
+                x[e] = v >= q ? v - q : v;
+            }
+        }
+    };
+    // One or two rows through the row pass.  The twiddles and their addresses
+    // are the same for every row; an opaque zero offset of their base and
+    // opaque copies of the lane indices keep the compiler from holding all of
+    // them in registers from one row to the next (they are recomputed and
+    // reloaded).  The offset, not the pointer, is hidden, so the loads stay
+    // global (not flat) loads.
+    auto pass_1 = [&](uint64_t (&x)[E]) {
+        uint32_t zoff = 0, lj = l, cj = c;
+        asm volatile("" : "+v"(zoff), "+v"(lj), "+v"(cj));
+        run_phases<LOG_M, EB, false, FP, false, 0, false, PRE, TB>(x, lds, cj, lj, sp0 + c, s0, twt + zoff, md);
+        __syncthreads();  // the next row's exchanges reuse the LDS
+    };
+    [[maybe_unused]] auto pass_2 = [&](uint64_t (&x)[2][E]) {
+        uint32_t zoff = 0, lj = l, cj = c;
+        asm volatile("" : "+v"(zoff), "+v"(lj), "+v"(cj));
+        run_phases_g<LOG_M, EB, 2, FP, 0, PRE, TB>(x, lds, cj, lj, sp0 + c, s0, twt + zoff, md);
+        __syncthreads();
+    };
+    auto digit_1 = [&](uint32_t j) {
+        uint64_t x[E];
+        load_row(ext(j), x);
+        pass_1(x);
+        settle(x);
+        accumulate(x, j);
+    };
+    [[maybe_unused]] auto digit_2 = [&](uint32_t j1, uint32_t j2) {
+        uint64_t x[2][E];
+        load_row(ext(j1), x[0]);
+        load_row(ext(j2), x[1]);
+        pass_2(x);
+        settle(x[0]);
+        accumulate(x[0], j1);
+        settle(x[1]);
+        accumulate(x[1], j2);
+    };
+
+    uint32_t jo = ~0u;  // the digit whose own rows include t: d itself, no transform needed
+    if constexpr (!SPECIAL) {
+        jo = t / a.alpha;
+        const size_t row0 = (size_t)t << log_n, row1 = (size_t)(a.level + t) << log_n;
+        const TwPair pm = FP ? a.gadget_fp[t] : a.gadget[t];  // P mod q
+        // acc_b += P s for s = an addend, canonical (FP: as a double, or a sum of two such or of two products)
+        auto add_p = [&](uint64_t s, uint64_t& acc) {
+            if constexpr (FP) {
+#pragma clang fp contract(off)
+                acc = as_u(as_f(acc) + fmulmod(as_f(s), as_f(pm.w), as_f(pm.wp), qd));
+            } else {
+                acc += shoup_lazy(s, pm.w, pm.wp, q);
+            }
+        };
+        if (a.mode == KS_PRODUCT) {
+            // d2 = a1 b1 is switched; d0 = a0 b0 and d1 = a0 b1 + a1 b0 are added
+            const uint64_t* __restrict__ A = a.src[z];
+            const uint64_t* __restrict__ B = a.src2[z];
+            const uint64_t* __restrict__ k0 = a.key + ((size_t)(2 * jo * a.krows + mi) << log_n) + w0;
+            const uint64_t* __restrict__ k1 = k0 + ((size_t)a.krows << log_n);
+            // two words of every operand at a time; the scheduling barrier
+            // after each half of them bounds the loads in flight (registers)
+#pragma unroll
+            for (int e = 0; e < E; e += 2) {
+                auto two = [&](const uint64_t* __restrict__ p) { return *reinterpret_cast<const ulonglong2*>(p + e); };
+                const ulonglong2 va1 = two(A + row1 + w0), vb1 = two(B + row1 + w0), va0 = two(A + row0 + w0),
+                                 vb0 = two(B + row0 + w0), vk0 = two(k0), vk1 = two(k1);
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const uint64_t a1 = h ? va1.y : va1.x, b1 = h ? vb1.y : vb1.x, a0 = h ? va0.y : va0.x,
+                                   b0 = h ? vb0.y : vb0.x, w0k = h ? vk0.y : vk0.x, w1k = h ? vk1.y : vk1.x;
+                    if constexpr (FP) {
+#pragma clang fp contract(off)
+                        const double x1 = as_f(fp_from_u64(a1)), y1 = as_f(fp_from_u64(b1));
+                        const double x0 = as_f(fp_from_u64(a0)), y0 = as_f(fp_from_u64(b0));
+                        const double y1q = y1 * qinv, y0q = y0 * qinv;
+                        const uint64_t d2 = as_u(fmulmod(x1, y1, y1q, qd));
+                        mac1(d2, w0k, acc0[e + h]);
+                        mac1(d2, w1k, acc1[e + h]);
+                        add_p(as_u(fmulmod(x0, y0, y0q, qd)), acc0[e + h]);
+                        add_p(as_u(fmulmod(x0, y1, y1q, qd) + fmulmod(x1, y0, y0q, qd)), acc1[e + h]);
+                    } else {
+                        const uint64_t d2 = mul_barrett(a1, b1, md);
+                        mac1(d2, w0k, acc0[e + h]);
+                        mac1(d2, w1k, acc1[e + h]);
+                        add_p(mul_barrett(a0, b0, md), acc0[e + h]);
+                        add_p(mul_barrett(a0, b1, md) + mul_barrett(a1, b0, md), acc1[e + h]);
+                    }
+                }
+                if ((e & 2) != 0) __builtin_amdgcn_sched_barrier(0);
+            }
+        } else {
+            uint64_t x[E];
+            if (a.mode == KS_ROTATE) {
+                // d = X^kappa image of c1's row t, its tile staged in LDS; the
+                // image of c0's row is added
+                galois_tile_to_lds<LOG_M, EB, TB>(a.src[z] + row1, tile, log_n, a.kappa, a.kappa_inv, lds, FP);
+#pragma unroll
+                for (int e = 0; e < E; ++e) x[e] = lds[lds_at<LOG_M, EB>(c, l * (uint32_t)E + (uint32_t)e)];
+                __syncthreads();
+                accumulate(x, jo);
+                galois_tile_to_lds<LOG_M, EB, TB>(a.src[z] + row0, tile, log_n, a.kappa, a.kappa_inv, lds, FP);
+#pragma unroll
+                for (int e = 0; e < E; ++e)
+                    add_p(lds[lds_at<LOG_M, EB>(c, l * (uint32_t)E + (uint32_t)e)], acc0[e]);
+                __syncthreads();  // the digits' exchanges reuse the LDS
+            } else {
+                load_vec(item + a.off_d + row0, x);
+                if constexpr (FP) {
+#pragma unroll
+                    for (int e = 0; e < E; ++e) x[e] = fp_from_u64(x[e]);
+                }
+                accumulate(x, jo);
+            }
+            if (a.has_add) {
+                const uint64_t* A = a.src2[z];  // may be the output: each word is read before it is written
+                uint64_t s[E];
+                load_vec(A + row0, s);
+#pragma unroll
+                for (int e = 0; e < E; ++e) add_p(FP ? fp_from_u64(s[e]) : s[e], acc0[e]);
+                load_vec(A + row1, s);
+#pragma unroll
+                for (int e = 0; e < E; ++e) add_p(FP ? fp_from_u64(s[e]) : s[e], acc1[e]);
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            if constexpr (FP) {
+                acc0[e] = as_u(freduce(as_f(acc0[e]), qd, qinv));
+                acc1[e] = as_u(freduce(as_f(acc1[e]), qd, qinv));
+            } else {
+                // at most three terms below 2q
+                for (int k = 0; k < 2; ++k) {
+                    acc0[e] = acc0[e] >= two_q ? acc0[e] - two_q : acc0[e];
+                    acc1[e] = acc1[e] >= two_q ? acc1[e] - two_q : acc1[e];
+                }
+            }
+        }
+    }
+    // every other digit through the row pass, G at a time (uniform control
+    // flow: t, level, alpha and beta are the same for the whole workgroup)
+    uint32_t pend = ~0u;
+    for (uint32_t j = 0; j < a.beta; ++j) {
+        if (j == jo) continue;
+        if constexpr (G == 1) {
+            digit_1(j);
+        } else {
+            if (pend == ~0u) {
+                pend = j;
+                continue;
+            }
+            digit_2(pend, j);
+            pend = ~0u;
+        }
+    }
+    if (pend != ~0u) digit_1(pend);
+
+    if constexpr (SPECIAL) {
+        // both accumulators through the row pass of their inverse transform
+        const TwPair* __restrict__ twi = tw_inv + ((size_t)mi << log_n);
+        auto finish = [&](uint64_t (&acc)[E], uint32_t b) {
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                if constexpr (FP)
+                    acc[e] = as_u(freduce(as_f(acc[e]), qd, qinv));
+                else
+                    acc[e] = settle_acc(acc[e]);
+            }
+            uint32_t zoff = 0, lj = l, cj = c;
+            asm volatile("" : "+v"(zoff), "+v"(lj), "+v"(cj));
+            run_phases<LOG_M, EB, true, FP, false, 0, false, PRE, TB>(acc, lds, cj, lj, sp0 + cj, s0, twi + zoff, md);
+            uint64_t* __restrict__ o = item + a.off_acc + ((size_t)(b * a.rows + t) << log_n);
+#pragma unroll
+            for (int e = 0; e < E; ++e) o[((size_t)(sp0 + cj) << LOG_M) | PIN::r_of(lj, e)] = acc[e];
+        };
+        finish(acc0, 0);
+        __syncthreads();
+        finish(acc1, 1);
+    } else {
+        const TwPair pinv = FP ? a.pinv_fp[t] : a.pinv[t];  // P^-1 mod q
+        // x: the transformed converted row; the result to row t of polynomial b
+        auto finish = [&](const uint64_t (&x)[E], const uint64_t (&acc)[E], uint32_t b) {
+            ulonglong2* __restrict__ o =
+                reinterpret_cast<ulonglong2*>(a.out[z] + ((size_t)(b * a.level + t) << log_n) + w0);
+            uint64_t r[E];
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                if constexpr (FP) {
+#pragma clang fp contract(off)
+                    // acc within q/2, the converted row within 4.5q
+                    const double y = freduce(as_f(acc[e]), qd, qinv) - as_f(x[e]);
+                    r[e] = fp_to_u64(as_u(fmulmod(y, as_f(pinv.w), as_f(pinv.wp), qd)), qd, qinv);
+                } else {
+                    const uint64_t v = x[e] >= two_q ? x[e] - two_q : x[e];
+                    r[e] = shoup(settle_acc(acc[e]) + q - (v >= q ? v - q : v), pinv.w, pinv.wp, q);
+                }
+            }
+#pragma unroll
+            for (int e = 0; e < E / 2; ++e) {
+                ulonglong2 v;
+                v.x = r[2 * e];
+                v.y = r[2 * e + 1];
+                o[e] = v;
+            }
+        };
+        auto conv = [&](uint32_t b) { return item + a.off_conv + ((size_t)(b * a.level + t) << log_n); };
+        if constexpr (G == 2) {
+            uint64_t x[2][E];
+            load_row(conv(0), x[0]);
+            load_row(conv(1), x[1]);
+            pass_2(x);
+            finish(x[0], acc0, 0);
+            finish(x[1], acc1, 1);
+        } else {
+            uint64_t x[E];
+            load_row(conv(0), x);
+            pass_1(x);
+            finish(x, acc0, 0);
+            load_row(conv(1), x);
+            pass_1(x);
+            finish(x, acc1, 1);
+        }
+    }
+}
+
+// Block order: blocks are issued to the eight XCDs round-robin; block id
+// 8 k + x runs item k mod n of the (row, tile) pair 8 floor(k / n) + x, so
+// the items sharing one key tile run on one XCD at about the same time and
+// the tile comes from HBM about once per launch, then from that XCD's L2.
+template <int LOG_M, int EB, int TB, bool FP, int G, bool SPECIAL>
+__global__ __launch_bounds__((1 << TB) >> EB) __attribute__((amdgpu_waves_per_eu(4)))
+void k_ks_rows(KsRows a, const DevMod* __restrict__ mods, const TwPair* __restrict__ tw,
+               const TwPair* __restrict__ tw_inv, uint32_t log_n) {
+    __shared__ uint64_t lds[(FP ? G : 1) * lds_words<LOG_M, EB, TB>()];
+    const uint32_t kx = blockIdx.x >> 3;
+    const uint32_t z = kx % a.n_items;
+    const uint32_t pair = (kx / a.n_items) * 8u + (blockIdx.x & 7u);
+    if (pair >= a.tiles * a.n_rows) return;  // whole workgroup, before any barrier
+    const uint32_t tile = pair % a.tiles;
+    const uint32_t t = a.row[pair / a.tiles];
+    const uint32_t mi = t < a.level ? t : a.L + (t - a.level);
+    ks_row<LOG_M, EB, TB, FP, G, SPECIAL>(a, lds, z, tile, t, mi, mods[mi], tw, tw_inv, log_n);
+}
+
+}  // namespace
+
+bool ks_rows_supported(uint32_t log_n) {
+    const uint32_t r = log_n - 4;
+    return r >= 8 && r <= 12;
+}
+
+void launch_ks_rows(uint32_t n, KsRows a, bool special, const KsConsts& kc, const DevTables& t,
+                    const uint32_t* fp_rows, uint32_t log_n, bool pair_digits, hipStream_t st, ProfHook* prof,
+                    uint32_t rows_sel) {
+    const uint32_t level = a.level;
+    a.n_items = n;
+    a.rows = level + kc.K;
+    a.alpha = kc.alpha;
+    a.beta = (level + kc.alpha - 1) / kc.alpha;
+    // the integer accumulators hold at most 8 terms below 2q (callers check)
+    if (a.beta > 8) {
+        fprintf(stderr, "launch_ks_rows: %u digits, at most 8 supported\n", a.beta);
+        abort();
+    }
+    a.L = kc.L;
+    a.krows = kc.L + kc.K;
+    for (int fp = 1; fp >= 0; --fp) {
+        if (!(rows_sel & (fp ? KS_ROWS_FP : KS_ROWS_INT))) continue;
+        // the rows of one arithmetic kind, in chunks that fit the row list
+        std::vector<uint16_t> rows;
+        for (uint32_t r = special ? level : 0; r < (special ? a.rows : level); ++r) {
+            const uint32_t mi = r < level ? r : kc.L + (r - level);
+            if ((int)fp_rows[mi] == fp) rows.push_back((uint16_t)r);
+        }
+        for (size_t r0 = 0; r0 < rows.size(); r0 += PFT_ROW_LIST) {
+            a.n_rows = (uint32_t)std::min<size_t>(PFT_ROW_LIST, rows.size() - r0);
+            for (uint32_t i = 0; i < a.n_rows; ++i) a.row[i] = rows[r0 + i];
+            // method bytes: the operands and the finished rows per item, the
+            // key rows once (extended and converted rows are pass boundaries);
+            // work: the row passes' butterflies and the products
+            const double N = (double)(1u << log_n), lm = (double)(log_n - 4);
+            const double in = special ? 0.0 : a.mode == KS_PRODUCT ? 4.0 : a.mode == KS_ROTATE ? 2.0 : 1.0;
+            const double io = in + (special ? 0.0 : 2.0 + (a.has_add ? 2.0 : 0.0));
+            const double bytes = 8.0 * N * a.n_rows * (n * io + 2.0 * a.beta);
+            const double ops = N * n * a.n_rows * (0.5 * lm * (a.beta + (special ? 2.0 : 1.0)) + 2.0 * a.beta);
+            const bool g2 = fp && pair_digits && !special;
+            if (prof) prof->begin(PK_KEY_INNER, st);
+            // A tile is one row-pass problem, at least 1024 words: the
+            // smallest that fills a wavefront pair with 8 residues per thread.
+            auto go = [&](auto lmc, auto tbc) {
+                constexpr int LM = decltype(lmc)::value, TB = decltype(tbc)::value, EB = 3;
+                a.tiles = (1u << log_n) >> TB;
+                const dim3 grid(8u * n * ((a.tiles * a.n_rows + 7u) / 8u)), block((1u << TB) >> EB);
+                auto run = [&](auto fpc, auto gc, auto spc) {
+                    hipLaunchKernelGGL(
+                        (k_ks_rows<LM, EB, TB, decltype(fpc)::value, decltype(gc)::value, decltype(spc)::value>), grid,
+                        block, 0, st, a, t.mods, t.tw_fwd, t.tw_inv, log_n);
+                };
+                using one = std::integral_constant<int, 1>;
+                using two = std::integral_constant<int, 2>;
+                if (special)
+                    fp ? run(std::true_type{}, one{}, std::true_type{}) : run(std::false_type{}, one{}, std::true_type{});
+                else if (g2)
+                    run(std::true_type{}, two{}, std::false_type{});
+                else
+                    fp ? run(std::true_type{}, one{}, std::false_type{}) : run(std::false_type{}, one{}, std::false_type{});
+            };
+            auto by = [&](auto lmc) {
+                constexpr int LM = decltype(lmc)::value;
+                go(lmc, std::integral_constant<int, (LM > 10 ? LM : 10)>{});
+            };
+            switch (log_n - 4) {
+                case 8: by(std::integral_constant<int, 8>{}); break;
+                case 9: by(std::integral_constant<int, 9>{}); break;
+                case 10: by(std::integral_constant<int, 10>{}); break;
+                case 11: by(std::integral_constant<int, 11>{}); break;
+                case 12: by(std::integral_constant<int, 12>{}); break;
+                default: break;
+            }
+            if (prof)
+                prof->end(PK_KEY_INNER, bytes, ops,
+                          1024u + (log_n - 4) + (fp ? 64u : 0u) + (g2 ? 128u : 0u) + (special ? 256u : 0u), st);
+        }
+    }
+}

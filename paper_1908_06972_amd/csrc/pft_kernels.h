@@ -41,38 +41,41 @@ struct NttSchedule {
 // Epilogue of a forward transform's final pass that finishes ModDown in
 // place of storing the transform: for transformed row i of polynomial p =
 // 2 z + b (z the item, b in {0, 1}) it writes
-//   out_z[b][i] = (acc - conv) P^-1 mod q_i (+ add) (+ add2)
-// where conv is the transformed value and acc / add / add2 sit at word
-// offsets d_acc[b] / d_add[b] / d_add2[b] from it (PFT_EPI_NO_ADD: no
-// addend), or acc is row i of polynomial b of an item's own ciphertext
-// (PFT_EPI_ITEM_ACC; RESCALE uses this with P^-1 replaced by q_last^-1).  out
-// may coincide with an addend (each element is read before it is written).
+//   out_z[b][i] = (acc - conv) P^-1 mod q_i (+ add) (+ row i of src[z][b])
+// where conv is the transformed value and acc / add sit at word offsets
+// d_acc[b] / d_add[b] from it (PFT_EPI_NO_ADD: no addend), or acc is row i of
+// polynomial b of an item's own ciphertext (PFT_EPI_ITEM_ACC; RESCALE uses
+// this with P^-1 replaced by q_last^-1); with has_add the ciphertext src[z]
+// ([2][level][N]) is added.  out may coincide with an addend (each element is
+// read before it is written).
+// For an inverse transform only `source` and the fields it names are used.
 #define PFT_EPI_NO_ADD INT64_MIN
 #define PFT_EPI_ITEM_ACC (INT64_MIN + 1)
+// Where the first pass of an inverse transform takes polynomial p's input:
+// its own rows (src_delta words past them), row i of src[p] ([level][N], NTT
+// domain) under X -> X^kappa (kappa_inv = kappa^-1 mod 2N), or the product
+// of rows i of src[p] and src2[p].
+enum : uint32_t { NTT_SRC_SELF = 0, NTT_SRC_PERM = 1, NTT_SRC_PROD = 2 };
 struct NttEpilogue {
     int64_t d_acc[2];   // or PFT_EPI_ITEM_ACC: acc of item z at acc_item[z] + (b acc_level + i) N
     int64_t d_add[2];
-    int64_t d_add2[2];  // a second addend, or PFT_EPI_NO_ADD
     uint64_t* out[PFT_MAX_POLYS / 2];  // per item of the launch: [2][level][N]
     const uint64_t* acc_item[PFT_MAX_POLYS / 2];
     uint32_t acc_level;
+    uint32_t has_add;
     const TwPair* pinv;                // [L]: P^-1 mod q_i (Shoup pairs)
     const TwPair* pinv_fp;             // [L]: the same as (w, w/q) doubles, used where q_i < 2^50
     uint32_t level;
-    // X -> X^kappa (kappa = 0: none) folded into a row pass: the first pass
-    // of an inverse transform reads row i of polynomial p from perm_src[p]
-    // + i N through the permutation; a forward epilogue adds, for the first
-    // polynomial of item z, row i of perm_src[z] through the permutation.
-    // kappa_inv = kappa^-1 mod 2N.
-    const uint64_t* perm_src[PFT_MAX_POLYS / 2];
+    uint32_t source;
+    const uint64_t* src[PFT_MAX_POLYS / 2];
+    const uint64_t* src2[PFT_MAX_POLYS / 2];
     uint64_t kappa, kappa_inv;
 };
 bool ntt_supported(uint32_t log_n);
 int ntt_candidates(uint32_t log_n, NttSchedule* out, int max_out);
 bool ntt_schedule_valid(uint32_t log_n, const NttSchedule& s);
-// epi, forward: finish ModDown in the final pass instead of storing (and
-// add the permuted addend when epi->kappa is set); inverse: only
-// epi->kappa / perm_src are used, by the first pass.
+// epi, forward: finish ModDown in the final pass instead of storing;
+// inverse: where the first pass takes its input.
 // first: a forward transform starts at pass `first` of the schedule (the
 // earlier passes already applied, e.g. by launch_modup_col_b); an inverse
 // transform stops before pass `first` (the remaining passes applied by the
@@ -174,40 +177,53 @@ void launch_moddown_col_b(uint32_t n, WsRef ws, uint64_t off_acc, uint64_t off_c
 // same way: tmp holds the output of the first transform pass.
 void launch_rescale_col_b(uint32_t n, WsRef ws, uint64_t off_last, uint64_t off_tmp, uint32_t level, uint32_t mode,
                           const DevTables& t, uint32_t log_n, hipStream_t st);
-// The key inner product fused with the remaining (row) pass of the forward
-// transform of ModUp's rows, for the items of a batch (ntt.hip): ext holds
-// the rows after the first pass of a (4, log_n - 4) schedule (as
-// launch_modup_col_b leaves them), d the NTT-domain input; writes
-// acc [2][level+K][N].  Needs row_inner_supported(log_n) and at most 8
-// digits; fp_rows[m] (host, by modulus index) is 1 where modulus m runs
-// fp64 arithmetic (one launch per kind).  kappa != 0: d is not read; its
-// own rows are the X -> X^kappa image of the rows of perm_src[z] (host
-// array of n device pointers, item z's input polynomial [level][N], NTT
-// domain), taken through the permutation as they are loaded.  pair_digits:
-// the fp64 rows take two digits through each row pass together (same
-// results).  prof: each launch (one per arithmetic kind) is timed as a
-// PK_KEY_INNER variant 1024 + (log_n - 4) (+ 64 fp64 rows, + 128 digit pairs).
+// The two launches of hybrid key switching around ModDown's conversion, fused
+// with the remaining (row) passes of the transforms (keyswitch.hip): ext holds
+// ModUp's rows after the first pass of a (4, log_n - 4) schedule (as
+// launch_modup_col_b leaves them), conv ModDown's.  special: the special rows
+// of acc_b = sum_j x_j key_{j,b} after the first (row) pass of their inverse
+// transform, as launch_moddown_col_b with ifuse takes them; otherwise the
+// finished ciphertext out_b = (acc_b - conv_b) P^-1 + add_b.  What is switched
+// (d) and added:
+//   KS_WS       d at ws_z + off_d ([level][N], NTT domain)
+//   KS_PRODUCT  d = a1 b1 of the ciphertexts a = src[z], b = src2[z]; a0 b0
+//               and a0 b1 + a1 b0 are added
+//   KS_ROTATE   d = the X -> X^kappa image of c1 of src[z], the image of c0
+//               is added
+// and, for KS_WS and KS_ROTATE with has_add, the ciphertext src2[z] is added
+// (it may be the output itself).  No output may overlap a src, nor a src2
+// with KS_PRODUCT: workgroups of one launch read those whole.
 #define PFT_ROW_LIST 64
-struct RowInner {
+enum : uint32_t { KS_WS = 0, KS_PRODUCT = 1, KS_ROTATE = 2 };
+struct KsRows {
     uint64_t* base;  // item z's workspace at base + z stride
     uint64_t stride;
-    uint64_t off_d, off_ext, off_acc;
+    uint64_t off_d, off_ext, off_acc, off_conv;
     const uint64_t* key;  // [dnum][2][L+K][N] in the storage form of launch_key_form
+    const TwPair *gadget, *gadget_fp;  // [L]: P mod q_i as Shoup pairs, and as (w, w/q) doubles where q_i < 2^50
+    const TwPair *pinv, *pinv_fp;      // [L]: P^-1 mod q_i the same way
     uint32_t n_items, level, rows, alpha, beta, L, krows, tiles;
+    uint32_t mode, has_add;
+    uint64_t kappa, kappa_inv;    // kappa^-1 mod 2N
     uint32_t n_rows;              // rows of this launch
     uint16_t row[PFT_ROW_LIST];   // their indices (0..level+K-1)
-    const uint64_t* perm_src[PFT_MAX_ITEMS];
-    uint64_t kappa, kappa_inv;
+    const uint64_t* src[PFT_MAX_ITEMS];
+    const uint64_t* src2[PFT_MAX_ITEMS];
+    uint64_t* out[PFT_MAX_ITEMS];
 };
-bool row_inner_supported(uint32_t log_n);
-// at most 8 digits (ceil(level / alpha) <= 8; aborts otherwise).  rows:
-// which rows this call launches, ROW_INNER_FP (those with q < 2^50),
-// ROW_INNER_INT (the others) or both.
-enum : uint32_t { ROW_INNER_INT = 1, ROW_INNER_FP = 2, ROW_INNER_ALL = 3 };
-void launch_row_inner(uint32_t n, WsRef ws, uint64_t off_d, uint64_t off_ext, uint64_t off_acc, const uint64_t* key,
-                      uint32_t level, const KsConsts& kc, const DevTables& t, const uint32_t* fp_rows,
-                      uint32_t log_n, const uint64_t* const* perm_src, uint64_t kappa, uint64_t kappa_inv,
-                      bool pair_digits, hipStream_t st, ProfHook* prof = nullptr, uint32_t rows = ROW_INNER_ALL);
+bool ks_rows_supported(uint32_t log_n);
+// Fills in the shape fields (and the row list) of `a` and launches the rows
+// of one arithmetic kind; at most 8 digits (ceil(level / alpha) <= 8; aborts
+// otherwise).  fp_rows[m] (host, by modulus index) is 1 where modulus m runs
+// fp64 arithmetic.  pair_digits: the fp64 rows take two digits through each
+// row pass together (same results).  rows: which rows this call launches,
+// KS_ROWS_FP (those with q < 2^50), KS_ROWS_INT (the others) or both.  prof:
+// each launch is timed as a PK_KEY_INNER variant 1024 + (log_n - 4) (+ 64
+// fp64 rows, + 128 digit pairs, + 256 special rows).
+enum : uint32_t { KS_ROWS_INT = 1, KS_ROWS_FP = 2, KS_ROWS_ALL = 3 };
+void launch_ks_rows(uint32_t n, KsRows a, bool special, const KsConsts& kc, const DevTables& t,
+                    const uint32_t* fp_rows, uint32_t log_n, bool pair_digits, hipStream_t st,
+                    ProfHook* prof = nullptr, uint32_t rows = KS_ROWS_ALL);
 // acc [2][level+K][N] = sum_j x_j * key_j  (key: [dnum][2][L+K][N], Montgomery form)
 void launch_key_inner_b(uint32_t n, WsRef ws, uint64_t off_d, uint64_t off_ext, uint64_t off_acc, const uint64_t* key,
                         uint32_t level, const KsConsts& kc, const DevTables& t, uint32_t log_n, hipStream_t st);

@@ -1,0 +1,52 @@
+"""The fused kernels of key switching (k_ks_rows): sums of a ciphertext and its
+rotation, and outputs that overlap another item's operands, for every
+row-pass length, both digit arrangements, and full, ragged and lowest levels;
+bit-exact against the oracle."""
+
+import pytest
+
+from oracle import ckks as C
+
+from .test_gpu_modup_fused import CASES, world
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(params=list(CASES))
+def fused(request):
+    w = world(request.param)
+    w.ctx.ntt_set_schedule(False, [c for c in w.col16 if c[1] == 0][0])
+    yield w
+    w.ctx.bconv_mode(True)
+    w.ctx.ntt_set_schedule(False, None)
+
+
+def levels(w):
+    return sorted({w.op.L, w.op.L - 1, 1})
+
+
+@pytest.mark.parametrize("pairs", [True, False])
+def test_rotate_and_sum(fused, pairs):
+    """ct + ROTATE(ct, 1): the addend enters through the accumulators."""
+    w = fused
+    w.ctx.bconv_mode(True, pairs=pairs)
+    for level in levels(w):
+        cts = [w.enc_pair(300 + 10 * level + i, level) for i in range(2)]
+        for g, (_, o) in zip(w.ctx.total_sum_batch([c[0] for c in cts], 2), cts):
+            w.assert_same(g, C.hadd(w.op, o, C.rotate(w.op, o, 1, w.rot[1])))
+
+
+def test_outputs_over_other_items_operands(fused):
+    """Each output is the next item's operand: the operands are read as they
+    were before the call."""
+    w = fused
+    for level in levels(w):
+        a, b = ([w.enc_pair(s + 10 * level + i, level) for i in range(3)] for s in (400, 500))
+        want = [C.hmul_relin(w.op, x[1], y[1], w.rlk) for x, y in zip(a, b)]
+        out = w.ctx.mul_relin_batch([x[0] for x in a], [y[0] for y in b], out=[a[1][0], b[0][0], a[0][0]])
+        for g, o in zip(out, want):
+            w.assert_same(g, o)
+        a = [w.enc_pair(600 + 10 * level + i, level) for i in range(3)]
+        want = [C.rotate(w.op, x[1], 5, w.rot[5]) for x in a]
+        for g, o in zip(w.ctx.rotate_batch([x[0] for x in a], 5, out=[a[1][0], a[2][0], a[0][0]]), want):
+            w.assert_same(g, o)
