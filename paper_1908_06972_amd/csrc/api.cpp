@@ -481,6 +481,9 @@ static int build_tables(pft_ctx* c) {
         d.last_inv = mulmod(ipw[n / 2], d.n_inv, q);  // psi^-brv(1) = psi^-(N/2)
         d.last_inv_sh = shoup_companion(d.last_inv, q);
         d.fp = ntt_fp(q) ? 1u : 0u;
+        d.nq = 0 - q;
+        d.rinv = d.fp ? 0u : (uint32_t)(((u128)1 << (d.bits + 31)) / q);
+        d.rsh = d.fp ? 0u : d.bits - 33;
         d.qd = (double)q;
         d.qinv = 1.0 / (double)q;
         d.n_inv_d = (double)d.n_inv;

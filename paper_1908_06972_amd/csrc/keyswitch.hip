@@ -69,7 +69,7 @@ __device__ __forceinline__ void ks_row(const KsRows& a, uint64_t* lds, uint32_t 
     constexpr int PRE = FP ? (G == 2 ? TW_PRE_FP2 : TW_PRE_FP1) : TW_PRE_INT;
 
     const uint32_t tid = threadIdx.x;
-    const uint64_t q = md.q, two_q = md.two_q;
+    [[maybe_unused]] const uint64_t q = md.q;
     const double qd = md.qd, qinv = md.qinv;
     const TwPair* __restrict__ twt = tw + ((size_t)mi << log_n);
     const uint32_t s0 = log_n - LOG_M;
@@ -77,11 +77,17 @@ __device__ __forceinline__ void ks_row(const KsRows& a, uint64_t* lds, uint32_t 
     const uint32_t c = C == 1 ? 0u : tid / T;
     const uint32_t l = C == 1 ? tid : tid % T;
     uint64_t* __restrict__ item = a.base + (size_t)z * a.stride;
-    // this thread's E consecutive words of the row: [w0, w0 + E)
-    const size_t w0 = ((size_t)(sp0 + c) << LOG_M) + (size_t)l * E;
+    // Rows are addressed as a uniform base and a 32-bit lane offset in bytes.
+    // This thread's E consecutive words of a row start at w0, its words in the
+    // row pass's input arrangement at r0.
+    const uint32_t w0 = (((sp0 + c) << LOG_M) + l * (uint32_t)E) * 8u;
+    const uint32_t r0 = (((sp0 + c) << LOG_M) | PIN::r_of(l, 0)) * 8u;
+    auto words = [](const uint64_t* p, uint32_t off) {
+        return reinterpret_cast<const uint64_t*>(reinterpret_cast<const char*>(p) + off);
+    };
 
     auto load_vec = [&](const uint64_t* __restrict__ p, uint64_t (&v)[E]) {
-        const ulonglong2* __restrict__ pv = reinterpret_cast<const ulonglong2*>(p + w0);
+        const ulonglong2* __restrict__ pv = reinterpret_cast<const ulonglong2*>(words(p, w0));
 #pragma unroll
         for (int e = 0; e < E / 2; ++e) {
             const ulonglong2 u = pv[e];
@@ -99,9 +105,7 @@ __device__ __forceinline__ void ks_row(const KsRows& a, uint64_t* lds, uint32_t 
             const double w = as_f(k);
             acc = as_u(as_f(acc) + fmulmod(as_f(x), w, w * qinv, qd));
         } else {
-            // REDC without its final subtraction: each term lies in [0, 2q)
-            const uint64_t lo = x * k, m = lo * md.mont_neg_qinv;
-            acc += mulhi64(x, k) + mulhi64(m, q) + (lo != 0 ? 1u : 0u);
+            acc = mont_add2(acc, x, k, md);
         }
     };
     // acc_b += x k, k the key tile key_{j,b}[t] of this thread's words
@@ -118,28 +122,14 @@ __device__ __forceinline__ void ks_row(const KsRows& a, uint64_t* lds, uint32_t 
     // a row after the conversion kernel's column pass into x
     auto load_row = [&](const uint64_t* __restrict__ src, uint64_t (&x)[E]) {
 #pragma unroll
-        for (int e = 0; e < E; ++e) x[e] = src[((size_t)(sp0 + c) << LOG_M) | PIN::r_of(l, e)];
+        for (int e = 0; e < E; ++e) x[e] = *words(src + ((size_t)e << PIN::WLO), r0);
     };
     auto ext = [&](uint32_t j) { return item + a.off_ext + ((size_t)(j * a.rows + t) << log_n); };
-    // an integer accumulator below 16q brought below q
-    [[maybe_unused]] auto settle_acc = [&](uint64_t v) -> uint64_t {
-#pragma unroll
-        for (int sh = 3; sh >= 0; --sh) {
-            const uint64_t m = q << sh;
-            v = v >= m ? v - m : v;
-        }
-        return v;
-    };
-    // the row pass's output brought within q/2 (FP) or below q
+    // the row pass's output brought within q/2 (FP; the integer products take any value)
     auto settle = [&](uint64_t (&x)[E]) {
+        if constexpr (FP) {
 #pragma unroll
-        for (int e = 0; e < E; ++e) {
-            if constexpr (FP) {
-                x[e] = as_u(freduce(as_f(x[e]), qd, qinv));
-            } else {
-                const uint64_t v = x[e] >= two_q ? x[e] - two_q : x[e];
-                x[e] = v >= q ? v - q : v;
-            }
+            for (int e = 0; e < E; ++e) x[e] = as_u(freduce(as_f(x[e]), qd, qinv));
         }
     };
     // One or two rows through the row pass.  The twiddles and their addresses
@@ -149,15 +139,15 @@ __device__ __forceinline__ void ks_row(const KsRows& a, uint64_t* lds, uint32_t 
     // reloaded).  The offset, not the pointer, is hidden, so the loads stay
     // global (not flat) loads.
     auto pass_1 = [&](uint64_t (&x)[E]) {
-        uint32_t zoff = 0, lj = l, cj = c;
-        asm volatile("" : "+v"(zoff), "+v"(lj), "+v"(cj));
-        run_phases<LOG_M, EB, false, FP, false, 0, false, PRE, TB>(x, lds, cj, lj, sp0 + c, s0, twt + zoff, md);
+        uint32_t lj = l, cj = c;
+        asm volatile("" : "+v"(lj), "+v"(cj));
+        run_phases<LOG_M, EB, false, FP, false, 0, false, PRE, TB>(x, lds, cj, lj, sp0 + c, s0, twt, md);
         __syncthreads();  // the next row's exchanges reuse the LDS
     };
     [[maybe_unused]] auto pass_2 = [&](uint64_t (&x)[2][E]) {
-        uint32_t zoff = 0, lj = l, cj = c;
-        asm volatile("" : "+v"(zoff), "+v"(lj), "+v"(cj));
-        run_phases_g<LOG_M, EB, 2, FP, 0, PRE, TB>(x, lds, cj, lj, sp0 + c, s0, twt + zoff, md);
+        uint32_t lj = l, cj = c;
+        asm volatile("" : "+v"(lj), "+v"(cj));
+        run_phases_g<LOG_M, EB, 2, FP, 0, PRE, TB>(x, lds, cj, lj, sp0 + c, s0, twt, md);
         __syncthreads();
     };
     auto digit_1 = [&](uint32_t j) {
@@ -196,15 +186,17 @@ __device__ __forceinline__ void ks_row(const KsRows& a, uint64_t* lds, uint32_t 
             // d2 = a1 b1 is switched; d0 = a0 b0 and d1 = a0 b1 + a1 b0 are added
             const uint64_t* __restrict__ A = a.src[z];
             const uint64_t* __restrict__ B = a.src2[z];
-            const uint64_t* __restrict__ k0 = a.key + ((size_t)(2 * jo * a.krows + mi) << log_n) + w0;
+            const uint64_t* __restrict__ k0 = a.key + ((size_t)(2 * jo * a.krows + mi) << log_n);
             const uint64_t* __restrict__ k1 = k0 + ((size_t)a.krows << log_n);
             // two words of every operand at a time; the scheduling barrier
             // after each half of them bounds the loads in flight (registers)
 #pragma unroll
             for (int e = 0; e < E; e += 2) {
-                auto two = [&](const uint64_t* __restrict__ p) { return *reinterpret_cast<const ulonglong2*>(p + e); };
-                const ulonglong2 va1 = two(A + row1 + w0), vb1 = two(B + row1 + w0), va0 = two(A + row0 + w0),
-                                 vb0 = two(B + row0 + w0), vk0 = two(k0), vk1 = two(k1);
+                auto two = [&](const uint64_t* __restrict__ p) {
+                    return *reinterpret_cast<const ulonglong2*>(words(p, w0) + e);
+                };
+                const ulonglong2 va1 = two(A + row1), vb1 = two(B + row1), va0 = two(A + row0), vb0 = two(B + row0),
+                                 vk0 = two(k0), vk1 = two(k1);
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
                     const uint64_t a1 = h ? va1.y : va1.x, b1 = h ? vb1.y : vb1.x, a0 = h ? va0.y : va0.x,
@@ -227,7 +219,7 @@ __device__ __forceinline__ void ks_row(const KsRows& a, uint64_t* lds, uint32_t 
                         add_p(mul_barrett(a0, b1, md) + mul_barrett(a1, b0, md), acc1[e + h]);
                     }
                 }
-                if ((e & 2) != 0) __builtin_amdgcn_sched_barrier(0);
+                if (!FP || (e & 2) != 0) __builtin_amdgcn_sched_barrier(0);
             }
         } else {
             uint64_t x[E];
@@ -269,11 +261,8 @@ __device__ __forceinline__ void ks_row(const KsRows& a, uint64_t* lds, uint32_t 
                 acc0[e] = as_u(freduce(as_f(acc0[e]), qd, qinv));
                 acc1[e] = as_u(freduce(as_f(acc1[e]), qd, qinv));
             } else {
-                // at most three terms below 2q
-                for (int k = 0; k < 2; ++k) {
-                    acc0[e] = acc0[e] >= two_q ? acc0[e] - two_q : acc0[e];
-                    acc1[e] = acc1[e] >= two_q ? acc1[e] - two_q : acc1[e];
-                }
+                acc0[e] = reduce_int(acc0[e], md);  // at most three terms below 2q
+                acc1[e] = reduce_int(acc1[e], md);
             }
         }
     }
@@ -304,14 +293,15 @@ __device__ __forceinline__ void ks_row(const KsRows& a, uint64_t* lds, uint32_t 
                 if constexpr (FP)
                     acc[e] = as_u(freduce(as_f(acc[e]), qd, qinv));
                 else
-                    acc[e] = settle_acc(acc[e]);
+                    acc[e] = reduce_int(acc[e], md);
             }
-            uint32_t zoff = 0, lj = l, cj = c;
-            asm volatile("" : "+v"(zoff), "+v"(lj), "+v"(cj));
-            run_phases<LOG_M, EB, true, FP, false, 0, false, PRE, TB>(acc, lds, cj, lj, sp0 + cj, s0, twi + zoff, md);
+            uint32_t lj = l, cj = c;
+            asm volatile("" : "+v"(lj), "+v"(cj));
+            run_phases<LOG_M, EB, true, FP, false, 0, false, PRE, TB>(acc, lds, cj, lj, sp0 + cj, s0, twi, md);
             uint64_t* __restrict__ o = item + a.off_acc + ((size_t)(b * a.rows + t) << log_n);
 #pragma unroll
-            for (int e = 0; e < E; ++e) o[((size_t)(sp0 + cj) << LOG_M) | PIN::r_of(lj, e)] = acc[e];
+            for (int e = 0; e < E; ++e)
+                *const_cast<uint64_t*>(words(o + ((size_t)e << PIN::WLO), r0)) = acc[e];
         };
         finish(acc0, 0);
         __syncthreads();
@@ -320,8 +310,8 @@ __device__ __forceinline__ void ks_row(const KsRows& a, uint64_t* lds, uint32_t 
         const TwPair pinv = FP ? a.pinv_fp[t] : a.pinv[t];  // P^-1 mod q
         // x: the transformed converted row; the result to row t of polynomial b
         auto finish = [&](const uint64_t (&x)[E], const uint64_t (&acc)[E], uint32_t b) {
-            ulonglong2* __restrict__ o =
-                reinterpret_cast<ulonglong2*>(a.out[z] + ((size_t)(b * a.level + t) << log_n) + w0);
+            ulonglong2* __restrict__ o = reinterpret_cast<ulonglong2*>(
+                const_cast<uint64_t*>(words(a.out[z] + ((size_t)(b * a.level + t) << log_n), w0)));
             uint64_t r[E];
 #pragma unroll
             for (int e = 0; e < E; ++e) {
@@ -331,8 +321,8 @@ __device__ __forceinline__ void ks_row(const KsRows& a, uint64_t* lds, uint32_t 
                     const double y = freduce(as_f(acc[e]), qd, qinv) - as_f(x[e]);
                     r[e] = fp_to_u64(as_u(fmulmod(y, as_f(pinv.w), as_f(pinv.wp), qd)), qd, qinv);
                 } else {
-                    const uint64_t v = x[e] >= two_q ? x[e] - two_q : x[e];
-                    r[e] = shoup(settle_acc(acc[e]) + q - (v >= q ? v - q : v), pinv.w, pinv.wp, q);
+                    // the converted row up to 6q
+                    r[e] = shoup(reduce_int(acc[e], md) + 6 * q - x[e], pinv.w, pinv.wp, q);
                 }
             }
 #pragma unroll

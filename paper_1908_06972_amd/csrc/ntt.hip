@@ -27,8 +27,8 @@
 //     fp64 instructions instead of some twenty 32-bit integer ones (bounds at
 //     fmulmod below).
 //   * otherwise (q < 2^60): 64-bit integer Shoup butterflies kept lazily
-//     reduced (forward below 8q inside a pass and below 4q between passes,
-//     inverse in [0, 2q)).
+//     reduced (forward up to 14q inside a pass and 6q between passes,
+//     inverse up to 8q and 4q).
 // Inputs below 4q are accepted; outputs of a full transform are in [0, q).
 #include "bconv_device.h"
 #include "ntt_device.h"
@@ -100,10 +100,16 @@ __global__ __launch_bounds__(4096 >> EB) void k_ntt_pass(PolyBatch b, const DevM
     const uint32_t c = C == 1 ? 0u : (COL ? tid % C : tid / T);
     const uint32_t l = C == 1 ? tid : (COL ? tid / C : tid % T);
     const uint32_t high = (sp0 + c) >> lbits;
-    // global index of element r of the workgroup's sub-problem cc
-    auto gidx = [&](uint32_t cc, uint32_t r) -> size_t {
+    // index in the row of element r of the workgroup's sub-problem cc
+    auto gidx = [&](uint32_t cc, uint32_t r) -> uint32_t {
         const uint32_t sp = sp0 + cc;
-        return ((((size_t)(sp >> lbits) << LOG_M) | r) << lbits) | (sp & lmask);
+        return ((((sp >> lbits) << LOG_M) | r) << lbits) | (sp & lmask);
+    };
+    // word i of a row: a uniform base and a 32-bit lane offset in bytes
+    auto word = [](auto* p, uint32_t i) {
+        using W = std::remove_pointer_t<decltype(p)>;
+        using B = std::conditional_t<std::is_const_v<W>, const char, char>;
+        return reinterpret_cast<W*>(reinterpret_cast<B*>(p) + i * 8u);
     };
 
     uint64_t x[E];
@@ -115,9 +121,10 @@ __global__ __launch_bounds__(4096 >> EB) void k_ntt_pass(PolyBatch b, const DevM
         lds_read<LOG_M, PH_IN, EB>(x, lds, c, l);
     } else if constexpr (SRC == NTT_SRC_PROD) {
         static_assert(VEC_IN, "each thread starts with E consecutive words");
-        const size_t w0 = ((size_t)row << log_n) + gidx(c, (uint32_t)E * l);
-        const ulonglong2* __restrict__ va = reinterpret_cast<const ulonglong2*>(ep.src[poly] + w0);
-        const ulonglong2* __restrict__ vb = reinterpret_cast<const ulonglong2*>(ep.src2[poly] + w0);
+        const uint32_t w0 = gidx(c, (uint32_t)E * l);
+        const size_t r0 = (size_t)row << log_n;
+        const ulonglong2* __restrict__ va = reinterpret_cast<const ulonglong2*>(word(ep.src[poly] + r0, w0));
+        const ulonglong2* __restrict__ vb = reinterpret_cast<const ulonglong2*>(word(ep.src2[poly] + r0, w0));
         auto prod = [&](uint64_t a, uint64_t b2) -> uint64_t {
             if (!fp) return mul_barrett(a, b2, md);
             const double y = as_f(fp_from_u64(b2));
@@ -130,7 +137,7 @@ __global__ __launch_bounds__(4096 >> EB) void k_ntt_pass(PolyBatch b, const DevM
             x[2 * e + 1] = prod(u.y, v.y);
         }
     } else if constexpr (DIRECT_IN && VEC_IN) {
-        const ulonglong2* __restrict__ srcv = reinterpret_cast<const ulonglong2*>(src + gidx(c, (uint32_t)E * l));
+        const ulonglong2* __restrict__ srcv = reinterpret_cast<const ulonglong2*>(word(src, gidx(c, (uint32_t)E * l)));
 #pragma unroll
         for (int e = 0; e < E / 2; ++e) {
             const ulonglong2 v = srcv[e];
@@ -140,7 +147,7 @@ __global__ __launch_bounds__(4096 >> EB) void k_ntt_pass(PolyBatch b, const DevM
     } else if constexpr (DIRECT_IN) {
 #pragma unroll
         for (int e = 0; e < E; ++e) {
-            const uint64_t v = src[gidx(c, PIN::r_of(l, e))];
+            const uint64_t v = *word(src + ((size_t)((uint32_t)e << PIN::WLO) << lbits), gidx(c, PIN::r_of(l, 0)));
             x[e] = convert_in ? fp_from_u64(v) : v;
         }
     } else {
@@ -148,7 +155,7 @@ __global__ __launch_bounds__(4096 >> EB) void k_ntt_pass(PolyBatch b, const DevM
         for (int k = 0; k < E; ++k) {
             const uint32_t idx = tid + NT * k;
             const uint32_t cc = idx / M, r = idx % M;
-            const uint64_t v = src[gidx(cc, r)];
+            const uint64_t v = *word(src, gidx(cc, r));
             lds[lds_at<LOG_M, EB>(cc, r)] = convert_in ? fp_from_u64(v) : v;
         }
         __syncthreads();
@@ -161,14 +168,14 @@ __global__ __launch_bounds__(4096 >> EB) void k_ntt_pass(PolyBatch b, const DevM
     else
         run_phases<LOG_M, EB, INV, false, FINAL, 0, COL, tw_pre_pass(EB)>(x, lds, c, l, high, s0, twt, md);
 
-    const uint64_t q = md.q, two_q = md.two_q;
+    const uint64_t q = md.q;
     const double qd = md.qd, qinv = md.qinv;
     auto finish = [&](uint64_t v) -> uint64_t {
         if constexpr (FINAL) {
             if (fp) {
                 v = fp_to_u64(v, qd, qinv);
             } else if constexpr (!INV) {
-                v = v >= two_q ? v - two_q : v;
+                v = reduce_int(v, md);
                 v = v >= q ? v - q : v;
             }
         }
@@ -202,13 +209,13 @@ __global__ __launch_bounds__(4096 >> EB) void k_ntt_pass(PolyBatch b, const DevM
             if constexpr (PAIRS) {
 #pragma unroll
                 for (int k = 0; k < CH; k += 2) {
-                    const ulonglong2 t = *reinterpret_cast<const ulonglong2*>(p + jj[k]);
+                    const ulonglong2 t = *reinterpret_cast<const ulonglong2*>(word(p, jj[k]));
                     v[k] = t.x;
                     v[k + 1] = t.y;
                 }
             } else {
 #pragma unroll
-                for (int k = 0; k < CH; ++k) v[k] = p[jj[k]];
+                for (int k = 0; k < CH; ++k) v[k] = *word(p, jj[k]);
             }
         };
 #pragma unroll
@@ -246,16 +253,16 @@ __global__ __launch_bounds__(4096 >> EB) void k_ntt_pass(PolyBatch b, const DevM
                     ulonglong2 t;
                     t.x = r[k];
                     t.y = r[k + 1];
-                    *reinterpret_cast<ulonglong2*>(out_row + jj[k]) = t;
+                    *reinterpret_cast<ulonglong2*>(word(out_row, jj[k])) = t;
                 }
             } else {
 #pragma unroll
-                for (int k = 0; k < CH; ++k) out_row[jj[k]] = r[k];
+                for (int k = 0; k < CH; ++k) *word(out_row, jj[k]) = r[k];
             }
         }
     };
     if constexpr (DIRECT_OUT && VEC_OUT && !EPI) {
-        ulonglong2* __restrict__ dst = reinterpret_cast<ulonglong2*>(data + gidx(c, (uint32_t)E * l));
+        ulonglong2* __restrict__ dst = reinterpret_cast<ulonglong2*>(word(data, gidx(c, (uint32_t)E * l)));
 #pragma unroll
         for (int e = 0; e < E / 2; ++e) {
             ulonglong2 v;
@@ -269,7 +276,8 @@ __global__ __launch_bounds__(4096 >> EB) void k_ntt_pass(PolyBatch b, const DevM
                       std::false_type{});
         else
 #pragma unroll
-            for (int e = 0; e < E; ++e) data[gidx(c, POUT::r_of(l, e))] = finish(x[e]);
+            for (int e = 0; e < E; ++e)
+                *word(data + ((size_t)((uint32_t)e << POUT::WLO) << lbits), gidx(c, POUT::r_of(l, 0))) = finish(x[e]);
     } else {
         lds_write<LOG_M, PH_OUT, EB>(x, lds, c, l);
         __syncthreads();
@@ -302,13 +310,13 @@ __global__ __launch_bounds__(4096 >> EB) void k_ntt_pass(PolyBatch b, const DevM
                 ulonglong2 v;
                 v.x = finish(lds[lds_at<LOG_M, EB>(cc, r)]);
                 v.y = finish(lds[lds_at<LOG_M, EB>(cc, r + 1)]);
-                *reinterpret_cast<ulonglong2*>(data + gidx(cc, r)) = v;
+                *reinterpret_cast<ulonglong2*>(word(data, gidx(cc, r))) = v;
             }
         } else {
 #pragma unroll
             for (int k = 0; k < E; ++k) {
                 const auto p = at(k);
-                data[gidx(p.first, p.second)] = finish(lds[lds_at<LOG_M, EB>(p.first, p.second)]);
+                *word(data, gidx(p.first, p.second)) = finish(lds[lds_at<LOG_M, EB>(p.first, p.second)]);
             }
         }
     }

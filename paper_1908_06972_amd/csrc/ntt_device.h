@@ -11,44 +11,34 @@
 
 namespace {
 
-// ---- integer butterflies (any q < 2^60)
+// ---- integer butterflies (51-bit to 60-bit q), 16q < 2^64
 
-// Harvey forward butterflies (WY by Shoup, below 2q for any Y < 2^64).
-// Without reducing X: X + WY and X - WY + 2q stay below B + 2q for X, Y
-// below B.
-__device__ __forceinline__ void fwd_bfly_low(uint64_t& X, uint64_t& Y, uint64_t w, uint64_t wp, uint64_t q,
-                                             uint64_t two_q) {
-    const uint64_t x = X;
-    const uint64_t t = shoup_lazy(Y, w, wp, q);
-    X = x + t;
-    Y = x - t + two_q;
-}
-// The same with X below 8q reduced below 2q in two steps.
-__device__ __forceinline__ void fwd_bfly_r8(uint64_t& X, uint64_t& Y, uint64_t w, uint64_t wp, uint64_t q,
-                                            uint64_t two_q) {
-    const uint64_t four_q = two_q << 1;
-    uint64_t x = X >= four_q ? X - four_q : X;
-    x = x >= two_q ? x - two_q : x;
-    const uint64_t t = shoup_lazy(Y, w, wp, q);
-    X = x + t;
-    Y = x - t + two_q;
+// Forward: with x = X (reduced below 2q first if `reduce`) and r = W Y mod q
+// up to 4q, X' = x + r and Y' = x - r + 4q, both at most 4q above x; Y may be
+// any 64-bit value.
+__device__ __forceinline__ void fwd_bfly_int(uint64_t& X, uint64_t& Y, const TwPair& tp, const DevMod& md,
+                                             bool reduce) {
+    const uint64_t x = reduce ? reduce_int(X, md) : X;
+    X = shoup_add4(x, Y, tp.w, tp.wp, md.nq);
+    Y = ((x << 1) + 4 * md.q) - X;
 }
 // Integer forward stages of a pass reduce X only at stages spp with
 // (LOG_M - 1 - spp) divisible by 3, counted from the pass's last stage so
-// that the last stage reduces: from inputs below 4q, the (at most two)
-// stages before a reducing one leave values below 6q and 8q (< 2^63 for q
-// < 2^60), the reducing stage brings X below 2q in two steps, and every
-// pass ends below 4q as with a reduction at every stage.
+// that the last stage reduces: from inputs up to 6q, the (at most two) stages
+// before a reducing one leave values up to 10q and 14q, the reducing stage
+// brings X below 2q and leaves at most 6q, and so does every pass.
 __device__ __forceinline__ constexpr bool int_fwd_reduces(int log_m, int spp) { return (log_m - 1 - spp) % 3 == 0; }
 
-// Gentleman-Sande inverse butterfly: X, Y in [0, 2q) -> X + Y, (X - Y) W in [0, 2q).
-__device__ __forceinline__ void inv_bfly(uint64_t& X, uint64_t& Y, uint64_t w, uint64_t wp, uint64_t q,
-                                         uint64_t two_q) {
-    uint64_t u = X + Y;
-    u = u >= two_q ? u - two_q : u;
-    uint64_t v = shoup_lazy(X + two_q - Y, w, wp, q);
-    X = u;
-    Y = v;
+// Inverse (Gentleman-Sande): X' = X + Y, Y' = (X - Y + B q) W up to 4q, for
+// X, Y up to B q.  X' is reduced below 2q on the odd stages of a pass and on
+// its last stage: from at most 4q an even stage leaves at most 8q (B = 4), an
+// odd one at most 4q (B = 8, X + Y at most 16q), and so does every pass.
+__device__ __forceinline__ void inv_bfly_int(uint64_t& X, uint64_t& Y, const TwPair& tp, const DevMod& md, int bit,
+                                             bool last) {
+    const uint64_t u = X + Y;
+    const uint64_t d = X + ((bit & 1) ? 8 : 4) * md.q - Y;
+    X = (bit & 1) || last ? reduce_int(u, md) : u;
+    Y = shoup_add4(0, d, tp.w, tp.wp, md.nq);
 }
 
 // ---- fp64 butterflies (q < 2^50): fmulmod / freduce in pft_device.h
@@ -172,10 +162,13 @@ struct PhaseTw {
             for (int m = 0; m < cnt(pos); ++m) t[LY.base[pos] + m] = load(pos, m << (pos + 1));
         }
     }
+    // uniform base, 32-bit lane offset, constant rest: one address per stage
     __device__ __forceinline__ TwPair load(int pos, int e) const {
         const int bit = pos + Ph::WLO;
         const int spp = LOG_M - 1 - bit;
-        return twt[(1u << (s0 + (uint32_t)spp)) + tw_index<LOG_M, PH, EB>(l, e, bit, high, spp)];
+        const char* base = reinterpret_cast<const char*>(twt + (1u << (s0 + (uint32_t)spp)));
+        const uint32_t lane = tw_index<LOG_M, PH, EB>(l, 0, bit, high, spp) * (uint32_t)sizeof(TwPair);
+        return reinterpret_cast<const TwPair*>(base + lane)[(uint32_t)e >> (bit + 1 - Ph::WLO)];
     }
     // the twiddle of the butterfly at window bit pos whose upper element is e
     __device__ __forceinline__ TwPair get(int pos, int e) const {
@@ -188,12 +181,12 @@ struct PhaseTw {
 // or below q; integers below 2q), so the first stage skips its reduction of
 // X; the bounds of the later stages are those of reduced inputs.
 template <int LOG_M, int PH, int EB, bool INV, bool FP, bool FOLD, int PRE, bool LOW = false>
-__device__ __forceinline__ void run_phase(uint64_t (&x)[1 << EB], const PhaseTw<LOG_M, PH, EB, INV, FOLD, PRE>& tw,
-                                          const DevMod& md) {
+__device__ __forceinline__ void run_phase(uint64_t (&x)[1 << EB],
+                                          const PhaseTw<LOG_M, PH, EB, INV, FOLD, PRE>& tw, const DevMod& md) {
     static_assert(!LOW || (!INV && PH == 0), "reduced inputs enter the first forward phase");
     using Ph = Phase<LOG_M, PH, EB>;
     constexpr int E = 1 << EB;
-    const uint64_t q = md.q, two_q = md.two_q;
+    [[maybe_unused]] const uint64_t q = md.q;
     const double qd = md.qd, qinv = md.qinv;
     if constexpr (!INV) {
 #pragma unroll
@@ -207,10 +200,8 @@ __device__ __forceinline__ void run_phase(uint64_t (&x)[1 << EB], const PhaseTw<
                 const bool first = LOW && PH == 0 && spp == 0;  // folded after unrolling
                 if constexpr (FP)
                     fwd_bfly_fp(x[e], x[e | (1 << pos)], tp, qd, qinv, spp % 3 == 0 && !first);
-                else if (first || !int_fwd_reduces(LOG_M, spp))
-                    fwd_bfly_low(x[e], x[e | (1 << pos)], tp.w, tp.wp, q, two_q);
                 else
-                    fwd_bfly_r8(x[e], x[e | (1 << pos)], tp.w, tp.wp, q, two_q);
+                    fwd_bfly_int(x[e], x[e | (1 << pos)], tp, md, int_fwd_reduces(LOG_M, spp) && !first);
             }
         }
     } else {
@@ -228,10 +219,9 @@ __device__ __forceinline__ void run_phase(uint64_t (&x)[1 << EB], const PhaseTw<
                         x[e] = as_u(fmulmod(a + b2, md.n_inv_d, md.n_inv_q, qd));
                         x[e | (1 << pos)] = as_u(fmulmod(a - b2, md.last_inv_d, md.last_inv_q, qd));
                     } else {
-                        uint64_t u = X + Y;
-                        u = u >= two_q ? u - two_q : u;
-                        x[e] = shoup(u, md.n_inv, md.n_inv_sh, q);
-                        x[e | (1 << pos)] = shoup(X + two_q - Y, md.last_inv, md.last_inv_sh, q);
+                        // inputs up to 8q; shoup takes any 64-bit value
+                        x[e] = shoup(X + Y, md.n_inv, md.n_inv_sh, q);
+                        x[e | (1 << pos)] = shoup(X + 8 * q - Y, md.last_inv, md.last_inv_sh, q);
                     }
                 }
             } else {
@@ -242,7 +232,7 @@ __device__ __forceinline__ void run_phase(uint64_t (&x)[1 << EB], const PhaseTw<
                     if constexpr (FP)
                         inv_bfly_fp(x[e], x[e | (1 << pos)], tp, qd, qinv, bit % 3 != 2);
                     else
-                        inv_bfly(x[e], x[e | (1 << pos)], tp.w, tp.wp, q, two_q);
+                        inv_bfly_int(x[e], x[e | (1 << pos)], tp, md, bit, bit == LOG_M - 1);
                 }
             }
         }
@@ -428,7 +418,6 @@ __device__ __forceinline__ void run_phase_g(uint64_t (&x)[G][1 << EB],
                                             const PhaseTw<LOG_M, PH, EB, false, false, PRE>& tw, const DevMod& md) {
     using Ph = Phase<LOG_M, PH, EB>;
     constexpr int E = 1 << EB;
-    const uint64_t q = md.q, two_q = md.two_q;
     const double qd = md.qd, qinv = md.qinv;
 #pragma unroll
     for (int bit = Ph::HB; bit >= Ph::LB; --bit) {
@@ -442,10 +431,8 @@ __device__ __forceinline__ void run_phase_g(uint64_t (&x)[G][1 << EB],
             for (int g = 0; g < G; ++g) {
                 if constexpr (FP)
                     fwd_bfly_fp(x[g][e], x[g][e | (1 << pos)], tp, qd, qinv, spp % 3 == 0);
-                else if (!int_fwd_reduces(LOG_M, spp))
-                    fwd_bfly_low(x[g][e], x[g][e | (1 << pos)], tp.w, tp.wp, q, two_q);
                 else
-                    fwd_bfly_r8(x[g][e], x[g][e | (1 << pos)], tp.w, tp.wp, q, two_q);
+                    fwd_bfly_int(x[g][e], x[g][e | (1 << pos)], tp, md, int_fwd_reduces(LOG_M, spp));
             }
         }
     }

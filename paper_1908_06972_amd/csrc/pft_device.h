@@ -29,6 +29,8 @@ struct DevMod {
     uint64_t last_inv, last_inv_sh; // psi^-brv(1) * N^-1: fused last inverse stage
     uint32_t bits;
     uint32_t fp;          // 1 if q < 2^50: the NTT runs its butterflies in fp64
+    uint64_t nq;          // 2^64 - q
+    uint32_t rinv, rsh;   // floor(2^(bits+31) / q) and bits - 33, bits >= 51 (reduce_int)
     // fp64 forms for the NTT when fp != 0: q, 1/q, and each constant c with
     // its quotient c/q, all rounded to nearest (c < q < 2^50 is exact).
     double qd, qinv;
@@ -93,6 +95,62 @@ __device__ __forceinline__ uint64_t shoup_lazy(uint64_t a, uint64_t w, uint64_t 
 __device__ __forceinline__ uint64_t shoup(uint64_t a, uint64_t w, uint64_t wp, uint64_t q) {
     uint64_t r = shoup_lazy(a, w, wp, q);
     return r >= q ? r - q : r;
+}
+
+// ---- 64-bit products as chains of v_mad_u64_u32 (32 x 32 + 64, full rate)
+// Written out by hand: from __umul64hi and 64-bit operators the compiler
+// spends more instructions on zero-extending the halves (moves) and on
+// carries (subtractions with borrow, each waiting on the mask) than on the
+// products.
+__device__ __forceinline__ uint64_t mad32(uint32_t a, uint32_t b, uint64_t c) { return (uint64_t)a * b + c; }
+__device__ __forceinline__ uint32_t lo32(uint64_t v) { return (uint32_t)v; }
+__device__ __forceinline__ uint32_t hi32(uint64_t v) { return (uint32_t)(v >> 32); }
+// p + h modulo 2^64 in one instruction (a 64-bit add would need h zero-extended to a register pair)
+__device__ __forceinline__ uint64_t add32(uint64_t p, uint32_t h) {
+    uint64_t r;
+    asm("v_mad_u64_u32 %0, vcc, %1, 1, %2" : "=v"(r) : "v"(h), "v"(p) : "vcc");
+    return r;
+}
+// c + a b + k n modulo 2^64
+__device__ __forceinline__ uint64_t mad64x2(uint64_t c, uint64_t a, uint64_t b, uint64_t k, uint64_t n) {
+    c = mad32(lo32(k), lo32(n), mad32(lo32(a), lo32(b), c));
+    const uint32_t hi = hi32(c) + lo32(a) * hi32(b) + hi32(a) * lo32(b) + lo32(k) * hi32(n) + hi32(k) * lo32(n);
+    return ((uint64_t)hi << 32) | lo32(c);
+}
+// x + r modulo 2^64 with r = a w mod q + e q in [0, 4q), any a < 2^64, w < q
+// with wp = floor(w 2^64 / q), nq = 2^64 - q: the quotient is Shoup's with
+// the low halves' product and the low parts of the cross products dropped
+// (at most 3 below floor(a w / q)).  13 instructions.
+__device__ __forceinline__ uint64_t shoup_add4(uint64_t x, uint64_t a, uint64_t w, uint64_t wp, uint64_t nq) {
+    const uint64_t k = add32(add32(mad32(hi32(a), hi32(wp), 0), __umulhi(hi32(a), lo32(wp))),
+                             __umulhi(lo32(a), hi32(wp)));
+    return mad64x2(x, a, w, k, nq);
+}
+// x - k q in [0, 2q) for any x < 2^64, q of at least 51 bits: k = floor of
+// (x's high half times rinv) 2^-(bits-1) never exceeds x / q and is less than
+// 1 + 2^-16 below it.  Five instructions against ten for two conditional
+// subtractions.
+__device__ __forceinline__ uint64_t reduce_int(uint64_t x, const DevMod& m) {
+    const uint32_t k = __umulhi(hi32(x), m.rinv) >> m.rsh;
+    const uint64_t c = mad32(k, lo32(m.nq), x);
+    return ((uint64_t)(hi32(c) + k * hi32(m.nq)) << 32) | lo32(c);
+}
+// acc + (x k + m q) 2^-64, m = -x k q^-1 mod 2^64: x k 2^-64 mod q in [0, 2q)
+// added to acc, for any x < 2^64 and k < q (Montgomery's reduction without
+// its final subtraction).
+__device__ __forceinline__ uint64_t mont_add2(uint64_t acc, uint64_t x, uint64_t k, const DevMod& md) {
+    const uint64_t a = mad32(lo32(x), lo32(k), 0);
+    const uint64_t b = add32(mad32(hi32(x), lo32(k), 0), hi32(a));
+    const uint64_t c = add32(mad32(lo32(x), hi32(k), 0), lo32(b));
+    const uint32_t l0 = lo32(a), l1 = lo32(c);  // x k = d 2^64 + l1 2^32 + l0
+    const uint64_t d = add32(add32(mad32(hi32(x), hi32(k), acc), hi32(b)), hi32(c));
+    const uint64_t n = md.mont_neg_qinv, q = md.q;
+    const uint64_t m0 = mad32(l0, lo32(n), 0);
+    const uint32_t ml = lo32(m0), mh = hi32(m0) + l0 * hi32(n) + l1 * lo32(n);
+    const uint64_t f = add32(mad32(mh, lo32(q), 0), __umulhi(ml, lo32(q)));
+    const uint64_t g = add32(mad32(ml, hi32(q), 0), lo32(f));
+    const uint64_t h = add32(add32(mad32(mh, hi32(q), d), hi32(f)), hi32(g));
+    return add32(h, (l0 | l1) != 0 ? 1u : 0u);
 }
 
 // ---- fp64 arithmetic for primes q < 2^50 (the NTT butterflies, base-conversion folds)

@@ -7,7 +7,7 @@ import pytest
 
 from oracle import ckks as C
 
-from .test_gpu_modup_fused import CASES, world
+from .test_gpu_modup_fused import CASES, World, world
 
 pytestmark = pytest.mark.gpu
 
@@ -50,3 +50,19 @@ def test_outputs_over_other_items_operands(fused):
         want = [C.rotate(w.op, x[1], 5, w.rot[5]) for x in a]
         for g, o in zip(w.ctx.rotate_batch([x[0] for x in a], 5, out=[a[1][0], a[2][0], a[0][0]]), want):
             w.assert_same(g, o)
+
+
+@pytest.mark.parametrize("bits", [51, 55, 59])
+def test_integer_rows_of_other_sizes(bits):
+    """Every prime on the 64-bit integer path and below 60 bits: products with
+    relinearisation and their rescale under every transform schedule."""
+    w = World(dict(log_n=12, n_q=4, q0_bits=bits, q_bits=bits, n_p=2, p_bits=bits, dnum=2, scale=2 ** 40))
+    (ga, oa), (gb, ob) = w.enc_pair(1, 4), w.enc_pair(2, 4)
+    prod = C.hmul_relin(w.op, oa, ob, w.rlk)
+    low = C.rescale(w.op, prod)
+    for sched in w.ctx.ntt_candidates():
+        for inverse in (False, True):
+            w.ctx.ntt_set_schedule(inverse, sched)
+        g = w.ctx.mul_relin(ga, gb)
+        w.assert_same(g, prod)
+        w.assert_same(w.ctx.rescale(g), low)
