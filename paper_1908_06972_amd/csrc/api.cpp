@@ -575,21 +575,37 @@ static int build_tables(pft_ctx* c) {
         }
         return w;
     };
-    const uint32_t up_rt = (L + K + 3) / 4, up_kb = (A + 1) / 2;
-    const uint32_t dn_rt = (L + 3) / 4, dn_kb = (K + 1) / 2;
+    // Targets in tiles of one arithmetic kind, the integer rows' first: a wave
+    // takes a tile through the fold and the first transform pass without
+    // branching between the kinds.
+    const uint32_t up_rt = (L + K + 3) / 4 + 1, up_kb = (A + 1) / 2;
+    const uint32_t dn_rt = (L + 3) / 4 + 1, dn_kb = (K + 1) / 2;
+    auto tiles_of = [&](uint8_t* tgt, const std::vector<uint32_t>& rows, auto&& mod_of) {
+        uint32_t n = 0;
+        for (int fp = 0; fp < 2; ++fp) {
+            for (uint32_t t : rows)
+                if ((int)ntt_fp(P->mods[mod_of(t)]) == fp) tgt[n++] = (uint8_t)t;
+            n = (n + 3) / 4 * 4;
+        }
+    };
+    std::vector<uint8_t> upt((size_t)L * dnum * up_rt * 4, (uint8_t)PFT_NO_ROW), dnt((size_t)dn_rt * 4, (uint8_t)PFT_NO_ROW);
     std::vector<uint64_t> upa((size_t)L * dnum * up_rt * up_kb * 64, 0), dna((size_t)dn_rt * dn_kb * 64, 0);
     std::vector<uint64_t> pw8(8);
     for (uint32_t lvl = 1; lvl <= L; ++lvl) {
         const uint32_t beta = (lvl + A - 1) / A;
         for (uint32_t j = 0; j < beta; ++j) {
-            const uint32_t i0 = j * A, na = std::min(i0 + A, lvl) - i0, T = lvl + K - na;
-            for (uint32_t rt = 0; rt < (T + 3) / 4; ++rt)
+            const uint32_t i0 = j * A, na = std::min(i0 + A, lvl) - i0;
+            uint8_t* tgt = &upt[((size_t)(lvl - 1) * dnum + j) * up_rt * 4];
+            std::vector<uint32_t> rows;
+            for (uint32_t t = 0; t < lvl + K; ++t)
+                if (t < i0 || t >= i0 + na) rows.push_back(t);
+            tiles_of(tgt, rows, [&](uint32_t t) { return t < lvl ? t : L + (t - lvl); });
+            for (uint32_t rt = 0; rt < up_rt && tgt[4 * rt] != PFT_NO_ROW; ++rt)
                 for (uint32_t kb = 0; kb < (na + 1) / 2; ++kb)
                     for (uint32_t lane = 0; lane < 64; ++lane) {
                         auto vm = [&](uint32_t half, uint32_t tl, uint32_t a) -> uint64_t {
-                            const uint32_t ii = 2 * kb + half, tt = 4 * rt + tl;
-                            if (ii >= na || tt >= T) return ~0ull;
-                            const uint32_t t = tt < i0 ? tt : tt + na;
+                            const uint32_t ii = 2 * kb + half, t = tgt[4 * rt + tl];
+                            if (ii >= na || t == PFT_NO_ROW) return ~0ull;
                             const uint64_t m = t < lvl ? P->q[t] : P->p[t - lvl];
                             uint64_t h = 1;  // (D_j / q_{i0+ii}) mod m
                             for (uint32_t o = i0; o < i0 + na; ++o)
@@ -601,12 +617,17 @@ static int build_tables(pft_ctx* c) {
                     }
         }
     }
+    {
+        std::vector<uint32_t> rows(L);
+        for (uint32_t t = 0; t < L; ++t) rows[t] = t;
+        tiles_of(dnt.data(), rows, [](uint32_t t) { return t; });
+    }
     for (uint32_t rt = 0; rt < dn_rt; ++rt)
         for (uint32_t kb = 0; kb < dn_kb; ++kb)
             for (uint32_t lane = 0; lane < 64; ++lane) {
                 auto vm = [&](uint32_t half, uint32_t tl, uint32_t a) -> uint64_t {
-                    const uint32_t k = 2 * kb + half, i = 4 * rt + tl;
-                    if (k >= K || i >= L) return ~0ull;
+                    const uint32_t k = 2 * kb + half, i = dnt[4 * rt + tl];
+                    if (k >= K || i == PFT_NO_ROW) return ~0ull;
                     const uint64_t m = P->q[i];
                     uint64_t h = 1;  // (P / p_k) mod q_i
                     for (uint32_t o = 0; o < K; ++o)
@@ -618,28 +639,30 @@ static int build_tables(pft_ctx* c) {
     std::vector<BconvRed> red(L + K);
     for (uint32_t mi = 0; mi < L + K; ++mi) {
         const uint64_t m = P->mods[mi];
-        const uint64_t c32 = powmod(2 % m, 32, m);
         red[mi].m = m;
         red[mi].negm = 0 - m;
         red[mi].cq0 = m << 30;
         red[mi].md = (double)m;
         red[mi].minv = 1.0 / (double)m;
-        red[mi].c32 = (double)c32;
-        red[mi].c32q = (double)c32 / (double)m;
+        red[mi].rinv = mods[mi].rinv;
+        red[mi].rsh = mods[mi].rsh;
         red[mi].fp = ntt_fp(m) ? 1u : 0u;
+        red[mi].row = 0;
         red[mi].pad = 0;
     }
 
     TwPair *d_hatinv, *d_phatinv, *d_pinv;
     uint64_t *d_cmat, *d_downc, *d_upa, *d_dna;
     BconvRed* d_red;
+    uint8_t *d_upt, *d_dnt;
+    if ((r = upload(c, &d_upt, upt)) || (r = upload(c, &d_dnt, dnt))) return r;
     if ((r = upload(c, &d_upa, upa)) || (r = upload(c, &d_dna, dna)) || (r = upload(c, &d_red, red))) return r;
     if ((r = upload(c, &d_hatinv, hatinv)) || (r = upload(c, &d_cmat, cmat)) || (r = upload(c, &d_phatinv, phatinv)) ||
         (r = upload(c, &d_downc, downc)) || (r = upload(c, &d_pinv, pinv)) || (r = upload(c, &c->rescale_qinv, rq)) ||
         (r = upload(c, &c->gadget, gadget)) || (r = upload(c, &c->to_mont, tomont)))
         return r;
-    c->kc = KsConsts{d_hatinv, d_cmat, d_phatinv, d_downc, d_pinv, d_upa, d_dna, d_red,
-                     up_rt,    up_kb,  dn_rt,       dn_kb,   L,      K,     dnum,  A};
+    c->kc = KsConsts{d_hatinv, d_cmat, d_phatinv, d_downc, d_pinv, d_upt, d_dnt, d_upa,
+                     d_dna,    d_red,  up_rt,       up_kb,   dn_rt,  dn_kb, L,     K,     dnum,  A};
     return PFT_OK;
 }
 
@@ -1736,9 +1759,9 @@ static void key_switch_b(pft_ctx* c, uint32_t n, WsRef ws, const KsLayout& K, co
     // its final radix-16 column pass (a schedule chosen among those ending
     // with one) and ModUp applies that pass to its inputs.
     const uint32_t nkb = (std::min(P->alpha, level) + 1) / 2, down_kb = (P->K + 1) / 2;
-    const bool fuse = c->bconv_mfma && c->bconv_fuse && lg >= 8 && nkb <= 6 && col16(full, rows - A) &&
+    const bool fuse = c->bconv_mfma && c->bconv_fuse && bconv_col_supported(lg, nkb, c->kc.up_rt) && col16(full, rows - A) &&
                       col16(last, rows - na_last);
-    const bool fuse_down = c->bconv_mfma && c->bconv_fuse && lg >= 8 && down_kb <= 6 &&
+    const bool fuse_down = c->bconv_mfma && c->bconv_fuse && bconv_col_supported(lg, down_kb, c->kc.down_rt) &&
                            first_pass_col16(c, 2ull * n * level);
     const bool ifuse_up = fuse && last_pass_col16(c, (uint64_t)n * level);
     const bool merged = fuse && fuse_down && c->inner_fuse && beta <= 8 && ks_rows_supported(lg);

@@ -167,6 +167,35 @@ __global__ __launch_bounds__(TB) void k_modup_b(WsRef ws, uint64_t off_d, uint64
     }
 }
 
+// Every row tile of a base conversion for this lane's coefficient, whose
+// input digits are bop: put(row, y) for each target row of the lane.
+template <uint32_t NKB, class F>
+__device__ __forceinline__ void bconv_tiles(const long (&bop)[NKB], const uint64_t* __restrict__ aop, uint32_t kbs,
+                                            uint32_t max_tiles, const BconvRed* s_red, uint32_t half, F&& put) {
+    // the constant digits of tile rt + 1 load while tile rt is folded
+    long av[NKB];
+#pragma unroll
+    for (uint32_t kb = 0; kb < NKB; ++kb) av[kb] = (long)aop[kb * 64];
+    for (uint32_t rt = 0; rt < max_tiles && s_red[4 * rt].row != PFT_NO_ROW; ++rt) {
+        const v16i zero = {};
+        v16i acc = __builtin_amdgcn_mfma_i32_32x32x16_i8(av[0], bop[0], zero, 0, 0, 0);
+#pragma unroll
+        for (uint32_t kb = 1; kb < NKB; ++kb) acc = __builtin_amdgcn_mfma_i32_32x32x16_i8(av[kb], bop[kb], acc, 0, 0, 0);
+        if (rt + 1 < max_tiles) {
+#pragma unroll
+            for (uint32_t kb = 0; kb < NKB; ++kb) av[kb] = (long)aop[((rt + 1) * kbs + kb) * 64];
+        }
+        int z[8];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            if (u == 0) tile_digits<0>(acc, z); else tile_digits<1>(acc, z);
+            const BconvRed& rc = s_red[4 * rt + 2 * half + u];
+            if (rc.row != PFT_NO_ROW)
+                put(rc.row, rc.fp ? fold_digits<true, false>(z, rc) : fold_digits<false, false>(z, rc));
+        }
+    }
+}
+
 // ModUp on the matrix cores: same inputs and outputs as k_modup_b.  A wave
 // converts 32 coefficients of digit j = blockIdx.y to every target row.  NKB
 // = ceil(alpha' / 2) k-blocks of 16 for alpha' = min(alpha, level); a digit
@@ -179,7 +208,7 @@ __global__ __launch_bounds__(TB) void k_modup_mfma_b(WsRef ws, uint64_t off_d, u
     const uint32_t j = blockIdx.y;
     const uint32_t i0 = j * kc.alpha;
     const uint32_t na = min(i0 + kc.alpha, level) - i0;
-    const uint32_t rows = level + kc.K, T = rows - na;
+    const uint32_t rows = level + kc.K;
     const size_t cbase = ((size_t)(level - 1) * kc.dnum + j) * kc.alpha;
     const uint64_t* __restrict__ d = ws_item(ws) + off_d;
     long bop[NKB];
@@ -193,36 +222,16 @@ __global__ __launch_bounds__(TB) void k_modup_mfma_b(WsRef ws, uint64_t off_d, u
         }
         bop[kb] = split_digits(x);
     }
-    const uint64_t* __restrict__ aop =
-        kc.up_aop + ((size_t)(level - 1) * kc.dnum + j) * kc.up_rt * kc.up_kb * 64 + lane;
+    const size_t lj = (size_t)(level - 1) * kc.dnum + j;
+    const uint8_t* __restrict__ tgt = kc.up_tgt + lj * kc.up_rt * 4;
+    const uint64_t* __restrict__ aop = kc.up_aop + lj * kc.up_rt * kc.up_kb * 64 + lane;
     uint64_t* __restrict__ outj = ws_item(ws) + off_ext + ((size_t)j * rows << log_n);
-    __shared__ BconvRed s_red[64];
-    stage_red(kc, s_red);
-    // the constant digits of tile rt + 1 load while tile rt is folded
-    long av[NKB];
-#pragma unroll
-    for (uint32_t kb = 0; kb < NKB; ++kb) av[kb] = (long)aop[kb * 64];
-    for (uint32_t rt = 0; rt * 4 < T; ++rt) {
-        const v16i zero = {};
-        v16i acc = __builtin_amdgcn_mfma_i32_32x32x16_i8(av[0], bop[0], zero, 0, 0, 0);
-#pragma unroll
-        for (uint32_t kb = 1; kb < NKB; ++kb) acc = __builtin_amdgcn_mfma_i32_32x32x16_i8(av[kb], bop[kb], acc, 0, 0, 0);
-        if ((rt + 1) * 4 < T) {
-#pragma unroll
-            for (uint32_t kb = 0; kb < NKB; ++kb) av[kb] = (long)aop[((rt + 1) * kc.up_kb + kb) * 64];
-        }
-        int z[8];
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            if (u == 0) tile_digits<0>(acc, z); else tile_digits<1>(acc, z);
-            const uint32_t tt = 4 * rt + 2 * half + u;
-            if (tt < T) {
-                const uint32_t t = tt < i0 ? tt : tt + na;
-                const uint32_t mi = t < level ? t : kc.L + (t - level);
-                outj[at(t, log_n, n)] = fold_digits(z, s_red[mi]);
-            }
-        }
-    }
+    __shared__ BconvRed s_red[PFT_MAX_SLOTS];
+    stage_red(kc, s_red, tgt, 4 * kc.up_rt, [](uint32_t t) { return t; },
+              [&](uint32_t t) { return t < level ? t : kc.L + (t - level); });
+    __syncthreads();
+    bconv_tiles<NKB>(bop, aop, kc.up_kb, kc.up_rt, s_red, half,
+                     [&](uint32_t t, uint64_t y) { outj[at(t, log_n, n)] = y; });
 }
 
 // ModDown conversion on the matrix cores: same inputs and outputs as
@@ -247,30 +256,13 @@ __global__ __launch_bounds__(TB) void k_moddown_mfma_b(WsRef ws, uint64_t off_ac
         }
         bop[kb] = split_digits(x);
     }
-    const uint64_t* __restrict__ aop = kc.down_aop + lane;
     uint64_t* __restrict__ conv = ws_item(ws) + off_conv;
-    __shared__ BconvRed s_red[64];
-    stage_red(kc, s_red);
-    long av[NKB];
-#pragma unroll
-    for (uint32_t kb = 0; kb < NKB; ++kb) av[kb] = (long)aop[kb * 64];
-    for (uint32_t rt = 0; rt * 4 < level; ++rt) {
-        const v16i zero = {};
-        v16i acc = __builtin_amdgcn_mfma_i32_32x32x16_i8(av[0], bop[0], zero, 0, 0, 0);
-#pragma unroll
-        for (uint32_t kb = 1; kb < NKB; ++kb) acc = __builtin_amdgcn_mfma_i32_32x32x16_i8(av[kb], bop[kb], acc, 0, 0, 0);
-        if ((rt + 1) * 4 < level) {
-#pragma unroll
-            for (uint32_t kb = 0; kb < NKB; ++kb) av[kb] = (long)aop[((rt + 1) * kc.down_kb + kb) * 64];
-        }
-        int z[8];
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            if (u == 0) tile_digits<0>(acc, z); else tile_digits<1>(acc, z);
-            const uint32_t i = 4 * rt + 2 * half + u;
-            if (i < level) conv[at(b * level + i, log_n, n)] = fold_digits(z, s_red[i]);
-        }
-    }
+    __shared__ BconvRed s_red[PFT_MAX_SLOTS];
+    stage_red(kc, s_red, kc.down_tgt, 4 * kc.down_rt, [&](uint32_t i) { return i < level ? i : PFT_NO_ROW; },
+              [](uint32_t i) { return i; });
+    __syncthreads();
+    bconv_tiles<NKB>(bop, kc.down_aop + lane, kc.down_kb, kc.down_rt, s_red, half,
+                     [&](uint32_t i, uint64_t y) { conv[at(b * level + i, log_n, n)] = y; });
 }
 
 // acc_b[t] = sum_j x_j[t] key_{j,b}[row(t)], x_j = d (NTT domain, at off_d)

@@ -412,157 +412,141 @@ void launch_pass(const PolyBatch& b, const DevTables& t, uint32_t log_n, uint32_
 // (stages 0-3, a radix-16 column pass) of the forward transform of every row
 // it produces.  ModUp (DOWN false): digit j = blockIdx.y of item z =
 // blockIdx.z, inputs the digit's rows of d, targets every row outside the
-// digit (q-limbs, then special primes), output ext_j.  ModDown (DOWN true):
+// digit (q-limbs and special primes), output ext_j.  ModDown (DOWN true):
 // polynomial b = blockIdx.y, inputs the K special rows of acc_b, targets the
-// q-limbs 0..level-1, output conv_b.  The workgroup converts the 256
-// coefficients u0 + u + t N/16 (u, t < 16): the same exact contraction on the
-// matrix cores and fold as the stand-alone conversion kernels, for up to 16
-// target rows at a time, into LDS; then thread (target, u) takes the 16
-// values t of its column through the four stages exactly as the first
-// transform pass does (on fp64 rows the fold's reduced double is already the
-// butterflies' input form) and stores them in that pass's output form, so the
-// transform continues with its second pass.
+// q-limbs 0..level-1, output conv_b.
+//
+// A workgroup converts the 512 coefficients u0 + u + t N/16 (u < 32, t < 16)
+// of 32 columns.  First a half-wave per input row takes its columns' 16
+// values, forms their digits and leaves them in LDS as the matrix operand of
+// block t (columns u).  Then each wave takes tiles of four target rows: per
+// block t the same exact contraction on the matrix cores and fold as the
+// stand-alone conversion kernels.  The 32 columns of an accumulator tile are
+// the 32 columns u, so a lane ends with all 16 values t of its column for two
+// targets, in registers, and takes them through the four stages exactly as
+// the first transform pass does (on fp64 rows the fold's reduced double is
+// already the butterflies' input form), storing that pass's output form; the
+// transform continues with its second pass.  The tiles hold rows of one
+// arithmetic kind, so a wave never runs both; no target goes through LDS.
 //
 // IFUSE: the input rows come from an inverse transform whose final pass (a
-// radix-16 column pass, stages 3-0 with N^-1 folded in) has not run; the
-// workgroup applies it to its 16 columns of each input row exactly as that
-// pass would (the same butterflies, the same conversion to canonical u64)
-// and stages the result in LDS before splitting the digits.
+// radix-16 column pass, stages 3-0 with N^-1 folded in) has not run; it is
+// applied to the 16 values of each column first.
+constexpr uint32_t BCONV_COLS = 32;
 template <uint32_t NKB, bool DOWN, bool IFUSE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_bconv_col_b(
     WsRef ws, uint64_t off_in, uint64_t off_out, uint32_t level, KsConsts kc, const DevMod* __restrict__ mods,
     const TwPair* __restrict__ tw, const TwPair* __restrict__ tw_inv, uint32_t log_n) {
-    constexpr uint32_t ROWP = 272;  // LDS words per target row (256 coefficients + padding)
-    __shared__ uint64_t ybuf[16 * ROWP];
-    __shared__ BconvRed s_red[64];
+    __shared__ uint64_t s_dig[2 * NKB * 16 * BCONV_COLS];  // [input row][t][u]
+    extern __shared__ uint4 s_dyn[];  // fold constants by slot, then 16 twiddles by slot
+    const uint32_t max_tiles = DOWN ? kc.down_rt : kc.up_rt;
+    BconvRed* s_red = reinterpret_cast<BconvRed*>(s_dyn);
+    TwPair* s_tw = reinterpret_cast<TwPair*>(s_red + 4 * max_tiles);
     const uint32_t tid = threadIdx.x, lane = tid & 63u, half = lane >> 5, wave = tid >> 6;
     const uint32_t S = 1u << (log_n - 4);
-    const uint32_t u0 = blockIdx.x * 16u;
+    const uint32_t u = lane & 31u, col = blockIdx.x * BCONV_COLS + u;
     const uint32_t j = blockIdx.y;  // digit (ModUp) or polynomial (ModDown)
     const uint32_t rows = level + kc.K;
-    // ModUp: the digit's limbs [i0, i0 + na) are the inputs and are skipped as targets
+    // ModUp: the digit's limbs [i0, i0 + na) are the inputs
     const uint32_t i0 = DOWN ? level : j * kc.alpha;
     const uint32_t na = DOWN ? kc.K : min(i0 + kc.alpha, level) - i0;
-    const uint32_t T = DOWN ? level : rows - na;
-    const size_t cbase = ((size_t)(level - 1) * kc.dnum + j) * kc.alpha;
+    const size_t lj = (size_t)(level - 1) * kc.dnum + j;
     uint64_t* item = ws.base + (size_t)blockIdx.z * ws.stride;
     const uint64_t* __restrict__ in = item + off_in + (DOWN ? ((size_t)j * rows << log_n) : 0);
     uint64_t* __restrict__ out = item + off_out + ((size_t)j * (DOWN ? level : rows) << log_n);
-    if constexpr (IFUSE) {
-        // the final inverse pass of each input row's 16 columns, into LDS
-        // rows 0..na-1 at column 16 t + u
-        const uint32_t ii = tid >> 4, u = tid & 15u;
+    auto mod_of = [&](uint32_t t) { return DOWN || t < level ? t : kc.L + (t - level); };
+    // fold constants and first twiddles of every slot
+    const uint8_t* __restrict__ tgt = DOWN ? kc.down_tgt : kc.up_tgt + lj * kc.up_rt * 4;
+    auto row_of = [&](uint32_t t) { return DOWN && t >= level ? PFT_NO_ROW : t; };
+    stage_red(kc, s_red, tgt, 4 * max_tiles, row_of, mod_of);
+    for (uint32_t i = tid; i < 64 * max_tiles; i += 256) {
+        const uint32_t t = row_of(tgt[i >> 4]);
+        if (t != PFT_NO_ROW) s_tw[i] = tw[((size_t)mod_of(t) << log_n) + (i & 15u)];
+    }
+    // the input rows' digits
+    for (uint32_t ii = tid >> 5; ii < 2 * NKB; ii += 8) {
+        uint64_t x[16];
         if (ii < na) {
             const uint32_t mi = DOWN ? kc.L + ii : i0 + ii;
             const DevMod md = mods[mi];
-            const TwPair* __restrict__ twt = tw_inv + ((size_t)mi << log_n);
-            const uint64_t* __restrict__ irow = in + ((size_t)(i0 + ii) << log_n) + u0 + u;
-            uint64_t x[16];
+            const TwPair hv = DOWN ? kc.down_phatinv[ii] : kc.modup_hatinv[lj * kc.alpha + ii];
+            const uint32_t off = (((i0 + ii) << log_n) + col) * 8u;
 #pragma unroll
-            for (int e = 0; e < 16; ++e) x[e] = irow[(size_t)e * S];
-            if (md.fp) {
-                run_phase<4, 0, 4, true, true, true>(x, 0u, 0u, 0u, twt, md);
+            for (int e = 0; e < 16; ++e)
+                x[e] = *reinterpret_cast<const uint64_t*>(reinterpret_cast<const char*>(in + (size_t)e * S) + off);
+            if constexpr (IFUSE) {
+                const TwPair* __restrict__ twt = tw_inv + ((size_t)mi << log_n);
+                if (md.fp) {
+                    run_phase<4, 0, 4, true, true, true>(x, 0u, 0u, 0u, twt, md);
 #pragma unroll
-                for (int e = 0; e < 16; ++e) x[e] = fp_to_u64(x[e], md.qd, md.qinv);
-            } else {
-                run_phase<4, 0, 4, true, false, true>(x, 0u, 0u, 0u, twt, md);
+                    for (int e = 0; e < 16; ++e) x[e] = fp_to_u64(x[e], md.qd, md.qinv);
+                } else {
+                    run_phase<4, 0, 4, true, false, true>(x, 0u, 0u, 0u, twt, md);
+                }
             }
 #pragma unroll
-            for (int e = 0; e < 16; ++e) ybuf[ii * ROWP + 16u * e + u] = x[e];
-        }
-        __syncthreads();
-    }
-    // input digits of this lane's coefficient in each of the wave's two
-    // 32-column blocks: column ci = 32 cb + (lane & 31) = 16 t + u
-    uint32_t ci[2];
-    long bop[2][NKB];
+            for (int e = 0; e < 16; ++e) x[e] = (uint64_t)split_digits(shoup(x[e], hv.w, hv.wp, md.q));
+        } else {
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        ci[h] = 32u * (2u * wave + (uint32_t)h) + (lane & 31u);
-        const uint32_t pos = u0 + (ci[h] & 15u) + (ci[h] >> 4) * S;
-#pragma unroll
-        for (uint32_t kb = 0; kb < NKB; ++kb) {
-            const uint32_t ii = 2 * kb + half;
-            uint64_t x = 0;
-            if (ii < na) {
-                const TwPair hv = DOWN ? kc.down_phatinv[ii] : kc.modup_hatinv[cbase + ii];
-                const uint64_t qi = mods[DOWN ? kc.L + ii : i0 + ii].q;
-                const uint64_t v = IFUSE ? ybuf[ii * ROWP + ci[h]] : in[((size_t)(i0 + ii) << log_n) + pos];
-                x = shoup(v, hv.w, hv.wp, qi);
-            }
-            bop[h][kb] = split_digits(x);
+            for (int e = 0; e < 16; ++e) x[e] = 0;
         }
+#pragma unroll
+        for (int e = 0; e < 16; ++e) s_dig[(ii * 16u + e) * BCONV_COLS + u] = x[e];
     }
+    __syncthreads();
     const uint32_t kbs = DOWN ? kc.down_kb : kc.up_kb;
     const uint64_t* __restrict__ aop =
-        (DOWN ? kc.down_aop : kc.up_aop + ((size_t)(level - 1) * kc.dnum + j) * kc.up_rt * kc.up_kb * 64) + lane;
-    const uint32_t tiles = (T + 3) / 4;
-    // target tt: its row and modulus index
-    auto row_of = [&](uint32_t tt) { return DOWN ? tt : (tt < i0 ? tt : tt + na); };
-    auto mod_of = [&](uint32_t t) { return t < level ? t : kc.L + (t - level); };
-    // the fold constants of every target (T <= L + K <= 64) into LDS in
-    // target order, so that a fold finds its own at s_red[tt]; the barrier
-    // also orders the LDS input reads above before the first target batch
-    // overwrites those rows
-    {
-        const uint64_t* src = reinterpret_cast<const uint64_t*>(kc.red);
-        uint64_t* dst = reinterpret_cast<uint64_t*>(s_red);
-        constexpr uint32_t WPR = sizeof(BconvRed) / 8;
-        for (uint32_t w = tid; w < T * WPR; w += blockDim.x) dst[w] = src[mod_of(row_of(w / WPR)) * WPR + w % WPR];
-        __syncthreads();
-    }
-    long av[NKB];
+        (DOWN ? kc.down_aop : kc.up_aop + lj * kc.up_rt * kc.up_kb * 64) + lane;
+    const uint64_t* dig = s_dig + half * 16u * BCONV_COLS + u;  // input rows 2 kb + half
+    auto tile = [&](uint32_t g, auto fpc) {
+        constexpr bool FP = decltype(fpc)::value;
+        const BconvRed* rc = s_red + 4 * g + 2 * half;
+        long av[NKB];
 #pragma unroll
-    for (uint32_t kb = 0; kb < NKB; ++kb) av[kb] = (long)aop[kb * 64];
-    for (uint32_t tb0 = 0; tb0 < T; tb0 += 16) {
-        const uint32_t nt = min(16u, T - tb0);
-        for (uint32_t rt = 0; rt * 4 < nt; ++rt) {
-            const uint32_t g = tb0 / 4 + rt;  // row tile of the constant operands
-            // the two column blocks one after the other (one accumulator tile live)
+        for (uint32_t kb = 0; kb < NKB; ++kb) av[kb] = (long)aop[(g * kbs + kb) * 64];
+        uint64_t x[2][16];
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const v16i zero = {};
-                v16i acc = __builtin_amdgcn_mfma_i32_32x32x16_i8(av[0], bop[h][0], zero, 0, 0, 0);
+        for (int t = 0; t < 16; ++t) {
+            v16i acc = {};
 #pragma unroll
-                for (uint32_t kb = 1; kb < NKB; ++kb)
-                    acc = __builtin_amdgcn_mfma_i32_32x32x16_i8(av[kb], bop[h][kb], acc, 0, 0, 0);
-                if (h == 1 && g + 1 < tiles) {
-#pragma unroll
-                    for (uint32_t kb = 0; kb < NKB; ++kb) av[kb] = (long)aop[((g + 1) * kbs + kb) * 64];
-                }
-#pragma unroll
-                for (int uu = 0; uu < 2; ++uu) {
-                    const uint32_t tt = 4 * g + 2 * half + (uint32_t)uu;
-                    if (tt < T) {
-                        int z[8];
-                        if (uu == 0) tile_digits<0>(acc, z); else tile_digits<1>(acc, z);
-                        // fp64 rows keep the fold's double (the pass's input form)
-                        ybuf[(tt - tb0) * ROWP + ci[h]] = fold_digits<true>(z, s_red[tt]);
-                    }
-                }
-            }
+            for (uint32_t kb = 0; kb < NKB; ++kb)
+                acc = __builtin_amdgcn_mfma_i32_32x32x16_i8(av[kb], (long)dig[(kb * 32u + t) * BCONV_COLS], acc, 0, 0, 0);
+            int z[8];
+            tile_digits<0>(acc, z);
+            x[0][t] = fold_digits<FP, true>(z, rc[0]);
+            tile_digits<1>(acc, z);
+            x[1][t] = fold_digits<FP, true>(z, rc[1]);
+            // keeps the folds here: moved down to the conditional stores they
+            // would hold all 16 accumulator tiles
+            asm volatile("" : "+v"(x[0][t]), "+v"(x[1][t]));
         }
-        __syncthreads();
-        const uint32_t tl = tid >> 4, u = tid & 15u;
-        if (tl < nt) {
-            const uint32_t t = row_of(tb0 + tl);
-            const uint32_t mi = mod_of(t);
-            const DevMod md = mods[mi];
-            const TwPair* __restrict__ twt = tw + ((size_t)mi << log_n);
-            uint64_t x[16];
 #pragma unroll
-            for (int e = 0; e < 16; ++e) x[e] = ybuf[tl * ROWP + 16u * e + u];
+        for (int v = 0; v < 2; ++v) {
+            const uint32_t row = rc[v].row;
+            if (row == PFT_NO_ROW) continue;
+            DevMod md;
+            md.q = rc[v].m;
+            md.nq = rc[v].negm;
+            md.rinv = rc[v].rinv;
+            md.rsh = rc[v].rsh;
+            md.qd = rc[v].md;
+            md.qinv = rc[v].minv;
             // the fold's values are reduced (within q/2 + 1, or below q)
-            if (md.fp) {
-                run_phase<4, 0, 4, false, true, false, true>(x, 0u, 0u, 0u, twt, md);
-            } else {
-                run_phase<4, 0, 4, false, false, false, true>(x, 0u, 0u, 0u, twt, md);
-            }
-            uint64_t* __restrict__ orow = out + ((size_t)t << log_n) + u0 + u;
+            run_phase<4, 0, 4, false, FP, false, true>(x[v], 0u, 0u, 0u, s_tw + (4 * g + 2 * half + v) * 16, md);
+            const uint32_t off = ((row << log_n) + col) * 8u;
 #pragma unroll
-            for (int e = 0; e < 16; ++e) orow[(size_t)e * S] = x[e];
+            for (int e = 0; e < 16; ++e)
+                *reinterpret_cast<uint64_t*>(reinterpret_cast<char*>(out + (size_t)e * S) + off) = x[v][e];
         }
-        __syncthreads();
+    };
+    for (uint32_t g = wave; g < max_tiles; g += 4) {
+        // a tile's first row is there and has the kind of the others
+        const uint32_t row = __builtin_amdgcn_readfirstlane(s_red[4 * g].row);
+        if (row == PFT_NO_ROW) break;
+        if (__builtin_amdgcn_readfirstlane(s_red[4 * g].fp))
+            tile(g, std::true_type{});
+        else
+            tile(g, std::false_type{});
     }
 }
 
@@ -674,12 +658,21 @@ bool ntt_schedule_valid(uint32_t log_n, const NttSchedule& s) {
     return false;
 }
 
+// fold constants and 16 twiddles for every slot
+static uint32_t bconv_col_dyn_lds(uint32_t tiles) {
+    return 4 * tiles * (uint32_t)(sizeof(BconvRed) + 16 * sizeof(TwPair));
+}
+bool bconv_col_supported(uint32_t log_n, uint32_t nkb, uint32_t tiles) {
+    return log_n >= 9 && nkb <= 6 && 2 * nkb * 16 * BCONV_COLS * 8 + bconv_col_dyn_lds(tiles) <= 65536;
+}
+
 template <bool DOWN, bool IFUSE>
 static void launch_bconv_col(uint32_t nkb, dim3 grid, hipStream_t st, WsRef ws, uint64_t off_in, uint64_t off_out,
                              uint32_t level, const KsConsts& kc, const DevTables& t, uint32_t log_n) {
+    const uint32_t lds = bconv_col_dyn_lds(DOWN ? kc.down_rt : kc.up_rt);
 #define PFT_BCONV_COL(K)                                                                                     \
     case K:                                                                                                  \
-        hipLaunchKernelGGL((k_bconv_col_b<K, DOWN, IFUSE>), grid, dim3(256), 0, st, ws, off_in, off_out, level, \
+        hipLaunchKernelGGL((k_bconv_col_b<K, DOWN, IFUSE>), grid, dim3(256), lds, st, ws, off_in, off_out, level, \
                            kc, t.mods, t.tw_fwd, t.tw_inv, log_n);                                           \
         break;
     switch (nkb) {
@@ -698,7 +691,7 @@ void launch_modup_col_b(uint32_t n, WsRef ws, uint64_t off_d, uint64_t off_ext, 
                         const DevTables& t, uint32_t log_n, bool ifuse, hipStream_t st) {
     const uint32_t beta = (level + kc.alpha - 1) / kc.alpha;
     const uint32_t nkb = (std::min(kc.alpha, level) + 1) / 2;
-    const dim3 grid((1u << log_n) / 256, beta, n);
+    const dim3 grid((1u << log_n) / (16 * BCONV_COLS), beta, n);
     if (ifuse)
         launch_bconv_col<false, true>(nkb, grid, st, ws, off_d, off_ext, level, kc, t, log_n);
     else
@@ -707,7 +700,7 @@ void launch_modup_col_b(uint32_t n, WsRef ws, uint64_t off_d, uint64_t off_ext, 
 
 void launch_moddown_col_b(uint32_t n, WsRef ws, uint64_t off_acc, uint64_t off_conv, uint32_t level,
                           const KsConsts& kc, const DevTables& t, uint32_t log_n, bool ifuse, hipStream_t st) {
-    const dim3 grid((1u << log_n) / 256, 2, n);
+    const dim3 grid((1u << log_n) / (16 * BCONV_COLS), 2, n);
     if (ifuse)
         launch_bconv_col<true, true>((kc.K + 1) / 2, grid, st, ws, off_acc, off_conv, level, kc, t, log_n);
     else

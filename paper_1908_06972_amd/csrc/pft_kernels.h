@@ -118,18 +118,21 @@ struct WsRef {
 };
 #define PFT_NO_OFFSET (~0ull)
 
-// Per-target constants of the digit fold (sum_b 256^b Z_b mod m).
+// Per-target constants of the digit fold (sum_b 256^b Z_b mod m) and of the
+// transform pass that follows it.
 struct BconvRed {
     uint64_t m;
-    uint64_t negm;  // 2^64 - m                      (m >= 2^50)
+    uint64_t negm;  // 2^64 - m
     uint64_t cq0;   // 2^30 m mod 2^64               (m >= 2^50)
     double md;      // m                             (m < 2^50)
     double minv;    // 1 / m
-    double c32;     // 2^32 mod m                    (m < 2^50)
-    double c32q;    // (2^32 mod m) / m              (m < 2^50)
+    uint32_t rinv, rsh;  // as in DevMod             (m >= 2^50)
     uint32_t fp;    // 1 when m < 2^50
-    uint32_t pad;
+    uint32_t row;   // in a kernel's copy by slot: the target row, PFT_NO_ROW: none
+    uint64_t pad;
 };
+#define PFT_NO_ROW 255u
+#define PFT_MAX_SLOTS 72  // targets (at most 64) in tiles of four, each kind's last tile padded
 static_assert(sizeof(BconvRed) == 64, "BconvRed is staged into LDS as 8 words");
 
 struct KsConsts {
@@ -138,7 +141,15 @@ struct KsConsts {
     const TwPair* down_phatinv;   // [K]
     const uint64_t* down_c;       // [K][L] Montgomery form
     const TwPair* down_pinv;      // [2L]: Shoup pairs, then fp64 pairs
-    // MFMA base conversion: int8 digit operands, one 64-bit word per lane
+    // MFMA base conversion: the target rows in tiles of four of one arithmetic
+    // kind (the 60-bit rows' tiles first), the last tile of a kind padded with
+    // PFT_NO_ROW; a list ends with its table or at a tile that starts with
+    // PFT_NO_ROW
+    // ModUp:   [L][dnum][up_rt][4]           (level-1, digit, row tile)
+    // ModDown: [down_rt][4]                  (rows at or above the level count as PFT_NO_ROW)
+    const uint8_t* up_tgt;
+    const uint8_t* down_tgt;
+    // and int8 digit operands in that order, one 64-bit word per lane
     // ModUp:   [L][dnum][up_rt][up_kb][64]   (level-1, digit, row tile, k block, lane)
     // ModDown: [down_rt][down_kb][64]
     const uint64_t* up_aop;
@@ -163,9 +174,10 @@ void launch_modup_b(uint32_t n, WsRef ws, uint64_t off_d, uint64_t off_ext, uint
 // ModUp on the matrix cores fused with the first pass of the forward
 // transform (a radix-16 column pass, stages 0-3) of every converted row:
 // ext holds the output of that pass; the transform continues at pass 1 of a
-// schedule whose first radix is 4 (ntt.hip).  Needs log_n >= 8.  ifuse: d
+// schedule whose first radix is 4 (ntt.hip).  ifuse: d
 // comes from an inverse transform of such a schedule that stopped before its
 // final (radix-16 column) pass; the kernel applies that pass to its inputs.
+bool bconv_col_supported(uint32_t log_n, uint32_t nkb, uint32_t tiles);  // its LDS fits (tiles: up_rt or down_rt)
 void launch_modup_col_b(uint32_t n, WsRef ws, uint64_t off_d, uint64_t off_ext, uint32_t level, const KsConsts& kc,
                         const DevTables& t, uint32_t log_n, bool ifuse, hipStream_t st);
 // ModDown's conversion (conv_b = base conversion of the K special rows of
