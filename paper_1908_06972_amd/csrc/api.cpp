@@ -2189,7 +2189,15 @@ extern "C" int pft_rotate(pft_ctx* c, const pft_ct* in, int32_t step, pft_ct* ou
     return pft_rotate_batch(c, 1, in, step, out);
 }
 
+static int rotate_core(pft_ctx* c, uint32_t n, const pft_ct* in, int32_t step, pft_ct* out, const pft_ct* add);
+
 extern "C" int pft_rotate_batch(pft_ctx* c, uint32_t n, const pft_ct* in, int32_t step, pft_ct* out) {
+    return rotate_core(c, n, in, step, out, nullptr);
+}
+
+// add: null, or the ciphertexts added to the rotations (of the inputs'
+// levels; add[i] may be out[i]; the step is then no multiple of N/2).
+static int rotate_core(pft_ctx* c, uint32_t n, const pft_ct* in, int32_t step, pft_ct* out, const pft_ct* add) {
     if (!c || !in || !out) return fail(PFT_EINVAL, "null argument");
     const bool identity = norm_step(step, c->P->n) == 0;
     if (!identity && !has_rot(c, step)) return fail(PFT_ENOKEY, "no rotation key for step %d", step);
@@ -2237,6 +2245,10 @@ extern "C" int pft_rotate_batch(pft_ctx* c, uint32_t n, const pft_ct* in, int32_
         ki.mode = KS_ROTATE;
         ki.src = I;
         ki.overlap = ks_overlap(cnt, O, I, 2 * nl);
+        if (add) {
+            for (uint32_t z = 0; z < cnt; ++z) ki.src2.p[z] = add[g[z]].data;
+            ki.has_add = true;
+        }
         ki.kappa = kappa;
         ki.kappa_inv = kappa_inv;
         key_switch_b(c, cnt, ws, K, *key, ki, O);
@@ -2493,7 +2505,7 @@ struct pft_ptmat {
     pft_ctx* ctx = nullptr;
     uint32_t n_o = 0, n_i = 0, n_in = 0, level = 0, b = 0, G = 0;
     double pt_scale = 0;
-    uint64_t* pt = nullptr;  // [G][n_in * b][level][N], NTT domain, times 2^64 mod q
+    uint64_t* pt = nullptr;  // [G][n_in * b][level][N], NTT domain, in the form of launch_key_form
     std::vector<int64_t> coeffs;  // host [n_in][G][b][N]: the integer plaintexts, for the plan export
 };
 
@@ -2541,9 +2553,11 @@ static int ptmat_upload(pft_ctx* c, pft_ptmat* m, const int64_t* coeffs) {
             const uint32_t nj = std::min<uint32_t>(PFT_SMALL_POLYS, J - j0);
             SmallBatch out = sb_rows(P, dst + (size_t)j0 * l * N, nj, l, l);
             launch_int_to_rns((const int64_t*)c->ws + (size_t)j0 * N, out, c->tabs, P->log_n, c->stream);
-            launch_mul_const(out, out, c->to_mont, c->tabs, P->log_n, c->stream);  // [0, q) kept; NTT below
         }
         ntt_rows(c, dst, J, l, l, false);
+        for (uint32_t j0 = 0; j0 < J; j0 += PFT_SMALL_POLYS)
+            launch_key_form(sb_rows(P, dst + (size_t)j0 * l * N, std::min<uint32_t>(PFT_SMALL_POLYS, J - j0), l, l),
+                            c->to_mont, c->tabs, P->log_n, c->stream);
         HIPCK(hipStreamSynchronize(c->stream));  // the staged host rows are reused for the next g
     }
     return PFT_OK;
@@ -2695,6 +2709,38 @@ static std::vector<pft_ct> cts_at(uint64_t* base, size_t stride, uint64_t off, u
     return v;
 }
 
+// The sums of a matrix-vector product over its giant steps and over the n_i /
+// n_o blocks, for documents whose acc[G] ciphertexts lie at off_acc (and one
+// more at off_tmp) of A + z stride: tot = sum_g ROTATE(acc[g], g b), then tot
+// += ROTATE(tot, s), each sum finished by the rotation's own key switch.  The
+// result goes to out.
+static int giant_steps(pft_ctx* c, uint32_t n_docs, uint64_t* A, size_t stride, uint64_t off_acc, uint64_t off_tmp,
+                       uint64_t ct_words, uint32_t l, double scale, const pft_ptmat& m, pft_ct* out) {
+    int r;
+    uint64_t tot = off_acc, spare = off_tmp;  // acc[0] collects the total
+    for (uint32_t g = 1; g < m.G; ++g) {
+        const std::vector<pft_ct> src = cts_at(A, stride, off_acc + g * ct_words, n_docs, l, scale);
+        std::vector<pft_ct> dst = cts_at(A, stride, tot, n_docs, l, scale);
+        if ((r = rotate_core(c, n_docs, src.data(), (int32_t)(g * m.b), dst.data(), dst.data()))) return r;
+    }
+    for (uint32_t s = m.n_o; s < m.n_i; s <<= 1) {
+        const std::vector<pft_ct> src = cts_at(A, stride, tot, n_docs, l, scale);
+        std::vector<pft_ct> dst = cts_at(A, stride, spare, n_docs, l, scale);
+        if ((r = rotate_core(c, n_docs, src.data(), (int32_t)s, dst.data(), src.data()))) return r;
+        std::swap(tot, spare);
+    }
+    for (uint32_t z0 = 0; z0 < n_docs; z0 += PFT_MAX_ITEMS) {
+        const uint32_t cnt = std::min<uint32_t>(PFT_MAX_ITEMS, n_docs - z0);
+        ItemPtrs I{}, O{};
+        for (uint32_t u = 0; u < cnt; ++u) {
+            I.p[u] = A + (z0 + u) * stride + tot;
+            O.p[u] = out[z0 + u].data;
+        }
+        launch_copy_rows_b(cnt, I, 0, O, 0, 2 * l, c->P->log_n, c->stream);
+    }
+    return PFT_OK;
+}
+
 extern "C" int pft_ptmatvec(pft_ctx* c, const pft_ptmat* m, uint32_t n_docs, const pft_ct* in, pft_ct* out) {
     if (!c || !m || !in || !out) return fail(PFT_EINVAL, "null argument");
     if (m->ctx != c) return fail(PFT_EINVAL, "plaintext matrix belongs to another context");
@@ -2716,7 +2762,7 @@ extern "C" int pft_ptmatvec(pft_ctx* c, const pft_ptmat* m, uint32_t n_docs, con
     const double scale = in[0].scale;
     const uint64_t ct_words = 2ull * l * P->n;
     // per document: baby[n_in][b] | acc[G] (acc[0] collects the total) | tmp
-    const uint64_t off_baby = 0, off_acc = (uint64_t)J * ct_words, off_tot = off_acc,
+    const uint64_t off_baby = 0, off_acc = (uint64_t)J * ct_words,
                    off_tmp = off_acc + (uint64_t)m->G * ct_words, stride = off_tmp + ct_words;
     if ((r = ensure_aux(c, (size_t)n_docs * stride * 8))) return r;
     uint64_t* A = c->aux;
@@ -2760,34 +2806,7 @@ extern "C" int pft_ptmatvec(pft_ctx* c, const pft_ptmat* m, uint32_t n_docs, con
                   });
         }
     }
-    for (uint32_t g = 1; g < m->G; ++g) {
-        std::vector<pft_ct> src = cts_at(A, stride, off_acc + g * ct_words, n_docs, l, scale * m->pt_scale);
-        std::vector<pft_ct> dst = cts_at(A, stride, off_tmp, n_docs, l, scale * m->pt_scale);
-        if ((r = pft_rotate_batch(c, n_docs, src.data(), (int32_t)(g * m->b), dst.data()))) return r;
-        for (uint32_t z0 = 0; z0 < n_docs; z0 += 65535) {
-            const uint32_t cnt = std::min<uint32_t>(65535, n_docs - z0);
-            launch_add_ct_b(cnt, WsRef{A + z0 * stride, stride}, off_tot, off_tmp, off_tot, l, c->tabs, lg, c->stream);
-        }
-    }
-    // rotate-and-sum over the n_i / n_o blocks
-    for (uint32_t s = m->n_o; s < m->n_i; s <<= 1) {
-        std::vector<pft_ct> src = cts_at(A, stride, off_tot, n_docs, l, scale * m->pt_scale);
-        std::vector<pft_ct> dst = cts_at(A, stride, off_tmp, n_docs, l, scale * m->pt_scale);
-        if ((r = pft_rotate_batch(c, n_docs, src.data(), (int32_t)s, dst.data()))) return r;
-        for (uint32_t z0 = 0; z0 < n_docs; z0 += 65535) {
-            const uint32_t cnt = std::min<uint32_t>(65535, n_docs - z0);
-            launch_add_ct_b(cnt, WsRef{A + z0 * stride, stride}, off_tot, off_tmp, off_tot, l, c->tabs, lg, c->stream);
-        }
-    }
-    for (uint32_t z0 = 0; z0 < n_docs; z0 += PFT_MAX_ITEMS) {
-        const uint32_t cnt = std::min<uint32_t>(PFT_MAX_ITEMS, n_docs - z0);
-        ItemPtrs I{}, O{};
-        for (uint32_t u = 0; u < cnt; ++u) {
-            I.p[u] = A + (z0 + u) * stride + off_tot;
-            O.p[u] = out[z0 + u].data;
-        }
-        launch_copy_rows_b(cnt, I, 0, O, 0, 2 * l, lg, c->stream);
-    }
+    if ((r = giant_steps(c, n_docs, A, stride, off_acc, off_tmp, ct_words, l, scale * m->pt_scale, *m, out))) return r;
     for (uint32_t z = 0; z < n_docs; ++z) {
         out[z].level = l;
         out[z].scale = scale * m->pt_scale;
@@ -2837,7 +2856,7 @@ extern "C" int pft_ctmatvec(pft_ctx* c, uint32_t n_o, uint32_t n_i, uint32_t n_i
     const uint32_t lg = P->log_n;
     const uint64_t nl = (uint64_t)l * P->n, ct_words = 2 * nl;
     // per document in aux: baby[n_in][b] | acc[G] (acc[0] collects the total) | tmp
-    const uint64_t off_baby = 0, off_acc = (uint64_t)J * ct_words, off_tot = off_acc,
+    const uint64_t off_baby = 0, off_acc = (uint64_t)J * ct_words,
                    off_tmp = off_acc + (uint64_t)G * ct_words, stride = off_tmp + ct_words;
     if ((r = ensure_aux(c, (size_t)n_docs * stride * 8))) return r;
     // per document in ws: the summed tensor [3][l][N], then key switching
@@ -2899,33 +2918,7 @@ extern "C" int pft_ctmatvec(pft_ctx* c, uint32_t n_o, uint32_t n_i, uint32_t n_i
             }
         }
     }
-    for (uint32_t g = 1; g < G; ++g) {
-        std::vector<pft_ct> src = cts_at(A, stride, off_acc + g * ct_words, n_docs, l, scale);
-        std::vector<pft_ct> dst = cts_at(A, stride, off_tmp, n_docs, l, scale);
-        if ((r = pft_rotate_batch(c, n_docs, src.data(), (int32_t)(g * b), dst.data()))) return r;
-        for (uint32_t z0 = 0; z0 < n_docs; z0 += 65535) {
-            const uint32_t cnt = std::min<uint32_t>(65535, n_docs - z0);
-            launch_add_ct_b(cnt, WsRef{A + z0 * stride, stride}, off_tot, off_tmp, off_tot, l, c->tabs, lg, c->stream);
-        }
-    }
-    for (uint32_t s = n_o; s < n_i; s <<= 1) {
-        std::vector<pft_ct> src = cts_at(A, stride, off_tot, n_docs, l, scale);
-        std::vector<pft_ct> dst = cts_at(A, stride, off_tmp, n_docs, l, scale);
-        if ((r = pft_rotate_batch(c, n_docs, src.data(), (int32_t)s, dst.data()))) return r;
-        for (uint32_t z0 = 0; z0 < n_docs; z0 += 65535) {
-            const uint32_t cnt = std::min<uint32_t>(65535, n_docs - z0);
-            launch_add_ct_b(cnt, WsRef{A + z0 * stride, stride}, off_tot, off_tmp, off_tot, l, c->tabs, lg, c->stream);
-        }
-    }
-    for (uint32_t z0 = 0; z0 < n_docs; z0 += PFT_MAX_ITEMS) {
-        const uint32_t cnt = std::min<uint32_t>(PFT_MAX_ITEMS, n_docs - z0);
-        ItemPtrs I{}, O{};
-        for (uint32_t u = 0; u < cnt; ++u) {
-            I.p[u] = A + (z0 + u) * stride + off_tot;
-            O.p[u] = out[z0 + u].data;
-        }
-        launch_copy_rows_b(cnt, I, 0, O, 0, 2 * l, lg, c->stream);
-    }
+    if ((r = giant_steps(c, n_docs, A, stride, off_acc, off_tmp, ct_words, l, scale, plan, out))) return r;
     for (uint32_t z = 0; z < n_docs; ++z) {
         out[z].level = l;
         out[z].scale = scale;
@@ -2938,7 +2931,7 @@ struct pft_ptdot {
     pft_ctx* ctx = nullptr;
     uint32_t n_out = 0, J = 0, level = 0;
     double pt_scale = 0;
-    uint64_t* pt = nullptr;  // [n_out][J][level][N], NTT domain, times 2^64 mod q
+    uint64_t* pt = nullptr;  // [n_out][J][level][N], NTT domain, in the form of launch_key_form
 };
 
 extern "C" int pft_ptdot_create_from_coeffs(pft_ctx* c, const int64_t* coeffs, uint32_t n_out, uint32_t J,
@@ -2974,8 +2967,8 @@ extern "C" int pft_ptdot_create_from_coeffs(pft_ctx* c, const int64_t* coeffs, u
         uint64_t* dst = m->pt + j0 * level * N;
         SmallBatch sb = sb_rows(P, dst, nj, level, level);
         launch_int_to_rns((const int64_t*)c->ws, sb, c->tabs, P->log_n, c->stream);
-        launch_mul_const(sb, sb, c->to_mont, c->tabs, P->log_n, c->stream);
         ntt_rows(c, dst, nj, level, level, false);
+        launch_key_form(sb, c->to_mont, c->tabs, P->log_n, c->stream);
         HIPCK(hipStreamSynchronize(c->stream));  // the staged rows are reused next
     }
     *out = m;

@@ -455,70 +455,106 @@ __global__ __launch_bounds__(TB) void k_rescale_expand_b(WsRef ws, uint64_t off_
     ws_item(ws)[off_tmp + at(b * nl + kq, log_n, k)] = r >= h ? r - h : r + qk - h;
 }
 
-// ws_z[off_out] = ws_z[off_a] + ws_z[off_b] over [2][level][N]
-__global__ __launch_bounds__(TB) void k_add_ct_b(WsRef ws, uint64_t off_a, uint64_t off_b, uint64_t off_out,
-                                                 uint32_t level, const DevMod* __restrict__ mods, uint32_t log_n) {
-    const uint32_t k = blockIdx.x * TB + threadIdx.x;
-    const uint32_t row = blockIdx.y;
-    const uint64_t q = mods[row % level].q;
-    uint64_t* __restrict__ w = ws_item(ws);
-    const size_t o = at(row, log_n, k);
-    w[off_out + o] = add_mod(w[off_a + o], w[off_b + o], q);
-}
-
 // The inner sums of up to PT_GT giant steps at once: for g < n_g,
 // acc_{z,g}[row] = sum_{j<J} baby_{z,j}[row] pt_{g,j}[row mod level], acc_{z,g}
 // at ws_z + off_acc + g ct_words, pt_{g,j} at pt + (g J + j) level N; each
 // baby residue is read once for all n_g giant steps (or outputs).  One thread
-// per (item, row, coefficient); the items of one coefficient block are
-// consecutive workgroups (items vary fastest), so the plaintext tiles they
-// share are fetched about once per launch.  The plaintext rows hold
-// plaintext * 2^64 mod q (Montgomery form); each 128-bit sum of full products
-// is reduced every 8 terms, which keeps it below q 2^64.
+// per (Z items, row, coefficient); the item groups of one coefficient block
+// are consecutive workgroups, so the plaintext tiles they share are fetched
+// about once per launch, and a plaintext residue is loaded once for Z items:
+// with one item a thread those loads (J n_g words an output set, from L2) and
+// 128-bit sums on every row took the time (6.1 ms for 32 items, 16 terms and
+// 8 outputs at N = 2^15, 16 rows, of whose 6.9 GB the copy rate takes 1.3 ms).
+// Plaintext rows in the form of launch_key_form.  Rows with q < 2^50: each
+// product by fmulmod (within 0.9q), the sums brought within q/2 every 8 terms
+// (below 7.7q < 2^53 before).  The other rows: full 128-bit products of the
+// Montgomery form, reduced every 8 terms, which keeps the sum below q 2^64.
 constexpr uint32_t PT_GT = 8;
+template <uint32_t Z>
 __global__ __launch_bounds__(TB) void k_pt_dot_multi_b(WsRef ws, uint32_t n_items, uint64_t off_baby,
                                                        uint64_t ct_words, const uint64_t* __restrict__ pt, uint32_t J,
                                                        uint32_t n_g, uint64_t off_acc, uint32_t level,
                                                        const DevMod* __restrict__ mods, uint32_t log_n) {
     using u128 = unsigned __int128;
     const uint32_t kblocks = (1u << log_n) / TB;
-    const uint32_t z = blockIdx.x % n_items;
-    const uint32_t rest = blockIdx.x / n_items;
+    const uint32_t groups = (n_items + Z - 1) / Z;
+    const uint32_t z0 = (blockIdx.x % groups) * Z;
+    const uint32_t nz = min(Z, n_items - z0);
+    const uint32_t rest = blockIdx.x / groups;
     const uint32_t k = (rest % kblocks) * TB + threadIdx.x;
     const uint32_t row = rest / kblocks, i = row % level;
     const DevMod md = mods[i];
-    uint64_t* __restrict__ w = ws.base + (size_t)z * ws.stride;
-    const size_t o = at(row, log_n, k);
+    uint64_t* __restrict__ w = ws.base + (size_t)z0 * ws.stride + ((size_t)row << log_n);
+    const uint64_t* __restrict__ pr = pt + ((size_t)i << log_n);
     const size_t pstep = ((size_t)J * level) << log_n;  // words between giant steps of pt
-    u128 a[PT_GT];
-    uint64_t res[PT_GT];
+    if (md.fp) {
+#pragma clang fp contract(off)
+        const double q = md.qd, qinv = md.qinv;
+        double a[Z][PT_GT];
 #pragma unroll
-    for (uint32_t g = 0; g < PT_GT; ++g) {
-        a[g] = 0;
-        res[g] = 0;
-    }
-    auto fold = [&](uint32_t g) {
-        res[g] = add_mod(res[g], mont_redc((uint64_t)a[g], (uint64_t)(a[g] >> 64), md.q, md.mont_neg_qinv), md.q);
-        a[g] = 0;
-    };
-    for (uint32_t j = 0; j < J; ++j) {
-        const uint64_t x = w[off_baby + j * ct_words + o];
-        const uint64_t* __restrict__ pj = pt + at(j * level + i, log_n, k);
+        for (uint32_t z = 0; z < Z; ++z)
 #pragma unroll
-        for (uint32_t g = 0; g < PT_GT; ++g)
-            if (g < n_g) a[g] += (u128)x * pj[g * pstep];
-        if ((j & 7u) == 7u) {
+            for (uint32_t g = 0; g < PT_GT; ++g) a[z][g] = 0.0;
+        for (uint32_t j = 0; j < J; ++j) {
+            double x[Z];
+#pragma unroll
+            for (uint32_t z = 0; z < Z; ++z)
+                x[z] = as_f(fp_from_u64(w[(z < nz ? z : 0) * ws.stride + off_baby + j * ct_words + k]));
+            const uint64_t* __restrict__ pj = pr + (((size_t)j * level) << log_n);
 #pragma unroll
             for (uint32_t g = 0; g < PT_GT; ++g)
-                if (g < n_g) fold(g);
-        }
-    }
+                if (g < n_g) {
+                    const double p = as_f(pj[g * pstep + k]), pq = p * qinv;
 #pragma unroll
-    for (uint32_t g = 0; g < PT_GT; ++g)
-        if (g < n_g) {
-            fold(g);
-            w[off_acc + g * ct_words + o] = res[g];
+                    for (uint32_t z = 0; z < Z; ++z) a[z][g] += fmulmod(x[z], p, pq, q);
+                }
+            if ((j & 7u) == 7u) {
+#pragma unroll
+                for (uint32_t z = 0; z < Z; ++z)
+#pragma unroll
+                    for (uint32_t g = 0; g < PT_GT; ++g) a[z][g] = freduce(a[z][g], q, qinv);
+            }
         }
+#pragma unroll
+        for (uint32_t z = 0; z < Z; ++z)
+            if (z < nz) {
+#pragma unroll
+                for (uint32_t g = 0; g < PT_GT; ++g)
+                    if (g < n_g) w[z * ws.stride + off_acc + g * ct_words + k] = fp_to_u64(as_u(a[z][g]), q, qinv);
+            }
+        return;
+    }
+    for (uint32_t z = 0; z < nz; ++z, w += ws.stride) {
+        u128 a[PT_GT];
+        uint64_t res[PT_GT];
+#pragma unroll
+        for (uint32_t g = 0; g < PT_GT; ++g) {
+            a[g] = 0;
+            res[g] = 0;
+        }
+        auto fold = [&](uint32_t g) {
+            res[g] = add_mod(res[g], mont_redc((uint64_t)a[g], (uint64_t)(a[g] >> 64), md.q, md.mont_neg_qinv), md.q);
+            a[g] = 0;
+        };
+        for (uint32_t j = 0; j < J; ++j) {
+            const uint64_t x = w[off_baby + j * ct_words + k];
+            const uint64_t* __restrict__ pj = pr + (((size_t)j * level) << log_n);
+#pragma unroll
+            for (uint32_t g = 0; g < PT_GT; ++g)
+                if (g < n_g) a[g] += (u128)x * pj[g * pstep + k];
+            if ((j & 7u) == 7u) {
+#pragma unroll
+                for (uint32_t g = 0; g < PT_GT; ++g)
+                    if (g < n_g) fold(g);
+            }
+        }
+#pragma unroll
+        for (uint32_t g = 0; g < PT_GT; ++g)
+            if (g < n_g) {
+                fold(g);
+                w[off_acc + g * ct_words + k] = res[g];
+            }
+    }
 }
 
 // out_z = in_z + c_z at X^0: in the evaluation domain the constant c_z[i]
@@ -538,11 +574,15 @@ __global__ __launch_bounds__(TB) void k_add_const_b(ItemPtrs in, ItemPtrs out, c
 // place of HMULPLAIN): d0 = sum e0 x0, d1 = sum (e0 x1 + e1 x0), d2 = sum
 // e1 x1.  Giant step g takes its diagonals from e.p[g J + j] and writes
 // [3][level][N] at item g n_items + z of ws + off_d; each baby residue is read
-// once for all of them.  The full 128-bit products are summed and brought
-// back by a Montgomery reduction every 8 diagonal terms (at most 16 products
-// below q^2 each: below q 2^64 for q < 2^60); the reductions' factor 2^-64
-// is undone once at the end by a Shoup product with 2^64 mod q (to_mont).
+// once for all of them, and a diagonal's residues once for the Z items of a
+// thread.  Rows with q < 2^50: each product by fmulmod (within 0.9q), the sums
+// brought within q/2 every 4 terms (below 7.7q < 2^53 before).  The other
+// rows: the full 128-bit products are summed and brought back by a Montgomery
+// reduction every 8 diagonal terms (at most 16 products below q^2 each: below
+// q 2^64 for q < 2^60); the reductions' factor 2^-64 is undone once at the
+// end by a Shoup product with 2^64 mod q (to_mont).
 constexpr uint32_t CT_GT = 4;
+template <uint32_t Z>
 __global__ __launch_bounds__(TB) void k_ct_dot_multi_b(ItemPtrs e, uint32_t J, uint32_t n_g, WsRef xs, uint64_t off_x,
                                                        uint64_t ct_words, WsRef ws, uint32_t n_items, uint64_t off_d,
                                                        uint32_t level, const DevMod* __restrict__ mods,
@@ -550,53 +590,111 @@ __global__ __launch_bounds__(TB) void k_ct_dot_multi_b(ItemPtrs e, uint32_t J, u
     using u128 = unsigned __int128;
     const uint32_t k = blockIdx.x * TB + threadIdx.x;
     const uint32_t i = blockIdx.y;
+    const uint32_t z0 = blockIdx.z * Z, nz = min(Z, n_items - z0);
     const DevMod md = mods[i];
     const uint64_t q = md.q;
-    const uint64_t* __restrict__ x = xs.base + (size_t)blockIdx.z * xs.stride + off_x;
-    const size_t o0 = at(i, log_n, k), o1 = at(level + i, log_n, k);
-    u128 s[CT_GT][3];
-    uint64_t d[CT_GT][3];
+    const size_t o0 = at(i, log_n, k), o1 = at(level + i, log_n, k), o2 = at(2 * level + i, log_n, k);
+    if (md.fp) {
+#pragma clang fp contract(off)
+        const double qd = md.qd, qinv = md.qinv;
+        const uint64_t* __restrict__ xb = xs.base + (size_t)z0 * xs.stride + off_x;
+        double a[Z][CT_GT][3];
 #pragma unroll
-    for (uint32_t g = 0; g < CT_GT; ++g)
+        for (uint32_t z = 0; z < Z; ++z)
 #pragma unroll
-        for (int t = 0; t < 3; ++t) {
-            s[g][t] = 0;
-            d[g][t] = 0;
+            for (uint32_t g = 0; g < CT_GT; ++g)
+#pragma unroll
+                for (int t = 0; t < 3; ++t) a[z][g][t] = 0.0;
+        for (uint32_t j = 0; j < J; ++j) {
+            double x0[Z], x1[Z];
+#pragma unroll
+            for (uint32_t z = 0; z < Z; ++z) {
+                const uint64_t* __restrict__ xz = xb + (z < nz ? z : 0) * xs.stride + j * ct_words;
+                x0[z] = as_f(fp_from_u64(xz[o0]));
+                x1[z] = as_f(fp_from_u64(xz[o1]));
+            }
+#pragma unroll
+            for (uint32_t g = 0; g < CT_GT; ++g)
+                if (g < n_g) {
+                    const uint64_t* __restrict__ E = e.p[g * J + j];
+                    const double e0 = as_f(fp_from_u64(E[o0])), e1 = as_f(fp_from_u64(E[o1]));
+                    const double e0q = e0 * qinv, e1q = e1 * qinv;
+#pragma unroll
+                    for (uint32_t z = 0; z < Z; ++z) {
+                        a[z][g][0] += fmulmod(x0[z], e0, e0q, qd);
+                        a[z][g][1] += fmulmod(x1[z], e0, e0q, qd);
+                        a[z][g][1] += fmulmod(x0[z], e1, e1q, qd);
+                        a[z][g][2] += fmulmod(x1[z], e1, e1q, qd);
+                    }
+                }
+            if ((j & 3u) == 3u) {
+#pragma unroll
+                for (uint32_t z = 0; z < Z; ++z)
+#pragma unroll
+                    for (uint32_t g = 0; g < CT_GT; ++g)
+#pragma unroll
+                        for (int t = 0; t < 3; ++t) a[z][g][t] = freduce(a[z][g][t], qd, qinv);
+            }
         }
-    auto fold = [&](uint32_t g) {
 #pragma unroll
-        for (int t = 0; t < 3; ++t) {
-            d[g][t] = add_mod(d[g][t], mont_redc((uint64_t)s[g][t], (uint64_t)(s[g][t] >> 64), q, md.mont_neg_qinv), q);
-            s[g][t] = 0;
+        for (uint32_t z = 0; z < Z; ++z)
+#pragma unroll
+            for (uint32_t g = 0; g < CT_GT; ++g)
+                if (z < nz && g < n_g) {
+                    uint64_t* __restrict__ dd = ws.base + (size_t)(g * n_items + z0 + z) * ws.stride + off_d;
+                    dd[o0] = fp_to_u64(as_u(a[z][g][0]), qd, qinv);
+                    dd[o1] = fp_to_u64(as_u(a[z][g][1]), qd, qinv);
+                    dd[o2] = fp_to_u64(as_u(a[z][g][2]), qd, qinv);
+                }
+        return;
+    }
+    const TwPair r = to_mont[i];
+    for (uint32_t z = z0; z < z0 + nz; ++z) {
+        const uint64_t* __restrict__ x = xs.base + (size_t)z * xs.stride + off_x;
+        u128 s[CT_GT][3];
+        uint64_t d[CT_GT][3];
+#pragma unroll
+        for (uint32_t g = 0; g < CT_GT; ++g)
+#pragma unroll
+            for (int t = 0; t < 3; ++t) {
+                s[g][t] = 0;
+                d[g][t] = 0;
+            }
+        auto fold = [&](uint32_t g) {
+#pragma unroll
+            for (int t = 0; t < 3; ++t) {
+                d[g][t] =
+                    add_mod(d[g][t], mont_redc((uint64_t)s[g][t], (uint64_t)(s[g][t] >> 64), q, md.mont_neg_qinv), q);
+                s[g][t] = 0;
+            }
+        };
+        for (uint32_t j = 0; j < J; ++j) {
+            const uint64_t x0 = x[j * ct_words + o0], x1 = x[j * ct_words + o1];
+#pragma unroll
+            for (uint32_t g = 0; g < CT_GT; ++g)
+                if (g < n_g) {
+                    const uint64_t* __restrict__ E = e.p[g * J + j];
+                    const uint64_t e0 = E[o0], e1 = E[o1];
+                    s[g][0] += (u128)e0 * x0;
+                    s[g][1] += (u128)e0 * x1 + (u128)e1 * x0;
+                    s[g][2] += (u128)e1 * x1;
+                }
+            if ((j & 7u) == 7u) {
+#pragma unroll
+                for (uint32_t g = 0; g < CT_GT; ++g)
+                    if (g < n_g) fold(g);
+            }
         }
-    };
-    for (uint32_t j = 0; j < J; ++j) {
-        const uint64_t x0 = x[j * ct_words + o0], x1 = x[j * ct_words + o1];
 #pragma unroll
         for (uint32_t g = 0; g < CT_GT; ++g)
             if (g < n_g) {
-                const uint64_t* __restrict__ E = e.p[g * J + j];
-                const uint64_t e0 = E[o0], e1 = E[o1];
-                s[g][0] += (u128)e0 * x0;
-                s[g][1] += (u128)e0 * x1 + (u128)e1 * x0;
-                s[g][2] += (u128)e1 * x1;
+                fold(g);
+                uint64_t* __restrict__ dd = ws.base + (size_t)(g * n_items + z) * ws.stride + off_d;
+                dd[o0] = shoup(d[g][0], r.w, r.wp, q);
+                dd[o1] = shoup(d[g][1], r.w, r.wp, q);
+                dd[o2] = shoup(d[g][2], r.w, r.wp, q);
             }
-        if ((j & 7u) == 7u) {
-#pragma unroll
-            for (uint32_t g = 0; g < CT_GT; ++g)
-                if (g < n_g) fold(g);
-        }
     }
-    const TwPair r = to_mont[i];
-#pragma unroll
-    for (uint32_t g = 0; g < CT_GT; ++g)
-        if (g < n_g) {
-            fold(g);
-            uint64_t* __restrict__ dd = ws.base + (size_t)(g * n_items + blockIdx.z) * ws.stride + off_d;
-            dd[o0] = shoup(d[g][0], r.w, r.wp, q);
-            dd[o1] = shoup(d[g][1], r.w, r.wp, q);
-            dd[at(2 * level + i, log_n, k)] = shoup(d[g][2], r.w, r.wp, q);
-        }
 }
 
 // out_z[b][i] = in_z[b][i] * c_z[i] (Shoup pairs, [n][level] on the device):
@@ -706,20 +804,25 @@ void launch_rescale_expand_b(uint32_t n, WsRef ws, uint64_t off_last, uint64_t o
                        off_tmp, level, mode, t.mods, log_n);
 }
 
-void launch_add_ct_b(uint32_t n, WsRef ws, uint64_t off_a, uint64_t off_b, uint64_t off_out, uint32_t level,
-                     const DevTables& t, uint32_t log_n, hipStream_t st) {
-    hipLaunchKernelGGL(k_add_ct_b, grid_nk(log_n, 2 * level, n), dim3(TB), 0, st, ws, off_a, off_b, off_out, level,
-                       t.mods, log_n);
-}
-
 uint32_t pt_dot_multi_steps() { return PT_GT; }
 
 void launch_pt_dot_multi_b(uint32_t n, WsRef ws, uint64_t off_baby, uint64_t ct_words, const uint64_t* pt, uint32_t J,
                            uint32_t n_g, uint64_t off_acc, uint32_t level, const DevTables& t, uint32_t log_n,
                            hipStream_t st) {
-    const uint64_t blocks = (uint64_t)n * ((1u << log_n) / TB) * 2 * level;
-    hipLaunchKernelGGL(k_pt_dot_multi_b, dim3((uint32_t)blocks), dim3(TB), 0, st, ws, n, off_baby, ct_words, pt, J, n_g,
-                       off_acc, level, t.mods, log_n);
+    // items per thread: as many as there are, up to the four whose sums (64
+    // registers) leave room for the products
+    auto go = [&](auto zc) {
+        constexpr uint32_t Z = decltype(zc)::value;
+        const uint64_t blocks = (uint64_t)((n + Z - 1) / Z) * ((1u << log_n) / TB) * 2 * level;
+        hipLaunchKernelGGL(k_pt_dot_multi_b<Z>, dim3((uint32_t)blocks), dim3(TB), 0, st, ws, n, off_baby, ct_words, pt,
+                           J, n_g, off_acc, level, t.mods, log_n);
+    };
+    if (n >= 3)
+        go(std::integral_constant<uint32_t, 4>{});
+    else if (n == 2)
+        go(std::integral_constant<uint32_t, 2>{});
+    else
+        go(std::integral_constant<uint32_t, 1>{});
 }
 
 void launch_add_const_b(uint32_t n, const ItemPtrs& in, const ItemPtrs& out, const TwPair* consts, uint32_t level,
@@ -733,8 +836,15 @@ uint32_t ct_dot_multi_steps() { return CT_GT; }
 void launch_ct_dot_multi_b(uint32_t n, const ItemPtrs& e, uint32_t J, uint32_t n_g, WsRef xs, uint64_t off_x,
                            uint64_t ct_words, WsRef ws, uint64_t off_d, uint32_t level, const TwPair* to_mont,
                            const DevTables& t, uint32_t log_n, hipStream_t st) {
-    hipLaunchKernelGGL(k_ct_dot_multi_b, grid_nk(log_n, level, n), dim3(TB), 0, st, e, J, n_g, xs, off_x, ct_words, ws,
-                       n, off_d, level, t.mods, to_mont, log_n);
+    auto go = [&](auto zc) {
+        constexpr uint32_t Z = decltype(zc)::value;
+        hipLaunchKernelGGL(k_ct_dot_multi_b<Z>, grid_nk(log_n, level, (n + Z - 1) / Z), dim3(TB), 0, st, e, J, n_g, xs,
+                           off_x, ct_words, ws, n, off_d, level, t.mods, to_mont, log_n);
+    };
+    if (n >= 2)
+        go(std::integral_constant<uint32_t, 2>{});
+    else
+        go(std::integral_constant<uint32_t, 1>{});
 }
 
 void launch_scale_const_b(uint32_t n, const ItemPtrs& in, const ItemPtrs& out, const TwPair* consts, uint32_t level,
