@@ -40,15 +40,20 @@ KERNEL_NAMES = {2: "k_modup_mfma_b", 3: "k_key_inner_items", 4: "k_moddown_mfma_
 
 def kernel_name(kid, variant):
     """Demangled kernel name of one instantiation (see pft_prof_read_variants)."""
+    if kid == 1 and variant >= 8192:  # the inverse row pass before the base conversions
+        v = variant - 8192
+        return "k_ks_inv<%d, %d, %d>" % (v & 63, 2 if v & 64 else 3, max(v & 63, 10))
     if kid in (0, 1) and variant:
         v = variant - 1
         b = lambda x: "true" if x else "false"  # noqa: E731
         name = "k_ntt_pass<%d, %d, %s, %s, %s, %s, %s" % (v & 31, 3 if v & 256 else 4, b(kid == 1), b(v & 32),
                                                           b(v & 64), b(v & 128), b(v & 512))
-        return name + (", true>" if v & 1024 else ">")  # X -> X^kappa folded into the pass
-    if kid == 3 and variant >= 1024:  # inner product fused with the row pass of ModUp's rows
+        return name + ">"
+    if kid == 3 and variant >= 1024:  # the fused row kernels of key switching and RESCALE
         v = variant - 1024
-        return "k_row_inner<%d, 3, %s, %d>" % (v & 63, "true" if v & 64 else "false", 2 if v & 128 else 1)
+        kind = 3 if v & 512 else 2 if v & 64 else 1  # rows of both kinds, fp64 rows, integer rows
+        return "k_ks_rows<%d, %d, %d, %du, %d, %s>" % (v & 63, 2 if v & 512 else 3, max(v & 63, 10), kind,
+                                                       2 if v & 128 else 1, "true" if v & 256 else "false")
     if kid == 8 and variant == 1:  # RESCALE's expansion fused with the first transform pass
         return "k_rescale_col_b"
     if kid in (2, 4) and variant >= 64:  # base conversion fused with the first (and last inverse) pass

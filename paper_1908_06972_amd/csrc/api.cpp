@@ -951,10 +951,7 @@ static void ntt_jobs(pft_ctx* c, const std::vector<NttJob>& jobs, uint32_t n_lim
             for (uint32_t i = 0; i < PFT_MAX_POLYS / 2; ++i) {
                 e.out[i] = s / 2 + i < PFT_MAX_POLYS / 2 ? epi->out[s / 2 + i] : nullptr;
                 e.acc_item[i] = s / 2 + i < PFT_MAX_POLYS / 2 ? epi->acc_item[s / 2 + i] : nullptr;
-                // src is per item for a forward epilogue, per polynomial for an inverse transform
-                const size_t pi = inverse ? s + i : s / 2 + i;
-                e.src[i] = pi < PFT_MAX_POLYS / 2 ? epi->src[pi] : nullptr;
-                e.src2[i] = pi < PFT_MAX_POLYS / 2 ? epi->src2[pi] : nullptr;
+                e.src[i] = s / 2 + i < PFT_MAX_POLYS / 2 ? epi->src[s / 2 + i] : nullptr;
             }
             launch_ntt(b, c->tabs, P->log_n, inverse, sched, c->stream, hook(c), &e, first);
         } else {
@@ -1726,14 +1723,23 @@ static bool ks_overlap(uint32_t n, const ItemPtrs& out, const ItemPtrs& x, uint6
     return false;
 }
 
+// Whether key switching and RESCALE run on the fused row kernels: their
+// transforms are a radix-16 column pass, which the conversions apply, and a
+// row pass.  That is every ring; a pinned forward schedule of other passes
+// asks for the separate transforms.
+static bool fused_rows(const pft_ctx* c) {
+    const NttSchedule& s = c->ntt_pinned[0];
+    return ks_rows_supported(c->P->log_n) && (s.n_passes == 0 || (s.n_passes == 2 && s.radix[0] == 4));
+}
+
 // Key switching for n items: out_z = ModDown(sum_j ModUp_j(d) key_j) + addends.
 //
-// Fused path: where the forward transforms of ModUp's and ModDown's rows start
-// with a radix-16 column pass, the conversion kernels apply that pass, and
-// launch_ks_rows does the rest of ModUp's rows, the key products and the rest
-// of ModDown in two launches, reading the operands of d and of the addends
-// directly.  Otherwise one launch per step, from the tensor or the images in
-// the workspace.
+// Fused path (five launches): launch_ks_inv forms d and starts its inverse
+// transform, the conversion kernels apply the column passes on both of their
+// sides, and launch_ks_rows does the rest of ModUp's rows, the key products
+// and the rest of ModDown in two launches, reading the operands of d and of
+// the addends directly.  Otherwise one launch per step, from the tensor or
+// the images in the workspace.
 static void key_switch_b(pft_ctx* c, uint32_t n, WsRef ws, const KsLayout& K, const SwitchKeyDev& key,
                          const KsInput& in, const ItemPtrs& out) {
     const pft_params* P = c->P;
@@ -1754,17 +1760,17 @@ static void key_switch_b(pft_ctx* c, uint32_t n, WsRef ws, const KsLayout& K, co
     auto col16 = [&](const std::vector<NttJob>& jobs, uint32_t limbs) {
         return jobs.empty() || first_pass_col16(c, (uint64_t)jobs.size() * limbs);
     };
-    // Where the forward schedules start with a radix-16 column pass, ModUp
-    // applies that pass itself; then d's inverse transform also stops before
-    // its final radix-16 column pass (a schedule chosen among those ending
-    // with one) and ModUp applies that pass to its inputs.
+    // Off the fused path, where the forward schedules start with a radix-16
+    // column pass, ModUp applies that pass itself; then d's inverse transform
+    // also stops before its final radix-16 column pass (a schedule chosen among
+    // those ending with one) and ModUp applies that pass to its inputs.
     const uint32_t nkb = (std::min(P->alpha, level) + 1) / 2, down_kb = (P->K + 1) / 2;
-    const bool fuse = c->bconv_mfma && c->bconv_fuse && bconv_col_supported(lg, nkb, c->kc.up_rt) && col16(full, rows - A) &&
-                      col16(last, rows - na_last);
-    const bool fuse_down = c->bconv_mfma && c->bconv_fuse && bconv_col_supported(lg, down_kb, c->kc.down_rt) &&
-                           first_pass_col16(c, 2ull * n * level);
-    const bool ifuse_up = fuse && last_pass_col16(c, (uint64_t)n * level);
-    const bool merged = fuse && fuse_down && c->inner_fuse && beta <= 8 && ks_rows_supported(lg);
+    const bool up_ok = c->bconv_mfma && c->bconv_fuse && bconv_col_supported(lg, nkb, c->kc.up_rt);
+    const bool down_ok = c->bconv_mfma && c->bconv_fuse && bconv_col_supported(lg, down_kb, c->kc.down_rt);
+    const bool merged = up_ok && down_ok && c->inner_fuse && beta <= 8 && fused_rows(c);
+    const bool fuse = merged || (up_ok && col16(full, rows - A) && col16(last, rows - na_last));
+    const bool fuse_down = merged || (down_ok && first_pass_col16(c, 2ull * n * level));
+    const bool ifuse_up = merged || (fuse && last_pass_col16(c, (uint64_t)n * level));
     // the operands of d and of the addends, read directly on the fused path
     // unless an output overlaps them
     uint32_t mode = in.mode;
@@ -1791,23 +1797,28 @@ static void key_switch_b(pft_ctx* c, uint32_t n, WsRef ws, const KsLayout& K, co
     }
     // d -> coefficient form at off_dcoef (d itself stays in the NTT domain for
     // the products with the key)
-    {
+    if (merged) {
+        KsInv ki{};
+        ki.base = ws.base;
+        ki.stride = ws.stride;
+        ki.off_d = off_d;
+        ki.off_out = K.off_dcoef;
+        ki.n_rows = level;
+        ki.mode = mode;
+        ki.src_row = mode == KS_WS ? 0 : level;
+        ki.src_step = ki.mod_step = 1;
+        ki.kappa = in.kappa;
+        ki.kappa_inv = in.kappa_inv;
+        for (uint32_t z = 0; z < n; ++z) {
+            ki.src[z] = src.p[z];
+            ki.src2[z] = src2.p[z];
+        }
+        launch_ks_inv(n, ki, c->tabs, lg, c->stream, hook(c));
+    } else {
         std::vector<NttJob> jobs;
         for (uint32_t z = 0; z < n; ++z) jobs.push_back(NttJob{ws.base + z * ws.stride + K.off_dcoef, 255u, 0u});
-        if (mode != KS_WS) {
-            NttEpilogue pe{};
-            for (uint32_t z = 0; z < n; ++z) {
-                pe.src[z] = src.p[z] + nl;
-                if (mode == KS_PRODUCT) pe.src2[z] = src2.p[z] + nl;
-            }
-            pe.source = mode == KS_PRODUCT ? NTT_SRC_PROD : NTT_SRC_PERM;
-            pe.kappa = in.kappa;
-            pe.kappa_inv = in.kappa_inv;
-            ntt_jobs(c, jobs, level, ~0u, true, 0, &pe, 0, ifuse_up ? 1u : 0u, ifuse_up);
-        } else {
-            ntt_jobs(c, jobs, level, ~0u, true, 0, nullptr, (int64_t)off_d - (int64_t)K.off_dcoef, ifuse_up ? 1u : 0u,
-                     ifuse_up);
-        }
+        ntt_jobs(c, jobs, level, ~0u, true, 0, nullptr, (int64_t)off_d - (int64_t)K.off_dcoef, ifuse_up ? 1u : 0u,
+                 ifuse_up);
     }
     // ModUp base conversion
     {
@@ -1908,12 +1919,12 @@ static void key_switch_b(pft_ctx* c, uint32_t n, WsRef ws, const KsLayout& K, co
             launch_ks_rows(n, kr, false, c->kc, c->tabs, c->fp_rows.data(), lg, c->inner_pairs, st, hook(c), kinds);
         };
         // on the context's own stream the 60-bit rows run on the helper
-        // stream beside the fp64 rows, so that each launch fills the
-        // other's tail; the helper's work is joined back before anything
+        // stream beside the fp64 rows (the small form takes both in one
+        // launch), so that each launch fills the other's tail; the helper's work is joined back before anything
         // later reads the output or the key.  While this family is being
         // timed per launch the two run one after the other, so that each
         // launch's time is its own.
-        const bool split = c->inner_st && c->stream == c->home && !c->prof.on(PK_KEY_INNER) &&
+        const bool split = !ks_small(n, level, lg) && c->inner_st && c->stream == c->home && !c->prof.on(PK_KEY_INNER) &&
                            hipEventRecord(c->inner_fork, c->stream) == hipSuccess &&
                            hipStreamWaitEvent(c->inner_st, c->inner_fork, 0) == hipSuccess;
         if (split) {
@@ -2081,43 +2092,66 @@ extern "C" int pft_rescale_batch(pft_ctx* c, uint32_t n, const pft_ct* in, uint3
             I.p[z] = in[g[z]].data;
             O.p[z] = out[g[z]].data;
         }
-        // limb l-1 of both polynomials -> coefficient form
-        launch_copy_rows_b(cnt, I, (uint64_t)(l - 1) * N, ws_items(ws, cnt), off_last, 1, lg, c->stream);
-        launch_copy_rows_b(cnt, I, (uint64_t)(2 * l - 1) * N, ws_items(ws, cnt), off_last + N, 1, lg, c->stream);
-        std::vector<NttJob> jl, jt;
-        for (uint32_t z = 0; z < cnt; ++z)
-            for (uint32_t b = 0; b < 2; ++b) {
-                jl.push_back(NttJob{ws.base + z * ws.stride + off_last + b * N, 255u, 0u});
-                jt.push_back(NttJob{ws.base + z * ws.stride + off_tmp + b * (l - 1) * N, 255u, 0u});
-            }
-        ntt_jobs(c, jl, 1, ~0u, true, l - 1);  // modulus of row 0 is q_{l-1}
         const double nd = (double)N;
-        // the expansion applies the first pass of tmp's transform itself
-        // where that schedule starts with a radix-16 column pass
-        const bool fuse = lg >= 8 && first_pass_col16(c, (uint64_t)jt.size() * (l - 1));
-        if (fuse)  // its rows leave after the first transform pass: layout cost
-            timed(c, PK_RESCALE, 8.0 * nd * 2.0 * cnt, 0,
+        // the fused row kernels read the input while the output is written
+        if (fused_rows(c) && !ks_overlap(cnt, O, I, 2 * (uint64_t)l * N)) {
+            KsInv ki{};
+            ki.base = ws.base;
+            ki.stride = ws.stride;
+            ki.off_out = off_last;
+            ki.n_rows = 2;
+            ki.mode = KS_RESCALE;
+            ki.src_row = ki.mod0 = l - 1;
+            ki.src_step = l;
+            for (uint32_t z = 0; z < cnt; ++z) ki.src[z] = I.p[z];
+            launch_ks_inv(cnt, ki, c->tabs, lg, c->stream, hook(c));
+            // its rows leave after the first transform pass: layout cost
+            timed(c, PK_RESCALE, 0.0, 0,
                   [&] { launch_rescale_col_b(cnt, ws, off_last, off_tmp, l, mode, c->tabs, lg, c->stream); }, 1u);
-        else
+            // out[b][k] = (c[b][k] - tmp[b][k]) q_last^-1 mod q_k
+            KsRows kr{};
+            kr.base = ws.base;
+            kr.stride = ws.stride;
+            kr.off_conv = off_tmp;
+            kr.level = l - 1;
+            kr.mode = KS_RESCALE;
+            kr.pinv = c->rescale_qinv + (size_t)(l - 1) * P->L;
+            kr.pinv_fp = c->rescale_qinv + (size_t)P->L * P->L + (size_t)(l - 1) * P->L;
+            for (uint32_t z = 0; z < cnt; ++z) {
+                kr.src[z] = I.p[z];
+                kr.out[z] = O.p[z];
+            }
+            launch_ks_rows(cnt, kr, false, c->kc, c->tabs, c->fp_rows.data(), lg, true, c->stream, hook(c));
+        } else {
+            // limb l-1 of both polynomials -> coefficient form
+            launch_copy_rows_b(cnt, I, (uint64_t)(l - 1) * N, ws_items(ws, cnt), off_last, 1, lg, c->stream);
+            launch_copy_rows_b(cnt, I, (uint64_t)(2 * l - 1) * N, ws_items(ws, cnt), off_last + N, 1, lg, c->stream);
+            std::vector<NttJob> jl, jt;
+            for (uint32_t z = 0; z < cnt; ++z)
+                for (uint32_t b = 0; b < 2; ++b) {
+                    jl.push_back(NttJob{ws.base + z * ws.stride + off_last + b * N, 255u, 0u});
+                    jt.push_back(NttJob{ws.base + z * ws.stride + off_tmp + b * (l - 1) * N, 255u, 0u});
+                }
+            ntt_jobs(c, jl, 1, ~0u, true, l - 1);  // modulus of row 0 is q_{l-1}
             timed(c, PK_RESCALE, 8.0 * nd * (2.0 + 2.0 * (l - 1)) * cnt, 0,
                   [&] { launch_rescale_expand_b(cnt, ws, off_last, off_tmp, l, mode, c->tabs, lg, c->stream); });
-        // the forward transform of tmp finishes in its final pass:
-        // out[b][k] = (c[b][k] - tmp[b][k]) q_last^-1 mod q_k
-        NttEpilogue epi{};
-        for (uint32_t b = 0; b < 2; ++b) {
-            epi.d_acc[b] = PFT_EPI_ITEM_ACC;
-            epi.d_add[b] = PFT_EPI_NO_ADD;
+            // the forward transform of tmp finishes in its final pass:
+            // out[b][k] = (c[b][k] - tmp[b][k]) q_last^-1 mod q_k
+            NttEpilogue epi{};
+            for (uint32_t b = 0; b < 2; ++b) {
+                epi.d_acc[b] = PFT_EPI_ITEM_ACC;
+                epi.d_add[b] = PFT_EPI_NO_ADD;
+            }
+            for (uint32_t z = 0; z < cnt; ++z) {
+                epi.out[z] = O.p[z];
+                epi.acc_item[z] = I.p[z];
+            }
+            epi.acc_level = l;
+            epi.level = l - 1;
+            epi.pinv = c->rescale_qinv + (size_t)(l - 1) * P->L;
+            epi.pinv_fp = c->rescale_qinv + (size_t)P->L * P->L + (size_t)(l - 1) * P->L;
+            ntt_jobs(c, jt, l - 1, ~0u, false, 0, &epi);
         }
-        for (uint32_t z = 0; z < cnt; ++z) {
-            epi.out[z] = O.p[z];
-            epi.acc_item[z] = I.p[z];
-        }
-        epi.acc_level = l;
-        epi.level = l - 1;
-        epi.pinv = c->rescale_qinv + (size_t)(l - 1) * P->L;
-        epi.pinv_fp = c->rescale_qinv + (size_t)P->L * P->L + (size_t)(l - 1) * P->L;
-        ntt_jobs(c, jt, l - 1, ~0u, false, 0, &epi, 0, fuse ? 1u : 0u,
-                 fuse && fwd_col16_restricted(c, (uint64_t)jt.size() * (l - 1)));
         for (uint32_t z = 0; z < cnt; ++z) {
             out[g[z]].level = l - 1;
             out[g[z]].scale = in[g[z]].scale / (double)P->q[l - 1];

@@ -1,6 +1,6 @@
 // keyswitch.hip -- the fused kernels of hybrid key switching around the base
 // conversions: everything between ModUp's rows and the finished ciphertext
-// in two launches.
+// in two launches, and the inverse transforms before them in one.
 //
 // The conversion kernels (ntt.hip) leave every extended row after the first
 // (radix-16 column) pass of its forward transform, so each still needs one
@@ -8,6 +8,9 @@
 // touches.  All that follows is tile-local as well: the products with the
 // key, ModDown's subtraction, the addends.  So a workgroup takes one tile of
 // one row of one item through the whole of it, in registers:
+//   * k_ks_inv, the rows of what is switched: the row pass of their inverse
+//     transform (ModUp's conversion applies the last pass), from operands
+//     that are formed as they are read;
 //   * k_ks_rows<.., SPECIAL true>, the K special rows: every digit through
 //     the row pass, products with the key summed into two accumulators, and
 //     the accumulators through the row pass of the inverse transform that
@@ -18,7 +21,14 @@
 //     out_b = (acc_b - conv_b) P^-1.  An addend enters the accumulators as P
 //     times itself, so the output is (acc_b - conv_b) P^-1 + add_b.
 // No accumulator of a ciphertext row, no transformed row and no tensor of a
-// product (d0, d1, d2 below) goes to memory.
+// product (d0, d1, d2 below) goes to memory.  RESCALE runs on the same
+// kernels: its last limb through k_ks_inv, its output rows through k_ks_rows
+// without digits.
+//
+// Two forms of each: 8 residues a thread (EB 3), and 4 (EB 2) where a launch
+// cannot fill the chip anyway: a tile's chain of passes then has twice the
+// waves, half the instructions per wave, and takes the rows of both
+// arithmetic kinds in one launch.
 #include "ntt_device.h"
 #include "pft_device.h"
 #include "pft_kernels.h"
@@ -32,10 +42,9 @@
 namespace {
 
 // Twiddles of the next register phase loaded ahead of an exchange (PhaseTw):
-// more spill at four waves per SIMD.
-constexpr int TW_PRE_FP2 = 3;
-constexpr int TW_PRE_FP1 = 1;
-constexpr int TW_PRE_INT = 1;
+// with 4 residues a thread all of them; with 8 more spill at four waves per
+// SIMD.
+constexpr int tw_pre_ks(int eb, bool fp, int g) { return eb == 2 ? 3 : fp && g == 2 ? 3 : 1; }
 
 // One tile's work (see the head of this file).  FP (rows with q < 2^50, the
 // key holding integer-valued doubles): every product is an fmulmod against
@@ -66,7 +75,7 @@ __device__ __forceinline__ void ks_row(const KsRows& a, uint64_t* lds, uint32_t 
     static_assert(PIN::WLO >= 4, "the row pass reads its input directly");
     static_assert(POUT::WLO == 0, "each thread ends with E consecutive words");
     static_assert(G == 1 || G == 2, "one or two tiles per row pass");
-    constexpr int PRE = FP ? (G == 2 ? TW_PRE_FP2 : TW_PRE_FP1) : TW_PRE_INT;
+    constexpr int PRE = tw_pre_ks(EB, FP, G);
 
     const uint32_t tid = threadIdx.x;
     [[maybe_unused]] const uint64_t q = md.q;
@@ -141,13 +150,13 @@ __device__ __forceinline__ void ks_row(const KsRows& a, uint64_t* lds, uint32_t 
     auto pass_1 = [&](uint64_t (&x)[E]) {
         uint32_t lj = l, cj = c;
         asm volatile("" : "+v"(lj), "+v"(cj));
-        run_phases<LOG_M, EB, false, FP, false, 0, false, PRE, TB>(x, lds, cj, lj, sp0 + c, s0, twt, md);
+        run_phases<LOG_M, EB, false, FP, false, false, PRE, TB>(x, lds, cj, lj, sp0 + c, s0, twt, md);
         __syncthreads();  // the next row's exchanges reuse the LDS
     };
     [[maybe_unused]] auto pass_2 = [&](uint64_t (&x)[2][E]) {
         uint32_t lj = l, cj = c;
         asm volatile("" : "+v"(lj), "+v"(cj));
-        run_phases_g<LOG_M, EB, 2, FP, 0, PRE, TB>(x, lds, cj, lj, sp0 + c, s0, twt, md);
+        run_phases_g<LOG_M, EB, 2, false, FP, false, 0, false, PRE, TB>(x, lds, cj, lj, sp0 + c, s0, twt, md);
         __syncthreads();
     };
     auto digit_1 = [&](uint32_t j) {
@@ -169,9 +178,20 @@ __device__ __forceinline__ void ks_row(const KsRows& a, uint64_t* lds, uint32_t 
     };
 
     uint32_t jo = ~0u;  // the digit whose own rows include t: d itself, no transform needed
-    if constexpr (!SPECIAL) {
+    const size_t row0 = (size_t)t << log_n, row1 = (size_t)(a.src_level + t) << log_n;
+    if (!SPECIAL && a.mode == KS_RESCALE) {
+        // the input's rows in the accumulators' place
+        load_vec(a.src[z] + row0, acc0);
+        load_vec(a.src[z] + row1, acc1);
+        if constexpr (FP) {
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                acc0[e] = fp_from_u64(acc0[e]);
+                acc1[e] = fp_from_u64(acc1[e]);
+            }
+        }
+    } else if constexpr (!SPECIAL) {
         jo = t / a.alpha;
-        const size_t row0 = (size_t)t << log_n, row1 = (size_t)(a.level + t) << log_n;
         const TwPair pm = FP ? a.gadget_fp[t] : a.gadget[t];  // P mod q
         // acc_b += P s for s = an addend, canonical (FP: as a double, or a sum of two such or of two products)
         auto add_p = [&](uint64_t s, uint64_t& acc) {
@@ -287,25 +307,42 @@ __device__ __forceinline__ void ks_row(const KsRows& a, uint64_t* lds, uint32_t 
     if constexpr (SPECIAL) {
         // both accumulators through the row pass of their inverse transform
         const TwPair* __restrict__ twi = tw_inv + ((size_t)mi << log_n);
-        auto finish = [&](uint64_t (&acc)[E], uint32_t b) {
-#pragma unroll
-            for (int e = 0; e < E; ++e) {
-                if constexpr (FP)
-                    acc[e] = as_u(freduce(as_f(acc[e]), qd, qinv));
-                else
-                    acc[e] = reduce_int(acc[e], md);
-            }
-            uint32_t lj = l, cj = c;
-            asm volatile("" : "+v"(lj), "+v"(cj));
-            run_phases<LOG_M, EB, true, FP, false, 0, false, PRE, TB>(acc, lds, cj, lj, sp0 + cj, s0, twi, md);
-            uint64_t* __restrict__ o = item + a.off_acc + ((size_t)(b * a.rows + t) << log_n);
+        uint64_t* __restrict__ o = item + a.off_acc + ((size_t)t << log_n);
+        auto put = [&](const uint64_t (&x)[E], uint32_t b) {
 #pragma unroll
             for (int e = 0; e < E; ++e)
-                *const_cast<uint64_t*>(words(o + ((size_t)e << PIN::WLO), r0)) = acc[e];
+                *const_cast<uint64_t*>(words(o + ((size_t)(b * a.rows) << log_n) + ((size_t)e << PIN::WLO), r0)) = x[e];
         };
-        finish(acc0, 0);
-        __syncthreads();
-        finish(acc1, 1);
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            if constexpr (FP) {
+                acc0[e] = as_u(freduce(as_f(acc0[e]), qd, qinv));
+                acc1[e] = as_u(freduce(as_f(acc1[e]), qd, qinv));
+            } else {
+                acc0[e] = reduce_int(acc0[e], md);
+                acc1[e] = reduce_int(acc1[e], md);
+            }
+        }
+        uint32_t lj = l, cj = c;
+        asm volatile("" : "+v"(lj), "+v"(cj));
+        if constexpr (G == 2) {
+            uint64_t x[2][E];
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                x[0][e] = acc0[e];
+                x[1][e] = acc1[e];
+            }
+            run_phases_g<LOG_M, EB, 2, true, FP, false, 0, false, PRE, TB>(x, lds, cj, lj, sp0 + cj, s0, twi, md);
+            put(x[0], 0);
+            put(x[1], 1);
+        } else {
+            run_phases<LOG_M, EB, true, FP, false, false, PRE, TB>(acc0, lds, cj, lj, sp0 + cj, s0, twi, md);
+            put(acc0, 0);
+            __syncthreads();
+            asm volatile("" : "+v"(lj), "+v"(cj));
+            run_phases<LOG_M, EB, true, FP, false, false, PRE, TB>(acc1, lds, cj, lj, sp0 + cj, s0, twi, md);
+            put(acc1, 1);
+        }
     } else {
         const TwPair pinv = FP ? a.pinv_fp[t] : a.pinv[t];  // P^-1 mod q
         // x: the transformed converted row; the result to row t of polynomial b
@@ -357,19 +394,121 @@ __device__ __forceinline__ void ks_row(const KsRows& a, uint64_t* lds, uint32_t 
 // 8 k + x runs item k mod n of the (row, tile) pair 8 floor(k / n) + x, so
 // the items sharing one key tile run on one XCD at about the same time and
 // the tile comes from HBM about once per launch, then from that XCD's L2.
-template <int LOG_M, int EB, int TB, bool FP, int G, bool SPECIAL>
+// Returns false past the last pair.
+__device__ __forceinline__ bool ks_block(uint32_t n_items, uint32_t tiles, uint32_t n_rows, uint32_t& z,
+                                         uint32_t& tile, uint32_t& r) {
+    const uint32_t kx = blockIdx.x >> 3;
+    z = kx % n_items;
+    const uint32_t pair = (kx / n_items) * 8u + (blockIdx.x & 7u);
+    tile = pair % tiles;
+    r = pair / tiles;
+    return pair < tiles * n_rows;
+}
+
+// KIND: the rows of a launch run fp64 (KS_ROWS_FP), integer (KS_ROWS_INT) or
+// either (KS_ROWS_ALL) arithmetic.
+template <int LOG_M, int EB, int TB, uint32_t KIND, int G, bool SPECIAL>
 __global__ __launch_bounds__((1 << TB) >> EB) __attribute__((amdgpu_waves_per_eu(4)))
 void k_ks_rows(KsRows a, const DevMod* __restrict__ mods, const TwPair* __restrict__ tw,
                const TwPair* __restrict__ tw_inv, uint32_t log_n) {
-    __shared__ uint64_t lds[(FP ? G : 1) * lds_words<LOG_M, EB, TB>()];
-    const uint32_t kx = blockIdx.x >> 3;
-    const uint32_t z = kx % a.n_items;
-    const uint32_t pair = (kx / a.n_items) * 8u + (blockIdx.x & 7u);
-    if (pair >= a.tiles * a.n_rows) return;  // whole workgroup, before any barrier
-    const uint32_t tile = pair % a.tiles;
-    const uint32_t t = a.row[pair / a.tiles];
+    __shared__ uint64_t lds[G * lds_words<LOG_M, EB, TB>()];
+    uint32_t z, tile, r;
+    if (!ks_block(a.n_items, a.tiles, a.n_rows, z, tile, r)) return;  // whole workgroup, before any barrier
+    const uint32_t t = a.row[r];
     const uint32_t mi = t < a.level ? t : a.L + (t - a.level);
-    ks_row<LOG_M, EB, TB, FP, G, SPECIAL>(a, lds, z, tile, t, mi, mods[mi], tw, tw_inv, log_n);
+    const DevMod md = mods[mi];
+    if (KIND == KS_ROWS_FP || (KIND == KS_ROWS_ALL && md.fp))
+        ks_row<LOG_M, EB, TB, true, G, SPECIAL>(a, lds, z, tile, t, mi, md, tw, tw_inv, log_n);
+    else
+        ks_row<LOG_M, EB, TB, false, G, SPECIAL>(a, lds, z, tile, t, mi, md, tw, tw_inv, log_n);
+}
+
+// The row pass (the first) of an inverse transform of rows that are read, or
+// formed, in the NTT domain; see KsInv.
+template <int LOG_M, int EB, int TB>
+__global__ __launch_bounds__((1 << TB) >> EB) __attribute__((amdgpu_waves_per_eu(4)))
+void k_ks_inv(KsInv a, const DevMod* __restrict__ mods, const TwPair* __restrict__ tw_inv, uint32_t log_n) {
+    constexpr int M = 1 << LOG_M;
+    constexpr int E = 1 << EB;
+    constexpr uint32_t NT = (1u << TB) >> EB;
+    constexpr int T = M / E;
+    constexpr int C = NT / T;
+    using PIN = Phase<LOG_M, 0, EB>;
+    __shared__ uint64_t lds[lds_words<LOG_M, EB, TB>()];
+    uint32_t z, tile, r;
+    if (!ks_block(a.n_items, a.tiles, a.n_rows, z, tile, r)) return;
+    const uint32_t mi = a.mod0 + r * a.mod_step;
+    const DevMod md = mods[mi];
+    const TwPair* __restrict__ twi = tw_inv + ((size_t)mi << log_n);
+    const uint32_t tid = threadIdx.x;
+    const uint32_t sp0 = tile * (uint32_t)C;
+    const uint32_t c = C == 1 ? 0u : tid / T;
+    const uint32_t l = C == 1 ? tid : tid % T;
+    const uint32_t w0 = (((sp0 + c) << LOG_M) + l * (uint32_t)E) * 8u;
+    const uint32_t r0 = (((sp0 + c) << LOG_M) | PIN::r_of(l, 0)) * 8u;
+    uint64_t* __restrict__ item = a.base + (size_t)z * a.stride;
+    const size_t row = (size_t)(a.src_row + r * a.src_step) << log_n;
+    auto two = [&](const uint64_t* __restrict__ p, int e) {
+        return *reinterpret_cast<const ulonglong2*>(reinterpret_cast<const char*>(p + e) + w0);
+    };
+    uint64_t x[E];
+    if (a.mode == KS_ROTATE) {
+        galois_tile_to_lds<LOG_M, EB, TB>(a.src[z] + row, tile, log_n, a.kappa, a.kappa_inv, lds, md.fp != 0);
+#pragma unroll
+        for (int e = 0; e < E; ++e) x[e] = lds[lds_at<LOG_M, EB>(c, l * (uint32_t)E + (uint32_t)e)];
+    } else if (a.mode == KS_PRODUCT) {
+        const uint64_t *A = a.src[z] + row, *B = a.src2[z] + row;
+#pragma unroll
+        for (int e = 0; e < E; e += 2) {
+            const ulonglong2 u = two(A, e), v = two(B, e);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const uint64_t p = h ? u.y : u.x, s = h ? v.y : v.x;
+                if (md.fp) {
+                    const double y = as_f(fp_from_u64(s));
+                    x[e + h] = as_u(fmulmod(as_f(fp_from_u64(p)), y, y * md.qinv, md.qd));  // within 0.9q
+                } else {
+                    x[e + h] = mul_barrett(p, s, md);
+                }
+            }
+        }
+    } else {
+        const uint64_t* A = a.mode == KS_WS ? item + a.off_d + row : a.src[z] + row;
+#pragma unroll
+        for (int e = 0; e < E; e += 2) {
+            const ulonglong2 u = two(A, e);
+            x[e] = md.fp ? fp_from_u64(u.x) : u.x;
+            x[e + 1] = md.fp ? fp_from_u64(u.y) : u.y;
+        }
+    }
+    constexpr int PRE = EB == 2 ? 3 : 8;
+    if (md.fp)
+        run_phases<LOG_M, EB, true, true, false, false, PRE, TB>(x, lds, c, l, sp0 + c, log_n - LOG_M, twi, md);
+    else
+        run_phases<LOG_M, EB, true, false, false, false, PRE, TB>(x, lds, c, l, sp0 + c, log_n - LOG_M, twi, md);
+    uint64_t* __restrict__ o = item + a.off_out + ((size_t)r << log_n);
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+        *reinterpret_cast<uint64_t*>(reinterpret_cast<char*>(o + ((size_t)e << PIN::WLO)) + r0) = x[e];
+}
+
+// Calls f(integral_constant LOG_M, integral_constant TB) for the row pass of
+// ring 2^log_n.  A tile is one row-pass problem, at least 1024 words: the
+// smallest that fills a pair of wavefronts with 8 residues a thread.
+template <class F>
+void by_row_pass(uint32_t log_n, F&& f) {
+    auto go = [&](auto lm) {
+        constexpr int LM = decltype(lm)::value;
+        f(lm, std::integral_constant<int, (LM > 10 ? LM : 10)>{});
+    };
+    switch (log_n - 4) {
+        case 8: go(std::integral_constant<int, 8>{}); break;
+        case 9: go(std::integral_constant<int, 9>{}); break;
+        case 10: go(std::integral_constant<int, 10>{}); break;
+        case 11: go(std::integral_constant<int, 11>{}); break;
+        case 12: go(std::integral_constant<int, 12>{}); break;
+        default: break;
+    }
 }
 
 }  // namespace
@@ -379,6 +518,30 @@ bool ks_rows_supported(uint32_t log_n) {
     return r >= 8 && r <= 12;
 }
 
+bool ks_small(uint32_t n, uint32_t rows, uint32_t log_n) {
+    return ((uint64_t)n * rows << log_n) <= KS_SMALL_WORDS;
+}
+
+void launch_ks_inv(uint32_t n, KsInv a, const DevTables& t, uint32_t log_n, hipStream_t st, ProfHook* prof) {
+    a.n_items = n;
+    const bool small = ks_small(n, a.n_rows, log_n);
+    if (prof) prof->begin(PK_NTT_INV, st);
+    by_row_pass(log_n, [&](auto lm, auto tb) {
+        constexpr int LM = decltype(lm)::value, TB = decltype(tb)::value;
+        a.tiles = (1u << log_n) >> TB;
+        const dim3 grid(8u * n * ((a.tiles * a.n_rows + 7u) / 8u));
+        if (small)
+            hipLaunchKernelGGL((k_ks_inv<LM, 2, TB>), grid, dim3((1u << TB) >> 2), 0, st, a, t.mods, t.tw_inv, log_n);
+        else
+            hipLaunchKernelGGL((k_ks_inv<LM, 3, TB>), grid, dim3((1u << TB) >> 3), 0, st, a, t.mods, t.tw_inv, log_n);
+    });
+    if (prof) {
+        const double words = (double)n * a.n_rows * (double)(1u << log_n);
+        prof->end(PK_NTT_INV, 8.0 * words * (a.mode == KS_PRODUCT ? 2.0 : 1.0), 0.5 * words * (log_n - 4),
+                  8192u + (log_n - 4) + (small ? 64u : 0u), st);
+    }
+}
+
 void launch_ks_rows(uint32_t n, KsRows a, bool special, const KsConsts& kc, const DevTables& t,
                     const uint32_t* fp_rows, uint32_t log_n, bool pair_digits, hipStream_t st, ProfHook* prof,
                     uint32_t rows_sel) {
@@ -386,7 +549,8 @@ void launch_ks_rows(uint32_t n, KsRows a, bool special, const KsConsts& kc, cons
     a.n_items = n;
     a.rows = level + kc.K;
     a.alpha = kc.alpha;
-    a.beta = (level + kc.alpha - 1) / kc.alpha;
+    a.beta = a.mode == KS_RESCALE ? 0 : (level + kc.alpha - 1) / kc.alpha;
+    a.src_level = a.mode == KS_RESCALE ? level + 1 : level;
     // the integer accumulators hold at most 8 terms below 2q (callers check)
     if (a.beta > 8) {
         fprintf(stderr, "launch_ks_rows: %u digits, at most 8 supported\n", a.beta);
@@ -394,62 +558,65 @@ void launch_ks_rows(uint32_t n, KsRows a, bool special, const KsConsts& kc, cons
     }
     a.L = kc.L;
     a.krows = kc.L + kc.K;
-    for (int fp = 1; fp >= 0; --fp) {
-        if (!(rows_sel & (fp ? KS_ROWS_FP : KS_ROWS_INT))) continue;
-        // the rows of one arithmetic kind, in chunks that fit the row list
+    const bool small = ks_small(n, special ? kc.K : level, log_n);
+    // the rows of one arithmetic kind (the small form: of both, the longer
+    // integer rows first), in chunks that fit the row list
+    for (uint32_t kind : {KS_ROWS_FP, KS_ROWS_INT}) {
+        if (!(rows_sel & kind) || (small && kind == KS_ROWS_FP && rows_sel == KS_ROWS_ALL)) continue;
         std::vector<uint16_t> rows;
-        for (uint32_t r = special ? level : 0; r < (special ? a.rows : level); ++r) {
-            const uint32_t mi = r < level ? r : kc.L + (r - level);
-            if ((int)fp_rows[mi] == fp) rows.push_back((uint16_t)r);
+        for (uint32_t k : {KS_ROWS_INT, KS_ROWS_FP}) {
+            if (k != kind && !(small && rows_sel == KS_ROWS_ALL)) continue;
+            for (uint32_t r = special ? level : 0; r < (special ? a.rows : level); ++r) {
+                const uint32_t mi = r < level ? r : kc.L + (r - level);
+                if (fp_rows[mi] == (k == KS_ROWS_FP ? 1u : 0u)) rows.push_back((uint16_t)r);
+            }
         }
         for (size_t r0 = 0; r0 < rows.size(); r0 += PFT_ROW_LIST) {
             a.n_rows = (uint32_t)std::min<size_t>(PFT_ROW_LIST, rows.size() - r0);
             for (uint32_t i = 0; i < a.n_rows; ++i) a.row[i] = rows[r0 + i];
-            // method bytes: the operands and the finished rows per item, the
-            // key rows once (extended and converted rows are pass boundaries);
-            // work: the row passes' butterflies and the products
-            const double N = (double)(1u << log_n), lm = (double)(log_n - 4);
-            const double in = special ? 0.0 : a.mode == KS_PRODUCT ? 4.0 : a.mode == KS_ROTATE ? 2.0 : 1.0;
-            const double io = in + (special ? 0.0 : 2.0 + (a.has_add ? 2.0 : 0.0));
-            const double bytes = 8.0 * N * a.n_rows * (n * io + 2.0 * a.beta);
-            const double ops = N * n * a.n_rows * (0.5 * lm * (a.beta + (special ? 2.0 : 1.0)) + 2.0 * a.beta);
-            const bool g2 = fp && pair_digits && !special;
+            const bool g2 = small || (kind == KS_ROWS_FP && pair_digits && !special);
             if (prof) prof->begin(PK_KEY_INNER, st);
-            // A tile is one row-pass problem, at least 1024 words: the
-            // smallest that fills a wavefront pair with 8 residues per thread.
-            auto go = [&](auto lmc, auto tbc) {
-                constexpr int LM = decltype(lmc)::value, TB = decltype(tbc)::value, EB = 3;
+            by_row_pass(log_n, [&](auto lm, auto tb) {
+                constexpr int LM = decltype(lm)::value, TB = decltype(tb)::value;
                 a.tiles = (1u << log_n) >> TB;
-                const dim3 grid(8u * n * ((a.tiles * a.n_rows + 7u) / 8u)), block((1u << TB) >> EB);
-                auto run = [&](auto fpc, auto gc, auto spc) {
+                const dim3 grid(8u * n * ((a.tiles * a.n_rows + 7u) / 8u));
+                auto run = [&](auto ebc, auto kindc, auto gc, auto spc) {
+                    constexpr int EB = decltype(ebc)::value;
                     hipLaunchKernelGGL(
-                        (k_ks_rows<LM, EB, TB, decltype(fpc)::value, decltype(gc)::value, decltype(spc)::value>), grid,
-                        block, 0, st, a, t.mods, t.tw_fwd, t.tw_inv, log_n);
+                        (k_ks_rows<LM, EB, TB, decltype(kindc)::value, decltype(gc)::value, decltype(spc)::value>),
+                        grid, dim3((1u << TB) >> EB), 0, st, a, t.mods, t.tw_fwd, t.tw_inv, log_n);
                 };
-                using one = std::integral_constant<int, 1>;
-                using two = std::integral_constant<int, 2>;
-                if (special)
-                    fp ? run(std::true_type{}, one{}, std::true_type{}) : run(std::false_type{}, one{}, std::true_type{});
+                using e2 = std::integral_constant<int, 2>;
+                using e3 = std::integral_constant<int, 3>;
+                using g_1 = std::integral_constant<int, 1>;
+                using g_2 = std::integral_constant<int, 2>;
+                using fp = std::integral_constant<uint32_t, KS_ROWS_FP>;
+                using in = std::integral_constant<uint32_t, KS_ROWS_INT>;
+                using all = std::integral_constant<uint32_t, KS_ROWS_ALL>;
+                if (small)
+                    special ? run(e2{}, all{}, g_2{}, std::true_type{}) : run(e2{}, all{}, g_2{}, std::false_type{});
+                else if (special)
+                    kind == KS_ROWS_FP ? run(e3{}, fp{}, g_1{}, std::true_type{})
+                                       : run(e3{}, in{}, g_1{}, std::true_type{});
                 else if (g2)
-                    run(std::true_type{}, two{}, std::false_type{});
+                    run(e3{}, fp{}, g_2{}, std::false_type{});
                 else
-                    fp ? run(std::true_type{}, one{}, std::false_type{}) : run(std::false_type{}, one{}, std::false_type{});
-            };
-            auto by = [&](auto lmc) {
-                constexpr int LM = decltype(lmc)::value;
-                go(lmc, std::integral_constant<int, (LM > 10 ? LM : 10)>{});
-            };
-            switch (log_n - 4) {
-                case 8: by(std::integral_constant<int, 8>{}); break;
-                case 9: by(std::integral_constant<int, 9>{}); break;
-                case 10: by(std::integral_constant<int, 10>{}); break;
-                case 11: by(std::integral_constant<int, 11>{}); break;
-                case 12: by(std::integral_constant<int, 12>{}); break;
-                default: break;
+                    kind == KS_ROWS_FP ? run(e3{}, fp{}, g_1{}, std::false_type{})
+                                       : run(e3{}, in{}, g_1{}, std::false_type{});
+            });
+            if (prof) {
+                // method bytes: the operands and the finished rows per item, the
+                // key rows once (extended and converted rows are pass boundaries);
+                // work: the row passes' butterflies and the products
+                const double N = (double)(1u << log_n), lm = (double)(log_n - 4);
+                const double in = special ? 0.0 : a.mode == KS_PRODUCT ? 4.0 : a.mode == KS_WS ? 1.0 : 2.0;
+                const double io = in + (special ? 0.0 : 2.0 + (a.has_add ? 2.0 : 0.0));
+                prof->end(PK_KEY_INNER, 8.0 * N * a.n_rows * (n * io + 2.0 * a.beta),
+                          N * n * a.n_rows * (0.5 * lm * (a.beta + (special ? 2.0 : 1.0)) + 2.0 * a.beta),
+                          1024u + (log_n - 4) + (small ? 512u : kind == KS_ROWS_FP ? 64u : 0u) + (g2 ? 128u : 0u) +
+                              (special ? 256u : 0u),
+                          st);
             }
-            if (prof)
-                prof->end(PK_KEY_INNER, bytes, ops,
-                          1024u + (log_n - 4) + (fp ? 64u : 0u) + (g2 ? 128u : 0u) + (special ? 256u : 0u), st);
         }
     }
 }

@@ -56,15 +56,10 @@ namespace {
 // Limbs with DevMod::fp run the fp64 butterflies: the first pass of a
 // transform converts its u64 input, later passes exchange the doubles through
 // HBM, and the final pass writes canonical u64.  Integer limbs keep u64.
-// SRC (the first pass of an inverse transform, a row pass): where the input
-// of polynomial p comes from instead of its own rows.  NTT_SRC_PERM: row i of
-// ep.src[p] under X -> X^kappa, staged through LDS; NTT_SRC_PROD: the product
-// of rows i of ep.src[p] and ep.src2[p] (the d2 of HMUL's tensor).
-template <int LOG_M, int EB, bool INV, bool COL, bool FINAL, bool STAGE, bool EPI, int SRC = NTT_SRC_SELF>
+template <int LOG_M, int EB, bool INV, bool COL, bool FINAL, bool STAGE, bool EPI>
 __global__ __launch_bounds__(4096 >> EB) void k_ntt_pass(PolyBatch b, const DevMod* __restrict__ mods,
                                                          const TwPair* __restrict__ tw, uint32_t log_n, uint32_t s0,
                                                          uint32_t first_pass, NttEpilogue ep) {
-    static_assert(SRC == NTT_SRC_SELF || (!COL && INV), "other sources feed an inverse transform's row pass");
     constexpr int M = 1 << LOG_M;
     constexpr int E = 1 << EB;          // residues per thread
     constexpr uint32_t NT = 4096 >> EB;  // threads per workgroup
@@ -115,28 +110,7 @@ __global__ __launch_bounds__(4096 >> EB) void k_ntt_pass(PolyBatch b, const DevM
     uint64_t x[E];
     const bool convert_in = fp && first_pass;
     const uint64_t* src = first_pass ? data + b.src_delta : data;  // may alias data (in place)
-    if constexpr (SRC == NTT_SRC_PERM) {
-        galois_tile_to_lds<LOG_M, EB>(ep.src[poly] + ((size_t)row << log_n), blockIdx.x, log_n, ep.kappa,
-                                      ep.kappa_inv, lds, convert_in);
-        lds_read<LOG_M, PH_IN, EB>(x, lds, c, l);
-    } else if constexpr (SRC == NTT_SRC_PROD) {
-        static_assert(VEC_IN, "each thread starts with E consecutive words");
-        const uint32_t w0 = gidx(c, (uint32_t)E * l);
-        const size_t r0 = (size_t)row << log_n;
-        const ulonglong2* __restrict__ va = reinterpret_cast<const ulonglong2*>(word(ep.src[poly] + r0, w0));
-        const ulonglong2* __restrict__ vb = reinterpret_cast<const ulonglong2*>(word(ep.src2[poly] + r0, w0));
-        auto prod = [&](uint64_t a, uint64_t b2) -> uint64_t {
-            if (!fp) return mul_barrett(a, b2, md);
-            const double y = as_f(fp_from_u64(b2));
-            return as_u(fmulmod(as_f(fp_from_u64(a)), y, y * md.qinv, md.qd));  // within 0.9q
-        };
-#pragma unroll
-        for (int e = 0; e < E / 2; ++e) {
-            const ulonglong2 u = va[e], v = vb[e];
-            x[2 * e] = prod(u.x, v.x);
-            x[2 * e + 1] = prod(u.y, v.y);
-        }
-    } else if constexpr (DIRECT_IN && VEC_IN) {
+    if constexpr (DIRECT_IN && VEC_IN) {
         const ulonglong2* __restrict__ srcv = reinterpret_cast<const ulonglong2*>(word(src, gidx(c, (uint32_t)E * l)));
 #pragma unroll
         for (int e = 0; e < E / 2; ++e) {
@@ -164,9 +138,9 @@ __global__ __launch_bounds__(4096 >> EB) void k_ntt_pass(PolyBatch b, const DevM
 
     // the final inverse pass (s0 = 0) folds N^-1 into stage 0
     if (fp)
-        run_phases<LOG_M, EB, INV, true, FINAL, 0, COL, tw_pre_pass(EB)>(x, lds, c, l, high, s0, twt, md);
+        run_phases<LOG_M, EB, INV, true, FINAL, COL, tw_pre_pass(EB)>(x, lds, c, l, high, s0, twt, md);
     else
-        run_phases<LOG_M, EB, INV, false, FINAL, 0, COL, tw_pre_pass(EB)>(x, lds, c, l, high, s0, twt, md);
+        run_phases<LOG_M, EB, INV, false, FINAL, COL, tw_pre_pass(EB)>(x, lds, c, l, high, s0, twt, md);
 
     const uint64_t q = md.q;
     const double qd = md.qd, qinv = md.qinv;
@@ -337,19 +311,6 @@ void launch_k(const PolyBatch& b, const DevTables& t, uint32_t log_n, uint32_t s
             return;
         }
     }
-    if constexpr (INV && !COL) {
-        // the first pass of an inverse transform with its input from elsewhere
-        if (epi && epi->source == NTT_SRC_PERM && first_pass) {
-            hipLaunchKernelGGL((k_ntt_pass<LOG_M, EB, INV, COL, FINAL, true, false, NTT_SRC_PERM>), grid,
-                               dim3(4096 >> EB), 0, st, b, t.mods, tw, log_n, s0, first_pass, ep);
-            return;
-        }
-        if (epi && epi->source == NTT_SRC_PROD && first_pass) {
-            hipLaunchKernelGGL((k_ntt_pass<LOG_M, EB, INV, COL, FINAL, false, false, NTT_SRC_PROD>), grid,
-                               dim3(4096 >> EB), 0, st, b, t.mods, tw, log_n, s0, first_pass, ep);
-            return;
-        }
-    }
     if (COL || stage)
         hipLaunchKernelGGL((k_ntt_pass<LOG_M, EB, INV, COL, FINAL, true, false>), grid, dim3(4096 >> EB), 0, st, b,
                            t.mods, tw, log_n, s0, first_pass, ep);
@@ -392,9 +353,8 @@ void launch_pass(const PolyBatch& b, const DevTables& t, uint32_t log_n, uint32_
         // words between two passes are the layout's cost, not the method's.
         // N/2 butterflies per stage.
         const bool fused = epi && !INV && final_pass && !col;
-        const uint32_t src = epi && INV && first_pass && !col ? epi->source : 0u;
         const uint32_t variant = 1u + (LOG_M | (col ? 32u : 0u) | (final_pass ? 64u : 0u) | (staged ? 128u : 0u) |
-                                       (e8 ? 256u : 0u) | (fused ? 512u : 0u) | src * 1024u);
+                                       (e8 ? 256u : 0u) | (fused ? 512u : 0u));
         // the ModDown epilogue reads acc (and the addends) and writes out in
         // place of the transform's own store
         double extra = 0.0;  // addends: half of the rows (one polynomial) each
@@ -402,7 +362,7 @@ void launch_pass(const PolyBatch& b, const DevTables& t, uint32_t log_n, uint32_
             for (int bb = 0; bb < 2; ++bb)
                 extra += (epi->d_add[bb] != PFT_EPI_NO_ADD ? 4.0 : 0.0) + (epi->has_add ? 4.0 : 0.0);
         }
-        const double in_b = first_pass ? (src == NTT_SRC_PROD ? 16.0 : 8.0) : 0.0, out_b = final_pass ? 8.0 : 0.0;
+        const double in_b = first_pass ? 8.0 : 0.0, out_b = final_pass ? 8.0 : 0.0;
         const double bytes = elems * (in_b + (fused ? 16.0 + extra : out_b));
         g_prof->end(kid, bytes, 0.5 * elems * LOG_M, variant);
     }
@@ -434,7 +394,7 @@ void launch_pass(const PolyBatch& b, const DevTables& t, uint32_t log_n, uint32_
 // applied to the 16 values of each column first.
 constexpr uint32_t BCONV_COLS = 32;
 template <uint32_t NKB, bool DOWN, bool IFUSE>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_bconv_col_b(
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k_bconv_col_b(
     WsRef ws, uint64_t off_in, uint64_t off_out, uint32_t level, KsConsts kc, const DevMod* __restrict__ mods,
     const TwPair* __restrict__ tw, const TwPair* __restrict__ tw_inv, uint32_t log_n) {
     __shared__ uint64_t s_dig[2 * NKB * 16 * BCONV_COLS];  // [input row][t][u]
@@ -459,12 +419,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     const uint8_t* __restrict__ tgt = DOWN ? kc.down_tgt : kc.up_tgt + lj * kc.up_rt * 4;
     auto row_of = [&](uint32_t t) { return DOWN && t >= level ? PFT_NO_ROW : t; };
     stage_red(kc, s_red, tgt, 4 * max_tiles, row_of, mod_of);
-    for (uint32_t i = tid; i < 64 * max_tiles; i += 256) {
+    for (uint32_t i = tid; i < 64 * max_tiles; i += blockDim.x) {
         const uint32_t t = row_of(tgt[i >> 4]);
         if (t != PFT_NO_ROW) s_tw[i] = tw[((size_t)mod_of(t) << log_n) + (i & 15u)];
     }
     // the input rows' digits
-    for (uint32_t ii = tid >> 5; ii < 2 * NKB; ii += 8) {
+    for (uint32_t ii = tid >> 5; ii < 2 * NKB; ii += blockDim.x >> 5) {
         uint64_t x[16];
         if (ii < na) {
             const uint32_t mi = DOWN ? kc.L + ii : i0 + ii;
@@ -539,7 +499,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
                 *reinterpret_cast<uint64_t*>(reinterpret_cast<char*>(out + (size_t)e * S) + off) = x[v][e];
         }
     };
-    for (uint32_t g = wave; g < max_tiles; g += 4) {
+    for (uint32_t g = wave; g < max_tiles; g += blockDim.x >> 6) {
         // a tile's first row is there and has the kind of the others
         const uint32_t row = __builtin_amdgcn_readfirstlane(s_red[4 * g].row);
         if (row == PFT_NO_ROW) break;
@@ -550,46 +510,66 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     }
 }
 
-// RESCALE's expansion fused with the first pass (stages 0-3, a radix-16
-// column pass) of the forward transform of its rows: thread (row k, column u)
-// reads the 16 values t of column u0 + u + t N/16 of last_b (polynomial b's
-// limb level-1 in coefficient form), forms ((c + h) mod q_last) - h mod q_k
-// (h = (q_last - 1)/2 rounding, 0 floor; q_last < q_k) and takes the column
-// through the four stages exactly as the first transform pass does (fp64
-// rows converted on entry); row k of tmp_b continues at the second pass.
+// RESCALE's expansion fused with the transforms around it.  last_b
+// (polynomial b's limb level-1) has had the row pass of its inverse transform;
+// a thread takes its column u through the last pass (stages 3-0 with N^-1
+// folded in), and from the 16 coefficients c forms ((c + h) mod q_last) - h
+// mod q_k (h = (q_last - 1)/2 rounding, 0 floor; q_last < q_k) for its rows k
+// and takes them through the first forward pass (stages 0-3; fp64 rows
+// converted on entry); row k of tmp_b continues at the second pass.  Wave w of
+// a workgroup takes rows w and w + 4 of its RESCALE_ROWS: a wave's row is
+// uniform, so its twiddles come through the scalar cache.
+constexpr uint32_t RESCALE_ROWS = 8;
 __global__ __launch_bounds__(256) void k_rescale_col_b(WsRef ws, uint64_t off_last, uint64_t off_tmp, uint32_t level,
                                                        uint32_t mode, const DevMod* __restrict__ mods,
-                                                       const TwPair* __restrict__ tw, uint32_t log_n) {
+                                                       const TwPair* __restrict__ tw,
+                                                       const TwPair* __restrict__ tw_inv, uint32_t log_n) {
     const uint32_t S = 1u << (log_n - 4);
-    const uint32_t u0 = blockIdx.x * 16u;
+    const uint32_t u = (blockIdx.x * 64u + (threadIdx.x & 63u)) * 8u;  // bytes
     const uint32_t nl = level - 1;
-    const uint32_t groups = (nl + 15) / 16;
-    const uint32_t b = blockIdx.y / groups;
-    const uint32_t k = (blockIdx.y - b * groups) * 16u + (threadIdx.x >> 4), u = threadIdx.x & 15u;
+    const uint32_t groups = (nl + RESCALE_ROWS - 1) / RESCALE_ROWS;
+    const uint32_t b = blockIdx.y / groups, g = blockIdx.y - b * groups;
+    uint32_t k = g * RESCALE_ROWS + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (k >= nl) return;  // no barrier in this kernel
-    const uint64_t ql = mods[level - 1].q;
-    const uint64_t h = mode == 0 ? (ql - 1) / 2 : 0;
     uint64_t* item = ws.base + (size_t)blockIdx.z * ws.stride;
-    const uint64_t* __restrict__ last = item + off_last + ((size_t)b << log_n) + u0 + u;
-    const DevMod md = mods[k];
-    uint64_t x[16];
+    const uint64_t* __restrict__ last = item + off_last + ((size_t)b << log_n);
+    const DevMod ml = mods[level - 1];
+    uint64_t r[16];
+#pragma unroll
+    for (int e = 0; e < 16; ++e)
+        r[e] = *reinterpret_cast<const uint64_t*>(reinterpret_cast<const char*>(last + (size_t)e * S) + u);
+    const TwPair* __restrict__ twl = tw_inv + ((size_t)(level - 1) << log_n);
+    if (ml.fp) {
+        run_phase<4, 0, 4, true, true, true>(r, 0u, 0u, 0u, twl, ml);
+#pragma unroll
+        for (int e = 0; e < 16; ++e) r[e] = fp_to_u64(r[e], ml.qd, ml.qinv);
+    } else {
+        run_phase<4, 0, 4, true, false, true>(r, 0u, 0u, 0u, twl, ml);
+    }
+    const uint64_t h = mode == 0 ? (ml.q - 1) / 2 : 0;
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
-        uint64_t r = last[(size_t)e * S] + h;
-        r = r >= ql ? r - ql : r;
-        x[e] = r >= h ? r - h : r + md.q - h;
+        r[e] += h;
+        r[e] = r[e] >= ml.q ? r[e] - ml.q : r[e];
     }
-    const TwPair* __restrict__ twt = tw + ((size_t)k << log_n);
-    if (md.fp) {
+    for (; k < min(nl, (g + 1) * RESCALE_ROWS); k += 4) {
+        const DevMod md = mods[k];
+        const TwPair* __restrict__ twt = tw + ((size_t)k << log_n);
+        uint64_t x[16];
 #pragma unroll
-        for (int e = 0; e < 16; ++e) x[e] = fp_from_u64(x[e]);
-        run_phase<4, 0, 4, false, true, false, true>(x, 0u, 0u, 0u, twt, md);  // canonical inputs
-    } else {
-        run_phase<4, 0, 4, false, false, false, true>(x, 0u, 0u, 0u, twt, md);
+        for (int e = 0; e < 16; ++e) x[e] = r[e] >= h ? r[e] - h : r[e] + md.q - h;
+        if (md.fp) {
+#pragma unroll
+            for (int e = 0; e < 16; ++e) x[e] = fp_from_u64(x[e]);
+            run_phase<4, 0, 4, false, true, false, true>(x, 0u, 0u, 0u, twt, md);  // canonical inputs
+        } else {
+            run_phase<4, 0, 4, false, false, false, true>(x, 0u, 0u, 0u, twt, md);
+        }
+        uint64_t* __restrict__ orow = item + off_tmp + ((size_t)(b * nl + k) << log_n);
+#pragma unroll
+        for (int e = 0; e < 16; ++e)
+            *reinterpret_cast<uint64_t*>(reinterpret_cast<char*>(orow + (size_t)e * S) + u) = x[e];
     }
-    uint64_t* __restrict__ orow = item + off_tmp + ((size_t)(b * nl + k) << log_n) + u0 + u;
-#pragma unroll
-    for (int e = 0; e < 16; ++e) orow[(size_t)e * S] = x[e];
 }
 
 template <bool INV>
@@ -670,9 +650,12 @@ template <bool DOWN, bool IFUSE>
 static void launch_bconv_col(uint32_t nkb, dim3 grid, hipStream_t st, WsRef ws, uint64_t off_in, uint64_t off_out,
                              uint32_t level, const KsConsts& kc, const DevTables& t, uint32_t log_n) {
     const uint32_t lds = bconv_col_dyn_lds(DOWN ? kc.down_rt : kc.up_rt);
+    // four waves take about two tiles each; where that leaves compute units
+    // without a second workgroup, eight waves a workgroup take one each
+    const uint32_t threads = (uint64_t)grid.x * grid.y * grid.z <= 512 ? 512 : 256;
 #define PFT_BCONV_COL(K)                                                                                     \
     case K:                                                                                                  \
-        hipLaunchKernelGGL((k_bconv_col_b<K, DOWN, IFUSE>), grid, dim3(256), lds, st, ws, off_in, off_out, level, \
+        hipLaunchKernelGGL((k_bconv_col_b<K, DOWN, IFUSE>), grid, dim3(threads), lds, st, ws, off_in, off_out, level, \
                            kc, t.mods, t.tw_fwd, t.tw_inv, log_n);                                           \
         break;
     switch (nkb) {
@@ -709,9 +692,9 @@ void launch_moddown_col_b(uint32_t n, WsRef ws, uint64_t off_acc, uint64_t off_c
 
 void launch_rescale_col_b(uint32_t n, WsRef ws, uint64_t off_last, uint64_t off_tmp, uint32_t level, uint32_t mode,
                           const DevTables& t, uint32_t log_n, hipStream_t st) {
-    const uint32_t groups = (level - 1 + 15) / 16;
-    hipLaunchKernelGGL(k_rescale_col_b, dim3((1u << log_n) / 256, 2 * groups, n), dim3(256), 0, st, ws, off_last,
-                       off_tmp, level, mode, t.mods, t.tw_fwd, log_n);
+    const uint32_t groups = (level - 1 + RESCALE_ROWS - 1) / RESCALE_ROWS;
+    hipLaunchKernelGGL(k_rescale_col_b, dim3((1u << log_n) / 1024, 2 * groups, n), dim3(256), 0, st, ws, off_last,
+                       off_tmp, level, mode, t.mods, t.tw_fwd, t.tw_inv, log_n);
 }
 
 void launch_ntt(const PolyBatch& b, const DevTables& t, uint32_t log_n, bool inverse, const NttSchedule& s,
@@ -731,9 +714,7 @@ void launch_ntt(const PolyBatch& b, const DevTables& t, uint32_t log_n, bool inv
             launch_radix<false>(s.radix[p], b, t, log_n, s0[p], p + 1 == s.n_passes, stage, e8,
                                 p + 1 == s.n_passes ? epi : nullptr, st, prof);
     } else {
-        // epi of an inverse transform: the input of its first pass
         for (uint32_t p = s.n_passes; p-- > first;)
-            launch_radix<true>(s.radix[p], b, t, log_n, s0[p], p == 0, stage, e8,
-                               p + 1 == s.n_passes && epi && epi->source ? epi : nullptr, st, prof);
+            launch_radix<true>(s.radix[p], b, t, log_n, s0[p], p == 0, stage, e8, nullptr, st, prof);
     }
 }

@@ -94,18 +94,11 @@ __device__ __forceinline__ uint32_t tw_index(uint32_t l, int e, int bit, uint32_
 }
 
 // Twiddles preloaded per register phase ahead of the exchange before it
-// (PhaseTw below): by the transform passes with 8 or 16 residues per
-// thread, and by the fused inner product (fp64 rows two digits or one per
-// pass, 60-bit rows); larger budgets spill or cost waves per SIMD.
+// (PhaseTw below) by the transform passes with 8 or 16 residues per thread;
+// larger budgets spill or cost waves per SIMD.
 constexpr int TW_PRE_PASS3 = 8;
 constexpr int TW_PRE_PASS4 = 3;
-constexpr int TW_PRE_INNER_FP2 = 3;
-constexpr int TW_PRE_INNER_FP1 = 1;
-constexpr int TW_PRE_INNER_INT = 1;
 constexpr int tw_pre_pass(int eb) { return eb == 3 ? TW_PRE_PASS3 : eb == 4 ? TW_PRE_PASS4 : 0; }
-constexpr int tw_pre_inner(bool fp, int g) {
-    return fp ? (g == 2 ? TW_PRE_INNER_FP2 : TW_PRE_INNER_FP1) : TW_PRE_INNER_INT;
-}
 // The twiddles of register phase PH for one thread.  At the stage whose
 // butterflies span window bit pos, the upper elements e that agree in
 // e >> (pos + 1) share one twiddle (tw_index drops the bits below), so the
@@ -177,75 +170,72 @@ struct PhaseTw {
     }
 };
 
+// One register phase of G independent tiles: each twiddle is loaded once and
+// serves the butterflies of every tile.
 // LOW (forward only): the inputs are already reduced (fp64 within q/2 + 1
 // or below q; integers below 2q), so the first stage skips its reduction of
 // X; the bounds of the later stages are those of reduced inputs.
-template <int LOG_M, int PH, int EB, bool INV, bool FP, bool FOLD, int PRE, bool LOW = false>
-__device__ __forceinline__ void run_phase(uint64_t (&x)[1 << EB],
-                                          const PhaseTw<LOG_M, PH, EB, INV, FOLD, PRE>& tw, const DevMod& md) {
+template <int LOG_M, int PH, int EB, int G, bool INV, bool FP, bool FOLD, int PRE, bool LOW = false>
+__device__ __forceinline__ void run_phase_g(uint64_t (&x)[G][1 << EB],
+                                            const PhaseTw<LOG_M, PH, EB, INV, FOLD, PRE>& tw, const DevMod& md) {
     static_assert(!LOW || (!INV && PH == 0), "reduced inputs enter the first forward phase");
     using Ph = Phase<LOG_M, PH, EB>;
     constexpr int E = 1 << EB;
     [[maybe_unused]] const uint64_t q = md.q;
     const double qd = md.qd, qinv = md.qinv;
-    if constexpr (!INV) {
 #pragma unroll
-        for (int bit = Ph::HB; bit >= Ph::LB; --bit) {
-            const int spp = LOG_M - 1 - bit;
-            const int pos = bit - Ph::WLO;
+    for (int k = 0; k <= Ph::HB - Ph::LB; ++k) {
+        const int bit = INV ? Ph::LB + k : Ph::HB - k;
+        const int spp = LOG_M - 1 - bit;
+        const int pos = bit - Ph::WLO;
 #pragma unroll
-            for (int e = 0; e < E; ++e) {
-                if (e & (1 << pos)) continue;
-                const TwPair tp = tw.get(pos, e);
-                const bool first = LOW && PH == 0 && spp == 0;  // folded after unrolling
-                if constexpr (FP)
-                    fwd_bfly_fp(x[e], x[e | (1 << pos)], tp, qd, qinv, spp % 3 == 0 && !first);
-                else
-                    fwd_bfly_int(x[e], x[e | (1 << pos)], tp, md, int_fwd_reduces(LOG_M, spp) && !first);
-            }
-        }
-    } else {
-#pragma unroll
-        for (int bit = Ph::LB; bit <= Ph::HB; ++bit) {
-            const int pos = bit - Ph::WLO;
-            if (FOLD && PH == 0 && bit == Ph::HB) {
+        for (int e = 0; e < E; ++e) {
+            if (e & (1 << pos)) continue;
+            const int f = e | (1 << pos);
+            if (INV && FOLD && PH == 0 && bit == Ph::HB) {
                 // stage 0 with N^-1 folded in (integer path: outputs fully reduced)
 #pragma unroll
-                for (int e = 0; e < E; ++e) {
-                    if (e & (1 << pos)) continue;
-                    uint64_t X = x[e], Y = x[e | (1 << pos)];
+                for (int g = 0; g < G; ++g) {
+                    const uint64_t X = x[g][e], Y = x[g][f];
                     if constexpr (FP) {
-                        const double a = as_f(X), b2 = as_f(Y);
-                        x[e] = as_u(fmulmod(a + b2, md.n_inv_d, md.n_inv_q, qd));
-                        x[e | (1 << pos)] = as_u(fmulmod(a - b2, md.last_inv_d, md.last_inv_q, qd));
+                        x[g][e] = as_u(fmulmod(as_f(X) + as_f(Y), md.n_inv_d, md.n_inv_q, qd));
+                        x[g][f] = as_u(fmulmod(as_f(X) - as_f(Y), md.last_inv_d, md.last_inv_q, qd));
                     } else {
                         // inputs up to 8q; shoup takes any 64-bit value
-                        x[e] = shoup(X + Y, md.n_inv, md.n_inv_sh, q);
-                        x[e | (1 << pos)] = shoup(X + 8 * q - Y, md.last_inv, md.last_inv_sh, q);
+                        x[g][e] = shoup(X + Y, md.n_inv, md.n_inv_sh, q);
+                        x[g][f] = shoup(X + 8 * q - Y, md.last_inv, md.last_inv_sh, q);
                     }
                 }
-            } else {
+                continue;
+            }
+            const TwPair tp = tw.get(pos, e);
 #pragma unroll
-                for (int e = 0; e < E; ++e) {
-                    if (e & (1 << pos)) continue;
-                    const TwPair tp = tw.get(pos, e);
+            for (int g = 0; g < G; ++g) {
+                if constexpr (INV) {
                     if constexpr (FP)
-                        inv_bfly_fp(x[e], x[e | (1 << pos)], tp, qd, qinv, bit % 3 != 2);
+                        inv_bfly_fp(x[g][e], x[g][f], tp, qd, qinv, bit % 3 != 2);
                     else
-                        inv_bfly_int(x[e], x[e | (1 << pos)], tp, md, bit, bit == LOG_M - 1);
+                        inv_bfly_int(x[g][e], x[g][f], tp, md, bit, bit == LOG_M - 1);
+                } else {
+                    const bool first = LOW && PH == 0 && spp == 0;  // folded after unrolling
+                    if constexpr (FP)
+                        fwd_bfly_fp(x[g][e], x[g][f], tp, qd, qinv, spp % 3 == 0 && !first);
+                    else
+                        fwd_bfly_int(x[g][e], x[g][f], tp, md, int_fwd_reduces(LOG_M, spp) && !first);
                 }
             }
         }
     }
 }
 
-// One register phase loading each twiddle at its use (a single-phase pass:
-// with no exchange in the way the compiler schedules the loads itself).
+// One register phase of one tile loading each twiddle at its use (a
+// single-phase pass: with no exchange in the way the compiler schedules the
+// loads itself).
 template <int LOG_M, int PH, int EB, bool INV, bool FP, bool FOLD, bool LOW = false>
 __device__ __forceinline__ void run_phase(uint64_t (&x)[1 << EB], uint32_t l, uint32_t high, uint32_t s0,
                                           const TwPair* __restrict__ twt, const DevMod& md) {
     const PhaseTw<LOG_M, PH, EB, INV, FOLD, 0> tw(twt, l, high, s0);
-    run_phase<LOG_M, PH, EB, INV, FP, FOLD, 0, LOW>(x, tw, md);
+    run_phase_g<LOG_M, PH, EB, 1, INV, FP, FOLD, 0, LOW>(reinterpret_cast<uint64_t(&)[1][1 << EB]>(x), tw, md);
 }
 
 // LDS word of element r of sub-problem c: c S + r + P (r >> 4), or, where
@@ -262,13 +252,19 @@ __device__ __forceinline__ void run_phase(uint64_t (&x)[1 << EB], uint32_t l, ui
 // row-pass pattern is conflict-free (radix 6 and 7 keep a two-way conflict
 // on one), and with 8 the swizzled forms make the row passes of radix 7-12
 // conflict-free where any padding leaves two-way conflicts (radix 9 and 10
-// keep one two-way conflict pattern as column passes).
+// keep one two-way conflict pattern as column passes), and with 4 (row passes
+// only) those of radix 8-12.
 template <int LOG_M, int EB> struct LdsPad;
 template <int EB> struct LdsPad<4, EB> { static constexpr uint32_t S = 17, P = 0, XA = 0, XB = 0; };
 template <> struct LdsPad<6, 4> { static constexpr uint32_t S = 69, P = 1, XA = 0, XB = 0; };
 template <> struct LdsPad<6, 3> { static constexpr uint32_t S = 73, P = 2, XA = 0, XB = 0; };
 template <> struct LdsPad<7, 4> { static constexpr uint32_t S = 145, P = 2, XA = 0, XB = 0; };
 template <> struct LdsPad<7, 3> { static constexpr uint32_t S = 129, P = 0, XA = 4, XB = 4; };
+template <> struct LdsPad<8, 2> { static constexpr uint32_t S = 256, P = 0, XA = 2, XB = 5; };
+template <> struct LdsPad<9, 2> { static constexpr uint32_t S = 512, P = 0, XA = 2, XB = 5; };
+template <> struct LdsPad<10, 2> { static constexpr uint32_t S = 1024, P = 0, XA = 2, XB = 5; };
+template <> struct LdsPad<11, 2> { static constexpr uint32_t S = 2048, P = 0, XA = 2, XB = 5; };
+template <> struct LdsPad<12, 2> { static constexpr uint32_t S = 4096, P = 0, XA = 2, XB = 5; };
 template <int EB> struct LdsPad<8, EB> { static constexpr uint32_t S = 273, P = 1, XA = 0, XB = 0; };
 template <> struct LdsPad<8, 3> { static constexpr uint32_t S = 257, P = 0, XA = 4, XB = 5; };
 template <int EB> struct LdsPad<9, EB> { static constexpr uint32_t S = 546, P = 1, XA = 0, XB = 0; };
@@ -350,31 +346,43 @@ __device__ __forceinline__ void wave_lds_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// The register phases of one pass in execution order (forward: 0, 1, ...;
-// inverse: the reverse), with an LDS exchange between consecutive phases.
-// Each thread writes back to the words it read last, so one barrier per
-// exchange suffices; an exchange that stays inside each wave needs none.
-template <int LOG_M, int EB, bool INV, bool FP, bool FOLD, int K, bool COL = false, int PRE = 0, int TB = 12>
-__device__ __forceinline__ void run_phases(uint64_t (&x)[1 << EB], uint64_t* lds, uint32_t c, uint32_t l,
-                                           uint32_t high, uint32_t s0, const TwPair* __restrict__ twt,
-                                           const DevMod& md) {
+// The register phases of one pass of G tiles in execution order (forward: 0,
+// 1, ...; inverse: the reverse), with an LDS exchange between consecutive
+// phases, each tile through its own LDS region (one barrier per exchange for
+// all of them).  Each thread writes back to the words it read last, so one
+// barrier per exchange suffices; an exchange that stays inside each wave
+// needs none.
+template <int LOG_M, int EB, int G, bool INV, bool FP, bool FOLD, int K, bool COL, int PRE, int TB>
+__device__ __forceinline__ void run_phases_g(uint64_t (&x)[G][1 << EB], uint64_t* lds, uint32_t c, uint32_t l,
+                                             uint32_t high, uint32_t s0, const TwPair* __restrict__ twt,
+                                             const DevMod& md) {
     constexpr int NPH = (LOG_M + EB - 1) / EB;
+    constexpr uint32_t W = lds_words<LOG_M, EB, TB>();
     if constexpr (K < NPH) {
         constexpr int PH = INV ? NPH - 1 - K : K;
         // the phase's twiddle loads go out before the exchange
         const PhaseTw<LOG_M, PH, EB, INV, FOLD, PRE> tw(twt, l, high, s0);
         if constexpr (K > 0) {
             constexpr int PREV = INV ? PH + 1 : PH - 1;
-            lds_write<LOG_M, PREV, EB>(x, lds, c, l);
+#pragma unroll
+            for (int g = 0; g < G; ++g) lds_write<LOG_M, PREV, EB>(x[g], lds + g * W, c, l);
             if constexpr (wave_local_exchange<LOG_M, EB, COL, TB>(PREV, PH))
                 wave_lds_sync();
             else
                 __syncthreads();
-            lds_read<LOG_M, PH, EB>(x, lds, c, l);
+#pragma unroll
+            for (int g = 0; g < G; ++g) lds_read<LOG_M, PH, EB>(x[g], lds + g * W, c, l);
         }
-        run_phase<LOG_M, PH, EB, INV, FP, FOLD, PRE>(x, tw, md);
-        run_phases<LOG_M, EB, INV, FP, FOLD, K + 1, COL, PRE, TB>(x, lds, c, l, high, s0, twt, md);
+        run_phase_g<LOG_M, PH, EB, G, INV, FP, FOLD, PRE>(x, tw, md);
+        run_phases_g<LOG_M, EB, G, INV, FP, FOLD, K + 1, COL, PRE, TB>(x, lds, c, l, high, s0, twt, md);
     }
+}
+template <int LOG_M, int EB, bool INV, bool FP, bool FOLD, bool COL = false, int PRE = 0, int TB = 12>
+__device__ __forceinline__ void run_phases(uint64_t (&x)[1 << EB], uint64_t* lds, uint32_t c, uint32_t l,
+                                           uint32_t high, uint32_t s0, const TwPair* __restrict__ twt,
+                                           const DevMod& md) {
+    run_phases_g<LOG_M, EB, 1, INV, FP, FOLD, 0, COL, PRE, TB>(reinterpret_cast<uint64_t(&)[1][1 << EB]>(x), lds, c, l,
+                                                               high, s0, twt, md);
 }
 
 // X -> X^kappa on an NTT-domain row (entry k holds the evaluation at
@@ -409,58 +417,6 @@ __device__ __forceinline__ void galois_tile_to_lds(const uint64_t* __restrict__ 
         lds[lds_at<LOG_M, EB>(d / M, d % M)] = to_fp ? fp_from_u64(v) : v;
     }
     __syncthreads();
-}
-
-// Forward register phase PH applied to G independent tiles at once: each
-// twiddle is loaded once and serves the butterflies of every tile.
-template <int LOG_M, int PH, int EB, int G, bool FP, int PRE>
-__device__ __forceinline__ void run_phase_g(uint64_t (&x)[G][1 << EB],
-                                            const PhaseTw<LOG_M, PH, EB, false, false, PRE>& tw, const DevMod& md) {
-    using Ph = Phase<LOG_M, PH, EB>;
-    constexpr int E = 1 << EB;
-    const double qd = md.qd, qinv = md.qinv;
-#pragma unroll
-    for (int bit = Ph::HB; bit >= Ph::LB; --bit) {
-        const int spp = LOG_M - 1 - bit;
-        const int pos = bit - Ph::WLO;
-#pragma unroll
-        for (int e = 0; e < E; ++e) {
-            if (e & (1 << pos)) continue;
-            const TwPair tp = tw.get(pos, e);
-#pragma unroll
-            for (int g = 0; g < G; ++g) {
-                if constexpr (FP)
-                    fwd_bfly_fp(x[g][e], x[g][e | (1 << pos)], tp, qd, qinv, spp % 3 == 0);
-                else
-                    fwd_bfly_int(x[g][e], x[g][e | (1 << pos)], tp, md, int_fwd_reduces(LOG_M, spp));
-            }
-        }
-    }
-}
-// The forward register phases of one pass for G tiles, each exchanging
-// through its own LDS region (one barrier per exchange for all of them).
-template <int LOG_M, int EB, int G, bool FP, int K, int PRE, int TB = 12>
-__device__ __forceinline__ void run_phases_g(uint64_t (&x)[G][1 << EB], uint64_t* lds, uint32_t c, uint32_t l,
-                                             uint32_t high, uint32_t s0, const TwPair* __restrict__ twt,
-                                             const DevMod& md) {
-    constexpr int NPH = (LOG_M + EB - 1) / EB;
-    constexpr uint32_t W = lds_words<LOG_M, EB, TB>();
-    if constexpr (K < NPH) {
-        // the phase's twiddle loads go out before the exchange
-        const PhaseTw<LOG_M, K, EB, false, false, PRE> tw(twt, l, high, s0);
-        if constexpr (K > 0) {
-#pragma unroll
-            for (int g = 0; g < G; ++g) lds_write<LOG_M, K - 1, EB>(x[g], lds + g * W, c, l);
-            if constexpr (wave_local_exchange<LOG_M, EB, false, TB>(K - 1, K))
-                wave_lds_sync();
-            else
-                __syncthreads();
-#pragma unroll
-            for (int g = 0; g < G; ++g) lds_read<LOG_M, K, EB>(x[g], lds + g * W, c, l);
-        }
-        run_phase_g<LOG_M, K, EB, G, FP, PRE>(x, tw, md);
-        run_phases_g<LOG_M, EB, G, FP, K + 1, PRE, TB>(x, lds, c, l, high, s0, twt, md);
-    }
 }
 
 }  // namespace

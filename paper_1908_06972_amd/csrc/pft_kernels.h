@@ -48,14 +48,8 @@ struct NttSchedule {
 // this with P^-1 replaced by q_last^-1); with has_add the ciphertext src[z]
 // ([2][level][N]) is added.  out may coincide with an addend (each element is
 // read before it is written).
-// For an inverse transform only `source` and the fields it names are used.
 #define PFT_EPI_NO_ADD INT64_MIN
 #define PFT_EPI_ITEM_ACC (INT64_MIN + 1)
-// Where the first pass of an inverse transform takes polynomial p's input:
-// its own rows (src_delta words past them), row i of src[p] ([level][N], NTT
-// domain) under X -> X^kappa (kappa_inv = kappa^-1 mod 2N), or the product
-// of rows i of src[p] and src2[p].
-enum : uint32_t { NTT_SRC_SELF = 0, NTT_SRC_PERM = 1, NTT_SRC_PROD = 2 };
 struct NttEpilogue {
     int64_t d_acc[2];   // or PFT_EPI_ITEM_ACC: acc of item z at acc_item[z] + (b acc_level + i) N
     int64_t d_add[2];
@@ -66,16 +60,12 @@ struct NttEpilogue {
     const TwPair* pinv;                // [L]: P^-1 mod q_i (Shoup pairs)
     const TwPair* pinv_fp;             // [L]: the same as (w, w/q) doubles, used where q_i < 2^50
     uint32_t level;
-    uint32_t source;
     const uint64_t* src[PFT_MAX_POLYS / 2];
-    const uint64_t* src2[PFT_MAX_POLYS / 2];
-    uint64_t kappa, kappa_inv;
 };
 bool ntt_supported(uint32_t log_n);
 int ntt_candidates(uint32_t log_n, NttSchedule* out, int max_out);
 bool ntt_schedule_valid(uint32_t log_n, const NttSchedule& s);
-// epi, forward: finish ModDown in the final pass instead of storing;
-// inverse: where the first pass takes its input.
+// epi (forward): finish ModDown in the final pass instead of storing.
 // first: a forward transform starts at pass `first` of the schedule (the
 // earlier passes already applied, e.g. by launch_modup_col_b); an inverse
 // transform stops before pass `first` (the remaining passes applied by the
@@ -186,7 +176,9 @@ void launch_modup_col_b(uint32_t n, WsRef ws, uint64_t off_d, uint64_t off_ext, 
 void launch_moddown_col_b(uint32_t n, WsRef ws, uint64_t off_acc, uint64_t off_conv, uint32_t level,
                           const KsConsts& kc, const DevTables& t, uint32_t log_n, bool ifuse, hipStream_t st);
 // RESCALE's expansion of last_z [2][N] into tmp_z [2][level-1][N] fused the
-// same way: tmp holds the output of the first transform pass.
+// same way, on both sides: last is limb level-1 after the first (row) pass of
+// its inverse transform (launch_ks_inv), tmp the output of the first pass of
+// the forward transform.
 void launch_rescale_col_b(uint32_t n, WsRef ws, uint64_t off_last, uint64_t off_tmp, uint32_t level, uint32_t mode,
                           const DevTables& t, uint32_t log_n, hipStream_t st);
 // The two launches of hybrid key switching around ModDown's conversion, fused
@@ -202,11 +194,14 @@ void launch_rescale_col_b(uint32_t n, WsRef ws, uint64_t off_last, uint64_t off_
 //               and a0 b1 + a1 b0 are added
 //   KS_ROTATE   d = the X -> X^kappa image of c1 of src[z], the image of c0
 //               is added
+//   KS_RESCALE  no digits (d, ext and key are not read): out_b[t] = (row t of
+//               polynomial b of src[z], which has level + 1 rows, - conv_b[t])
+//               times pinv (q_level^-1)
 // and, for KS_WS and KS_ROTATE with has_add, the ciphertext src2[z] is added
 // (it may be the output itself).  No output may overlap a src, nor a src2
 // with KS_PRODUCT: workgroups of one launch read those whole.
 #define PFT_ROW_LIST 64
-enum : uint32_t { KS_WS = 0, KS_PRODUCT = 1, KS_ROTATE = 2 };
+enum : uint32_t { KS_WS = 0, KS_PRODUCT = 1, KS_ROTATE = 2, KS_RESCALE = 3 };
 struct KsRows {
     uint64_t* base;  // item z's workspace at base + z stride
     uint64_t stride;
@@ -214,7 +209,7 @@ struct KsRows {
     const uint64_t* key;  // [dnum][2][L+K][N] in the storage form of launch_key_form
     const TwPair *gadget, *gadget_fp;  // [L]: P mod q_i as Shoup pairs, and as (w, w/q) doubles where q_i < 2^50
     const TwPair *pinv, *pinv_fp;      // [L]: P^-1 mod q_i the same way
-    uint32_t n_items, level, rows, alpha, beta, L, krows, tiles;
+    uint32_t n_items, level, rows, alpha, beta, L, krows, tiles, src_level;
     uint32_t mode, has_add;
     uint64_t kappa, kappa_inv;    // kappa^-1 mod 2N
     uint32_t n_rows;              // rows of this launch
@@ -224,14 +219,37 @@ struct KsRows {
     uint64_t* out[PFT_MAX_ITEMS];
 };
 bool ks_rows_supported(uint32_t log_n);
+// Launches of at most this many words (rows times N, all items) take the
+// 4-residue forms.
+#define KS_SMALL_WORDS (1ull << 21)
+bool ks_small(uint32_t n, uint32_t rows, uint32_t log_n);
+// The first (row) pass of the inverse transform of n_rows rows r of item z,
+// from their NTT domain to off_out + r N, left for the final radix-16 column
+// pass (which launch_modup_col_b with ifuse and launch_rescale_col_b apply).
+// Row r has modulus index mod0 + r mod_step and is, with R = src_row + r
+// src_step, row R of ws_z + off_d (KS_WS), the product of rows R of src[z] and
+// src2[z] (KS_PRODUCT), row R of src[z] under X -> X^kappa (KS_ROTATE) or row R
+// of src[z] (KS_RESCALE).
+struct KsInv {
+    uint64_t* base;
+    uint64_t stride;
+    uint64_t off_d, off_out;
+    uint32_t n_items, n_rows, tiles, mode;
+    uint32_t src_row, src_step, mod0, mod_step;
+    uint64_t kappa, kappa_inv;
+    const uint64_t* src[PFT_MAX_ITEMS];
+    const uint64_t* src2[PFT_MAX_ITEMS];
+};
+void launch_ks_inv(uint32_t n, KsInv a, const DevTables& t, uint32_t log_n, hipStream_t st, ProfHook* prof = nullptr);
 // Fills in the shape fields (and the row list) of `a` and launches the rows
-// of one arithmetic kind; at most 8 digits (ceil(level / alpha) <= 8; aborts
-// otherwise).  fp_rows[m] (host, by modulus index) is 1 where modulus m runs
-// fp64 arithmetic.  pair_digits: the fp64 rows take two digits through each
-// row pass together (same results).  rows: which rows this call launches,
-// KS_ROWS_FP (those with q < 2^50), KS_ROWS_INT (the others) or both.  prof:
-// each launch is timed as a PK_KEY_INNER variant 1024 + (log_n - 4) (+ 64
-// fp64 rows, + 128 digit pairs, + 256 special rows).
+// of one arithmetic kind, or of both at once in the small form; at most 8
+// digits (ceil(level / alpha) <= 8; aborts otherwise).  fp_rows[m] (host, by
+// modulus index) is 1 where modulus m runs fp64 arithmetic.  pair_digits: the
+// fp64 rows take two digits through each row pass together (same results).
+// rows: which rows this call launches, KS_ROWS_FP (those with q < 2^50),
+// KS_ROWS_INT (the others) or both.  prof: each launch is timed as a
+// PK_KEY_INNER variant 1024 + (log_n - 4) (+ 64 fp64 rows, + 128 digit pairs,
+// + 256 special rows, + 512 small form).
 enum : uint32_t { KS_ROWS_INT = 1, KS_ROWS_FP = 2, KS_ROWS_ALL = 3 };
 void launch_ks_rows(uint32_t n, KsRows a, bool special, const KsConsts& kc, const DevTables& t,
                     const uint32_t* fp_rows, uint32_t log_n, bool pair_digits, hipStream_t st,

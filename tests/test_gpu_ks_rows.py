@@ -5,6 +5,7 @@ bit-exact against the oracle."""
 
 import pytest
 
+import synth as S
 from oracle import ckks as C
 
 from .test_gpu_modup_fused import CASES, World, world
@@ -66,3 +67,21 @@ def test_integer_rows_of_other_sizes(bits):
         g = w.ctx.mul_relin(ga, gb)
         w.assert_same(g, prod)
         w.assert_same(w.ctx.rescale(g), low)
+
+
+@pytest.mark.parametrize("name,items", [("a6_n12", 64), ("a3_n13", 64), ("a2_n14", 32), ("a4_n15", 16)])
+def test_large_launches_equal_small_ones(name, items):
+    """Enough items for the 8-residue forms of the fused kernels (a launch of
+    more than 2^21 words), against the same calls one item at a time."""
+    w = world(name)
+    L = w.op.L
+    assert items * L * w.n > 2 ** 21 >= 2 * L * w.n
+    a, b = ([w.ctx.encrypt_seeded(S.plaintext_coeffs(S.rng(s + i), w.n, 2 ** 30), L, w.op.scale, s + i)
+             for i in range(items)] for s in (3000, 4000))
+    prod = w.ctx.mul_relin_batch(a, b)
+    for big, one in ((prod, lambda i: w.ctx.mul_relin(a[i], b[i])),
+                     (w.ctx.rotate_batch(a, 5), lambda i: w.ctx.rotate(a[i], 5)),
+                     (w.ctx.total_sum_batch(b, 2), lambda i: w.ctx.total_sum(b[i], 2)),
+                     (w.ctx.rescale_batch(prod), lambda i: w.ctx.rescale(prod[i]))):
+        for i in range(items):
+            assert bool((big[i].data == one(i).data).all())
