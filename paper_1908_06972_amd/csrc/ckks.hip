@@ -465,12 +465,15 @@ __global__ __launch_bounds__(TB) void k_rescale_expand_b(WsRef ws, uint64_t off_
 // with one item a thread those loads (J n_g words an output set, from L2) and
 // 128-bit sums on every row took the time (6.1 ms for 32 items, 16 terms and
 // 8 outputs at N = 2^15, 16 rows, of whose 6.9 GB the copy rate takes 1.3 ms).
+// NG (8, 4 or 2) is n_g rounded up: the loads of a term are NG unconditional
+// ones in flight together: 38.0 -> 36.6 ms for the bag-of-words layer of 32
+// documents at N = 2^15 against loads that each waited on a condition.
 // Plaintext rows in the form of launch_key_form.  Rows with q < 2^50: each
 // product by fmulmod (within 0.9q), the sums brought within q/2 every 8 terms
 // (below 7.7q < 2^53 before).  The other rows: full 128-bit products of the
 // Montgomery form, reduced every 8 terms, which keeps the sum below q 2^64.
 constexpr uint32_t PT_GT = 8;
-template <uint32_t Z>
+template <uint32_t Z, uint32_t NG>
 __global__ __launch_bounds__(TB) void k_pt_dot_multi_b(WsRef ws, uint32_t n_items, uint64_t off_baby,
                                                        uint64_t ct_words, const uint64_t* __restrict__ pt, uint32_t J,
                                                        uint32_t n_g, uint64_t off_acc, uint32_t level,
@@ -490,45 +493,49 @@ __global__ __launch_bounds__(TB) void k_pt_dot_multi_b(WsRef ws, uint32_t n_item
     if (md.fp) {
 #pragma clang fp contract(off)
         const double q = md.qd, qinv = md.qinv;
-        double a[Z][PT_GT];
+        double a[Z][NG];
 #pragma unroll
         for (uint32_t z = 0; z < Z; ++z)
 #pragma unroll
-            for (uint32_t g = 0; g < PT_GT; ++g) a[z][g] = 0.0;
+            for (uint32_t g = 0; g < NG; ++g) a[z][g] = 0.0;
         for (uint32_t j = 0; j < J; ++j) {
             double x[Z];
 #pragma unroll
             for (uint32_t z = 0; z < Z; ++z)
                 x[z] = as_f(fp_from_u64(w[(z < nz ? z : 0) * ws.stride + off_baby + j * ct_words + k]));
             const uint64_t* __restrict__ pj = pr + (((size_t)j * level) << log_n);
+            // past n_g the last output's terms again, not stored: a condition
+            // would have each load waited for by itself
+            double p[NG];
 #pragma unroll
-            for (uint32_t g = 0; g < PT_GT; ++g)
-                if (g < n_g) {
-                    const double p = as_f(pj[g * pstep + k]), pq = p * qinv;
+            for (uint32_t g = 0; g < NG; ++g) p[g] = as_f(pj[min(g, n_g - 1) * pstep + k]);
 #pragma unroll
-                    for (uint32_t z = 0; z < Z; ++z) a[z][g] += fmulmod(x[z], p, pq, q);
-                }
+            for (uint32_t g = 0; g < NG; ++g) {
+                const double pq = p[g] * qinv;
+#pragma unroll
+                for (uint32_t z = 0; z < Z; ++z) a[z][g] += fmulmod(x[z], p[g], pq, q);
+            }
             if ((j & 7u) == 7u) {
 #pragma unroll
                 for (uint32_t z = 0; z < Z; ++z)
 #pragma unroll
-                    for (uint32_t g = 0; g < PT_GT; ++g) a[z][g] = freduce(a[z][g], q, qinv);
+                    for (uint32_t g = 0; g < NG; ++g) a[z][g] = freduce(a[z][g], q, qinv);
             }
         }
 #pragma unroll
         for (uint32_t z = 0; z < Z; ++z)
             if (z < nz) {
 #pragma unroll
-                for (uint32_t g = 0; g < PT_GT; ++g)
+                for (uint32_t g = 0; g < NG; ++g)
                     if (g < n_g) w[z * ws.stride + off_acc + g * ct_words + k] = fp_to_u64(as_u(a[z][g]), q, qinv);
             }
         return;
     }
     for (uint32_t z = 0; z < nz; ++z, w += ws.stride) {
-        u128 a[PT_GT];
-        uint64_t res[PT_GT];
+        u128 a[NG];
+        uint64_t res[NG];
 #pragma unroll
-        for (uint32_t g = 0; g < PT_GT; ++g) {
+        for (uint32_t g = 0; g < NG; ++g) {
             a[g] = 0;
             res[g] = 0;
         }
@@ -540,16 +547,14 @@ __global__ __launch_bounds__(TB) void k_pt_dot_multi_b(WsRef ws, uint32_t n_item
             const uint64_t x = w[off_baby + j * ct_words + k];
             const uint64_t* __restrict__ pj = pr + (((size_t)j * level) << log_n);
 #pragma unroll
-            for (uint32_t g = 0; g < PT_GT; ++g)
-                if (g < n_g) a[g] += (u128)x * pj[g * pstep + k];
+            for (uint32_t g = 0; g < NG; ++g) a[g] += (u128)x * pj[min(g, n_g - 1) * pstep + k];
             if ((j & 7u) == 7u) {
 #pragma unroll
-                for (uint32_t g = 0; g < PT_GT; ++g)
-                    if (g < n_g) fold(g);
+                for (uint32_t g = 0; g < NG; ++g) fold(g);
             }
         }
 #pragma unroll
-        for (uint32_t g = 0; g < PT_GT; ++g)
+        for (uint32_t g = 0; g < NG; ++g)
             if (g < n_g) {
                 fold(g);
                 w[off_acc + g * ct_words + k] = res[g];
@@ -582,7 +587,7 @@ __global__ __launch_bounds__(TB) void k_add_const_b(ItemPtrs in, ItemPtrs out, c
 // q 2^64 for q < 2^60); the reductions' factor 2^-64 is undone once at the
 // end by a Shoup product with 2^64 mod q (to_mont).
 constexpr uint32_t CT_GT = 4;
-template <uint32_t Z>
+template <uint32_t Z, uint32_t NG>
 __global__ __launch_bounds__(TB) void k_ct_dot_multi_b(ItemPtrs e, uint32_t J, uint32_t n_g, WsRef xs, uint64_t off_x,
                                                        uint64_t ct_words, WsRef ws, uint32_t n_items, uint64_t off_d,
                                                        uint32_t level, const DevMod* __restrict__ mods,
@@ -598,11 +603,11 @@ __global__ __launch_bounds__(TB) void k_ct_dot_multi_b(ItemPtrs e, uint32_t J, u
 #pragma clang fp contract(off)
         const double qd = md.qd, qinv = md.qinv;
         const uint64_t* __restrict__ xb = xs.base + (size_t)z0 * xs.stride + off_x;
-        double a[Z][CT_GT][3];
+        double a[Z][NG][3];
 #pragma unroll
         for (uint32_t z = 0; z < Z; ++z)
 #pragma unroll
-            for (uint32_t g = 0; g < CT_GT; ++g)
+            for (uint32_t g = 0; g < NG; ++g)
 #pragma unroll
                 for (int t = 0; t < 3; ++t) a[z][g][t] = 0.0;
         for (uint32_t j = 0; j < J; ++j) {
@@ -614,24 +619,24 @@ __global__ __launch_bounds__(TB) void k_ct_dot_multi_b(ItemPtrs e, uint32_t J, u
                 x1[z] = as_f(fp_from_u64(xz[o1]));
             }
 #pragma unroll
-            for (uint32_t g = 0; g < CT_GT; ++g)
-                if (g < n_g) {
-                    const uint64_t* __restrict__ E = e.p[g * J + j];
-                    const double e0 = as_f(fp_from_u64(E[o0])), e1 = as_f(fp_from_u64(E[o1]));
-                    const double e0q = e0 * qinv, e1q = e1 * qinv;
+            for (uint32_t g = 0; g < NG; ++g) {
+                // past n_g the last giant step's terms again, not stored
+                const uint64_t* __restrict__ E = e.p[min(g, n_g - 1) * J + j];
+                const double e0 = as_f(fp_from_u64(E[o0])), e1 = as_f(fp_from_u64(E[o1]));
+                const double e0q = e0 * qinv, e1q = e1 * qinv;
 #pragma unroll
-                    for (uint32_t z = 0; z < Z; ++z) {
-                        a[z][g][0] += fmulmod(x0[z], e0, e0q, qd);
-                        a[z][g][1] += fmulmod(x1[z], e0, e0q, qd);
-                        a[z][g][1] += fmulmod(x0[z], e1, e1q, qd);
-                        a[z][g][2] += fmulmod(x1[z], e1, e1q, qd);
-                    }
+                for (uint32_t z = 0; z < Z; ++z) {
+                    a[z][g][0] += fmulmod(x0[z], e0, e0q, qd);
+                    a[z][g][1] += fmulmod(x1[z], e0, e0q, qd);
+                    a[z][g][1] += fmulmod(x0[z], e1, e1q, qd);
+                    a[z][g][2] += fmulmod(x1[z], e1, e1q, qd);
                 }
+            }
             if ((j & 3u) == 3u) {
 #pragma unroll
                 for (uint32_t z = 0; z < Z; ++z)
 #pragma unroll
-                    for (uint32_t g = 0; g < CT_GT; ++g)
+                    for (uint32_t g = 0; g < NG; ++g)
 #pragma unroll
                         for (int t = 0; t < 3; ++t) a[z][g][t] = freduce(a[z][g][t], qd, qinv);
             }
@@ -639,7 +644,7 @@ __global__ __launch_bounds__(TB) void k_ct_dot_multi_b(ItemPtrs e, uint32_t J, u
 #pragma unroll
         for (uint32_t z = 0; z < Z; ++z)
 #pragma unroll
-            for (uint32_t g = 0; g < CT_GT; ++g)
+            for (uint32_t g = 0; g < NG; ++g)
                 if (z < nz && g < n_g) {
                     uint64_t* __restrict__ dd = ws.base + (size_t)(g * n_items + z0 + z) * ws.stride + off_d;
                     dd[o0] = fp_to_u64(as_u(a[z][g][0]), qd, qinv);
@@ -651,10 +656,10 @@ __global__ __launch_bounds__(TB) void k_ct_dot_multi_b(ItemPtrs e, uint32_t J, u
     const TwPair r = to_mont[i];
     for (uint32_t z = z0; z < z0 + nz; ++z) {
         const uint64_t* __restrict__ x = xs.base + (size_t)z * xs.stride + off_x;
-        u128 s[CT_GT][3];
-        uint64_t d[CT_GT][3];
+        u128 s[NG][3];
+        uint64_t d[NG][3];
 #pragma unroll
-        for (uint32_t g = 0; g < CT_GT; ++g)
+        for (uint32_t g = 0; g < NG; ++g)
 #pragma unroll
             for (int t = 0; t < 3; ++t) {
                 s[g][t] = 0;
@@ -671,7 +676,7 @@ __global__ __launch_bounds__(TB) void k_ct_dot_multi_b(ItemPtrs e, uint32_t J, u
         for (uint32_t j = 0; j < J; ++j) {
             const uint64_t x0 = x[j * ct_words + o0], x1 = x[j * ct_words + o1];
 #pragma unroll
-            for (uint32_t g = 0; g < CT_GT; ++g)
+            for (uint32_t g = 0; g < NG; ++g)
                 if (g < n_g) {
                     const uint64_t* __restrict__ E = e.p[g * J + j];
                     const uint64_t e0 = E[o0], e1 = E[o1];
@@ -681,12 +686,12 @@ __global__ __launch_bounds__(TB) void k_ct_dot_multi_b(ItemPtrs e, uint32_t J, u
                 }
             if ((j & 7u) == 7u) {
 #pragma unroll
-                for (uint32_t g = 0; g < CT_GT; ++g)
+                for (uint32_t g = 0; g < NG; ++g)
                     if (g < n_g) fold(g);
             }
         }
 #pragma unroll
-        for (uint32_t g = 0; g < CT_GT; ++g)
+        for (uint32_t g = 0; g < NG; ++g)
             if (g < n_g) {
                 fold(g);
                 uint64_t* __restrict__ dd = ws.base + (size_t)(g * n_items + z) * ws.stride + off_d;
@@ -810,19 +815,27 @@ void launch_pt_dot_multi_b(uint32_t n, WsRef ws, uint64_t off_baby, uint64_t ct_
                            uint32_t n_g, uint64_t off_acc, uint32_t level, const DevTables& t, uint32_t log_n,
                            hipStream_t st) {
     // items per thread: as many as there are, up to the four whose sums (64
-    // registers) leave room for the products
-    auto go = [&](auto zc) {
-        constexpr uint32_t Z = decltype(zc)::value;
+    // registers for eight outputs) leave room for the products
+    auto go = [&](auto zc, auto gc) {
+        constexpr uint32_t Z = decltype(zc)::value, NG = decltype(gc)::value;
         const uint64_t blocks = (uint64_t)((n + Z - 1) / Z) * ((1u << log_n) / TB) * 2 * level;
-        hipLaunchKernelGGL(k_pt_dot_multi_b<Z>, dim3((uint32_t)blocks), dim3(TB), 0, st, ws, n, off_baby, ct_words, pt,
-                           J, n_g, off_acc, level, t.mods, log_n);
+        hipLaunchKernelGGL((k_pt_dot_multi_b<Z, NG>), dim3((uint32_t)blocks), dim3(TB), 0, st, ws, n, off_baby, ct_words,
+                           pt, J, n_g, off_acc, level, t.mods, log_n);
     };
-    if (n >= 3)
-        go(std::integral_constant<uint32_t, 4>{});
-    else if (n == 2)
-        go(std::integral_constant<uint32_t, 2>{});
+    auto by_items = [&](auto gc) {
+        if (n >= 3)
+            go(std::integral_constant<uint32_t, 4>{}, gc);
+        else if (n == 2)
+            go(std::integral_constant<uint32_t, 2>{}, gc);
+        else
+            go(std::integral_constant<uint32_t, 1>{}, gc);
+    };
+    if (n_g > 4)
+        by_items(std::integral_constant<uint32_t, 8>{});
+    else if (n_g > 2)
+        by_items(std::integral_constant<uint32_t, 4>{});
     else
-        go(std::integral_constant<uint32_t, 1>{});
+        by_items(std::integral_constant<uint32_t, 2>{});
 }
 
 void launch_add_const_b(uint32_t n, const ItemPtrs& in, const ItemPtrs& out, const TwPair* consts, uint32_t level,
@@ -836,15 +849,18 @@ uint32_t ct_dot_multi_steps() { return CT_GT; }
 void launch_ct_dot_multi_b(uint32_t n, const ItemPtrs& e, uint32_t J, uint32_t n_g, WsRef xs, uint64_t off_x,
                            uint64_t ct_words, WsRef ws, uint64_t off_d, uint32_t level, const TwPair* to_mont,
                            const DevTables& t, uint32_t log_n, hipStream_t st) {
-    auto go = [&](auto zc) {
-        constexpr uint32_t Z = decltype(zc)::value;
-        hipLaunchKernelGGL(k_ct_dot_multi_b<Z>, grid_nk(log_n, level, (n + Z - 1) / Z), dim3(TB), 0, st, e, J, n_g, xs,
-                           off_x, ct_words, ws, n, off_d, level, t.mods, to_mont, log_n);
+    auto go = [&](auto zc, auto gc) {
+        constexpr uint32_t Z = decltype(zc)::value, NG = decltype(gc)::value;
+        hipLaunchKernelGGL((k_ct_dot_multi_b<Z, NG>), grid_nk(log_n, level, (n + Z - 1) / Z), dim3(TB), 0, st, e, J, n_g,
+                           xs, off_x, ct_words, ws, n, off_d, level, t.mods, to_mont, log_n);
     };
-    if (n >= 2)
-        go(std::integral_constant<uint32_t, 2>{});
+    using one = std::integral_constant<uint32_t, 1>;
+    using two = std::integral_constant<uint32_t, 2>;
+    using four = std::integral_constant<uint32_t, 4>;
+    if (n_g > 2)
+        n >= 2 ? go(two{}, four{}) : go(one{}, four{});
     else
-        go(std::integral_constant<uint32_t, 1>{});
+        n >= 2 ? go(two{}, two{}) : go(one{}, two{});
 }
 
 void launch_scale_const_b(uint32_t n, const ItemPtrs& in, const ItemPtrs& out, const TwPair* consts, uint32_t level,
