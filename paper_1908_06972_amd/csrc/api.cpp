@@ -1846,7 +1846,9 @@ static void key_switch_b(pft_ctx* c, uint32_t n, WsRef ws, const KsLayout& K, co
         }
     }
     KsRows kr{};
+    KsSplit split{1, beta, false};
     if (merged) {
+        split = ks_split(n, level, c->kc, c->fp_rows.data(), lg);
         kr.base = ws.base;
         kr.stride = ws.stride;
         kr.off_d = off_d;
@@ -1869,7 +1871,8 @@ static void key_switch_b(pft_ctx* c, uint32_t n, WsRef ws, const KsLayout& K, co
             kr.out[z] = out.p[z];
         }
         // the special rows of both accumulators, ready for ModDown's conversion
-        launch_ks_rows(n, kr, true, c->kc, c->tabs, c->fp_rows.data(), lg, c->inner_pairs, c->stream, hook(c));
+        launch_ks_rows(n, kr, true, c->kc, c->tabs, c->fp_rows.data(), lg, c->inner_pairs, c->stream, hook(c),
+                       KS_ROWS_ALL, split);
     } else {
         const uint32_t first = fuse ? 1u : 0u;
         if (!full.empty())
@@ -1903,9 +1906,14 @@ static void key_switch_b(pft_ctx* c, uint32_t n, WsRef ws, const KsLayout& K, co
         ntt_jobs(c, jobs, P->K, level, true, 0, nullptr, 0, ifuse_down ? 1u : 0u, ifuse_down);
     }
     if (fuse_down) {
+        BconvIn sum{{K.off_acc + ((uint64_t)level << lg), K.off_acc + ((uint64_t)(rows + level) << lg)}, {0, 0}, 1};
+        if (split.parts > 1)
+            sum = BconvIn{{K.off_ext + ((uint64_t)level << lg), K.off_acc},
+                          {(uint64_t)split.group * rows << lg, (uint64_t)P->K << lg},
+                          split.parts};
         timed(c, PK_MODDOWN_CONV, 8.0 * N * (ifuse_down ? 0.0 : 2.0 * P->K) * n, 2.0 * N * P->K * level * n,
               [&] {
-                  launch_moddown_col_b(n, ws, K.off_acc, K.off_conv, level, c->kc, c->tabs, lg, ifuse_down,
+                  launch_moddown_col_b(n, ws, sum, K.off_conv, level, c->kc, c->tabs, lg, ifuse_down,
                                        c->stream);
               },
               64u + down_kb + (ifuse_down ? 16u : 0u));
@@ -1916,7 +1924,8 @@ static void key_switch_b(pft_ctx* c, uint32_t n, WsRef ws, const KsLayout& K, co
     }
     if (merged) {
         auto finish = [&](hipStream_t st, uint32_t kinds) {
-            launch_ks_rows(n, kr, false, c->kc, c->tabs, c->fp_rows.data(), lg, c->inner_pairs, st, hook(c), kinds);
+            launch_ks_rows(n, kr, false, c->kc, c->tabs, c->fp_rows.data(), lg, c->inner_pairs, st, hook(c), kinds,
+                           split);
         };
         // on the context's own stream the 60-bit rows run on the helper
         // stream beside the fp64 rows (the small form takes both in one
@@ -1924,10 +1933,10 @@ static void key_switch_b(pft_ctx* c, uint32_t n, WsRef ws, const KsLayout& K, co
         // later reads the output or the key.  While this family is being
         // timed per launch the two run one after the other, so that each
         // launch's time is its own.
-        const bool split = !ks_small(n, level, lg) && c->inner_st && c->stream == c->home && !c->prof.on(PK_KEY_INNER) &&
+        const bool fork = !ks_small(n, level, lg) && c->inner_st && c->stream == c->home && !c->prof.on(PK_KEY_INNER) &&
                            hipEventRecord(c->inner_fork, c->stream) == hipSuccess &&
                            hipStreamWaitEvent(c->inner_st, c->inner_fork, 0) == hipSuccess;
-        if (split) {
+        if (fork) {
             finish(c->inner_st, KS_ROWS_INT);
             finish(c->stream, KS_ROWS_FP);
             if (hipEventRecord(c->inner_join, c->inner_st) != hipSuccess ||

@@ -61,8 +61,8 @@ constexpr int tw_pre_ks(int eb, bool fp, int g) { return eb == 2 ? 3 : fp && g =
 // instruction streams); the two converted rows of the output are such a pair
 // too.
 template <int LOG_M, int EB, int TB, bool FP, int G, bool SPECIAL>
-__device__ __forceinline__ void ks_row(const KsRows& a, uint64_t* lds, uint32_t z, uint32_t tile, uint32_t t,
-                                       uint32_t mi, const DevMod& md, const TwPair* __restrict__ tw,
+__device__ __forceinline__ void ks_row(const KsRows& a, uint64_t* lds, uint32_t z, uint32_t tile, uint32_t entry,
+                                       uint32_t t, uint32_t mi, const DevMod& md, const TwPair* __restrict__ tw,
                                        const TwPair* __restrict__ tw_inv, uint32_t log_n) {
     constexpr int M = 1 << LOG_M;
     constexpr int E = 1 << EB;
@@ -76,6 +76,9 @@ __device__ __forceinline__ void ks_row(const KsRows& a, uint64_t* lds, uint32_t 
     static_assert(POUT::WLO == 0, "each thread ends with E consecutive words");
     static_assert(G == 1 || G == 2, "one or two tiles per row pass");
     constexpr int PRE = tw_pre_ks(EB, FP, G);
+    // integer ciphertext rows of the small form: their sums may be formed in
+    // the special rows' launch (early) and be there in the last one (ready)
+    constexpr bool SPLIT = EB == 2 && !FP;
 
     const uint32_t tid = threadIdx.x;
     [[maybe_unused]] const uint64_t q = md.q;
@@ -103,6 +106,14 @@ __device__ __forceinline__ void ks_row(const KsRows& a, uint64_t* lds, uint32_t 
             v[2 * e] = u.x;
             v[2 * e + 1] = u.y;
         }
+    };
+    const bool early = SPECIAL && SPLIT && t < a.level;
+    const bool ready = !SPECIAL && SPLIT && (entry >> KS_ROW_EARLY) != 0;
+    const uint32_t part = SPECIAL ? (entry >> KS_ROW_PART) & 7u : 0u;
+    // an early row's part s of polynomial 1
+    [[maybe_unused]] auto early1 = [&](uint32_t s) {
+        const uint32_t e = (entry >> KS_ROW_EARLY) - 1u;
+        return item + a.off_acc + ((size_t)(a.parts * (a.rows - a.level + e) + s) << log_n);
     };
     uint64_t acc0[E], acc1[E];  // FP: doubles; otherwise residues
 #pragma unroll
@@ -134,6 +145,16 @@ __device__ __forceinline__ void ks_row(const KsRows& a, uint64_t* lds, uint32_t 
         for (int e = 0; e < E; ++e) x[e] = *words(src + ((size_t)e << PIN::WLO), r0);
     };
     auto ext = [&](uint32_t j) { return item + a.off_ext + ((size_t)(j * a.rows + t) << log_n); };
+    auto store_vec = [&](uint64_t* __restrict__ p, const uint64_t (&v)[E]) {
+        ulonglong2* __restrict__ pv = reinterpret_cast<ulonglong2*>(const_cast<uint64_t*>(words(p, w0)));
+#pragma unroll
+        for (int e = 0; e < E / 2; ++e) {
+            ulonglong2 u;
+            u.x = v[2 * e];
+            u.y = v[2 * e + 1];
+            pv[e] = u;
+        }
+    };
     // the row pass's output brought within q/2 (FP; the integer products take any value)
     auto settle = [&](uint64_t (&x)[E]) {
         if constexpr (FP) {
@@ -288,8 +309,11 @@ __device__ __forceinline__ void ks_row(const KsRows& a, uint64_t* lds, uint32_t 
     }
     // every other digit through the row pass, G at a time (uniform control
     // flow: t, level, alpha and beta are the same for the whole workgroup)
+    if (early) jo = t / a.alpha;
+    const uint32_t j0 = SPECIAL ? part * a.group : 0u;
+    const uint32_t j1 = ready ? 0u : SPECIAL ? min(a.beta, j0 + a.group) : a.beta;
     uint32_t pend = ~0u;
-    for (uint32_t j = 0; j < a.beta; ++j) {
+    for (uint32_t j = j0; j < j1; ++j) {
         if (j == jo) continue;
         if constexpr (G == 1) {
             digit_1(j);
@@ -304,14 +328,43 @@ __device__ __forceinline__ void ks_row(const KsRows& a, uint64_t* lds, uint32_t 
     }
     if (pend != ~0u) digit_1(pend);
 
+    if constexpr (SPLIT) {
+        if (ready) {  // at most four parts below 2q each onto sums below 2q
+            for (uint32_t s = 0; s < a.parts; ++s) {
+                uint64_t x[2][E];
+                load_vec(ext(s * a.group), x[0]);
+                load_vec(early1(s), x[1]);
+#pragma unroll
+                for (int e = 0; e < E; ++e) {
+                    acc0[e] += x[0][e];
+                    acc1[e] += x[1][e];
+                }
+            }
+        }
+        if (early) {
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                acc0[e] = reduce_int(acc0[e], md);
+                acc1[e] = reduce_int(acc1[e], md);
+            }
+            store_vec(ext(j0), acc0);
+            store_vec(early1(part), acc1);
+            return;
+        }
+    }
     if constexpr (SPECIAL) {
         // both accumulators through the row pass of their inverse transform
         const TwPair* __restrict__ twi = tw_inv + ((size_t)mi << log_n);
-        uint64_t* __restrict__ o = item + a.off_acc + ((size_t)t << log_n);
+        uint64_t* o0 = item + a.off_acc + ((size_t)t << log_n);
+        uint64_t* o1 = o0 + ((size_t)a.rows << log_n);
+        if (a.parts > 1) {  // see KsSplit
+            o0 = ext(j0);
+            o1 = item + a.off_acc + ((size_t)(part * (a.rows - a.level) + t - a.level) << log_n);
+        }
         auto put = [&](const uint64_t (&x)[E], uint32_t b) {
 #pragma unroll
             for (int e = 0; e < E; ++e)
-                *const_cast<uint64_t*>(words(o + ((size_t)(b * a.rows) << log_n) + ((size_t)e << PIN::WLO), r0)) = x[e];
+                *const_cast<uint64_t*>(words((b ? o1 : o0) + ((size_t)e << PIN::WLO), r0)) = x[e];
         };
 #pragma unroll
         for (int e = 0; e < E; ++e) {
@@ -414,13 +467,13 @@ void k_ks_rows(KsRows a, const DevMod* __restrict__ mods, const TwPair* __restri
     __shared__ uint64_t lds[G * lds_words<LOG_M, EB, TB>()];
     uint32_t z, tile, r;
     if (!ks_block(a.n_items, a.tiles, a.n_rows, z, tile, r)) return;  // whole workgroup, before any barrier
-    const uint32_t t = a.row[r];
+    const uint32_t entry = a.row[r], t = entry & KS_ROW_MASK;
     const uint32_t mi = t < a.level ? t : a.L + (t - a.level);
     const DevMod md = mods[mi];
     if (KIND == KS_ROWS_FP || (KIND == KS_ROWS_ALL && md.fp))
-        ks_row<LOG_M, EB, TB, true, G, SPECIAL>(a, lds, z, tile, t, mi, md, tw, tw_inv, log_n);
+        ks_row<LOG_M, EB, TB, true, G, SPECIAL>(a, lds, z, tile, entry, t, mi, md, tw, tw_inv, log_n);
     else
-        ks_row<LOG_M, EB, TB, false, G, SPECIAL>(a, lds, z, tile, t, mi, md, tw, tw_inv, log_n);
+        ks_row<LOG_M, EB, TB, false, G, SPECIAL>(a, lds, z, tile, entry, t, mi, md, tw, tw_inv, log_n);
 }
 
 // The row pass (the first) of an inverse transform of rows that are read, or
@@ -522,6 +575,42 @@ bool ks_small(uint32_t n, uint32_t rows, uint32_t log_n) {
     return ((uint64_t)n * rows << log_n) <= KS_SMALL_WORDS;
 }
 
+// parts: a tile of a special row costs a workgroup ceil(beta / parts) digits'
+// passes and two of the inverse (splitting repeats the latter), a round of
+// workgroups being one per compute unit (two of the 1024-word tiles' four
+// waves).  At N = 2^15, level 16, one item (64 tiles of 60-bit rows, four
+// digits) the launch takes 15.6 us in four parts, 23.3 in one, and ModDown's
+// conversion 16.0 instead of 14.1; one HMULT at N = 2^16, level 24 (96 tiles,
+// two parts) 172 -> 161 us.
+// early: where the last launch is a single round, its few integer rows are
+// what it ends with: 28.7 -> 24.1 us at N = 2^15, level 16, the special rows'
+// launch 15.6 -> 17.5.  With more rounds they hide (six items: 5028 us without,
+// 5065 with, for a predict step).
+KsSplit ks_split(uint32_t n, uint32_t level, const KsConsts& kc, const uint32_t* fp_rows, uint32_t log_n) {
+    const uint32_t beta = (level + kc.alpha - 1) / kc.alpha;
+    KsSplit s{1, beta, false};
+    if (beta < 2 || !ks_small(n, std::max(level, kc.K), log_n)) return s;
+    const uint32_t tile_log = std::max(log_n - 4, 10u), slots = tile_log == 10 ? 512 : 256;
+    auto rounds = [&](uint64_t rows) { return (uint32_t)((((n * rows) << log_n >> tile_log) + slots - 1) / slots); };
+    uint32_t ints = 0;
+    for (uint32_t r = 0; r < level; ++r) ints += fp_rows[r] ? 0 : 1;
+    s.early = ints > 0 && ints <= kc.K && rounds(level) == 1;
+    if (!s.early) ints = 0;
+    uint32_t best = ~0u;
+    for (uint32_t parts = 1; parts <= std::min(beta, 4u); ++parts) {
+        const uint32_t group = (beta + parts - 1) / parts;
+        // every part has a digit, and polynomial 1's parts fit (KsSplit)
+        if ((parts - 1) * group >= beta || (parts > 1 && parts * (kc.K + ints) > 2 * (level + kc.K))) continue;
+        const uint32_t cost = rounds(kc.K * parts) * (group + 2);
+        if (cost < best) {
+            best = cost;
+            s.parts = parts;
+            s.group = group;
+        }
+    }
+    return s;
+}
+
 void launch_ks_inv(uint32_t n, KsInv a, const DevTables& t, uint32_t log_n, hipStream_t st, ProfHook* prof) {
     a.n_items = n;
     const bool small = ks_small(n, a.n_rows, log_n);
@@ -544,7 +633,7 @@ void launch_ks_inv(uint32_t n, KsInv a, const DevTables& t, uint32_t log_n, hipS
 
 void launch_ks_rows(uint32_t n, KsRows a, bool special, const KsConsts& kc, const DevTables& t,
                     const uint32_t* fp_rows, uint32_t log_n, bool pair_digits, hipStream_t st, ProfHook* prof,
-                    uint32_t rows_sel) {
+                    uint32_t rows_sel, KsSplit split) {
     const uint32_t level = a.level;
     a.n_items = n;
     a.rows = level + kc.K;
@@ -558,22 +647,38 @@ void launch_ks_rows(uint32_t n, KsRows a, bool special, const KsConsts& kc, cons
     }
     a.L = kc.L;
     a.krows = kc.L + kc.K;
+    a.parts = split.parts;
+    a.group = split.parts > 1 ? split.group : a.beta;
     const bool small = ks_small(n, special ? kc.K : level, log_n);
     // the rows of one arithmetic kind (the small form: of both, the longer
     // integer rows first), in chunks that fit the row list
     for (uint32_t kind : {KS_ROWS_FP, KS_ROWS_INT}) {
         if (!(rows_sel & kind) || (small && kind == KS_ROWS_FP && rows_sel == KS_ROWS_ALL)) continue;
-        std::vector<uint16_t> rows;
+        std::vector<uint32_t> rows;
         for (uint32_t k : {KS_ROWS_INT, KS_ROWS_FP}) {
             if (k != kind && !(small && rows_sel == KS_ROWS_ALL)) continue;
             for (uint32_t r = special ? level : 0; r < (special ? a.rows : level); ++r) {
                 const uint32_t mi = r < level ? r : kc.L + (r - level);
-                if (fp_rows[mi] == (k == KS_ROWS_FP ? 1u : 0u)) rows.push_back((uint16_t)r);
+                if (fp_rows[mi] != (k == KS_ROWS_FP ? 1u : 0u)) continue;
+                for (uint32_t s = 0; s < (special ? a.parts : 1u); ++s) rows.push_back(r | s << KS_ROW_PART);
+            }
+        }
+        if (split.early) {
+            // last, being shorter than the other rows
+            std::vector<uint32_t> ints;
+            for (uint32_t r = 0, e = 1; r < level; ++r)
+                if (!fp_rows[r]) ints.push_back(r | e++ << KS_ROW_EARLY);
+            if (special) {
+                for (uint32_t i : ints)
+                    for (uint32_t s = 0; s < a.parts; ++s) rows.push_back(i | s << KS_ROW_PART);
+            } else {
+                rows.erase(rows.begin(), rows.begin() + ints.size());
+                rows.insert(rows.end(), ints.begin(), ints.end());
             }
         }
         for (size_t r0 = 0; r0 < rows.size(); r0 += PFT_ROW_LIST) {
             a.n_rows = (uint32_t)std::min<size_t>(PFT_ROW_LIST, rows.size() - r0);
-            for (uint32_t i = 0; i < a.n_rows; ++i) a.row[i] = rows[r0 + i];
+            std::copy_n(rows.begin() + r0, a.n_rows, a.row);
             const bool g2 = small || (kind == KS_ROWS_FP && pair_digits && !special);
             if (prof) prof->begin(PK_KEY_INNER, st);
             by_row_pass(log_n, [&](auto lm, auto tb) {
@@ -611,8 +716,12 @@ void launch_ks_rows(uint32_t n, KsRows a, bool special, const KsConsts& kc, cons
                 const double N = (double)(1u << log_n), lm = (double)(log_n - 4);
                 const double in = special ? 0.0 : a.mode == KS_PRODUCT ? 4.0 : a.mode == KS_WS ? 1.0 : 2.0;
                 const double io = in + (special ? 0.0 : 2.0 + (a.has_add ? 2.0 : 0.0));
-                prof->end(PK_KEY_INNER, 8.0 * N * a.n_rows * (n * io + 2.0 * a.beta),
-                          N * n * a.n_rows * (0.5 * lm * (a.beta + (special ? 2.0 : 1.0)) + 2.0 * a.beta),
+                // a special row once for all its parts, an early row with the last launch
+                const double m = (double)std::count_if(a.row, a.row + a.n_rows, [&](uint32_t e) {
+                    return !special || (e >> KS_ROW_PART) == 0;
+                });
+                prof->end(PK_KEY_INNER, 8.0 * N * m * (n * io + 2.0 * a.beta),
+                          N * n * m * (0.5 * lm * (a.beta + (special ? 2.0 : 1.0)) + 2.0 * a.beta),
                           1024u + (log_n - 4) + (small ? 512u : kind == KS_ROWS_FP ? 64u : 0u) + (g2 ? 128u : 0u) +
                               (special ? 256u : 0u),
                           st);

@@ -395,7 +395,7 @@ void launch_pass(const PolyBatch& b, const DevTables& t, uint32_t log_n, uint32_
 constexpr uint32_t BCONV_COLS = 32;
 template <uint32_t NKB, bool DOWN, bool IFUSE>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k_bconv_col_b(
-    WsRef ws, uint64_t off_in, uint64_t off_out, uint32_t level, KsConsts kc, const DevMod* __restrict__ mods,
+    WsRef ws, BconvIn src, uint64_t off_out, uint32_t level, KsConsts kc, const DevMod* __restrict__ mods,
     const TwPair* __restrict__ tw, const TwPair* __restrict__ tw_inv, uint32_t log_n) {
     __shared__ uint64_t s_dig[2 * NKB * 16 * BCONV_COLS];  // [input row][t][u]
     extern __shared__ uint4 s_dyn[];  // fold constants by slot, then 16 twiddles by slot
@@ -412,7 +412,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
     const uint32_t na = DOWN ? kc.K : min(i0 + kc.alpha, level) - i0;
     const size_t lj = (size_t)(level - 1) * kc.dnum + j;
     uint64_t* item = ws.base + (size_t)blockIdx.z * ws.stride;
-    const uint64_t* __restrict__ in = item + off_in + (DOWN ? ((size_t)j * rows << log_n) : 0);
+    // ModDown: the special rows themselves; ModUp: d's rows
+    const uint64_t* __restrict__ in = item + src.off[DOWN ? j : 0];
     uint64_t* __restrict__ out = item + off_out + ((size_t)j * (DOWN ? level : rows) << log_n);
     auto mod_of = [&](uint32_t t) { return DOWN || t < level ? t : kc.L + (t - level); };
     // fold constants and first twiddles of every slot
@@ -423,6 +424,38 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
         const uint32_t t = row_of(tgt[i >> 4]);
         if (t != PFT_NO_ROW) s_tw[i] = tw[((size_t)mod_of(t) << log_n) + (i & 15u)];
     }
+    if constexpr (DOWN && IFUSE) {
+        // the sums of the parts, four of a row's 16 residues a thread (every
+        // load of all parts in flight at once): at most four terms below 4q
+        // (fp64: within 4.5q) each, reduced for the next butterflies
+        if (src.parts > 1) {
+            for (uint32_t w = tid >> 5; w < 4 * na; w += blockDim.x >> 5) {
+                const uint32_t ii = w >> 2, e0 = (w & 3u) * 4u;
+                const DevMod md = mods[kc.L + ii];
+                const uint64_t* __restrict__ p = in + (size_t)e0 * S + (((size_t)ii << log_n) + col);
+                uint64_t y[4][4];
+#pragma unroll
+                for (uint32_t s = 0; s < 4; ++s)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) y[s][e] = p[min(s, src.parts - 1) * src.step[j] + (size_t)e * S];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    uint64_t v = y[0][e];
+                    if (md.fp) {
+#pragma unroll
+                        for (uint32_t s = 1; s < 4; ++s) v = s < src.parts ? as_u(as_f(v) + as_f(y[s][e])) : v;
+                        v = as_u(freduce(as_f(v), md.qd, md.qinv));
+                    } else {
+#pragma unroll
+                        for (uint32_t s = 1; s < 4; ++s) v = s < src.parts ? v + y[s][e] : v;
+                        v = reduce_int(v, md);
+                    }
+                    s_dig[(ii * 16u + e0 + e) * BCONV_COLS + u] = v;
+                }
+            }
+            __syncthreads();
+        }
+    }
     // the input rows' digits
     for (uint32_t ii = tid >> 5; ii < 2 * NKB; ii += blockDim.x >> 5) {
         uint64_t x[16];
@@ -430,10 +463,15 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
             const uint32_t mi = DOWN ? kc.L + ii : i0 + ii;
             const DevMod md = mods[mi];
             const TwPair hv = DOWN ? kc.down_phatinv[ii] : kc.modup_hatinv[lj * kc.alpha + ii];
-            const uint32_t off = (((i0 + ii) << log_n) + col) * 8u;
+            const uint32_t off = (((DOWN ? ii : i0 + ii) << log_n) + col) * 8u;
+            if (DOWN && IFUSE && src.parts > 1) {
 #pragma unroll
-            for (int e = 0; e < 16; ++e)
-                x[e] = *reinterpret_cast<const uint64_t*>(reinterpret_cast<const char*>(in + (size_t)e * S) + off);
+                for (int e = 0; e < 16; ++e) x[e] = s_dig[(ii * 16u + e) * BCONV_COLS + u];
+            } else {
+#pragma unroll
+                for (int e = 0; e < 16; ++e)
+                    x[e] = *reinterpret_cast<const uint64_t*>(reinterpret_cast<const char*>(in + (size_t)e * S) + off);
+            }
             if constexpr (IFUSE) {
                 const TwPair* __restrict__ twt = tw_inv + ((size_t)mi << log_n);
                 if (md.fp) {
@@ -647,7 +685,7 @@ bool bconv_col_supported(uint32_t log_n, uint32_t nkb, uint32_t tiles) {
 }
 
 template <bool DOWN, bool IFUSE>
-static void launch_bconv_col(uint32_t nkb, dim3 grid, hipStream_t st, WsRef ws, uint64_t off_in, uint64_t off_out,
+static void launch_bconv_col(uint32_t nkb, dim3 grid, hipStream_t st, WsRef ws, const BconvIn& in, uint64_t off_out,
                              uint32_t level, const KsConsts& kc, const DevTables& t, uint32_t log_n) {
     const uint32_t lds = bconv_col_dyn_lds(DOWN ? kc.down_rt : kc.up_rt);
     // four waves take about two tiles each; where that leaves compute units
@@ -655,7 +693,7 @@ static void launch_bconv_col(uint32_t nkb, dim3 grid, hipStream_t st, WsRef ws, 
     const uint32_t threads = (uint64_t)grid.x * grid.y * grid.z <= 512 ? 512 : 256;
 #define PFT_BCONV_COL(K)                                                                                     \
     case K:                                                                                                  \
-        hipLaunchKernelGGL((k_bconv_col_b<K, DOWN, IFUSE>), grid, dim3(threads), lds, st, ws, off_in, off_out, level, \
+        hipLaunchKernelGGL((k_bconv_col_b<K, DOWN, IFUSE>), grid, dim3(threads), lds, st, ws, in, off_out, level, \
                            kc, t.mods, t.tw_fwd, t.tw_inv, log_n);                                           \
         break;
     switch (nkb) {
@@ -675,19 +713,20 @@ void launch_modup_col_b(uint32_t n, WsRef ws, uint64_t off_d, uint64_t off_ext, 
     const uint32_t beta = (level + kc.alpha - 1) / kc.alpha;
     const uint32_t nkb = (std::min(kc.alpha, level) + 1) / 2;
     const dim3 grid((1u << log_n) / (16 * BCONV_COLS), beta, n);
+    const BconvIn in{{off_d, off_d}, {0, 0}, 1};
     if (ifuse)
-        launch_bconv_col<false, true>(nkb, grid, st, ws, off_d, off_ext, level, kc, t, log_n);
+        launch_bconv_col<false, true>(nkb, grid, st, ws, in, off_ext, level, kc, t, log_n);
     else
-        launch_bconv_col<false, false>(nkb, grid, st, ws, off_d, off_ext, level, kc, t, log_n);
+        launch_bconv_col<false, false>(nkb, grid, st, ws, in, off_ext, level, kc, t, log_n);
 }
 
-void launch_moddown_col_b(uint32_t n, WsRef ws, uint64_t off_acc, uint64_t off_conv, uint32_t level,
+void launch_moddown_col_b(uint32_t n, WsRef ws, const BconvIn& in, uint64_t off_conv, uint32_t level,
                           const KsConsts& kc, const DevTables& t, uint32_t log_n, bool ifuse, hipStream_t st) {
     const dim3 grid((1u << log_n) / (16 * BCONV_COLS), 2, n);
     if (ifuse)
-        launch_bconv_col<true, true>((kc.K + 1) / 2, grid, st, ws, off_acc, off_conv, level, kc, t, log_n);
+        launch_bconv_col<true, true>((kc.K + 1) / 2, grid, st, ws, in, off_conv, level, kc, t, log_n);
     else
-        launch_bconv_col<true, false>((kc.K + 1) / 2, grid, st, ws, off_acc, off_conv, level, kc, t, log_n);
+        launch_bconv_col<true, false>((kc.K + 1) / 2, grid, st, ws, in, off_conv, level, kc, t, log_n);
 }
 
 void launch_rescale_col_b(uint32_t n, WsRef ws, uint64_t off_last, uint64_t off_tmp, uint32_t level, uint32_t mode,

@@ -172,8 +172,14 @@ void launch_modup_col_b(uint32_t n, WsRef ws, uint64_t off_d, uint64_t off_ext, 
                         const DevTables& t, uint32_t log_n, bool ifuse, hipStream_t st);
 // ModDown's conversion (conv_b = base conversion of the K special rows of
 // acc_b to the q-limbs 0..level-1) fused the same way: conv holds the output
-// of the first transform pass.
-void launch_moddown_col_b(uint32_t n, WsRef ws, uint64_t off_acc, uint64_t off_conv, uint32_t level,
+// of the first transform pass.  The special rows of acc_b are the sums of
+// `parts` (at most 4; ifuse) rows, `in`: part s of row r of polynomial b at
+// in.off[b] + s in.step[b] + r N.
+struct BconvIn {
+    uint64_t off[2], step[2];
+    uint32_t parts;
+};
+void launch_moddown_col_b(uint32_t n, WsRef ws, const BconvIn& in, uint64_t off_conv, uint32_t level,
                           const KsConsts& kc, const DevTables& t, uint32_t log_n, bool ifuse, hipStream_t st);
 // RESCALE's expansion of last_z [2][N] into tmp_z [2][level-1][N] fused the
 // same way, on both sides: last is limb level-1 after the first (row) pass of
@@ -212,13 +218,32 @@ struct KsRows {
     uint32_t n_items, level, rows, alpha, beta, L, krows, tiles, src_level;
     uint32_t mode, has_add;
     uint64_t kappa, kappa_inv;    // kappa^-1 mod 2N
-    uint32_t n_rows;              // rows of this launch
-    uint16_t row[PFT_ROW_LIST];   // their indices (0..level+K-1)
+    uint32_t parts, group;        // see KsSplit
+    uint32_t n_rows;              // entries of this launch
+    uint32_t row[PFT_ROW_LIST];   // their rows (0..level+K-1), parts and early rows (KS_ROW_PART, KS_ROW_EARLY)
     const uint64_t* src[PFT_MAX_ITEMS];
     const uint64_t* src2[PFT_MAX_ITEMS];
     uint64_t* out[PFT_MAX_ITEMS];
 };
 bool ks_rows_supported(uint32_t log_n);
+// A row list's entry: the row, in the special rows' launch the group of digits
+// it takes, and 1 + its index among the early rows, or 0.
+enum : uint32_t { KS_ROW_MASK = 0x1ff, KS_ROW_PART = 9, KS_ROW_EARLY = 12 };
+// How a key switch whose launches cannot fill the chip spreads its integer
+// rows (ks_split).  parts > 1: each special row is taken by `parts`
+// workgroups a tile, each with `group` digits, whose sums go through the
+// inverse row pass by themselves; ModDown's conversion adds the parts.  early:
+// the digits of the integer ciphertext rows (but their own) are taken in the
+// special rows' launch, in the same parts, and the last launch adds their
+// sums.  The parts lie in rows that the fused path has no other use for: part
+// s of row r's polynomial 0 over row r of the group's first digit (ext, which
+// only that workgroup reads), of its polynomial 1 at off_acc + (s K + r -
+// level) N for a special row, for early row e at off_acc + (parts (K + e) + s) N.
+struct KsSplit {
+    uint32_t parts, group;
+    bool early;
+};
+KsSplit ks_split(uint32_t n, uint32_t level, const KsConsts& kc, const uint32_t* fp_rows, uint32_t log_n);
 // Launches of at most this many words (rows times N, all items) take the
 // 4-residue forms.  Up to there the 8-residue forms' waves (2^22 / 512 = 8
 // per SIMD, in two rounds at their registers) do not hide the passes'
@@ -257,7 +282,7 @@ void launch_ks_inv(uint32_t n, KsInv a, const DevTables& t, uint32_t log_n, hipS
 enum : uint32_t { KS_ROWS_INT = 1, KS_ROWS_FP = 2, KS_ROWS_ALL = 3 };
 void launch_ks_rows(uint32_t n, KsRows a, bool special, const KsConsts& kc, const DevTables& t,
                     const uint32_t* fp_rows, uint32_t log_n, bool pair_digits, hipStream_t st,
-                    ProfHook* prof = nullptr, uint32_t rows = KS_ROWS_ALL);
+                    ProfHook* prof = nullptr, uint32_t rows = KS_ROWS_ALL, KsSplit split = {1, 8, false});
 // acc [2][level+K][N] = sum_j x_j * key_j  (key: [dnum][2][L+K][N], Montgomery form)
 void launch_key_inner_b(uint32_t n, WsRef ws, uint64_t off_d, uint64_t off_ext, uint64_t off_acc, const uint64_t* key,
                         uint32_t level, const KsConsts& kc, const DevTables& t, uint32_t log_n, hipStream_t st);

@@ -86,3 +86,18 @@ def test_large_launches_equal_small_ones(name, n_q, items):
                      (w.ctx.rescale_batch(prod), lambda i: w.ctx.rescale(prod[i]))):
         for i in range(items):
             assert bool((big[i].data == one(i).data).all())
+
+
+@pytest.mark.parametrize("n_q,n_p,dnum,q_bits,p_bits", [(5, 1, 5, 40, 60), (8, 1, 8, 40, 60), (6, 2, 3, 55, 60),
+                                                        (7, 3, 3, 45, 50)])
+def test_small_launches_in_parts(n_q, n_p, dnum, q_bits, p_bits):
+    """Special rows in two to four parts of one or two digits (integer and
+    fp64), none to all of the ciphertext rows on the integer path, at every
+    level."""
+    w = World(dict(log_n=12, n_q=n_q, q0_bits=60, q_bits=q_bits, n_p=n_p, p_bits=p_bits, dnum=dnum, scale=2 ** 40))
+    for level in range(w.op.L, 0, -1):
+        (ga, oa), (gb, ob) = w.enc_pair(10 + level, level), w.enc_pair(30 + level, level)
+        w.assert_same(w.ctx.mul_relin(ga, gb), C.hmul_relin(w.op, oa, ob, w.rlk))
+        rot = C.rotate(w.op, oa, 1, w.rot[1])
+        w.assert_same(w.ctx.rotate(ga, 1), rot)
+        w.assert_same(w.ctx.total_sum(ga, 2), C.hadd(w.op, oa, rot))
