@@ -57,8 +57,9 @@ def kernel_name(kid, variant):
     if kid == 8 and variant == 1:  # RESCALE's expansion fused with the first transform pass
         return "k_rescale_col_b"
     if kid in (2, 4) and variant >= 64:  # base conversion fused with the first (and last inverse) pass
-        return "k_bconv_col_b<%du, %s, %s>" % ((variant - 64) & 15, "true" if kid == 4 else "false",
-                                               "true" if (variant - 64) & 16 else "false")
+        b = lambda x: "true" if x else "false"  # noqa: E731
+        v = variant - 64
+        return "k_bconv_col_b<%du, %s, %s, %s>" % (v & 15, b(kid == 4), b(v & 16), b(v & 32))
     if kid in (2, 3, 4) and variant:  # templated on the k-block count / the number of digits
         return "%s<%du>" % (KERNEL_NAMES[kid], variant)
     return KERNEL_NAMES.get(kid, FAMILIES[kid])

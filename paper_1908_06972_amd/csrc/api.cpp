@@ -1838,7 +1838,7 @@ static void key_switch_b(pft_ctx* c, uint32_t n, WsRef ws, const KsLayout& K, co
                       launch_modup_col_b(n, ws, K.off_dcoef, K.off_ext, level, c->kc, c->tabs, lg, ifuse_up,
                                          c->stream);
                   },
-                  64u + nkb + (ifuse_up ? 16u : 0u));
+                  bconv_col_variant(lg, nkb, beta, n, 1, ifuse_up));
         } else {
             timed(c, PK_MODUP, 8.0 * N * (rd + wr) * n, N * macs * n, [&] {
                 launch_modup_b(n, ws, K.off_dcoef, K.off_ext, level, c->kc, c->tabs, lg, c->bconv_mfma, c->stream);
@@ -1916,7 +1916,7 @@ static void key_switch_b(pft_ctx* c, uint32_t n, WsRef ws, const KsLayout& K, co
                   launch_moddown_col_b(n, ws, sum, K.off_conv, level, c->kc, c->tabs, lg, ifuse_down,
                                        c->stream);
               },
-              64u + down_kb + (ifuse_down ? 16u : 0u));
+              bconv_col_variant(lg, down_kb, 2, n, split.parts, ifuse_down));
     } else {
         timed(c, PK_MODDOWN_CONV, 8.0 * N * (2.0 * P->K + 2.0 * level) * n, 2.0 * N * P->K * level * n, [&] {
             launch_moddown_conv_b(n, ws, K.off_acc, K.off_conv, level, c->kc, c->tabs, lg, c->bconv_mfma, c->stream);

@@ -392,8 +392,13 @@ void launch_pass(const PolyBatch& b, const DevTables& t, uint32_t log_n, uint32_
 // IFUSE: the input rows come from an inverse transform whose final pass (a
 // radix-16 column pass, stages 3-0 with N^-1 folded in) has not run; it is
 // applied to the 16 values of each column first.
+//
+// SMALL (with IFUSE): the form of launches that leave compute units with one
+// or two workgroups, where the length of a wave's chain counts: four threads
+// share a column's inverse pass (the sums of ModDown's parts too), and two
+// waves a tile of targets.
 constexpr uint32_t BCONV_COLS = 32;
-template <uint32_t NKB, bool DOWN, bool IFUSE>
+template <uint32_t NKB, bool DOWN, bool IFUSE, bool SMALL>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k_bconv_col_b(
     WsRef ws, BconvIn src, uint64_t off_out, uint32_t level, KsConsts kc, const DevMod* __restrict__ mods,
     const TwPair* __restrict__ tw, const TwPair* __restrict__ tw_inv, uint32_t log_n) {
@@ -424,54 +429,87 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
         const uint32_t t = row_of(tgt[i >> 4]);
         if (t != PFT_NO_ROW) s_tw[i] = tw[((size_t)mod_of(t) << log_n) + (i & 15u)];
     }
-    if constexpr (DOWN && IFUSE) {
-        // the sums of the parts, four of a row's 16 residues a thread (every
-        // load of all parts in flight at once): at most four terms below 4q
-        // (fp64: within 4.5q) each, reduced for the next butterflies
-        if (src.parts > 1) {
-            for (uint32_t w = tid >> 5; w < 4 * na; w += blockDim.x >> 5) {
-                const uint32_t ii = w >> 2, e0 = (w & 3u) * 4u;
-                const DevMod md = mods[kc.L + ii];
-                const uint64_t* __restrict__ p = in + (size_t)e0 * S + (((size_t)ii << log_n) + col);
+    // the input rows' digits
+    auto word = [&](const uint64_t* __restrict__ p, uint32_t ii, uint32_t e) {
+        const uint32_t off = (((DOWN ? ii : i0 + ii) << log_n) + col) * 8u;
+        return *reinterpret_cast<const uint64_t*>(reinterpret_cast<const char*>(p + (size_t)e * S) + off);
+    };
+    auto slot = [&](uint32_t ii, uint32_t e) -> uint64_t& { return s_dig[(ii * 16u + e) * BCONV_COLS + u]; };
+    if constexpr (SMALL) {
+        // four residues of a column a thread: stages 3 and 2 over residues
+        // 4 c .. 4 c + 3, through LDS, stages 1 and 0 over c, c + 4, ..
+        for (uint32_t w = tid >> 5; w < 4 * na; w += blockDim.x >> 5) {
+            const uint32_t ii = w >> 2, c = w & 3u;
+            const uint32_t mi = DOWN ? kc.L + ii : i0 + ii;
+            const DevMod md = mods[mi];
+            const TwPair* __restrict__ twt = tw_inv + ((size_t)mi << log_n);
+            uint64_t x[4];
+            if (DOWN && src.parts > 1) {
+                // at most four terms below 4q (fp64: within 4.5q) each, every
+                // load in flight at once
                 uint64_t y[4][4];
 #pragma unroll
                 for (uint32_t s = 0; s < 4; ++s)
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) y[s][e] = p[min(s, src.parts - 1) * src.step[j] + (size_t)e * S];
+                    for (uint32_t e = 0; e < 4; ++e)
+                        y[s][e] = word(in + min(s, src.parts - 1) * src.step[j], ii, 4 * c + e);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
+                for (uint32_t e = 0; e < 4; ++e) {
                     uint64_t v = y[0][e];
                     if (md.fp) {
 #pragma unroll
                         for (uint32_t s = 1; s < 4; ++s) v = s < src.parts ? as_u(as_f(v) + as_f(y[s][e])) : v;
-                        v = as_u(freduce(as_f(v), md.qd, md.qinv));
+                        x[e] = as_u(freduce(as_f(v), md.qd, md.qinv));
                     } else {
 #pragma unroll
                         for (uint32_t s = 1; s < 4; ++s) v = s < src.parts ? v + y[s][e] : v;
-                        v = reduce_int(v, md);
+                        x[e] = reduce_int(v, md);
                     }
-                    s_dig[(ii * 16u + e0 + e) * BCONV_COLS + u] = v;
                 }
+            } else {
+#pragma unroll
+                for (uint32_t e = 0; e < 4; ++e) x[e] = word(in, ii, 4 * c + e);
             }
-            __syncthreads();
+            if (md.fp)
+                run_phase<4, 1, 2, true, true, true>(x, c, 0u, 0u, twt, md);
+            else
+                run_phase<4, 1, 2, true, false, true>(x, c, 0u, 0u, twt, md);
+#pragma unroll
+            for (uint32_t e = 0; e < 4; ++e) slot(ii, 4 * c + e) = x[e];
+        }
+        __syncthreads();
+        for (uint32_t w = tid >> 5; w < 8 * NKB; w += blockDim.x >> 5) {
+            const uint32_t ii = w >> 2, c = w & 3u;
+            uint64_t x[4] = {};
+            if (ii < na) {
+                const uint32_t mi = DOWN ? kc.L + ii : i0 + ii;
+                const DevMod md = mods[mi];
+                const TwPair* __restrict__ twt = tw_inv + ((size_t)mi << log_n);
+                const TwPair hv = DOWN ? kc.down_phatinv[ii] : kc.modup_hatinv[lj * kc.alpha + ii];
+#pragma unroll
+                for (uint32_t e = 0; e < 4; ++e) x[e] = slot(ii, 4 * e + c);
+                if (md.fp) {
+                    run_phase<4, 0, 2, true, true, true>(x, c, 0u, 0u, twt, md);
+#pragma unroll
+                    for (uint32_t e = 0; e < 4; ++e) x[e] = fp_to_u64(x[e], md.qd, md.qinv);
+                } else {
+                    run_phase<4, 0, 2, true, false, true>(x, c, 0u, 0u, twt, md);
+                }
+#pragma unroll
+                for (uint32_t e = 0; e < 4; ++e) x[e] = (uint64_t)split_digits(shoup(x[e], hv.w, hv.wp, md.q));
+            }
+#pragma unroll
+            for (uint32_t e = 0; e < 4; ++e) slot(ii, 4 * e + c) = x[e];
         }
     }
-    // the input rows' digits
-    for (uint32_t ii = tid >> 5; ii < 2 * NKB; ii += blockDim.x >> 5) {
+    for (uint32_t ii = tid >> 5; !SMALL && ii < 2 * NKB; ii += blockDim.x >> 5) {
         uint64_t x[16];
         if (ii < na) {
             const uint32_t mi = DOWN ? kc.L + ii : i0 + ii;
             const DevMod md = mods[mi];
             const TwPair hv = DOWN ? kc.down_phatinv[ii] : kc.modup_hatinv[lj * kc.alpha + ii];
-            const uint32_t off = (((DOWN ? ii : i0 + ii) << log_n) + col) * 8u;
-            if (DOWN && IFUSE && src.parts > 1) {
 #pragma unroll
-                for (int e = 0; e < 16; ++e) x[e] = s_dig[(ii * 16u + e) * BCONV_COLS + u];
-            } else {
-#pragma unroll
-                for (int e = 0; e < 16; ++e)
-                    x[e] = *reinterpret_cast<const uint64_t*>(reinterpret_cast<const char*>(in + (size_t)e * S) + off);
-            }
+            for (int e = 0; e < 16; ++e) x[e] = word(in, ii, e);
             if constexpr (IFUSE) {
                 const TwPair* __restrict__ twt = tw_inv + ((size_t)mi << log_n);
                 if (md.fp) {
@@ -489,20 +527,22 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
             for (int e = 0; e < 16; ++e) x[e] = 0;
         }
 #pragma unroll
-        for (int e = 0; e < 16; ++e) s_dig[(ii * 16u + e) * BCONV_COLS + u] = x[e];
+        for (int e = 0; e < 16; ++e) slot(ii, e) = x[e];
     }
     __syncthreads();
     const uint32_t kbs = DOWN ? kc.down_kb : kc.up_kb;
     const uint64_t* __restrict__ aop =
         (DOWN ? kc.down_aop : kc.up_aop + lj * kc.up_rt * kc.up_kb * 64) + lane;
     const uint64_t* dig = s_dig + half * 16u * BCONV_COLS + u;  // input rows 2 kb + half
-    auto tile = [&](uint32_t g, auto fpc) {
+    // targets V0 .. V1 - 1 of this lane's two of tile g
+    auto tile = [&](uint32_t g, auto fpc, auto v0c, auto v1c) {
         constexpr bool FP = decltype(fpc)::value;
+        constexpr int V0 = decltype(v0c)::value, V1 = decltype(v1c)::value;
         const BconvRed* rc = s_red + 4 * g + 2 * half;
         long av[NKB];
 #pragma unroll
         for (uint32_t kb = 0; kb < NKB; ++kb) av[kb] = (long)aop[(g * kbs + kb) * 64];
-        uint64_t x[2][16];
+        uint64_t x[V1 - V0][16];
 #pragma unroll
         for (int t = 0; t < 16; ++t) {
             v16i acc = {};
@@ -510,16 +550,23 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
             for (uint32_t kb = 0; kb < NKB; ++kb)
                 acc = __builtin_amdgcn_mfma_i32_32x32x16_i8(av[kb], (long)dig[(kb * 32u + t) * BCONV_COLS], acc, 0, 0, 0);
             int z[8];
-            tile_digits<0>(acc, z);
-            x[0][t] = fold_digits<FP, true>(z, rc[0]);
-            tile_digits<1>(acc, z);
-            x[1][t] = fold_digits<FP, true>(z, rc[1]);
+            if constexpr (V0 == 0) {
+                tile_digits<0>(acc, z);
+                x[0][t] = fold_digits<FP, true>(z, rc[0]);
+            }
+            if constexpr (V1 == 2) {
+                tile_digits<1>(acc, z);
+                x[1 - V0][t] = fold_digits<FP, true>(z, rc[1]);
+            }
             // keeps the folds here: moved down to the conditional stores they
             // would hold all 16 accumulator tiles
-            asm volatile("" : "+v"(x[0][t]), "+v"(x[1][t]));
+            if constexpr (V1 - V0 == 2)
+                asm volatile("" : "+v"(x[0][t]), "+v"(x[1][t]));
+            else
+                asm volatile("" : "+v"(x[0][t]));
         }
 #pragma unroll
-        for (int v = 0; v < 2; ++v) {
+        for (int v = V0; v < V1; ++v) {
             const uint32_t row = rc[v].row;
             if (row == PFT_NO_ROW) continue;
             DevMod md;
@@ -530,21 +577,33 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
             md.qd = rc[v].md;
             md.qinv = rc[v].minv;
             // the fold's values are reduced (within q/2 + 1, or below q)
-            run_phase<4, 0, 4, false, FP, false, true>(x[v], 0u, 0u, 0u, s_tw + (4 * g + 2 * half + v) * 16, md);
+            run_phase<4, 0, 4, false, FP, false, true>(x[v - V0], 0u, 0u, 0u, s_tw + (4 * g + 2 * half + v) * 16, md);
             const uint32_t off = ((row << log_n) + col) * 8u;
 #pragma unroll
             for (int e = 0; e < 16; ++e)
-                *reinterpret_cast<uint64_t*>(reinterpret_cast<char*>(out + (size_t)e * S) + off) = x[v][e];
+                *reinterpret_cast<uint64_t*>(reinterpret_cast<char*>(out + (size_t)e * S) + off) = x[v - V0][e];
         }
     };
-    for (uint32_t g = wave; g < max_tiles; g += blockDim.x >> 6) {
+    using i0_ = std::integral_constant<int, 0>;
+    using i1_ = std::integral_constant<int, 1>;
+    using i2_ = std::integral_constant<int, 2>;
+    for (uint32_t k = wave; k < (SMALL ? 2 : 1) * max_tiles; k += blockDim.x >> 6) {
+        const uint32_t g = SMALL ? k >> 1 : k;
         // a tile's first row is there and has the kind of the others
         const uint32_t row = __builtin_amdgcn_readfirstlane(s_red[4 * g].row);
         if (row == PFT_NO_ROW) break;
+        auto run = [&](auto fpc) {
+            if constexpr (!SMALL)
+                tile(g, fpc, i0_{}, i2_{});
+            else if (k & 1u)
+                tile(g, fpc, i1_{}, i2_{});
+            else
+                tile(g, fpc, i0_{}, i1_{});
+        };
         if (__builtin_amdgcn_readfirstlane(s_red[4 * g].fp))
-            tile(g, std::true_type{});
+            run(std::true_type{});
         else
-            tile(g, std::false_type{});
+            run(std::false_type{});
     }
 }
 
@@ -684,17 +743,35 @@ bool bconv_col_supported(uint32_t log_n, uint32_t nkb, uint32_t tiles) {
     return log_n >= 9 && nkb <= 6 && 2 * nkb * 16 * BCONV_COLS * 8 + bconv_col_dyn_lds(tiles) <= 65536;
 }
 
+// Up to two workgroups of 32 columns a compute unit, the eight-wave form with
+// four threads a column: one item at N = 2^15, level 16 (256 and 128
+// workgroups) 18.0 -> 16.1 us for ModUp's and 16.0 -> 14.6 for ModDown's.
+// With more of them the threads that only one of the two phases has work for
+// cost more than the shorter chain gives (six items: 4942 us with 1024 as the
+// line, 4962 with 2048 for a predict step).  Parts are summed by that form.
+constexpr uint64_t BCONV_SMALL_BLOCKS = 512;
+static bool bconv_col_small(uint32_t log_n, uint32_t groups, uint32_t n, uint32_t parts) {
+    return parts > 1 || (((uint64_t)n * groups << log_n) / (16 * BCONV_COLS)) <= BCONV_SMALL_BLOCKS;
+}
+uint32_t bconv_col_variant(uint32_t log_n, uint32_t nkb, uint32_t groups, uint32_t n, uint32_t parts, bool ifuse) {
+    return 64u + nkb + (ifuse ? 16u : 0u) + (ifuse && bconv_col_small(log_n, groups, n, parts) ? 32u : 0u);
+}
 template <bool DOWN, bool IFUSE>
 static void launch_bconv_col(uint32_t nkb, dim3 grid, hipStream_t st, WsRef ws, const BconvIn& in, uint64_t off_out,
                              uint32_t level, const KsConsts& kc, const DevTables& t, uint32_t log_n) {
     const uint32_t lds = bconv_col_dyn_lds(DOWN ? kc.down_rt : kc.up_rt);
+    const bool small = bconv_col_small(log_n, grid.y, grid.z, in.parts);
     // four waves take about two tiles each; where that leaves compute units
     // without a second workgroup, eight waves a workgroup take one each
-    const uint32_t threads = (uint64_t)grid.x * grid.y * grid.z <= 512 ? 512 : 256;
+    const uint32_t threads = small ? 512 : 256;
 #define PFT_BCONV_COL(K)                                                                                     \
     case K:                                                                                                  \
-        hipLaunchKernelGGL((k_bconv_col_b<K, DOWN, IFUSE>), grid, dim3(threads), lds, st, ws, in, off_out, level, \
-                           kc, t.mods, t.tw_fwd, t.tw_inv, log_n);                                           \
+        if (IFUSE && small)                                                                                  \
+            hipLaunchKernelGGL((k_bconv_col_b<K, DOWN, IFUSE, IFUSE>), grid, dim3(threads), lds, st, ws, in, \
+                               off_out, level, kc, t.mods, t.tw_fwd, t.tw_inv, log_n);                       \
+        else                                                                                                 \
+            hipLaunchKernelGGL((k_bconv_col_b<K, DOWN, IFUSE, false>), grid, dim3(threads), lds, st, ws, in, \
+                               off_out, level, kc, t.mods, t.tw_fwd, t.tw_inv, log_n);                       \
         break;
     switch (nkb) {
         PFT_BCONV_COL(1)

@@ -168,6 +168,9 @@ void launch_modup_b(uint32_t n, WsRef ws, uint64_t off_d, uint64_t off_ext, uint
 // comes from an inverse transform of such a schedule that stopped before its
 // final (radix-16 column) pass; the kernel applies that pass to its inputs.
 bool bconv_col_supported(uint32_t log_n, uint32_t nkb, uint32_t tiles);  // its LDS fits (tiles: up_rt or down_rt)
+// the variant a launch is timed as: 64 + k-blocks, + 16 ifuse, + 32 the form of
+// few workgroups (groups: digits, or the two polynomials of ModDown)
+uint32_t bconv_col_variant(uint32_t log_n, uint32_t nkb, uint32_t groups, uint32_t n, uint32_t parts, bool ifuse);
 void launch_modup_col_b(uint32_t n, WsRef ws, uint64_t off_d, uint64_t off_ext, uint32_t level, const KsConsts& kc,
                         const DevTables& t, uint32_t log_n, bool ifuse, hipStream_t st);
 // ModDown's conversion (conv_b = base conversion of the K special rows of
