@@ -455,16 +455,31 @@ __global__ __launch_bounds__(TB) void k_rescale_expand_b(WsRef ws, uint64_t off_
     ws_item(ws)[off_tmp + at(b * nl + kq, log_n, k)] = r >= h ? r - h : r + qk - h;
 }
 
+// Block order of the dot products: blocks go to the eight XCDs round-robin;
+// block 8 k + x runs group k mod groups of the (row, coefficient block) pair
+// 8 floor(k / groups) + x, so the groups that share an operand's tile run on
+// one XCD at about the same time.  A row has a multiple of eight blocks.
+__device__ __forceinline__ void dot_block(uint32_t groups, uint32_t log_n, uint32_t& group, uint32_t& row,
+                                          uint32_t& k) {
+    const uint32_t kx = blockIdx.x >> 3, kb = log_n - 8;
+    static_assert(TB == 256, "a block's coefficients");
+    group = kx % groups;
+    const uint32_t pair = (kx / groups) * 8u + (blockIdx.x & 7u);
+    k = (pair & ((1u << kb) - 1u)) * TB + threadIdx.x;
+    row = pair >> kb;
+}
+
 // The inner sums of up to PT_GT giant steps at once: for g < n_g,
 // acc_{z,g}[row] = sum_{j<J} baby_{z,j}[row] pt_{g,j}[row mod level], acc_{z,g}
 // at ws_z + off_acc + g ct_words, pt_{g,j} at pt + (g J + j) level N; each
 // baby residue is read once for all n_g giant steps (or outputs).  One thread
-// per (Z items, row, coefficient); the item groups of one coefficient block
-// are consecutive workgroups, so the plaintext tiles they share are fetched
-// about once per launch, and a plaintext residue is loaded once for Z items:
-// with one item a thread those loads (J n_g words an output set, from L2) and
-// 128-bit sums on every row took the time (6.1 ms for 32 items, 16 terms and
-// 8 outputs at N = 2^15, 16 rows, of whose 6.9 GB the copy rate takes 1.3 ms).
+// per (Z polynomials of the 2 n_items, row mod level, coefficient), the
+// groups of polynomials that share a plaintext tile on one XCD (dot_block):
+// a plaintext residue is loaded once for Z polynomials and comes from HBM
+// once per launch.  With one row's two polynomials far apart and the groups
+// spread over the XCDs the tiles came again and again (32 items, 16 terms, 8
+// outputs at N = 2^15, level 16: 2162 us, now 1807, of which 6.9 GB take 1300
+// at the copy rate and the products 1000; one item 262, now 158).
 // NG (8, 4 or 2) is n_g rounded up: the loads of a term are NG unconditional
 // ones in flight together: 38.0 -> 36.6 ms for the bag-of-words layer of 32
 // documents at N = 2^15 against loads that each waited on a condition.
@@ -479,30 +494,32 @@ __global__ __launch_bounds__(TB) void k_pt_dot_multi_b(WsRef ws, uint32_t n_item
                                                        uint32_t n_g, uint64_t off_acc, uint32_t level,
                                                        const DevMod* __restrict__ mods, uint32_t log_n) {
     using u128 = unsigned __int128;
-    const uint32_t kblocks = (1u << log_n) / TB;
-    const uint32_t groups = (n_items + Z - 1) / Z;
-    const uint32_t z0 = (blockIdx.x % groups) * Z;
-    const uint32_t nz = min(Z, n_items - z0);
-    const uint32_t rest = blockIdx.x / groups;
-    const uint32_t k = (rest % kblocks) * TB + threadIdx.x;
-    const uint32_t row = rest / kblocks, i = row % level;
+    uint32_t v0, i, k;
+    dot_block((2 * n_items + Z - 1) / Z, log_n, v0, i, k);
+    v0 *= Z;
+    const uint32_t nz = min(Z, 2 * n_items - v0);
     const DevMod md = mods[i];
-    uint64_t* __restrict__ w = ws.base + (size_t)z0 * ws.stride + ((size_t)row << log_n);
+    // row i of polynomial v mod 2 of item v / 2
+    auto vec = [&](uint32_t v) {
+        return ws.base + (size_t)(v >> 1) * ws.stride + ((size_t)((v & 1u) * level + i) << log_n);
+    };
     const uint64_t* __restrict__ pr = pt + ((size_t)i << log_n);
     const size_t pstep = ((size_t)J * level) << log_n;  // words between giant steps of pt
     if (md.fp) {
 #pragma clang fp contract(off)
         const double q = md.qd, qinv = md.qinv;
         double a[Z][NG];
+        uint64_t* __restrict__ w[Z];
 #pragma unroll
-        for (uint32_t z = 0; z < Z; ++z)
+        for (uint32_t z = 0; z < Z; ++z) {
+            w[z] = vec(v0 + (z < nz ? z : 0));
 #pragma unroll
             for (uint32_t g = 0; g < NG; ++g) a[z][g] = 0.0;
+        }
         for (uint32_t j = 0; j < J; ++j) {
             double x[Z];
 #pragma unroll
-            for (uint32_t z = 0; z < Z; ++z)
-                x[z] = as_f(fp_from_u64(w[(z < nz ? z : 0) * ws.stride + off_baby + j * ct_words + k]));
+            for (uint32_t z = 0; z < Z; ++z) x[z] = as_f(fp_from_u64(w[z][off_baby + j * ct_words + k]));
             const uint64_t* __restrict__ pj = pr + (((size_t)j * level) << log_n);
             // past n_g the last output's terms again, not stored: a condition
             // would have each load waited for by itself
@@ -527,11 +544,12 @@ __global__ __launch_bounds__(TB) void k_pt_dot_multi_b(WsRef ws, uint32_t n_item
             if (z < nz) {
 #pragma unroll
                 for (uint32_t g = 0; g < NG; ++g)
-                    if (g < n_g) w[z * ws.stride + off_acc + g * ct_words + k] = fp_to_u64(as_u(a[z][g]), q, qinv);
+                    if (g < n_g) w[z][off_acc + g * ct_words + k] = fp_to_u64(as_u(a[z][g]), q, qinv);
             }
         return;
     }
-    for (uint32_t z = 0; z < nz; ++z, w += ws.stride) {
+    for (uint32_t z = 0; z < nz; ++z) {
+        uint64_t* __restrict__ w = vec(v0 + z);
         u128 a[NG];
         uint64_t res[NG];
 #pragma unroll
@@ -586,6 +604,8 @@ __global__ __launch_bounds__(TB) void k_add_const_b(ItemPtrs in, ItemPtrs out, c
 // reduction every 8 diagonal terms (at most 16 products below q^2 each: below
 // q 2^64 for q < 2^60); the reductions' factor 2^-64 is undone once at the
 // end by a Shoup product with 2^64 mod q (to_mont).
+// The item groups that share a diagonal's tiles run on one XCD (dot_block): 219
+// -> 168 us for six items, 16 terms, 4 giant steps at N = 2^15, level 6.
 constexpr uint32_t CT_GT = 4;
 template <uint32_t Z, uint32_t NG>
 __global__ __launch_bounds__(TB) void k_ct_dot_multi_b(ItemPtrs e, uint32_t J, uint32_t n_g, WsRef xs, uint64_t off_x,
@@ -593,9 +613,10 @@ __global__ __launch_bounds__(TB) void k_ct_dot_multi_b(ItemPtrs e, uint32_t J, u
                                                        uint32_t level, const DevMod* __restrict__ mods,
                                                        const TwPair* __restrict__ to_mont, uint32_t log_n) {
     using u128 = unsigned __int128;
-    const uint32_t k = blockIdx.x * TB + threadIdx.x;
-    const uint32_t i = blockIdx.y;
-    const uint32_t z0 = blockIdx.z * Z, nz = min(Z, n_items - z0);
+    uint32_t z0, i, k;
+    dot_block((n_items + Z - 1) / Z, log_n, z0, i, k);
+    z0 *= Z;
+    const uint32_t nz = min(Z, n_items - z0);
     const DevMod md = mods[i];
     const uint64_t q = md.q;
     const size_t o0 = at(i, log_n, k), o1 = at(level + i, log_n, k), o2 = at(2 * level + i, log_n, k);
@@ -814,21 +835,19 @@ uint32_t pt_dot_multi_steps() { return PT_GT; }
 void launch_pt_dot_multi_b(uint32_t n, WsRef ws, uint64_t off_baby, uint64_t ct_words, const uint64_t* pt, uint32_t J,
                            uint32_t n_g, uint64_t off_acc, uint32_t level, const DevTables& t, uint32_t log_n,
                            hipStream_t st) {
-    // items per thread: as many as there are, up to the four whose sums (64
-    // registers for eight outputs) leave room for the products
+    // polynomials per thread: as many as there are, up to the four whose sums
+    // (64 registers for eight outputs) leave room for the products
     auto go = [&](auto zc, auto gc) {
         constexpr uint32_t Z = decltype(zc)::value, NG = decltype(gc)::value;
-        const uint64_t blocks = (uint64_t)((n + Z - 1) / Z) * ((1u << log_n) / TB) * 2 * level;
+        const uint64_t blocks = (uint64_t)((2 * n + Z - 1) / Z) * ((1u << log_n) / TB) * level;
         hipLaunchKernelGGL((k_pt_dot_multi_b<Z, NG>), dim3((uint32_t)blocks), dim3(TB), 0, st, ws, n, off_baby, ct_words,
                            pt, J, n_g, off_acc, level, t.mods, log_n);
     };
     auto by_items = [&](auto gc) {
-        if (n >= 3)
+        if (n >= 2)
             go(std::integral_constant<uint32_t, 4>{}, gc);
-        else if (n == 2)
-            go(std::integral_constant<uint32_t, 2>{}, gc);
         else
-            go(std::integral_constant<uint32_t, 1>{}, gc);
+            go(std::integral_constant<uint32_t, 2>{}, gc);
     };
     if (n_g > 4)
         by_items(std::integral_constant<uint32_t, 8>{});
@@ -851,8 +870,8 @@ void launch_ct_dot_multi_b(uint32_t n, const ItemPtrs& e, uint32_t J, uint32_t n
                            const DevTables& t, uint32_t log_n, hipStream_t st) {
     auto go = [&](auto zc, auto gc) {
         constexpr uint32_t Z = decltype(zc)::value, NG = decltype(gc)::value;
-        hipLaunchKernelGGL((k_ct_dot_multi_b<Z, NG>), grid_nk(log_n, level, (n + Z - 1) / Z), dim3(TB), 0, st, e, J, n_g,
-                           xs, off_x, ct_words, ws, n, off_d, level, t.mods, to_mont, log_n);
+        hipLaunchKernelGGL((k_ct_dot_multi_b<Z, NG>), dim3((n + Z - 1) / Z * ((1u << log_n) / TB) * level), dim3(TB), 0,
+                           st, e, J, n_g, xs, off_x, ct_words, ws, n, off_d, level, t.mods, to_mont, log_n);
     };
     using one = std::integral_constant<uint32_t, 1>;
     using two = std::integral_constant<uint32_t, 2>;
