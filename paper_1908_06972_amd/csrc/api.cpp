@@ -1564,13 +1564,19 @@ extern "C" int pft_pt_from_coeffs(pft_ctx* c, const int64_t* m, uint32_t level, 
 // ---------------------------------------------------------------------------
 static bool scales_match(double a, double b) { return std::fabs(a - b) <= std::ldexp(std::fabs(a), -40); }
 
-extern "C" int pft_add(pft_ctx* c, const pft_ct* a, const pft_ct* b, pft_ct* out) {
+static int check_add(const pft_ctx* c, const pft_ct* a, const pft_ct* b, const pft_ct* out) {
     int r;
-    if (!c) return fail(PFT_EINVAL, "null ctx");
     if ((r = check_ct(c, a)) || (r = check_ct(c, b))) return r;
     if (!out || !out->data) return fail(PFT_EINVAL, "null output");
     if (a->level != b->level) return fail(PFT_ELEVEL, "HADD needs equal levels (%u vs %u)", a->level, b->level);
     if (!scales_match(a->scale, b->scale)) return fail(PFT_ESCALE, "HADD needs equal scales");
+    return PFT_OK;
+}
+
+extern "C" int pft_add(pft_ctx* c, const pft_ct* a, const pft_ct* b, pft_ct* out) {
+    int r;
+    if (!c) return fail(PFT_EINVAL, "null ctx");
+    if ((r = check_add(c, a, b, out))) return r;
     const pft_params* P = c->P;
     const uint32_t l = a->level;
     const SmallBatch O = sb_rows(P, out->data, 2, l, l), A = sb_rows(P, a->data, 2, l, l),
@@ -1713,6 +1719,11 @@ struct KsInput {
     ItemPtrs src, src2;
     bool has_add, overlap;
     uint64_t kappa, kappa_inv;
+    // items with rotations of their own (`many`, on the fused path alone):
+    // their keys and kappas, in place of the call's
+    bool many;
+    const uint64_t* keys[PFT_MAX_ITEMS];
+    KsGalois gals[PFT_MAX_ITEMS];
 };
 
 // Whether any of the n outputs ([2][level][N]) overlaps any operand.
@@ -1730,6 +1741,16 @@ static bool ks_overlap(uint32_t n, const ItemPtrs& out, const ItemPtrs& x, uint6
 static bool fused_rows(const pft_ctx* c) {
     const NttSchedule& s = c->ntt_pinned[0];
     return ks_rows_supported(c->P->log_n) && (s.n_passes == 0 || (s.n_passes == 2 && s.radix[0] == 4));
+}
+
+// Whether a key switch at this level takes the fused path.
+static bool ks_fused(const pft_ctx* c, uint32_t level) {
+    const pft_params* P = c->P;
+    const uint32_t lg = P->log_n;
+    return c->bconv_mfma && c->bconv_fuse && c->inner_fuse && fused_rows(c) &&
+           (level + P->alpha - 1) / P->alpha <= 8 &&
+           bconv_col_supported(lg, (std::min(P->alpha, level) + 1) / 2, c->kc.up_rt) &&
+           bconv_col_supported(lg, (P->K + 1) / 2, c->kc.down_rt);
 }
 
 // Key switching for n items: out_z = ModDown(sum_j ModUp_j(d) key_j) + addends.
@@ -1767,7 +1788,7 @@ static void key_switch_b(pft_ctx* c, uint32_t n, WsRef ws, const KsLayout& K, co
     const uint32_t nkb = (std::min(P->alpha, level) + 1) / 2, down_kb = (P->K + 1) / 2;
     const bool up_ok = c->bconv_mfma && c->bconv_fuse && bconv_col_supported(lg, nkb, c->kc.up_rt);
     const bool down_ok = c->bconv_mfma && c->bconv_fuse && bconv_col_supported(lg, down_kb, c->kc.down_rt);
-    const bool merged = up_ok && down_ok && c->inner_fuse && beta <= 8 && fused_rows(c);
+    const bool merged = ks_fused(c, level);
     const bool fuse = merged || (up_ok && col16(full, rows - A) && col16(last, rows - na_last));
     const bool fuse_down = merged || (down_ok && first_pass_col16(c, 2ull * n * level));
     const bool ifuse_up = merged || (fuse && last_pass_col16(c, (uint64_t)n * level));
@@ -1807,11 +1828,10 @@ static void key_switch_b(pft_ctx* c, uint32_t n, WsRef ws, const KsLayout& K, co
         ki.mode = mode;
         ki.src_row = mode == KS_WS ? 0 : level;
         ki.src_step = ki.mod_step = 1;
-        ki.kappa = in.kappa;
-        ki.kappa_inv = in.kappa_inv;
         for (uint32_t z = 0; z < n; ++z) {
-            ki.src[z] = src.p[z];
-            ki.src2[z] = src2.p[z];
+            ki.item[z].gal = in.many ? in.gals[z] : KsGalois{(uint32_t)in.kappa, (uint32_t)in.kappa_inv};
+            ki.item[z].src = src.p[z];
+            ki.item[z].src2 = src2.p[z];
         }
         launch_ks_inv(n, ki, c->tabs, lg, c->stream, hook(c));
     } else {
@@ -1855,7 +1875,6 @@ static void key_switch_b(pft_ctx* c, uint32_t n, WsRef ws, const KsLayout& K, co
         kr.off_ext = K.off_ext;
         kr.off_acc = K.off_acc;
         kr.off_conv = K.off_conv;
-        kr.key = key.data;
         kr.gadget = c->gadget;
         kr.gadget_fp = c->gadget + P->L;
         kr.pinv = c->kc.down_pinv;
@@ -1863,12 +1882,12 @@ static void key_switch_b(pft_ctx* c, uint32_t n, WsRef ws, const KsLayout& K, co
         kr.level = level;
         kr.mode = mode;
         kr.has_add = has_add ? 1u : 0u;
-        kr.kappa = in.kappa;
-        kr.kappa_inv = in.kappa_inv;
         for (uint32_t z = 0; z < n; ++z) {
-            kr.src[z] = src.p[z];
-            kr.src2[z] = src2.p[z];
-            kr.out[z] = out.p[z];
+            kr.item[z].key = in.many ? in.keys[z] : key.data;
+            kr.item[z].gal = in.many ? in.gals[z] : KsGalois{(uint32_t)in.kappa, (uint32_t)in.kappa_inv};
+            kr.item[z].src = src.p[z];
+            kr.item[z].src2 = src2.p[z];
+            kr.item[z].out = out.p[z];
         }
         // the special rows of both accumulators, ready for ModDown's conversion
         launch_ks_rows(n, kr, true, c->kc, c->tabs, c->fp_rows.data(), lg, c->inner_pairs, c->stream, hook(c),
@@ -2112,7 +2131,7 @@ extern "C" int pft_rescale_batch(pft_ctx* c, uint32_t n, const pft_ct* in, uint3
             ki.mode = KS_RESCALE;
             ki.src_row = ki.mod0 = l - 1;
             ki.src_step = l;
-            for (uint32_t z = 0; z < cnt; ++z) ki.src[z] = I.p[z];
+            for (uint32_t z = 0; z < cnt; ++z) ki.item[z].src = I.p[z];
             launch_ks_inv(cnt, ki, c->tabs, lg, c->stream, hook(c));
             // its rows leave after the first transform pass: layout cost
             timed(c, PK_RESCALE, 0.0, 0,
@@ -2127,8 +2146,8 @@ extern "C" int pft_rescale_batch(pft_ctx* c, uint32_t n, const pft_ct* in, uint3
             kr.pinv = c->rescale_qinv + (size_t)(l - 1) * P->L;
             kr.pinv_fp = c->rescale_qinv + (size_t)P->L * P->L + (size_t)(l - 1) * P->L;
             for (uint32_t z = 0; z < cnt; ++z) {
-                kr.src[z] = I.p[z];
-                kr.out[z] = O.p[z];
+                kr.item[z].src = I.p[z];
+                kr.item[z].out = O.p[z];
             }
             launch_ks_rows(cnt, kr, false, c->kc, c->tabs, c->fp_rows.data(), lg, true, c->stream, hook(c));
         } else {
@@ -2232,18 +2251,26 @@ extern "C" int pft_rotate(pft_ctx* c, const pft_ct* in, int32_t step, pft_ct* ou
     return pft_rotate_batch(c, 1, in, step, out);
 }
 
-static int rotate_core(pft_ctx* c, uint32_t n, const pft_ct* in, int32_t step, pft_ct* out, const pft_ct* add);
+static int rotate_core(pft_ctx* c, uint32_t n, const pft_ct* in, int32_t step, pft_ct* out, const pft_ct* add,
+                       const int32_t* steps = nullptr);
 
 extern "C" int pft_rotate_batch(pft_ctx* c, uint32_t n, const pft_ct* in, int32_t step, pft_ct* out) {
     return rotate_core(c, n, in, step, out, nullptr);
 }
 
 // add: null, or the ciphertexts added to the rotations (of the inputs'
-// levels; add[i] may be out[i]; the step is then no multiple of N/2).
-static int rotate_core(pft_ctx* c, uint32_t n, const pft_ct* in, int32_t step, pft_ct* out, const pft_ct* add) {
+// levels; add[i] may be out[i]; the step is then no multiple of N/2).  steps:
+// null, or a step of each item's own (no multiple of N/2 either; the callers
+// check that every level takes the fused path and that the key cache is not
+// limited, so that all the keys stay).
+static int rotate_core(pft_ctx* c, uint32_t n, const pft_ct* in, int32_t step, pft_ct* out, const pft_ct* add,
+                       const int32_t* steps) {
     if (!c || !in || !out) return fail(PFT_EINVAL, "null argument");
-    const bool identity = norm_step(step, c->P->n) == 0;
-    if (!identity && !has_rot(c, step)) return fail(PFT_ENOKEY, "no rotation key for step %d", step);
+    const bool identity = !steps && norm_step(step, c->P->n) == 0;
+    for (uint32_t i = 0; i < (steps ? n : 1u); ++i) {
+        const int32_t s = steps ? steps[i] : step;
+        if (!identity && !has_rot(c, s)) return fail(PFT_ENOKEY, "no rotation key for step %d", s);
+    }
     int r;
     for (uint32_t i = 0; i < n; ++i) {
         if ((r = check_ct(c, &in[i]))) return r;
@@ -2268,7 +2295,7 @@ static int rotate_core(pft_ctx* c, uint32_t n, const pft_ct* in, int32_t step, p
             return PFT_OK;
         });
     }
-    const SwitchKeyDev* key = use_rot(c, step, &r);
+    const SwitchKeyDev* key = use_rot(c, steps ? steps[0] : step, &r);
     if (!key) return r;
     const pft_params* P = c->P;
     const uint64_t kappa = galois_element(step, P->n), kappa_inv = galois_inverse(kappa, P->n);
@@ -2294,6 +2321,14 @@ static int rotate_core(pft_ctx* c, uint32_t n, const pft_ct* in, int32_t step, p
         }
         ki.kappa = kappa;
         ki.kappa_inv = kappa_inv;
+        for (uint32_t z = 0; steps && z < cnt; ++z) {
+            const SwitchKeyDev* kz = use_rot(c, steps[g[z]], &rr);
+            if (!kz) return rr;
+            const uint64_t kap = galois_element(steps[g[z]], P->n);
+            ki.many = true;
+            ki.keys[z] = kz->data;
+            ki.gals[z] = KsGalois{(uint32_t)kap, (uint32_t)galois_inverse(kap, P->n)};
+        }
         key_switch_b(c, cnt, ws, K, *key, ki, O);
         for (uint32_t z = 0; z < cnt; ++z) {
             out[g[z]].level = l;
@@ -3392,8 +3427,29 @@ struct ExecGroup {
     uint32_t kind, level, mode;
     int32_t step;
     std::vector<uint32_t> ops;
+    bool many;  // rotations by a step of each op's own
 };
 }  // namespace
+
+// The sums of one group of an op list (equal levels).
+static int add_batch(pft_ctx* c, uint32_t n, const pft_ct* a, const pft_ct* b, pft_ct* out) {
+    int r;
+    for (uint32_t i = 0; i < n; ++i)
+        if ((r = check_add(c, &a[i], &b[i], &out[i]))) return r;
+    for (uint32_t i0 = 0; i0 < n; i0 += PFT_MAX_ITEMS) {
+        const uint32_t cnt = std::min<uint32_t>(PFT_MAX_ITEMS, n - i0);
+        ItemPtrs A{}, B{}, O{};
+        for (uint32_t z = 0; z < cnt; ++z) {
+            A.p[z] = a[i0 + z].data;
+            B.p[z] = b[i0 + z].data;
+            O.p[z] = out[i0 + z].data;
+            out[i0 + z].level = a[i0 + z].level;
+            out[i0 + z].scale = a[i0 + z].scale;
+        }
+        launch_add_b(cnt, A, B, O, a[0].level, c->tabs, c->P->log_n, c->stream);
+    }
+    return PFT_OK;
+}
 
 static int exec_group(pft_ctx* c, pft_ct* cts, const pft_op* ops, const ExecGroup& g) {
     const uint32_t n = (uint32_t)g.ops.size();
@@ -3415,12 +3471,15 @@ static int exec_group(pft_ctx* c, pft_ct* cts, const pft_op* ops, const ExecGrou
             ntt_jobs(c, jobs, g.level, ~0u, g.kind == PFT_OP_INTT);
             return PFT_OK;
         }
-        case PFT_OP_ADD:
-            for (uint32_t i = 0; i < n && !r; ++i) r = pft_add(c, &a[i], &b[i], &o[i]);
-            break;
+        case PFT_OP_ADD: r = add_batch(c, n, a.data(), b.data(), o.data()); break;
         case PFT_OP_MUL_RELIN: r = pft_mul_relin_batch(c, n, a.data(), b.data(), o.data()); break;
         case PFT_OP_RESCALE: r = pft_rescale_batch(c, n, a.data(), g.mode, o.data()); break;
-        case PFT_OP_ROTATE: r = pft_rotate_batch(c, n, a.data(), g.step, o.data()); break;
+        case PFT_OP_ROTATE: {
+            std::vector<int32_t> steps(n);
+            for (uint32_t i = 0; i < n; ++i) steps[i] = ops[g.ops[i]].step;
+            r = rotate_core(c, n, a.data(), g.step, o.data(), nullptr, g.many ? steps.data() : nullptr);
+            break;
+        }
         default: return fail(PFT_EINVAL, "unknown op kind %u", g.kind);
     }
     if (r) return r;
@@ -3489,7 +3548,7 @@ static int plan_ops(const pft_op* ops, uint32_t n_ops, const uint32_t* levels, u
             return g.kind == op.kind && g.level == in_level[j] && g.mode == mode && g.step == step;
         });
         if (it == gs.end()) {
-            gs.push_back(ExecGroup{op.kind, in_level[j], mode, step, {}});
+            gs.push_back(ExecGroup{op.kind, in_level[j], mode, step, {}, false});
             it = gs.end() - 1;
         }
         it->ops.push_back(j);
@@ -3521,6 +3580,29 @@ extern "C" int pft_exec_batch(pft_ctx* c, pft_ct* cts, uint32_t n_cts, const pft
     const int nw = plan_ops(ops, n_ops, levels.data(), n_cts, plan);
     if (nw < 0) return nw;
     const uint32_t n_waves = (uint32_t)nw;
+    // Rotations of one wave and level run together whatever their steps (each
+    // item with its own key): five launches for the level instead of five a
+    // step, which each filled a small part of the chip and cost more to issue
+    // than to run.  64 pairs at N = 2^14 with 16 steps: 2500 -> 1445 us (with
+    // one launch for a level's sums).  Not where the keys share a limited cache,
+    // nor off the fused path.
+    for (auto& gs : plan) {
+        std::vector<ExecGroup> merged;
+        for (auto& g : gs) {
+            const bool can = g.kind == PFT_OP_ROTATE && norm_step(g.step, c->P->n) != 0 && !c->rot_cache_max &&
+                             ks_fused(c, g.level);
+            auto it = !can ? merged.end() : std::find_if(merged.begin(), merged.end(), [&](const ExecGroup& m) {
+                return m.many && m.level == g.level;
+            });
+            if (it == merged.end()) {
+                merged.push_back(g);
+                merged.back().many = can;
+            } else {
+                it->ops.insert(it->ops.end(), g.ops.begin(), g.ops.end());
+            }
+        }
+        gs = std::move(merged);
+    }
     size_t max_groups = 0;
     for (auto& gs : plan) max_groups = std::max(max_groups, gs.size());
     int r;

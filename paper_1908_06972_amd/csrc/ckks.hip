@@ -580,6 +580,13 @@ __global__ __launch_bounds__(TB) void k_pt_dot_multi_b(WsRef ws, uint32_t n_item
     }
 }
 
+__global__ __launch_bounds__(TB) void k_add_b(ItemPtrs a, ItemPtrs b, ItemPtrs out, uint32_t level,
+                                              const DevMod* __restrict__ mods, uint32_t log_n) {
+    const uint32_t row = blockIdx.y, z = blockIdx.z;
+    const size_t o = at(row, log_n, blockIdx.x * TB + threadIdx.x);
+    out.p[z][o] = add_mod(a.p[z][o], b.p[z][o], mods[row % level].q);
+}
+
 // out_z = in_z + c_z at X^0: in the evaluation domain the constant c_z[i]
 // (mod q_i) is added to every entry of limb i of c0; c1 is copied.
 __global__ __launch_bounds__(TB) void k_add_const_b(ItemPtrs in, ItemPtrs out, const TwPair* __restrict__ consts,
@@ -765,6 +772,11 @@ void launch_mul_const(const SmallBatch& out, const SmallBatch& a, const TwPair* 
 void launch_tensor_b(uint32_t n, const ItemPtrs& a, const ItemPtrs& b, WsRef ws, uint64_t off_d, uint32_t level,
                      const DevTables& t, uint32_t log_n, hipStream_t st) {
     hipLaunchKernelGGL(k_tensor_b, grid_nk(log_n, level, n), dim3(TB), 0, st, a, b, ws, off_d, level, t.mods, log_n);
+}
+
+void launch_add_b(uint32_t n, const ItemPtrs& a, const ItemPtrs& b, const ItemPtrs& out, uint32_t level,
+                  const DevTables& t, uint32_t log_n, hipStream_t st) {
+    hipLaunchKernelGGL(k_add_b, grid_nk(log_n, 2 * level, n), dim3(TB), 0, st, a, b, out, level, t.mods, log_n);
 }
 
 void launch_copy_rows_b(uint32_t n, const ItemPtrs& src, uint64_t src_off, const ItemPtrs& dst, uint64_t dst_off,

@@ -61,7 +61,7 @@ constexpr int tw_pre_ks(int eb, bool fp, int g) { return eb == 2 ? 3 : fp && g =
 // instruction streams); the two converted rows of the output are such a pair
 // too.
 template <int LOG_M, int EB, int TB, bool FP, int G, bool SPECIAL>
-__device__ __forceinline__ void ks_row(const KsRows& a, uint64_t* lds, uint32_t z, uint32_t tile, uint32_t entry,
+__device__ __forceinline__ void ks_row(const KsRows& a, const KsItem& it, uint64_t* lds, uint32_t z, uint32_t tile, uint32_t entry,
                                        uint32_t t, uint32_t mi, const DevMod& md, const TwPair* __restrict__ tw,
                                        const TwPair* __restrict__ tw_inv, uint32_t log_n) {
     constexpr int M = 1 << LOG_M;
@@ -89,6 +89,7 @@ __device__ __forceinline__ void ks_row(const KsRows& a, uint64_t* lds, uint32_t 
     const uint32_t c = C == 1 ? 0u : tid / T;
     const uint32_t l = C == 1 ? tid : tid % T;
     uint64_t* __restrict__ item = a.base + (size_t)z * a.stride;
+    const uint64_t* __restrict__ key = it.key;
     // Rows are addressed as a uniform base and a 32-bit lane offset in bytes.
     // This thread's E consecutive words of a row start at w0, its words in the
     // row pass's input arrangement at r0.
@@ -131,7 +132,7 @@ __device__ __forceinline__ void ks_row(const KsRows& a, uint64_t* lds, uint32_t 
     // acc_b += x k, k the key tile key_{j,b}[t] of this thread's words
     auto mac = [&](const uint64_t (&x)[E], uint32_t j, int b, uint64_t (&acc)[E]) {
         uint64_t k[E];
-        load_vec(a.key + ((size_t)((2 * j + b) * a.krows + mi) << log_n), k);
+        load_vec(key + ((size_t)((2 * j + b) * a.krows + mi) << log_n), k);
 #pragma unroll
         for (int e = 0; e < E; ++e) mac1(x[e], k[e], acc[e]);
     };
@@ -202,8 +203,8 @@ __device__ __forceinline__ void ks_row(const KsRows& a, uint64_t* lds, uint32_t 
     const size_t row0 = (size_t)t << log_n, row1 = (size_t)(a.src_level + t) << log_n;
     if (!SPECIAL && a.mode == KS_RESCALE) {
         // the input's rows in the accumulators' place
-        load_vec(a.src[z] + row0, acc0);
-        load_vec(a.src[z] + row1, acc1);
+        load_vec(it.src + row0, acc0);
+        load_vec(it.src + row1, acc1);
         if constexpr (FP) {
 #pragma unroll
             for (int e = 0; e < E; ++e) {
@@ -225,9 +226,9 @@ __device__ __forceinline__ void ks_row(const KsRows& a, uint64_t* lds, uint32_t 
         };
         if (a.mode == KS_PRODUCT) {
             // d2 = a1 b1 is switched; d0 = a0 b0 and d1 = a0 b1 + a1 b0 are added
-            const uint64_t* __restrict__ A = a.src[z];
-            const uint64_t* __restrict__ B = a.src2[z];
-            const uint64_t* __restrict__ k0 = a.key + ((size_t)(2 * jo * a.krows + mi) << log_n);
+            const uint64_t* __restrict__ A = it.src;
+            const uint64_t* __restrict__ B = it.src2;
+            const uint64_t* __restrict__ k0 = key + ((size_t)(2 * jo * a.krows + mi) << log_n);
             const uint64_t* __restrict__ k1 = k0 + ((size_t)a.krows << log_n);
             // two words of every operand at a time; the scheduling barrier
             // after each half of them bounds the loads in flight (registers)
@@ -267,12 +268,12 @@ __device__ __forceinline__ void ks_row(const KsRows& a, uint64_t* lds, uint32_t 
             if (a.mode == KS_ROTATE) {
                 // d = X^kappa image of c1's row t, its tile staged in LDS; the
                 // image of c0's row is added
-                galois_tile_to_lds<LOG_M, EB, TB>(a.src[z] + row1, tile, log_n, a.kappa, a.kappa_inv, lds, FP);
+                galois_tile_to_lds<LOG_M, EB, TB>(it.src + row1, tile, log_n, it.gal.kappa, it.gal.kappa_inv, lds, FP);
 #pragma unroll
                 for (int e = 0; e < E; ++e) x[e] = lds[lds_at<LOG_M, EB>(c, l * (uint32_t)E + (uint32_t)e)];
                 __syncthreads();
                 accumulate(x, jo);
-                galois_tile_to_lds<LOG_M, EB, TB>(a.src[z] + row0, tile, log_n, a.kappa, a.kappa_inv, lds, FP);
+                galois_tile_to_lds<LOG_M, EB, TB>(it.src + row0, tile, log_n, it.gal.kappa, it.gal.kappa_inv, lds, FP);
 #pragma unroll
                 for (int e = 0; e < E; ++e)
                     add_p(lds[lds_at<LOG_M, EB>(c, l * (uint32_t)E + (uint32_t)e)], acc0[e]);
@@ -286,7 +287,7 @@ __device__ __forceinline__ void ks_row(const KsRows& a, uint64_t* lds, uint32_t 
                 accumulate(x, jo);
             }
             if (a.has_add) {
-                const uint64_t* A = a.src2[z];  // may be the output: each word is read before it is written
+                const uint64_t* A = it.src2;  // may be the output: each word is read before it is written
                 uint64_t s[E];
                 load_vec(A + row0, s);
 #pragma unroll
@@ -401,7 +402,7 @@ __device__ __forceinline__ void ks_row(const KsRows& a, uint64_t* lds, uint32_t 
         // x: the transformed converted row; the result to row t of polynomial b
         auto finish = [&](const uint64_t (&x)[E], const uint64_t (&acc)[E], uint32_t b) {
             ulonglong2* __restrict__ o = reinterpret_cast<ulonglong2*>(
-                const_cast<uint64_t*>(words(a.out[z] + ((size_t)(b * a.level + t) << log_n), w0)));
+                const_cast<uint64_t*>(words(it.out + ((size_t)(b * a.level + t) << log_n), w0)));
             uint64_t r[E];
 #pragma unroll
             for (int e = 0; e < E; ++e) {
@@ -467,13 +468,14 @@ void k_ks_rows(KsRows a, const DevMod* __restrict__ mods, const TwPair* __restri
     __shared__ uint64_t lds[G * lds_words<LOG_M, EB, TB>()];
     uint32_t z, tile, r;
     if (!ks_block(a.n_items, a.tiles, a.n_rows, z, tile, r)) return;  // whole workgroup, before any barrier
+    const KsItem it = a.item[z];
     const uint32_t entry = a.row[r], t = entry & KS_ROW_MASK;
     const uint32_t mi = t < a.level ? t : a.L + (t - a.level);
     const DevMod md = mods[mi];
     if (KIND == KS_ROWS_FP || (KIND == KS_ROWS_ALL && md.fp))
-        ks_row<LOG_M, EB, TB, true, G, SPECIAL>(a, lds, z, tile, entry, t, mi, md, tw, tw_inv, log_n);
+        ks_row<LOG_M, EB, TB, true, G, SPECIAL>(a, it, lds, z, tile, entry, t, mi, md, tw, tw_inv, log_n);
     else
-        ks_row<LOG_M, EB, TB, false, G, SPECIAL>(a, lds, z, tile, entry, t, mi, md, tw, tw_inv, log_n);
+        ks_row<LOG_M, EB, TB, false, G, SPECIAL>(a, it, lds, z, tile, entry, t, mi, md, tw, tw_inv, log_n);
 }
 
 // The row pass (the first) of an inverse transform of rows that are read, or
@@ -490,6 +492,7 @@ void k_ks_inv(KsInv a, const DevMod* __restrict__ mods, const TwPair* __restrict
     __shared__ uint64_t lds[lds_words<LOG_M, EB, TB>()];
     uint32_t z, tile, r;
     if (!ks_block(a.n_items, a.tiles, a.n_rows, z, tile, r)) return;
+    const KsInvItem it = a.item[z];
     const uint32_t mi = a.mod0 + r * a.mod_step;
     const DevMod md = mods[mi];
     const TwPair* __restrict__ twi = tw_inv + ((size_t)mi << log_n);
@@ -506,11 +509,11 @@ void k_ks_inv(KsInv a, const DevMod* __restrict__ mods, const TwPair* __restrict
     };
     uint64_t x[E];
     if (a.mode == KS_ROTATE) {
-        galois_tile_to_lds<LOG_M, EB, TB>(a.src[z] + row, tile, log_n, a.kappa, a.kappa_inv, lds, md.fp != 0);
+        galois_tile_to_lds<LOG_M, EB, TB>(it.src + row, tile, log_n, it.gal.kappa, it.gal.kappa_inv, lds, md.fp != 0);
 #pragma unroll
         for (int e = 0; e < E; ++e) x[e] = lds[lds_at<LOG_M, EB>(c, l * (uint32_t)E + (uint32_t)e)];
     } else if (a.mode == KS_PRODUCT) {
-        const uint64_t *A = a.src[z] + row, *B = a.src2[z] + row;
+        const uint64_t *A = it.src + row, *B = it.src2 + row;
 #pragma unroll
         for (int e = 0; e < E; e += 2) {
             const ulonglong2 u = two(A, e), v = two(B, e);
@@ -526,7 +529,7 @@ void k_ks_inv(KsInv a, const DevMod* __restrict__ mods, const TwPair* __restrict
             }
         }
     } else {
-        const uint64_t* A = a.mode == KS_WS ? item + a.off_d + row : a.src[z] + row;
+        const uint64_t* A = a.mode == KS_WS ? item + a.off_d + row : it.src + row;
 #pragma unroll
         for (int e = 0; e < E; e += 2) {
             const ulonglong2 u = two(A, e);

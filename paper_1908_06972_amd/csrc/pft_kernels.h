@@ -152,6 +152,9 @@ struct KsConsts {
 // d [3][level][N] at ws_z + off_d from ciphertexts a_z, b_z.
 void launch_tensor_b(uint32_t n, const ItemPtrs& a, const ItemPtrs& b, WsRef ws, uint64_t off_d, uint32_t level,
                      const DevTables& t, uint32_t log_n, hipStream_t st);
+// out_z = a_z + b_z, `rows` rows each (moduli r mod level); out_z may be a_z or b_z.
+void launch_add_b(uint32_t n, const ItemPtrs& a, const ItemPtrs& b, const ItemPtrs& out, uint32_t level,
+                  const DevTables& t, uint32_t log_n, hipStream_t st);
 void launch_copy_rows_b(uint32_t n, const ItemPtrs& src, uint64_t src_off, const ItemPtrs& dst, uint64_t dst_off,
                         uint32_t rows, uint32_t log_n, hipStream_t st);
 // NTT-domain X -> X^kappa of `rows` rows of in_z into ws_z + off_out.
@@ -211,22 +214,33 @@ void launch_rescale_col_b(uint32_t n, WsRef ws, uint64_t off_last, uint64_t off_
 // with KS_PRODUCT: workgroups of one launch read those whole.
 #define PFT_ROW_LIST 64
 enum : uint32_t { KS_WS = 0, KS_PRODUCT = 1, KS_ROTATE = 2, KS_RESCALE = 3 };
+struct KsGalois {
+    uint32_t kappa, kappa_inv;  // kappa^-1 mod 2N
+};
+// What a launch has of its own per item, in one place: a workgroup's scalar
+// loads of the arguments miss once for all of it.
+struct KsItem {
+    const uint64_t *src, *src2;
+    uint64_t* out;
+    const uint64_t* key;  // [dnum][2][L+K][N] in the storage form of launch_key_form
+    KsGalois gal;
+};
+struct KsInvItem {
+    const uint64_t *src, *src2;
+    KsGalois gal;
+};
 struct KsRows {
     uint64_t* base;  // item z's workspace at base + z stride
     uint64_t stride;
     uint64_t off_d, off_ext, off_acc, off_conv;
-    const uint64_t* key;  // [dnum][2][L+K][N] in the storage form of launch_key_form
     const TwPair *gadget, *gadget_fp;  // [L]: P mod q_i as Shoup pairs, and as (w, w/q) doubles where q_i < 2^50
     const TwPair *pinv, *pinv_fp;      // [L]: P^-1 mod q_i the same way
     uint32_t n_items, level, rows, alpha, beta, L, krows, tiles, src_level;
     uint32_t mode, has_add;
-    uint64_t kappa, kappa_inv;    // kappa^-1 mod 2N
     uint32_t parts, group;        // see KsSplit
     uint32_t n_rows;              // entries of this launch
     uint32_t row[PFT_ROW_LIST];   // their rows (0..level+K-1), parts and early rows (KS_ROW_PART, KS_ROW_EARLY)
-    const uint64_t* src[PFT_MAX_ITEMS];
-    const uint64_t* src2[PFT_MAX_ITEMS];
-    uint64_t* out[PFT_MAX_ITEMS];
+    KsItem item[PFT_MAX_ITEMS];
 };
 bool ks_rows_supported(uint32_t log_n);
 // A row list's entry: the row, in the special rows' launch the group of digits
@@ -268,9 +282,7 @@ struct KsInv {
     uint64_t off_d, off_out;
     uint32_t n_items, n_rows, tiles, mode;
     uint32_t src_row, src_step, mod0, mod_step;
-    uint64_t kappa, kappa_inv;
-    const uint64_t* src[PFT_MAX_ITEMS];
-    const uint64_t* src2[PFT_MAX_ITEMS];
+    KsInvItem item[PFT_MAX_ITEMS];
 };
 void launch_ks_inv(uint32_t n, KsInv a, const DevTables& t, uint32_t log_n, hipStream_t st, ProfHook* prof = nullptr);
 // Fills in the shape fields (and the row list) of `a` and launches the rows

@@ -8,7 +8,7 @@ import pytest
 import synth as S
 from oracle import ckks as C
 
-from .test_gpu_modup_fused import CASES, World, world
+from .test_gpu_modup_fused import CASES, STEPS, World, world
 
 pytestmark = pytest.mark.gpu
 
@@ -101,3 +101,31 @@ def test_small_launches_in_parts(n_q, n_p, dnum, q_bits, p_bits):
         rot = C.rotate(w.op, oa, 1, w.rot[1])
         w.assert_same(w.ctx.rotate(ga, 1), rot)
         w.assert_same(w.ctx.total_sum(ga, 2), C.hadd(w.op, oa, rot))
+
+
+@pytest.mark.parametrize("cache", [0, 1])
+def test_op_list_rotations_of_many_steps(cache):
+    """One wave of rotations by different steps at two levels, more of them
+    than a launch takes, the identity among them, and their sums in place;
+    with and without a limited key cache."""
+    w = World(CASES["a2_n12"])
+    ctx = w.ctx
+    if cache:
+        ctx = type(ctx)(w.lp)
+        ctx.set_key_cache(cache)
+        ctx.keygen(31, STEPS)
+    x = [w.enc_pair(900 + i, lv) for i, lv in enumerate((4, 3))]
+    cts, ops, want = [g for g, _ in x], [], []
+    rot = {(i, st): o if st == 0 else C.rotate(w.op, o, st, w.rot[st]) for i, (_, o) in enumerate(x) for st in (0, 1, 5)}
+    for i in range(240):
+        src, st = (i // 2) % 2, (0, 1, 5)[i % 3]
+        cts.append(ctx.empty_ct(x[src][0].level))
+        ops.append(("rotate", src, 0, len(cts) - 1, st, 0))
+        want.append((src, st))
+    ops += [("add", 2 + i, want[i][0], 2 + i, 0, 0) for i in range(240)]
+    ctx.exec_batch(cts, ops)
+    for i, key in enumerate(want):
+        if i < 12 or i > 230:
+            w.assert_same(cts[2 + i], C.hadd(w.op, rot[key], x[key[0]][1]))
+        else:
+            assert bool((cts[2 + i].data == cts[2 + want.index(key)].data).all())
