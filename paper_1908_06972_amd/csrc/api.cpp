@@ -2431,13 +2431,19 @@ extern "C" int pft_total_sum_batch(pft_ctx* c, uint32_t n, const pft_ct* in, uin
             I.p[z] = in[g[z]].data;
             O.p[z] = out[g[z]].data;
         }
-        launch_copy_rows_b(cnt, I, 0, ws_items(ws, cnt), off_cur, 2 * l, lg, c->stream);
-        // the running sum alternates between the two regions: the step reads
-        // one (its X^kappa image and itself) and writes the other
+        // the running sum alternates between the two regions: a step reads one
+        // (its X^kappa image and itself) and writes the other; the first step
+        // reads the inputs themselves and the last writes the outputs
+        // (without steps, or where a single one has overlapping ends, copies:
+        // two passes over the batch, 27.66 -> 27.44 ms for eight products and a
+        // sum over 2^15 slots of 16 ciphertexts at N = 2^16)
+        const bool direct = n_slots > 2 || (n_slots == 2 && !ks_overlap(cnt, O, I, 2 * nl));
         uint64_t a = off_cur, b = off_rot;
+        ItemPtrs cur = direct ? I : ws_items(ws, cnt, a);
+        if (!direct) launch_copy_rows_b(cnt, I, 0, cur, 0, 2 * l, lg, c->stream);
         for (uint32_t s = 1; s < n_slots; s <<= 1) {
             // cur + ROTATE(cur, s)   (Alg. 2): (cur0 + kappa(cur0) + ks0, cur1 + ks1),
-            // finished by the ModDown epilogue into the other region
+            // finished by the last launch of the key switch
             const uint64_t kappa = galois_element((int32_t)s, P->n);
             int ke;
             const SwitchKeyDev* rk = use_rot(c, (int32_t)s, &ke);
@@ -2445,14 +2451,16 @@ extern "C" int pft_total_sum_batch(pft_ctx* c, uint32_t n, const pft_ct* in, uin
             KsInput ki{};
             ki.mode = KS_ROTATE;
             ki.off_pre = b;
-            ki.src = ki.src2 = ws_items(ws, cnt, a);
+            ki.src = ki.src2 = cur;
             ki.has_add = true;
             ki.kappa = kappa;
             ki.kappa_inv = galois_inverse(kappa, P->n);
-            key_switch_b(c, cnt, ws, K, *rk, ki, ws_items(ws, cnt, b));
+            const ItemPtrs dst = direct && 2 * s == n_slots ? O : ws_items(ws, cnt, b);
+            key_switch_b(c, cnt, ws, K, *rk, ki, dst);
+            cur = dst;
             std::swap(a, b);
         }
-        launch_copy_rows_b(cnt, ws_items(ws, cnt, a), 0, O, 0, 2 * l, lg, c->stream);
+        if (!direct) launch_copy_rows_b(cnt, cur, 0, O, 0, 2 * l, lg, c->stream);
         for (uint32_t z = 0; z < cnt; ++z) {
             out[g[z]].level = l;
             out[g[z]].scale = in[g[z]].scale;

@@ -129,3 +129,20 @@ def test_op_list_rotations_of_many_steps(cache):
             w.assert_same(cts[2 + i], C.hadd(w.op, rot[key], x[key[0]][1]))
         else:
             assert bool((cts[2 + i].data == cts[2 + want.index(key)].data).all())
+
+
+@pytest.mark.parametrize("n_slots", [1, 2, 4])
+def test_total_sum_over_its_inputs(n_slots):
+    """Outputs that are the inputs, in order and shifted by one: read before
+    they are written."""
+    w = world("a2_n12")
+    ctx = type(w.ctx)(w.lp)
+    ctx.keygen(31, [1, 2])
+    enc = [lambda i=i: ctx.encrypt_seeded(S.plaintext_coeffs(S.rng(950 + i), w.n, 2 ** 30), 3, w.op.scale, 950 + i)
+           for i in range(3)]
+    want = [ctx.total_sum(e(), n_slots) for e in enc]
+    for shift in (0, 1):
+        x = [e() for e in enc]
+        out = ctx.total_sum_batch(x, n_slots, out=[x[(i + shift) % 3] for i in range(3)])
+        for g, o in zip(out, want):
+            assert bool((g.data == o.data).all())
