@@ -582,16 +582,18 @@ int pft_prof_read(pft_ctx* ctx, uint32_t kid, double* total_ms, uint64_t* launch
  * bytes, ops); returns the number of distinct variants.  variant 0: the
  * family's single kernel; NTT passes (families 0 and 1): 1 + (radix | 32 if a
  * column pass | 64 if the transform's final pass | 128 if staged | 256 if 8
- * residues per thread | 512 if the pass finishes ModDown | 1024 if X^kappa
- * is folded into it), naming k_ntt_pass<radix, log2 residues per thread,
- * inverse, column, final, staged, ModDown epilogue[, true]>; base
- * conversions on the matrix cores (families 2 and 4): the number of 16-deep
- * k-blocks, naming k_modup_mfma_b<kb> and k_moddown_mfma_b<kb>, or 64 + kb
- * (+ 16 with the inverse pass folded in) for the conversions fused with
- * transform passes, naming k_bconv_col_b<kb, ModDown, inverse pass>; the key
- * inner product (family 3): the number of digits beta, naming
- * k_key_inner_items<beta>, or 1024 + the radix of the row pass it is fused
- * with, naming k_row_inner<radix, 3>.  Any output may be NULL. */
+ * residues per thread | 512 if the pass finishes ModDown), naming
+ * k_ntt_pass<radix, log2 residues per thread, inverse, column, final, staged,
+ * ModDown epilogue>; 8192 + the radix (+ 64 with 4 residues per thread): the
+ * inverse row pass of key switching, k_ks_inv; base conversions on the matrix
+ * cores (families 2 and 4): the number of 16-deep k-blocks, naming
+ * k_modup_mfma_b<kb> and k_moddown_mfma_b<kb>, or 64 + kb (+ 16 with the
+ * inverse pass folded in, + 32 the form of few workgroups) for the conversions
+ * fused with transform passes, naming k_bconv_col_b<kb, ModDown, inverse pass,
+ * few>; the key inner product (family 3): the number of digits beta, naming
+ * k_key_inner_items<beta>, or 1024 + the radix of the row pass (+ 64 fp64
+ * rows, + 128 digit pairs, + 256 special rows, + 512 with 4 residues per
+ * thread), naming k_ks_rows.  Any output may be NULL. */
 int pft_prof_read_variants(pft_ctx* ctx, uint32_t kid, uint32_t max_count, uint32_t* variants, double* total_ms,
                            uint64_t* launches, double* bytes, double* ops);
 

@@ -29,6 +29,17 @@
 // cannot fill the chip anyway: a tile's chain of passes then has twice the
 // waves, half the instructions per wave, and takes the rows of both
 // arithmetic kinds in one launch.
+//
+// Measured (MI355X).  16 HMULTs at N = 2^16, level 24, four digits: the fp64
+// ciphertext rows 880 us (VALU issue 55%, 2.4 GB at 2.8 TB/s: the chain of
+// loads, passes and products at two workgroups a compute unit bounds it, and
+// neither the next rows' loads nor the key tiles ahead of the pass, which spill
+// or cost a workgroup, nor 8-byte twiddles moved it), the special rows 308 (60-bit
+// butterflies, VALU issue 85%), the one integer row 222 beside the fp64 rows,
+// k_ks_inv 170.  Before, with the key products, the inverse and ModDown's
+// passes and the tensor as launches of their own, the whole call took 2045 us;
+// 1525 now.  One item at N = 2^15, level 16: k_ks_inv 7.8, special rows 16.4,
+// last launch 24.3 us, each a few dependent rounds of memory and of LDS.
 #include "ntt_device.h"
 #include "pft_device.h"
 #include "pft_kernels.h"

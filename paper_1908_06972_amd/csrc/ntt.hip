@@ -393,6 +393,11 @@ void launch_pass(const PolyBatch& b, const DevTables& t, uint32_t log_n, uint32_
 // radix-16 column pass, stages 3-0 with N^-1 folded in) has not run; it is
 // applied to the 16 values of each column first.
 //
+// Bound by the VALU: the integer butterflies of 60-bit rows, the fold, the
+// inputs' products.  16 items at N = 2^16, level 24: ModUp's 338 us and
+// ModDown's 171 (500 and 231 when the folded values went through LDS to
+// another thread's column and a wave's tile mixed the arithmetic kinds).
+//
 // SMALL (with IFUSE): the form of launches that leave compute units with one
 // or two workgroups, where the length of a wave's chain counts: four threads
 // share a column's inverse pass (the sums of ModDown's parts too), and two

@@ -262,12 +262,15 @@ struct KsSplit {
 };
 KsSplit ks_split(uint32_t n, uint32_t level, const KsConsts& kc, const uint32_t* fp_rows, uint32_t log_n);
 // Launches of at most this many words (rows times N, all items) take the
-// 4-residue forms.  Up to there the 8-residue forms' waves (2^22 / 512 = 8
-// per SIMD, in two rounds at their registers) do not hide the passes'
-// latency: 2^21 -> 2^22 took six documents' predict step at N = 2^15 from
-// 5285 to 5077 us; far above it the 8-residue forms read each twiddle half as
-// often (16 HMULTs at N = 2^16, level 24: 1565 us, 1693 with 4 residues).
-#define KS_SMALL_WORDS (1ull << 22)
+// 4-residue forms.  Up to 2^22 the 8-residue forms' waves (8 per SIMD, in two
+// rounds at their registers) do not hide the passes' latency: 2^21 -> 2^22
+// took six documents' predict step at N = 2^15 from 5285 to 5077 us.  Up to
+// 2^23 both forms take the same time (five rotations at N = 2^16, level 17: 355
+// us), but the 8-residue form needs its two launches side by side for it: 401
+// where the helper stream has the hardware queue of the context's own.  Far
+// above it the 8-residue forms read each twiddle half as often (16 HMULTs at
+// N = 2^16, level 24: 1565 us, 1693 with 4 residues).
+#define KS_SMALL_WORDS (1ull << 23)
 bool ks_small(uint32_t n, uint32_t rows, uint32_t log_n);
 // The first (row) pass of the inverse transform of n_rows rows r of item z,
 // from their NTT domain to off_out + r N, left for the final radix-16 column

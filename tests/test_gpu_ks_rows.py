@@ -69,14 +69,15 @@ def test_integer_rows_of_other_sizes(bits):
         w.assert_same(w.ctx.rescale(g), low)
 
 
-@pytest.mark.parametrize("name,n_q,items", [("a6_n12", 18, 64), ("a3_n13", 10, 64), ("a2_n14", 8, 64),
-                                            ("a4_n15", 8, 64)])
-def test_large_launches_equal_small_ones(name, n_q, items):
+@pytest.mark.parametrize("name,n_q,n_p,items", [("a6_n12", 36, 6, 64), ("a3_n13", 18, 3, 64), ("a2_n14", 10, 2, 64),
+                                                ("a4_n15", 10, 5, 64)])
+def test_large_launches_equal_small_ones(name, n_q, n_p, items):
     """Enough items for the 8-residue forms of the fused kernels (a launch of
-    more than 2^22 words), against the same calls one item at a time."""
-    w = World(dict(CASES[name], n_q=n_q, dnum=-(-n_q // CASES[name]["n_p"])))
+    more than 2^23 words; the last case's special rows too), against the same
+    calls one item at a time."""
+    w = World(dict(CASES[name], n_q=n_q, n_p=n_p, dnum=n_q // n_p))
     L = w.op.L
-    assert items * L * w.n > 2 ** 22 >= 2 * L * w.n
+    assert items * L * w.n > 2 ** 23 >= 2 * L * w.n
     a, b = ([w.ctx.encrypt_seeded(S.plaintext_coeffs(S.rng(s + i), w.n, 2 ** 30), L, w.op.scale, s + i)
              for i in range(items)] for s in (3000, 4000))
     prod = w.ctx.mul_relin_batch(a, b)
