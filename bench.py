@@ -156,16 +156,17 @@ def _find(dirpath, suffix):
 
 
 def _step_dispatches(rows, key_id, key_start):
-    """Dispatches of the job steps after the first one: from the first HMUL
-    tensor kernel of the second step on (a step launches CHAIN_DEPTH tensor
-    kernels).  This excludes key generation, encryption and the first step,
-    during which the NTT autotuner times its candidates; every later step
-    launches the same kernels with the same shapes."""
+    """Dispatches of the job steps after the first one.  A step launches
+    CHAIN_DEPTH expansions of RESCALE, each after two inverse row passes (its
+    HMUL's and its own): from the first of those two of the second step on.
+    This excludes key generation, encryption and the first step; every later
+    step launches the same kernels with the same shapes."""
     rows = sorted(rows, key=lambda r: int(r[key_id]))
-    tensors = sorted({int(r[key_id]) for r in rows if "k_tensor_b" in r["Kernel_Name"]})
-    if len(tensors) <= CHAIN_DEPTH:
+    ids = lambda name: sorted({int(r[key_id]) for r in rows if name in r["Kernel_Name"]})  # noqa: E731
+    rescales = ids("k_rescale_col_b")
+    if len(rescales) <= CHAIN_DEPTH:
         return []
-    first = tensors[CHAIN_DEPTH]
+    first = [i for i in ids("k_ks_inv") if i < rescales[CHAIN_DEPTH]][-2]
     return [r for r in rows if int(r[key_id]) >= first]
 
 
@@ -303,9 +304,10 @@ def summarize(trace_dir, fetch_dir, write_dir, kernel, kid, commands, n_top=6, s
     # every kernel of the profiled steps: counted traffic per step
     def step_total(dirpath, counter):
         rows = _step_dispatches(_csv_rows(_find(dirpath, "counter_collection.csv")), "Dispatch_Id", "Start_Timestamp")
-        tensors = {int(r["Dispatch_Id"]) for r in rows if "k_tensor_b" in r["Kernel_Name"]}
-        steps = len(tensors) / float(CHAIN_DEPTH)
-        tot = sum(float(r["Counter_Value"]) for r in rows if r.get("Counter_Name") == counter)
+        rescales = {int(r["Dispatch_Id"]) for r in rows if "k_rescale_col_b" in r["Kernel_Name"]}
+        steps = len(rescales) / float(CHAIN_DEPTH)
+        tot = sum(float(r["Counter_Value"]) for r in rows
+                  if r.get("Counter_Name") == counter and "k_copy_rows_b" not in r["Kernel_Name"])
         return tot, steps
     f_tot, f_steps = step_total(fetch_dir, "FETCH_SIZE")
     w_tot, w_steps = step_total(write_dir, "WRITE_SIZE")
@@ -1247,6 +1249,9 @@ def main():
         prof_enable(ctx, 1 << FAMILIES.index("key_inner_product"))
         for i in range(1 + args.profile_steps):
             job_step(ctx, cts)
+            # a plain copy of the batch (rotation by all slots), the
+            # calibration of the traffic counters; not counted with the step
+            ctx.rotate_batch(cts, ctx.params.n // 2)
             sync()
             log("profile step %d done" % i)
         save_tuning()
