@@ -109,7 +109,7 @@ class Roctx:
 
 # source files whose text determines the kernels (for the validity of stored
 # counter figures: any change to device code invalidates them all)
-KERNEL_SOURCES = ["ntt.hip", "keyswitch.hip", "ckks.hip", "sampler.hip", "ntt_device.h", "pft_device.h",
+KERNEL_SOURCES = ["ntt.hip", "keyswitch.hip", "ckks.hip", "sampler.hip", "ntt_device.h", "pft_device.h", "ks_split.h",
                   "bconv_device.h", "pft_kernels.h"]
 PROFILE_DIR = os.path.join(ROOT, "profiles")
 CSRC = os.path.join(ROOT, "paper_1908_06972_amd", "csrc")

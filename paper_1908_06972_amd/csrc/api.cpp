@@ -1868,7 +1868,8 @@ static void key_switch_b(pft_ctx* c, uint32_t n, WsRef ws, const KsLayout& K, co
     KsRows kr{};
     KsSplit split{1, beta, false};
     if (merged) {
-        split = ks_split(n, level, c->kc, c->fp_rows.data(), lg);
+        const uint32_t ints = (uint32_t)std::count(c->fp_rows.begin(), c->fp_rows.begin() + level, 0u);
+        split = ks_split(n, level, A, P->K, ints, lg);
         kr.base = ws.base;
         kr.stride = ws.stride;
         kr.off_d = off_d;
@@ -1926,9 +1927,10 @@ static void key_switch_b(pft_ctx* c, uint32_t n, WsRef ws, const KsLayout& K, co
     }
     if (fuse_down) {
         BconvIn sum{{K.off_acc + ((uint64_t)level << lg), K.off_acc + ((uint64_t)(rows + level) << lg)}, {0, 0}, 1};
-        if (split.parts > 1)
-            sum = BconvIn{{K.off_ext + ((uint64_t)level << lg), K.off_acc},
-                          {(uint64_t)split.group * rows << lg, (uint64_t)P->K << lg},
+        if (split.packed())
+            sum = BconvIn{{K.off_ext + ((uint64_t)level << lg), K.off_acc + ((uint64_t)ks_special_row1(P->K, 0, 0) << lg)},
+                          {(uint64_t)split.group * rows << lg,
+                           (uint64_t)(ks_special_row1(P->K, 0, 1) - ks_special_row1(P->K, 0, 0)) << lg},
                           split.parts};
         timed(c, PK_MODDOWN_CONV, 8.0 * N * (ifuse_down ? 0.0 : 2.0 * P->K) * n, 2.0 * N * P->K * level * n,
               [&] {

@@ -125,7 +125,7 @@ __device__ __forceinline__ void ks_row(const KsRows& a, const KsItem& it, uint64
     // an early row's part s of polynomial 1
     [[maybe_unused]] auto early1 = [&](uint32_t s) {
         const uint32_t e = (entry >> KS_ROW_EARLY) - 1u;
-        return item + a.off_acc + ((size_t)(a.parts * (a.rows - a.level + e) + s) << log_n);
+        return item + a.off_acc + ((size_t)ks_early_row1(a.rows - a.level, a.parts, e, s) << log_n);
     };
     uint64_t acc0[E], acc1[E];  // FP: doubles; otherwise residues
 #pragma unroll
@@ -369,9 +369,9 @@ __device__ __forceinline__ void ks_row(const KsRows& a, const KsItem& it, uint64
         const TwPair* __restrict__ twi = tw_inv + ((size_t)mi << log_n);
         uint64_t* o0 = item + a.off_acc + ((size_t)t << log_n);
         uint64_t* o1 = o0 + ((size_t)a.rows << log_n);
-        if (a.parts > 1) {  // see KsSplit
+        if (a.packed) {  // see KsSplit
             o0 = ext(j0);
-            o1 = item + a.off_acc + ((size_t)(part * (a.rows - a.level) + t - a.level) << log_n);
+            o1 = item + a.off_acc + ((size_t)ks_special_row1(a.rows - a.level, t - a.level, part) << log_n);
         }
         auto put = [&](const uint64_t (&x)[E], uint32_t b) {
 #pragma unroll
@@ -585,46 +585,6 @@ bool ks_rows_supported(uint32_t log_n) {
     return r >= 8 && r <= 12;
 }
 
-bool ks_small(uint32_t n, uint32_t rows, uint32_t log_n) {
-    return ((uint64_t)n * rows << log_n) <= KS_SMALL_WORDS;
-}
-
-// parts: a tile of a special row costs a workgroup ceil(beta / parts) digits'
-// passes and two of the inverse (splitting repeats the latter), a round of
-// workgroups being one per compute unit (two of the 1024-word tiles' four
-// waves).  At N = 2^15, level 16, one item (64 tiles of 60-bit rows, four
-// digits) the launch takes 15.6 us in four parts, 23.3 in one, and ModDown's
-// conversion 16.0 instead of 14.1; one HMULT at N = 2^16, level 24 (96 tiles,
-// two parts) 172 -> 161 us.
-// early: where the last launch is a single round, its few integer rows are
-// what it ends with: 28.7 -> 24.1 us at N = 2^15, level 16, the special rows'
-// launch 15.6 -> 17.5.  With more rounds they hide (six items: 5028 us without,
-// 5065 with, for a predict step).
-KsSplit ks_split(uint32_t n, uint32_t level, const KsConsts& kc, const uint32_t* fp_rows, uint32_t log_n) {
-    const uint32_t beta = (level + kc.alpha - 1) / kc.alpha;
-    KsSplit s{1, beta, false};
-    if (beta < 2 || !ks_small(n, std::max(level, kc.K), log_n)) return s;
-    const uint32_t tile_log = std::max(log_n - 4, 10u), slots = tile_log == 10 ? 512 : 256;
-    auto rounds = [&](uint64_t rows) { return (uint32_t)((((n * rows) << log_n >> tile_log) + slots - 1) / slots); };
-    uint32_t ints = 0;
-    for (uint32_t r = 0; r < level; ++r) ints += fp_rows[r] ? 0 : 1;
-    s.early = ints > 0 && ints <= kc.K && rounds(level) == 1;
-    if (!s.early) ints = 0;
-    uint32_t best = ~0u;
-    for (uint32_t parts = 1; parts <= std::min(beta, 4u); ++parts) {
-        const uint32_t group = (beta + parts - 1) / parts;
-        // every part has a digit, and polynomial 1's parts fit (KsSplit)
-        if ((parts - 1) * group >= beta || (parts > 1 && parts * (kc.K + ints) > 2 * (level + kc.K))) continue;
-        const uint32_t cost = rounds(kc.K * parts) * (group + 2);
-        if (cost < best) {
-            best = cost;
-            s.parts = parts;
-            s.group = group;
-        }
-    }
-    return s;
-}
-
 void launch_ks_inv(uint32_t n, KsInv a, const DevTables& t, uint32_t log_n, hipStream_t st, ProfHook* prof) {
     a.n_items = n;
     const bool small = ks_small(n, a.n_rows, log_n);
@@ -663,6 +623,7 @@ void launch_ks_rows(uint32_t n, KsRows a, bool special, const KsConsts& kc, cons
     a.krows = kc.L + kc.K;
     a.parts = split.parts;
     a.group = split.parts > 1 ? split.group : a.beta;
+    a.packed = split.packed() ? 1u : 0u;
     const bool small = ks_small(n, special ? kc.K : level, log_n);
     // the rows of one arithmetic kind (the small form: of both, the longer
     // integer rows first), in chunks that fit the row list

@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "ks_split.h"
 #include "pft_device.h"
 
 // Device-resident per-parameter-set tables.
@@ -237,7 +238,7 @@ struct KsRows {
     const TwPair *pinv, *pinv_fp;      // [L]: P^-1 mod q_i the same way
     uint32_t n_items, level, rows, alpha, beta, L, krows, tiles, src_level;
     uint32_t mode, has_add;
-    uint32_t parts, group;        // see KsSplit
+    uint32_t parts, group, packed;  // see KsSplit
     uint32_t n_rows;              // entries of this launch
     uint32_t row[PFT_ROW_LIST];   // their rows (0..level+K-1), parts and early rows (KS_ROW_PART, KS_ROW_EARLY)
     KsItem item[PFT_MAX_ITEMS];
@@ -246,32 +247,6 @@ bool ks_rows_supported(uint32_t log_n);
 // A row list's entry: the row, in the special rows' launch the group of digits
 // it takes, and 1 + its index among the early rows, or 0.
 enum : uint32_t { KS_ROW_MASK = 0x1ff, KS_ROW_PART = 9, KS_ROW_EARLY = 12 };
-// How a key switch whose launches cannot fill the chip spreads its integer
-// rows (ks_split).  parts > 1: each special row is taken by `parts`
-// workgroups a tile, each with `group` digits, whose sums go through the
-// inverse row pass by themselves; ModDown's conversion adds the parts.  early:
-// the digits of the integer ciphertext rows (but their own) are taken in the
-// special rows' launch, in the same parts, and the last launch adds their
-// sums.  The parts lie in rows that the fused path has no other use for: part
-// s of row r's polynomial 0 over row r of the group's first digit (ext, which
-// only that workgroup reads), of its polynomial 1 at off_acc + (s K + r -
-// level) N for a special row, for early row e at off_acc + (parts (K + e) + s) N.
-struct KsSplit {
-    uint32_t parts, group;
-    bool early;
-};
-KsSplit ks_split(uint32_t n, uint32_t level, const KsConsts& kc, const uint32_t* fp_rows, uint32_t log_n);
-// Launches of at most this many words (rows times N, all items) take the
-// 4-residue forms.  Up to 2^22 the 8-residue forms' waves (8 per SIMD, in two
-// rounds at their registers) do not hide the passes' latency: 2^21 -> 2^22
-// took six documents' predict step at N = 2^15 from 5285 to 5077 us.  Up to
-// 2^23 both forms take the same time (five rotations at N = 2^16, level 17: 355
-// us), but the 8-residue form needs its two launches side by side for it: 401
-// where the helper stream has the hardware queue of the context's own.  Far
-// above it the 8-residue forms read each twiddle half as often (16 HMULTs at
-// N = 2^16, level 24: 1565 us, 1693 with 4 residues).
-#define KS_SMALL_WORDS (1ull << 23)
-bool ks_small(uint32_t n, uint32_t rows, uint32_t log_n);
 // The first (row) pass of the inverse transform of n_rows rows r of item z,
 // from their NTT domain to off_out + r N, left for the final radix-16 column
 // pass (which launch_modup_col_b with ifuse and launch_rescale_col_b apply).
