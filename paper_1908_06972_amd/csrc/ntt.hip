@@ -450,8 +450,12 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
             const TwPair* __restrict__ twt = tw_inv + ((size_t)mi << log_n);
             uint64_t x[4];
             if (DOWN && src.parts > 1) {
-                // at most four terms below 4q (fp64: within 4.5q) each, every
-                // load in flight at once
+                // at most four terms, every load in flight at once.  Integer
+                // terms are below 4q, their sum below 16q.  An fp64 term
+                // may be past 2q (a row pass of 9 or 12 stages ends on one
+                // that does not reduce; within 3q by the butterflies'
+                // bounds), and four of those past 2^53, where doubles are no
+                // longer exact: each is brought within q/2 first.
                 uint64_t y[4][4];
 #pragma unroll
                 for (uint32_t s = 0; s < 4; ++s)
@@ -462,9 +466,12 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
                 for (uint32_t e = 0; e < 4; ++e) {
                     uint64_t v = y[0][e];
                     if (md.fp) {
+#pragma clang fp contract(off)
+                        double f = freduce(as_f(v), md.qd, md.qinv);
 #pragma unroll
-                        for (uint32_t s = 1; s < 4; ++s) v = s < src.parts ? as_u(as_f(v) + as_f(y[s][e])) : v;
-                        x[e] = as_u(freduce(as_f(v), md.qd, md.qinv));
+                        for (uint32_t s = 1; s < 4; ++s)
+                            f = s < src.parts ? f + freduce(as_f(y[s][e]), md.qd, md.qinv) : f;
+                        x[e] = as_u(freduce(f, md.qd, md.qinv));
                     } else {
 #pragma unroll
                         for (uint32_t s = 1; s < 4; ++s) v = s < src.parts ? v + y[s][e] : v;

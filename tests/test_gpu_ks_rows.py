@@ -8,6 +8,7 @@ import pytest
 import synth as S
 from oracle import ckks as C
 
+from .ks_split_host import split
 from .test_gpu_modup_fused import CASES, STEPS, World, world
 
 pytestmark = pytest.mark.gpu
@@ -102,6 +103,18 @@ def test_small_launches_in_parts(n_q, n_p, dnum, q_bits, p_bits):
         rot = C.rotate(w.op, oa, 1, w.rot[1])
         w.assert_same(w.ctx.rotate(ga, 1), rot)
         w.assert_same(w.ctx.total_sum(ga, 2), C.hadd(w.op, oa, rot))
+
+
+@pytest.mark.parametrize("log_n", [13, 16])
+def test_fp64_special_rows_in_parts(log_n):
+    """50-bit special primes in three and four parts where the inverse row
+    pass (9 and 12 stages) ends on a stage that does not reduce."""
+    w = World(dict(log_n=log_n, n_q=4, q0_bits=50, q_bits=50, n_p=1, p_bits=50, dnum=4, scale=2 ** 40))
+    for level in (4, 3):
+        assert split(1, level, 1, 1, 0, log_n) == (level, 1, False)
+        (ga, oa), (gb, ob) = w.enc_pair(50 + level, level), w.enc_pair(70 + level, level)
+        w.assert_same(w.ctx.mul_relin(ga, gb), C.hmul_relin(w.op, oa, ob, w.rlk))
+        w.assert_same(w.ctx.rotate(ga, 5), C.rotate(w.op, oa, 5, w.rot[5]))
 
 
 @pytest.mark.parametrize("cache", [0, 1])
