@@ -404,7 +404,7 @@ void launch_pass(const PolyBatch& b, const DevTables& t, uint32_t log_n, uint32_
 // waves a tile of targets.
 constexpr uint32_t BCONV_COLS = 32;
 template <uint32_t NKB, bool DOWN, bool IFUSE, bool SMALL>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k_bconv_col_b(
+__global__ __launch_bounds__(SMALL ? 1024 : 512) __attribute__((amdgpu_waves_per_eu(4))) void k_bconv_col_b(
     WsRef ws, BconvIn src, uint64_t off_out, uint32_t level, KsConsts kc, const DevMod* __restrict__ mods,
     const TwPair* __restrict__ tw, const TwPair* __restrict__ tw_inv, uint32_t log_n) {
     __shared__ uint64_t s_dig[2 * NKB * 16 * BCONV_COLS];  // [input row][t][u]
@@ -751,8 +751,11 @@ bool ntt_schedule_valid(uint32_t log_n, const NttSchedule& s) {
 static uint32_t bconv_col_dyn_lds(uint32_t tiles) {
     return 4 * tiles * (uint32_t)(sizeof(BconvRed) + 16 * sizeof(TwPair));
 }
+// A workgroup may take a compute unit's whole 160 KB.  The largest, 12 inputs
+// and 72 slots, takes 70.5: two still share a compute unit, as the registers
+// allow for any size.
 bool bconv_col_supported(uint32_t log_n, uint32_t nkb, uint32_t tiles) {
-    return log_n >= 9 && nkb <= 6 && 2 * nkb * 16 * BCONV_COLS * 8 + bconv_col_dyn_lds(tiles) <= 65536;
+    return log_n >= 9 && nkb <= 6 && 2 * nkb * 16 * BCONV_COLS * 8 + bconv_col_dyn_lds(tiles) <= 160 * 1024;
 }
 
 // Up to two workgroups of 32 columns a compute unit, the eight-wave form with
@@ -771,11 +774,15 @@ uint32_t bconv_col_variant(uint32_t log_n, uint32_t nkb, uint32_t groups, uint32
 template <bool DOWN, bool IFUSE>
 static void launch_bconv_col(uint32_t nkb, dim3 grid, hipStream_t st, WsRef ws, const BconvIn& in, uint64_t off_out,
                              uint32_t level, const KsConsts& kc, const DevTables& t, uint32_t log_n) {
-    const uint32_t lds = bconv_col_dyn_lds(DOWN ? kc.down_rt : kc.up_rt);
+    const uint32_t tiles = DOWN ? kc.down_rt : kc.up_rt, lds = bconv_col_dyn_lds(tiles);
     const bool small = bconv_col_small(log_n, grid.y, grid.z, in.parts);
     // four waves take about two tiles each; where that leaves compute units
-    // without a second workgroup, eight waves a workgroup take one each
-    const uint32_t threads = small ? 512 : 256;
+    // without a second workgroup, eight waves a workgroup take one each, and
+    // sixteen where a workgroup has a compute unit to itself and more than
+    // eight tiles (one HMULT at N = 2^12, 36 limbs in three digits, 13 tiles:
+    // 74.9 -> 65.7 us; 68.2 through separate launches)
+    const bool alone = IFUSE && small && tiles > 8 && grid.x * grid.y * grid.z <= 256;
+    const uint32_t threads = alone ? 1024 : small ? 512 : 256;
 #define PFT_BCONV_COL(K)                                                                                     \
     case K:                                                                                                  \
         if (IFUSE && small)                                                                                  \

@@ -3,10 +3,13 @@ rotation, and outputs that overlap another item's operands, for every
 row-pass length, both digit arrangements, and full, ragged and lowest levels;
 bit-exact against the oracle."""
 
+import ctypes
+
 import pytest
 
 import synth as S
 from oracle import ckks as C
+from paper_1908_06972_amd import native as N
 
 from .ks_split_host import split
 from .test_gpu_modup_fused import CASES, STEPS, World, world
@@ -115,6 +118,27 @@ def test_fp64_special_rows_in_parts(log_n):
         (ga, oa), (gb, ob) = w.enc_pair(50 + level, level), w.enc_pair(70 + level, level)
         w.assert_same(w.ctx.mul_relin(ga, gb), C.hmul_relin(w.op, oa, ob, w.rlk))
         w.assert_same(w.ctx.rotate(ga, 5), C.rotate(w.op, oa, 5, w.rot[5]))
+
+
+@pytest.mark.parametrize("n_q,n_p,dnum", [(36, 12, 3), (50, 12, 5)])
+def test_conversions_of_many_rows(n_q, n_p, dnum):
+    """Digits of 12 limbs, 12 special primes and long chains, whose operands
+    and constants pass 64 KB of LDS: on the fused kernels, one item and a
+    batch, against the oracle."""
+    w = World(dict(log_n=12, n_q=n_q, q0_bits=60, q_bits=40, n_p=n_p, p_bits=60, dnum=dnum, scale=2 ** 40))
+    for level in (n_q, n_q - 1, 1):
+        pairs = [(w.enc_pair(50 + 3 * level + i, level), w.enc_pair(300 + 3 * level + i, level)) for i in range(3)]
+        prod = [C.hmul_relin(w.op, x[1], y[1], w.rlk) for x, y in pairs]
+        N.check(w.ctx.lib.pft_prof_enable(w.ctx.handle, 1 << 3))  # the key inner product's kernels
+        w.assert_same(w.ctx.mul_relin(pairs[0][0][0], pairs[0][1][0]), prod[0])
+        var = (ctypes.c_uint32 * 16)()
+        k = w.ctx.lib.pft_prof_read_variants(w.ctx.handle, 3, 16, var, None, None, None, None)
+        N.check(w.ctx.lib.pft_prof_enable(w.ctx.handle, 0))
+        assert k > 0 and min(var[:k]) >= 1024  # k_ks_rows
+        for g, o in zip(w.ctx.mul_relin_batch([x[0] for x, _ in pairs], [y[0] for _, y in pairs]), prod):
+            w.assert_same(g, o)
+        rot = C.rotate(w.op, pairs[0][0][1], 5, w.rot[5])
+        w.assert_same(w.ctx.rotate(pairs[0][0][0], 5), rot)
 
 
 @pytest.mark.parametrize("cache", [0, 1])
