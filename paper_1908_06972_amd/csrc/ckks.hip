@@ -480,9 +480,12 @@ __device__ __forceinline__ void dot_block(uint32_t groups, uint32_t log_n, uint3
 // spread over the XCDs the tiles came again and again (32 items, 16 terms, 8
 // outputs at N = 2^15, level 16: 2162 us, now 1807, of which 6.9 GB take 1300
 // at the copy rate and the products 1000; one item 262, now 158).
-// NG (8, 4 or 2) is n_g rounded up: the loads of a term are NG unconditional
+// NG (8, 4, 2 or 1) is n_g rounded up: the loads of a term are NG unconditional
 // ones in flight together: 38.0 -> 36.6 ms for the bag-of-words layer of 32
-// documents at N = 2^15 against loads that each waited on a condition.
+// documents at N = 2^15 against loads that each waited on a condition.  One
+// output alone takes four terms at a time: one document, 16 terms at N = 2^15,
+// level 6, a whole call 37.5 us as half of NG 2, 36.7 a term at a time, 33.1
+// so (with a single term it takes 21).
 // Plaintext rows in the form of launch_key_form.  Rows with q < 2^50: each
 // product by fmulmod (within 0.9q), the sums brought within q/2 every 8 terms
 // (below 7.7q < 2^53 before).  The other rows: full 128-bit products of the
@@ -494,6 +497,7 @@ __global__ __launch_bounds__(TB) void k_pt_dot_multi_b(WsRef ws, uint32_t n_item
                                                        uint32_t n_g, uint64_t off_acc, uint32_t level,
                                                        const DevMod* __restrict__ mods, uint32_t log_n) {
     using u128 = unsigned __int128;
+    constexpr uint32_t UNROLL = NG == 1 ? 4 : 1;
     uint32_t v0, i, k;
     dot_block((2 * n_items + Z - 1) / Z, log_n, v0, i, k);
     v0 *= Z;
@@ -516,6 +520,7 @@ __global__ __launch_bounds__(TB) void k_pt_dot_multi_b(WsRef ws, uint32_t n_item
 #pragma unroll
             for (uint32_t g = 0; g < NG; ++g) a[z][g] = 0.0;
         }
+#pragma unroll UNROLL
         for (uint32_t j = 0; j < J; ++j) {
             double x[Z];
 #pragma unroll
@@ -561,6 +566,7 @@ __global__ __launch_bounds__(TB) void k_pt_dot_multi_b(WsRef ws, uint32_t n_item
             res[g] = add_mod(res[g], mont_redc((uint64_t)a[g], (uint64_t)(a[g] >> 64), md.q, md.mont_neg_qinv), md.q);
             a[g] = 0;
         };
+#pragma unroll UNROLL
         for (uint32_t j = 0; j < J; ++j) {
             const uint64_t x = w[off_baby + j * ct_words + k];
             const uint64_t* __restrict__ pj = pr + (((size_t)j * level) << log_n);
@@ -865,8 +871,10 @@ void launch_pt_dot_multi_b(uint32_t n, WsRef ws, uint64_t off_baby, uint64_t ct_
         by_items(std::integral_constant<uint32_t, 8>{});
     else if (n_g > 2)
         by_items(std::integral_constant<uint32_t, 4>{});
-    else
+    else if (n_g > 1)
         by_items(std::integral_constant<uint32_t, 2>{});
+    else
+        by_items(std::integral_constant<uint32_t, 1>{});
 }
 
 void launch_add_const_b(uint32_t n, const ItemPtrs& in, const ItemPtrs& out, const TwPair* consts, uint32_t level,
@@ -890,8 +898,10 @@ void launch_ct_dot_multi_b(uint32_t n, const ItemPtrs& e, uint32_t J, uint32_t n
     using four = std::integral_constant<uint32_t, 4>;
     if (n_g > 2)
         n >= 2 ? go(two{}, four{}) : go(one{}, four{});
-    else
+    else if (n_g > 1)
         n >= 2 ? go(two{}, two{}) : go(one{}, two{});
+    else
+        n >= 2 ? go(two{}, one{}) : go(one{}, one{});
 }
 
 void launch_scale_const_b(uint32_t n, const ItemPtrs& in, const ItemPtrs& out, const TwPair* consts, uint32_t level,

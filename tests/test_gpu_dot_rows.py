@@ -7,6 +7,7 @@ import pytest
 
 import synth as S
 from oracle import ckks as C
+from oracle import training as T
 
 from .test_gpu_modup_fused import CASES, World, world
 
@@ -46,3 +47,14 @@ def test_encrypted_dot_groups():
     for n in (2, 3):
         for a, g in zip(one, w.ctx.ctmatvec(diags, n_o, n_i, 1, docs[:n])):
             assert np.array_equal(a, w.ctx.export(g))
+
+
+@pytest.mark.parametrize("n_o,n_i", [(1, 2), (2, 2)])
+@pytest.mark.parametrize("docs", [1, 2, 3])
+def test_encrypted_dot_of_one_giant_step(n_o, n_i, docs):
+    w, level = world("a2_n12"), 4
+    diags = [w.enc_pair(80 + i, level) for i in range(n_o)]
+    ins = [w.enc_pair(90 + d, level) for d in range(docs)]
+    got = w.ctx.ctmatvec([g for g, _ in diags], n_o, n_i, 1, [[g] for g, _ in ins])
+    for g, (_, x) in zip(got, ins):
+        w.assert_same(g, T.ctmatvec(w.op, [x], [[[o for _, o in diags]]], n_o, n_i, w.rlk, w.rot))
