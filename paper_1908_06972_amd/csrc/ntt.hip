@@ -450,29 +450,31 @@ __global__ __launch_bounds__(SMALL ? 1024 : 512) __attribute__((amdgpu_waves_per
             const TwPair* __restrict__ twt = tw_inv + ((size_t)mi << log_n);
             uint64_t x[4];
             if (DOWN && src.parts > 1) {
-                // at most four terms, every load in flight at once.  Integer
+                // two to four terms, every load in flight at once.  Integer
                 // terms are below 4q, their sum below 16q.  An fp64 term
                 // may be past 2q (a row pass of 9 or 12 stages ends on one
                 // that does not reduce; within 3q by the butterflies'
-                // bounds), and four of those past 2^53, where doubles are no
-                // longer exact: each is brought within q/2 first.
+                // bounds): two of them stay below 2^53, four may not, where
+                // doubles are no longer exact, so each pair is brought
+                // within q/2 before they meet.
                 uint64_t y[4][4];
 #pragma unroll
                 for (uint32_t s = 0; s < 4; ++s)
 #pragma unroll
                     for (uint32_t e = 0; e < 4; ++e)
                         y[s][e] = word(in + min(s, src.parts - 1) * src.step[j], ii, 4 * c + e);
-#pragma unroll
-                for (uint32_t e = 0; e < 4; ++e) {
-                    uint64_t v = y[0][e];
-                    if (md.fp) {
+                if (md.fp) {
 #pragma clang fp contract(off)
-                        double f = freduce(as_f(v), md.qd, md.qinv);
 #pragma unroll
-                        for (uint32_t s = 1; s < 4; ++s)
-                            f = s < src.parts ? f + freduce(as_f(y[s][e]), md.qd, md.qinv) : f;
-                        x[e] = as_u(freduce(f, md.qd, md.qinv));
-                    } else {
+                    for (uint32_t e = 0; e < 4; ++e) {
+                        const double t2 = src.parts > 2 ? as_f(y[2][e]) : 0.0, t3 = src.parts > 3 ? as_f(y[3][e]) : 0.0;
+                        x[e] = as_u(freduce(as_f(y[0][e]) + as_f(y[1][e]), md.qd, md.qinv) +
+                                    freduce(t2 + t3, md.qd, md.qinv));
+                    }
+                } else {
+#pragma unroll
+                    for (uint32_t e = 0; e < 4; ++e) {
+                        uint64_t v = y[0][e];
 #pragma unroll
                         for (uint32_t s = 1; s < 4; ++s) v = s < src.parts ? v + y[s][e] : v;
                         x[e] = reduce_int(v, md);
@@ -762,8 +764,10 @@ bool bconv_col_supported(uint32_t log_n, uint32_t nkb, uint32_t tiles) {
 // four threads a column: one item at N = 2^15, level 16 (256 and 128
 // workgroups) 18.0 -> 16.1 us for ModUp's and 16.0 -> 14.6 for ModDown's.
 // With more of them the threads that only one of the two phases has work for
-// cost more than the shorter chain gives (six items: 4942 us with 1024 as the
-// line, 4962 with 2048 for a predict step).  Parts are summed by that form.
+// cost more than the shorter chain gives.  The line at 128, 256, 512, 1024 and
+// 2048 workgroups: one bag-of-words document at N = 2^15 2704, 2604, 2578, 2578
+// and 2577 us, six documents' predict step 4879, 4878, 4827, 4837 and 4863, five
+// rotations at N = 2^16 351 up to 1024 and 358.  Parts are summed by that form.
 constexpr uint64_t BCONV_SMALL_BLOCKS = 512;
 static bool bconv_col_small(uint32_t log_n, uint32_t groups, uint32_t n, uint32_t parts) {
     return parts > 1 || (((uint64_t)n * groups << log_n) / (16 * BCONV_COLS)) <= BCONV_SMALL_BLOCKS;
