@@ -282,8 +282,9 @@ int pft_mul_relin_batch_noalloc(pft_ctx* ctx, uint32_t n, const pft_ct* a, const
  * (adds (q-1)/2 before the exact division, the RESCALE of Sec. 3.4), mode 1
  * floors (Alg. 3 as printed), PFT_RESCALE_DEFAULT takes the parameter set's
  * rescale_mode.  out->data needs 2*(level-1)*N uint64 and must
- * not alias in.  (Where the forward schedule starts with a radix-16 column
- * pass, the expansion of the last limb applies that pass itself.) */
+ * not alias in.  (Three launches, the expansion of the last limb applying the
+ * column passes of the transforms around it, unless the pinned forward
+ * schedule does not start with a radix-16 column pass.) */
 #define PFT_RESCALE_DEFAULT 2u
 int pft_rescale(pft_ctx* ctx, const pft_ct* in, uint32_t mode, pft_ct* out);
 int pft_rescale_batch(pft_ctx* ctx, uint32_t n, const pft_ct* in, uint32_t mode, pft_ct* out);
@@ -469,16 +470,17 @@ int pft_ntt_tuning_import(pft_ctx* ctx, const uint32_t* entries, uint32_t count)
  * through stages 0-3.  In mode 2 the inverse transform of the conversion's
  * inputs also stops before its final radix-16 column pass (its schedule is
  * then chosen among those ending with one) and the conversion applies that
- * pass while loading.  Mode 3 (the default) is mode 2 with the key inner
- * product fused into the remaining (row) pass of the forward transform of
- * ModUp's rows: where that transform's schedule is (4, log_n - 4), log_n in
- * {12, 13, 14, 16}, and at most 8 digits are active, one kernel takes each
- * extended row through its row pass and accumulates its products with the
- * key, so the extended digits are read once and only the accumulators are
- * written (otherwise as mode 2); its rows below 2^50 take two digits through
- * each row pass together (one twiddle load and one LDS barrier serve both).
- * Mode 4 is mode 3 with one digit per row pass.  The results are identical
- * in every mode.  PFT_EINVAL for any other mode. */
+ * pass while loading.  Mode 3 (the default) runs a key switch in five
+ * launches: the conversions of mode 2 and, around them, kernels that take a
+ * tile of a row through everything else in registers (the operands' tensor or
+ * X^kappa image, the row passes of every transform, the products with the
+ * key, ModDown and the addends), so that no accumulator of a ciphertext row
+ * is written.  It applies to every ring and batch with at most 8 active
+ * digits, unless the pinned forward schedule does not start with a radix-16
+ * column pass (otherwise as mode 2).  In large launches its rows below 2^50
+ * take two digits through each row pass together (one twiddle load and one
+ * LDS barrier serve both); mode 4 is mode 3 with one digit per row pass there.
+ * The results are identical in every mode.  PFT_EINVAL for any other mode. */
 int pft_bconv_mode(pft_ctx* ctx, int mode);
 
 /* ---- op-list executor ---------------------------------------------------
@@ -496,8 +498,9 @@ int pft_bconv_mode(pft_ctx* ctx, int mode);
  * Output buffers are caller-owned and sized for their level.  The list is
  * split into dependency waves (an op waits for every earlier op that writes
  * what it touches or reads what it writes); inside a wave, ops of equal kind,
- * input level and step/mode run as one batched call, and the groups of a wave
- * run concurrently on side streams forked from the context stream (joined
+ * input level and step/mode run as one batched call (rotations of a level
+ * whatever their steps, unless the key cache is limited or the level is off
+ * the five-launch key switch), and the groups of a wave run concurrently on side streams forked from the context stream (joined
  * before the next wave), each with its own library workspace, so ciphertexts
  * of different levels share the device.  Captured between pft_graph_begin and
  * pft_graph_end, the list becomes one graph with a branch per group (run it
@@ -515,7 +518,9 @@ int pft_exec_batch(pft_ctx* ctx, pft_ct* cts, uint32_t n_cts, const pft_op* ops,
 /* The plan pft_exec_batch would follow, on the host only: for input levels
  * levels[0..n_cts), writes each op's wave and its group index within the
  * wave (either array may be NULL) and returns the number of waves, or the
- * error pft_exec_batch would return for the list. */
+ * error pft_exec_batch would return for the list.  Groups here are of one
+ * step; pft_exec_batch then joins those of a wave's rotations that can run
+ * together. */
 int pft_exec_plan(const pft_op* ops, uint32_t n_ops, const uint32_t* levels, uint32_t n_cts, uint32_t* wave,
                   uint32_t* group);
 /* The plan of PtMatVec (Sec. 4.1) as an op list another implementation can

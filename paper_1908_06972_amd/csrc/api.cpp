@@ -1950,10 +1950,10 @@ static void key_switch_b(pft_ctx* c, uint32_t n, WsRef ws, const KsLayout& K, co
         };
         // on the context's own stream the 60-bit rows run on the helper
         // stream beside the fp64 rows (the small form takes both in one
-        // launch), so that each launch fills the other's tail; the helper's work is joined back before anything
-        // later reads the output or the key.  While this family is being
-        // timed per launch the two run one after the other, so that each
-        // launch's time is its own.
+        // launch), so that each launch fills the other's tail; the helper's
+        // work is joined back before anything later reads the output or the
+        // key.  While this family is being timed per launch the two run one
+        // after the other, so that each launch's time is its own.
         const bool fork = !ks_small(n, level, lg) && c->inner_st && c->stream == c->home && !c->prof.on(PK_KEY_INNER) &&
                            hipEventRecord(c->inner_fork, c->stream) == hipSuccess &&
                            hipStreamWaitEvent(c->inner_st, c->inner_fork, 0) == hipSuccess;

@@ -8,14 +8,15 @@
 #include <algorithm>
 
 // Launches of at most this many words (rows times N, all items) take the
-// 4-residue forms.  Up to 2^22 the 8-residue forms' waves (8 per SIMD, in two
-// rounds at their registers) do not hide the passes' latency: 2^21 -> 2^22
-// took six documents' predict step at N = 2^15 from 5285 to 5077 us.  Up to
-// 2^23 both forms take the same time (five rotations at N = 2^16, level 17: 355
-// us), but the 8-residue form needs its two launches side by side for it: 401
-// where the helper stream has the hardware queue of the context's own.  Far
-// above it the 8-residue forms read each twiddle half as often (16 HMULTs at
-// N = 2^16, level 24: 1565 us, 1693 with 4 residues).
+// 4-residue forms: below the line the 8-residue forms' waves (8 per SIMD, in
+// two rounds at their registers) do not hide the passes' latency, far above it
+// they read each twiddle half as often.  Launches of 2^22.4 to 2^22.6 words
+// with the line at 2^22 and at 2^23: four HMULTs at N = 2^16, level 24, 466 and
+// 443 us, eight at level 12 401 and 373, 24 at N = 2^15, level 8, 381 and 356;
+// five rotations at N = 2^16, level 17, 355 either way, but 401 with the
+// 8-residue form where the helper stream has the hardware queue of the
+// context's own.  At 2^24 a chain of 16 products at N = 2^16 takes 27.87 ms,
+// 27.35 at 2^23, and 16 HMULTs at level 24 1693 us with 4 residues, 1565 with 8.
 #define KS_SMALL_WORDS (1ull << 23)
 inline bool ks_small(uint32_t n, uint32_t rows, uint32_t log_n) {
     return ((uint64_t)n * rows << log_n) <= KS_SMALL_WORDS;

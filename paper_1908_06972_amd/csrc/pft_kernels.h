@@ -153,7 +153,7 @@ struct KsConsts {
 // d [3][level][N] at ws_z + off_d from ciphertexts a_z, b_z.
 void launch_tensor_b(uint32_t n, const ItemPtrs& a, const ItemPtrs& b, WsRef ws, uint64_t off_d, uint32_t level,
                      const DevTables& t, uint32_t log_n, hipStream_t st);
-// out_z = a_z + b_z, `rows` rows each (moduli r mod level); out_z may be a_z or b_z.
+// out_z = a_z + b_z, ciphertexts [2][level][N]; out_z may be a_z or b_z.
 void launch_add_b(uint32_t n, const ItemPtrs& a, const ItemPtrs& b, const ItemPtrs& out, uint32_t level,
                   const DevTables& t, uint32_t log_n, hipStream_t st);
 void launch_copy_rows_b(uint32_t n, const ItemPtrs& src, uint64_t src_off, const ItemPtrs& dst, uint64_t dst_off,
